@@ -93,3 +93,43 @@ def test_constraint_pass_and_sampling_on_its_output(dtype):
                 assert ids[b] in set(int(i) for i in allow[b])        # only allowed tokens are ever drawn
     print(f"{dtype}: {summary}", flush=True)
     s.close()
+
+
+@pytest.mark.parametrize("V,src_off,dst_off,dst_pad", [
+    (1, 0, 0, 0), (3, 1, 3, 0), (4, 0, 1, 0), (8191, 0, 0, 1), (8192, 0, 0, 0), (8195, 2, 2, 1), (8196, 0, 3, 4), (16_387, 3, 1, 1)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_slices_row_ends_and_alignments(V, src_off, dst_off, dst_pad, dtype):
+    """The pass cuts a row into slices of 8192 columns, aligned to the output's 16-byte groups: row lengths
+    around a slice, inputs and outputs that start off a group, a bias list longer than the staged
+    2048 ids with columns named several times, allow-lists at the slices' edges.  Bit for bit."""
+    import torch
+    rng = np.random.default_rng(V + 7 * src_off)
+    B = 3
+    z = rng.standard_normal((B, V)).astype(np.float32)
+    bits = synth.f32_to_bf16_bits(z)
+    if dtype == "bf16":
+        z = synth.bf16_bits_to_f32(bits)
+    bias_ids = [rng.integers(0, V, n).astype(np.int32) for n in (3000, 0, 5)]
+    bias_vals = [rng.standard_normal(len(x)).astype(np.float32) for x in bias_ids]
+    edges = np.unique(np.clip([0, 1, 2, 3, 4, 8190, 8191, 8192, 8193, 8194, 8195, 8196, V - 1], 0, V - 1)).astype(np.int32)
+    allow = [np.zeros(0, np.int32), edges, edges[::-1].copy()]
+    bp, bi = _csr(bias_ids, np.int32)
+    _, bv = _csr(bias_vals, np.float32)
+    ap, ai = _csr(allow, np.int32)
+    want = np.stack([O.apply_constraints(z[b], list(bias_ids[b]), list(bias_vals[b]), list(allow[b]) if len(allow[b]) else None) for b in range(B)])
+    raw = np.zeros(B * V + src_off, z.dtype if dtype == "f32" else np.uint16)
+    raw[src_off:] = (z if dtype == "f32" else bits).reshape(-1)
+    src = _dev(raw.view(np.float32) if dtype == "f32" else raw.view(np.int16))
+    stride = V + dst_pad
+    out = torch.full((dst_off + B * stride + 4,), 7.0, dtype=torch.float32, device="cuda:0")
+    esz = 4 if dtype == "f32" else 2
+    args = [_dev(x) for x in (bp, bi, bv, ap, ai)]
+    rc = binding.simple_apply_logit_constraints(src.data_ptr() + src_off * esz, B, V, binding.SIMPLE_F32 if dtype == "f32" else binding.SIMPLE_BF16, V,
+                                                *[t.data_ptr() for t in args], out.data_ptr() + 4 * dst_off, stride,
+                                                torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == 0
+    got = out.cpu().numpy()
+    rows = got[dst_off:dst_off + B * stride].reshape(B, stride)
+    assert np.array_equal(rows[:, :V].view(np.uint32), want.view(np.uint32))
+    assert np.all(rows[:, V:] == 7.0) and np.all(got[:dst_off] == 7.0) and np.all(got[dst_off + B * stride:] == 7.0)
