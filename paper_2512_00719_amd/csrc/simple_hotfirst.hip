@@ -17,10 +17,16 @@
 // rows without penalties; the rest is queued for the general kernel.  So each row of the call gets
 // the ids of the speculative sampler as the definition over the whole row gives them.
 //
-// One workgroup per row.  Masses are 2^44 fixed-point integers relative to the row maximum (the
-// stable softmax numerator of Eq. (2)), so sums do not depend on the order of the additions; the
-// inverse CDF runs in ascending token id: per tile of 256 x 16 bytes a sum, the tile that holds the
-// target, the thread in it, the column in the thread's group.
+// One workgroup per row.  Masses are relative to the row maximum (the stable softmax numerator of Eq.
+// (2)); a 16-byte group of columns is summed in double precision in column order and rounded once to a
+// 2^44 fixed-point integer, and everything above a group adds integers, so no sum depends on the order
+// of the additions.  The inverse CDF runs in ascending token id: per tile of 2048 groups a sum, the
+// tile that holds the target, the group in it, the column in the group.
+//
+// What bounds it: an accepted row is one trip through memory for its hot columns and a chain of
+// barriers; a rejected row streams its tail through one compute unit, 12 vector instructions a column
+// (a double-precision add costs what a single-precision one does here, so the mass needs no conversion
+// to integers per column), and the launch ends with the rejected rows.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -32,91 +38,166 @@ namespace hotfirst {
 
 using fast::FS;
 using fast::Io;
+using fast::u32x4;
 using fast::u64;
 
-constexpr int HT = 256;
+constexpr int HT = 512;            // threads per row
 constexpr int HWV = HT / 64;
-constexpr int MAX_TILES = 1024;  // tiles of a row's tail (V below 2^20 with float32, 2^21 with bfloat16)
+constexpr int HU = 4;              // 16-byte groups per thread and tile
+constexpr int STEP = 256;          // the hot set is a whole number of steps of 256 groups
+constexpr int MAX_STEPS = 1024;    // steps of hot set or tail (V below 2^20 with float32, 2^21 with bfloat16)
+constexpr int MAX_TILES = MAX_STEPS * STEP / (HT * HU) + 1;
+static_assert(MAX_TILES <= HT, "one tile per thread in the scan over tiles");
 
-__device__ __forceinline__ u64 wfix_y(float y, float y_max) {  // exp(y - y_max) * 2^44, float32 exponential with a split log2(e)
-  const float d = y - y_max;
-  const float t = fmaf(d, fast::L2E_HI, d * fast::L2E_LO);
-  return fast::float_to_u64(__builtin_amdgcn_exp2f(t) * 0x1p44f);
+// Tempered value (the IEEE quotient z / tau) and mass exp(y - y_max) of a column: float32 exponential
+// with a split log2(e).
+template <typename DT> using Raw = typename Io<DT>::Raw;
+__device__ __forceinline__ float mass_of(float z, double inv_tau, float y_max) {
+  const float d = (float)((double)z * inv_tau) - y_max;
+  return __builtin_amdgcn_exp2f(fmaf(d, fast::L2E_HI, d * fast::L2E_LO));
 }
+__device__ __forceinline__ u64 to_fix(double m) { return (u64)__double2ull_rn(m * fast::WSCALE); }
 
-// Sums of the masses of columns [c0, c1) by tile (tile i covers columns c0 + i * TILE ...), into
-// tsum[]; returns (all threads) their total.  bad is raised for a NaN or +inf tempered value.
+// The columns [c0, c1) of a row as 16-byte groups (c0 is a whole number of them); the columns behind the
+// last whole group make one more, filled up with -inf (no mass).
 template <typename DT>
-__device__ inline u64 tile_masses(const DT* rowp, int c0, int c1, double inv_tau, float y_max, u64* tsum, FS& S, bool& bad) {
-  constexpr int EPL = Io<DT>::EPL;
-  constexpr int TILE = HT * EPL;
+struct Span {
+  static constexpr int EPL = Io<DT>::EPL;
+  static constexpr uint32_t NONE = sizeof(DT) == 4 ? 0xFF800000u : 0xFF80FF80u;  // -inf
+  const DT* p;
+  int c0, whole, n_tiles;
+  Raw<DT> last;
+  __device__ __forceinline__ Span(const DT* rowp, int c0_, int c1) {
+    c0 = c0_; p = rowp + c0;
+    whole = (c1 - c0) / EPL;
+    n_tiles = ((c1 - c0 + EPL - 1) / EPL + HT * HU - 1) / (HT * HU);
+    uint32_t w[4] = {NONE, NONE, NONE, NONE};
+#pragma unroll 1
+    for (int i = c1 - c0 - 1; i >= whole * EPL; --i) {  // they move in from the low end
+      if constexpr (sizeof(DT) == 4) { w[3] = w[2]; w[2] = w[1]; w[1] = w[0]; w[0] = __float_as_uint(p[i]); }
+      else {
+        w[3] = (w[3] << 16) | (w[2] >> 16); w[2] = (w[2] << 16) | (w[1] >> 16); w[1] = (w[1] << 16) | (w[0] >> 16);
+        w[0] = (w[0] << 16) | (uint32_t)p[i];
+      }
+    }
+    last = __builtin_bit_cast(Raw<DT>, u32x4{w[0], w[1], w[2], w[3]});
+  }
+};
+// A thread's groups of one tile: group tile * HT * HU + u * HT + tid.
+template <typename DT>
+struct Tile { Raw<DT> r[HU]; };
+template <typename DT>
+__device__ __forceinline__ void tile_load(Tile<DT>& T, const Span<DT>& C, int tile) {
+  const int g0 = tile * HU * HT + (int)threadIdx.x;
+  const Raw<DT>* q = reinterpret_cast<const Raw<DT>*>(C.p);
+  if ((tile + 1) * HU * HT <= C.whole) {
+#pragma unroll
+    for (int u = 0; u < HU; ++u) T.r[u] = fast::as_global(q)[g0 + u * HT];
+  } else {
+    const Raw<DT> none = __builtin_bit_cast(Raw<DT>, u32x4{Span<DT>::NONE, Span<DT>::NONE, Span<DT>::NONE, Span<DT>::NONE});
+#pragma unroll
+    for (int u = 0; u < HU; ++u) {
+      const int g = g0 + u * HT;
+      T.r[u] = g == C.whole ? C.last : none;
+      if (g < C.whole) T.r[u] = fast::as_global(q)[g];
+    }
+  }
+}
+// Mass of one group, as summed everywhere; a NaN or +inf among its columns makes `sum` one.
+template <typename DT>
+__device__ __forceinline__ u64 group_mass(const Raw<DT>& r, double inv_tau, float y_max, double& sum) {
+  float z[Io<DT>::EPL];
+  Io<DT>::unpack(r, z);
+  sum = 0.0;
+#pragma unroll
+  for (int e = 0; e < Io<DT>::EPL; ++e) sum += (double)mass_of(z[e], inv_tau, y_max);
+  return to_fix(sum);
+}
+// Sums of the masses of columns [c0, c1) by tile into tsum[]; returns (all threads) their total.  bad is
+// raised for a NaN or +inf tempered value.  `first`: the first tile, already loaded; the next tile is
+// in flight while one is summed.
+template <typename DT>
+__device__ __forceinline__ u64 tile_masses(const Tile<DT>& first, const Span<DT>& C, double inv_tau, float y_max, u64* tsum, FS& S, bool& bad) {
   const int tid = threadIdx.x, lane = tid & 63;
-  const int n_tiles = (c1 - c0 + TILE - 1) / TILE;
+  const int n_tiles = C.n_tiles;
   for (int i = tid; i < n_tiles; i += HT) tsum[i] = 0ull;
   __syncthreads();
   u64 total = 0ull;
+  double check = 0.0;
+  Tile<DT> T = first;
   for (int i = 0; i < n_tiles; ++i) {
-    const int idx0 = c0 + i * TILE + tid * EPL;
+    Tile<DT> N = T;
+    if (i + 1 < n_tiles) tile_load<DT>(N, C, i + 1);
     u64 m = 0ull;
-    if (idx0 + EPL <= c1) {
-      float z[EPL];
-      Io<DT>::unpack(Io<DT>::load(rowp + idx0), z);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const float y = (float)((double)z[e] * inv_tau);
-        bad = bad || (y != y) || y == INFINITY;
-        m += wfix_y(y, y_max);
-      }
-    } else {
-      for (int idx = idx0; idx < c1; ++idx) {
-        const float y = (float)((double)Io<DT>::one(rowp + idx) * inv_tau);
-        bad = bad || (y != y) || y == INFINITY;
-        m += wfix_y(y, y_max);
-      }
+    for (int u = 0; u < HU; ++u) {
+      double s;
+      m += group_mass<DT>(T.r[u], inv_tau, y_max, s);
+      check += s;
+      __builtin_amdgcn_sched_barrier(0);  // one group at a time: eight columns are enough to fill the pipe, four groups spill
     }
     const u64 w = wave_sum(m);
     if (lane == 0 && w) atomicAdd(&tsum[i], w);
     total += m;
+    T = N;
   }
+  bad = bad || !(check < (double)INFINITY);
   return fast::blk_sum_u64<HWV>(S, total);  // barriers inside: the tile sums are complete after it
 }
 
 // The column of [c0, c1) at which the running mass (ascending id) first exceeds tfix; its mass in w_out.
 template <typename DT>
-__device__ inline int locate(const DT* rowp, int c0, int c1, double inv_tau, float y_max, const u64* tsum, u64 tfix, FS& S, u64& w_out) {
+__device__ __forceinline__ int locate(const Span<DT>& C, double inv_tau, float y_max, const u64* tsum, u64 tfix, FS& S, u64 (&part)[HU][HWV], u64& w_out) {
   constexpr int EPL = Io<DT>::EPL;
-  constexpr int TILE = HT * EPL;
-  const int tid = threadIdx.x;
-  const int n_tiles = (c1 - c0 + TILE - 1) / TILE;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_tiles = C.n_tiles;
   if (tid == 0) { S.bd = -1; S.out_id = -1; S.out_w = 0ull; }
   __syncthreads();
-  // the tile: an exclusive scan over the tile sums, HT tiles per round
-  u64 carry = 0ull;
-  for (int t0 = 0; t0 < n_tiles; t0 += HT) {
-    const u64 m = (t0 + tid < n_tiles) ? tsum[t0 + tid] : 0ull;
+  {
+    const u64 m = tid < n_tiles ? tsum[tid] : 0ull;
     unsigned ce, ct; u64 me, mt;
     fast::blk_excl_scan2<HWV>(S, 0u, m, ce, me, ct, mt);
-    if (m > 0ull && carry + me <= tfix && carry + me + m > tfix) { S.bd = t0 + tid; S.mab_d = carry + me; }
-    carry += mt;
-    __syncthreads();
+    if (m > 0ull && me <= tfix && me + m > tfix) { S.bd = tid; S.mab_d = me; }
   }
+  __syncthreads();
   const int tile = S.bd;
   if (tile < 0) return -1;
-  const int idx0 = c0 + tile * TILE + tid * EPL;
-  u64 w[EPL], sum = 0ull;
+  Tile<DT> T;
+  tile_load<DT>(T, C, tile);
+  u64 g[HU], incl[HU];
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) {
-    w[e] = 0ull;
-    if (idx0 + e < c1) w[e] = wfix_y((float)((double)Io<DT>::one(rowp + idx0 + e) * inv_tau), y_max);
-    sum += w[e];
+  for (int u = 0; u < HU; ++u) {
+    double s;
+    g[u] = group_mass<DT>(T.r[u], inv_tau, y_max, s);
+    incl[u] = wave_incl_scan(g[u]);
+    if (lane == 63) part[u][wave] = incl[u];
+    __builtin_amdgcn_sched_barrier(0);
   }
-  unsigned ce, ct; u64 me, mt;
-  fast::blk_excl_scan2<HWV>(S, 0u, sum, ce, me, ct, mt);
-  u64 run = S.mab_d + me;
+  __syncthreads();
+  u64 base = S.mab_d, start = 0ull;
+  Raw<DT> r = T.r[0];
+  int hit = -1;  // the group that holds the target, if it is one of this thread's
 #pragma unroll
-  for (int e = 0; e < EPL; ++e) {
-    if (w[e] > 0ull && run <= tfix && run + w[e] > tfix) { S.out_id = idx0 + e; S.out_w = w[e]; }
-    run += w[e];
+  for (int u = 0; u < HU; ++u) {
+    u64 before = base;
+#pragma unroll
+    for (int w = 0; w < HWV; ++w) { const u64 x = part[u][w]; if (w < wave) before += x; base += x; }
+    const u64 lo = before + incl[u] - g[u];
+    if (g[u] > 0ull && lo <= tfix && lo + g[u] > tfix) { hit = u; start = lo; r = T.r[u]; }
+  }
+  if (hit >= 0) {
+    float z[EPL];
+    Io<DT>::unpack(r, z);
+    double sum = 0.0;
+    u64 lo = 0ull;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      const double m = (double)mass_of(z[e], inv_tau, y_max);
+      sum += m;
+      const u64 hi = to_fix(sum);  // the last one is the group's mass
+      if (start + lo <= tfix && start + hi > tfix) { S.out_id = C.c0 + ((tile * HU + hit) * HT + tid) * EPL + e; S.out_w = to_fix(m); }
+      lo = hi;
+    }
   }
   __syncthreads();
   w_out = S.out_w;
@@ -124,11 +205,11 @@ __device__ inline int locate(const DT* rowp, int c0, int c1, double inv_tau, flo
 }
 
 template <typename DT>
-__global__ __launch_bounds__(HT) void hot_first_rows_kernel(const SampleArgs a, int H, const simple_tail_stats* __restrict__ tail) {
+__global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs a, int H, const simple_tail_stats* __restrict__ tail) {
   constexpr int EPL = Io<DT>::EPL;
-  constexpr int TILE = HT * EPL;
   __shared__ FS S;
   __shared__ u64 tsum[MAX_TILES];
+  __shared__ u64 part[HU][HWV];
   const int tid = threadIdx.x;
   const int row = blockIdx.x;
   const int V = a.V;
@@ -143,18 +224,26 @@ __global__ __launch_bounds__(HT) void hot_first_rows_kernel(const SampleArgs a, 
     if (tid == 0) { const unsigned slot = atomicAdd(&a.pend[a.parity], 1u); a.pend[2 + slot] = (uint32_t)row; a.out[row] = PENDING; }
     return;
   }
+  Tile<DT> T0;  // the first tile of the hot columns (all of them up to 8192 or 16,384): read once, used for the maximum and the masses
+  const Span<DT> hot(rowp, 0, H);
+  tile_load<DT>(T0, hot, 0);
   const double inv_tau = 1.0 / (double)par.temperature;
   double u[3];
   row_uniforms(a.seed, a.row_offset + (uint64_t)row, a.step, u);
   // ---- maximum of the hot columns, then of the row ----
   uint32_t kmax = KEY_NEG_INF;
   bool bad = false;
-  for (int idx0 = tid * EPL; idx0 < H; idx0 += TILE) {  // H is a whole number of tiles
-    float z[EPL];
-    Io<DT>::unpack(Io<DT>::load(rowp + idx0), z);
+  auto take_max = [&](const Tile<DT>& T) {
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) { bad = bad || (z[e] != z[e]); kmax = max(kmax, fkey(z[e])); }
-  }
+    for (int q = 0; q < HU; ++q) {
+      float z[EPL];
+      Io<DT>::unpack(T.r[q], z);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) { bad = bad || (z[e] != z[e]); kmax = max(kmax, fkey(z[e])); }
+    }
+  };
+  take_max(T0);
+  for (int i = 1; i < hot.n_tiles; ++i) { Tile<DT> T; tile_load<DT>(T, hot, i); take_max(T); }
   kmax = fast::wave_max_u32(kmax);
   if (tid == 0) { S.kmax = KEY_NEG_INF; S.flags = 0u; }
   __syncthreads();
@@ -168,7 +257,7 @@ __global__ __launch_bounds__(HT) void hot_first_rows_kernel(const SampleArgs a, 
   if (has_tail && (ts.tail_max != ts.tail_max || ts.tail_max == INFINITY || !(ts.tail_sum >= 0.0) || ts.tail_sum == (double)INFINITY)) bad = true;
   if (y_max == INFINITY || z_top == -INFINITY) bad = true;               // overflow of z / tau, or nothing to draw
   // ---- hot mass by tile, tail mass from the caller's statistics (Eq. (7)) ----
-  const u64 S_H = tile_masses<DT>(rowp, 0, H, inv_tau, y_max, tsum, S, bad);
+  const u64 S_H = tile_masses<DT>(T0, hot, inv_tau, y_max, tsum, S, bad);
   if (bad) atomicOr(&S.flags, SIMPLE_DIAG_ERROR | SIMPLE_DIAG_BAD_LOGIT);
   __syncthreads();
   simple_row_diag dg;
@@ -186,17 +275,19 @@ __global__ __launch_bounds__(HT) void hot_first_rows_kernel(const SampleArgs a, 
       dg.flags |= SIMPLE_DIAG_ACCEPTED;
       u64 tfix = (u64)__double2ull_rd(u[0] * (double)S_H);
       if (tfix >= S_H) tfix = S_H - 1ull;
-      id = locate<DT>(rowp, 0, H, inv_tau, y_max, tsum, tfix, S, w_id);
+      id = locate<DT>(hot, inv_tau, y_max, tsum, tfix, S, part, w_id);
     } else {
       // rejected: the tail proposal r of Eq. (8), over the columns the kernel has not read yet
       bool bad_t = false;
-      const u64 S_T_exact = tile_masses<DT>(rowp, H, V, inv_tau, y_max, tsum, S, bad_t);
+      const Span<DT> rest(rowp, H, V);
+      tile_load<DT>(T0, rest, 0);
+      const u64 S_T_exact = tile_masses<DT>(T0, rest, inv_tau, y_max, tsum, S, bad_t);
       if (bad_t) atomicOr(&S.flags, SIMPLE_DIAG_ERROR | SIMPLE_DIAG_BAD_LOGIT);
       __syncthreads();
       if (!(S.flags & SIMPLE_DIAG_ERROR) && S_T_exact > 0ull) {
         u64 tfix = (u64)__double2ull_rd(u[2] * (double)S_T_exact);
         if (tfix >= S_T_exact) tfix = S_T_exact - 1ull;
-        id = locate<DT>(rowp, H, V, inv_tau, y_max, tsum, tfix, S, w_id);
+        id = locate<DT>(rest, inv_tau, y_max, tsum, tfix, S, part, w_id);
         S_K = S_H + S_T_exact;  // p~ of the drawn id over the masses as summed here
       }
     }
@@ -243,7 +334,7 @@ hipError_t launch_hot_first(const SampleArgs& a, int dtype, int H, const simple_
   return hipGetLastError();
 }
 
-int hot_first_tile(int dtype) { return hotfirst::HT * (dtype == SIMPLE_F32 ? 4 : 8); }
-int hot_first_max_tiles() { return hotfirst::MAX_TILES; }
+int hot_first_tile(int dtype) { return hotfirst::STEP * (dtype == SIMPLE_F32 ? 4 : 8); }
+int hot_first_max_tiles() { return hotfirst::MAX_STEPS; }
 
 }  // namespace simple

@@ -172,3 +172,44 @@ def test_hot_first_at_the_size_of_the_shvs_configuration():
     summary = P.compare(ids, dg, P.run_oracle(wh, 4, rows=rows), rows)
     print(f"full size: {summary}; accepted {int(acc.sum())} of {B}", flush=True)
     s.close()
+
+
+@pytest.mark.parametrize("dtype,H,n_tail", [("f32", 1024, 1), ("f32", 1024, 8191), ("f32", 9216, 8192), ("f32", 1024, 16_389),
+                                            ("bf16", 2048, 3), ("bf16", 2048, 16_384), ("bf16", 18_432, 16_385), ("bf16", 2048, 40_007)])
+def test_hot_first_row_ends_around_a_tile(dtype, H, n_tail):
+    """Tails that end inside a 16-byte group, with one, exactly one tile, or one column more than a tile of
+    2048 groups, and a hot set longer than the tile the kernel keeps in registers; rows whose draw is
+    rejected (a tail as heavy as the hot set) and rows whose draw is accepted."""
+    import torch
+    rng = np.random.default_rng(n_tail)
+    B, V = 24, H + n_tail
+    stride = (V + 7) // 8 * 8
+    z = rng.standard_normal((B, V)).astype(np.float32)
+    z[::2, H:] += np.float32(np.log(max(H / n_tail, 1.0)) + 1.0)
+    bits = synth.f32_to_bf16_bits(z)
+    if dtype == "bf16":
+        z = synth.bf16_bits_to_f32(bits)
+    params = synth.make_params(B, temperature=[1.0, 0.8, 1.2] * 8)
+    padded = np.full((B, stride), 1e30, np.float32) if dtype == "f32" else np.full((B, stride), 0x7149, np.uint16)
+    padded[:, :V] = z if dtype == "f32" else bits
+    wh = synth.Workload("tile-ends", B, V, dtype, z if dtype == "f32" else bits, params, np.zeros(B + 1, np.int64), np.zeros(0, np.int32),
+                        hot_ids=np.arange(H, dtype=np.int32))
+    lg = _dev(padded if dtype == "f32" else padded.view(np.int16))
+    ts = _dev(tail_stats(z, params, H).view(np.uint8).reshape(B, 16))
+    par = _dev(params.view(np.uint8).reshape(B, 32))
+    s = binding.Sampler(V, 0, max_B=B)
+    accepted = 0
+    for step in range(3):
+        out = torch.full((B,), -9, dtype=torch.int32, device="cuda:0")
+        diag = torch.zeros(B * 32, dtype=torch.uint8, device="cuda:0")
+        rc = binding.simple_sample_hot_first(s.ctx, lg.data_ptr(), B, V, binding.SIMPLE_F32 if dtype == "f32" else binding.SIMPLE_BF16, stride,
+                                             par.data_ptr(), H, ts.data_ptr(), wh.seed, step, 0, out.data_ptr(), diag.data_ptr(),
+                                             torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert rc == 0
+        dg = diag.cpu().numpy().view(binding.ROW_DIAG_DTYPE)
+        P.compare(out.cpu().numpy(), dg, P.run_oracle(wh, step), range(B))
+        assert not (dg["flags"] & binding.DIAG_GENERAL).any()
+        accepted += int(((dg["flags"] & binding.DIAG_ACCEPTED) > 0).sum())
+    assert 0 < accepted < 3 * B
+    s.close()
