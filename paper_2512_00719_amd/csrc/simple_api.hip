@@ -76,15 +76,15 @@ LdsLayout make_layout(int64_t V, int64_t max_nnz, bool with_history) {
   return L;
 }
 
-// The single-pass kernel needs 16-byte aligned rows, a vocabulary whose columns fit 18 bits, 16-bit
-// token counts and at least two tiles per wave.  Its row state is sized so that four workgroups of
+// The single-pass kernel needs rows that start at an element's boundary (`elem`), a vocabulary whose
+// columns fit 18 bits, 16-bit token counts and at least two tiles per wave.  Its row state is sized so that four workgroups of
 // 256 threads share a compute unit when the history tables allow it, else 512 threads are used.  A
 // batch with fewer rows than that many workgroups gets more threads per row (up to 1024: sixteen
 // waves, what a compute unit holds of this kernel), so that the compute units it reaches are full.
-FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_history, bool vec, int lds_limit,
+FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_history, bool elem, int lds_limit,
                             int64_t B, int n_cu) {
   FastLayout F{};
-  if (!vec || V >= ((int64_t)1 << 18) || max_nnz > 65535) return F;
+  if (!elem || V >= ((int64_t)1 << 18) || max_nnz > 65535) return F;
   const int64_t tile = 64 * 4 * ((dtype == SIMPLE_F32) ? 4 : 8);
   const uint32_t n_words = (uint32_t)((V + 31) / 32), n_pairs = (n_words + 1u) / 2u;
   uint32_t off = 0;
@@ -338,6 +338,7 @@ static int sample_impl(simple_ctx* ctx, const simple_state* state, const int32_t
   }
   const size_t esz = (dtype == SIMPLE_F32) ? 4 : 2;
   const bool vec = ((reinterpret_cast<uintptr_t>(logits_dev) & 15u) == 0) && (((size_t)row_stride_elems * esz) % 16 == 0);
+  const bool elem = (reinterpret_cast<uintptr_t>(logits_dev) & (esz - 1u)) == 0;
   simple::SampleArgs a{};
   a.logits = logits_dev; a.stride = row_stride_elems; a.V = (int)V;
   a.params = params_dev; a.hist_ptr = hist_ptr_dev; a.hist_ids = hist_ids_dev;
@@ -360,7 +361,7 @@ static int sample_impl(simple_ctx* ctx, const simple_state* state, const int32_t
   a.L = simple::make_layout(V, ctx->max_nnz, with_hist);
   // rows go out in launches that neither queue can overflow
   const int64_t per_launch = ctx->slots;
-  a.F = simple::make_fast_layout(V, dtype, with_hist ? ctx->max_nnz : 0, with_hist, vec, ctx->lds_limit,
+  a.F = simple::make_fast_layout(V, dtype, with_hist ? ctx->max_nnz : 0, with_hist, elem, ctx->lds_limit,
                                  B < per_launch ? B : per_launch, ctx->n_cu);
   a.gated = (a.F.total != 0u || tail) ? 1 : 0;
   a.pattern_on = (dtype == SIMPLE_BF16 && V < ((int64_t)1 << 18)) ? (tail ? 2 : (a.F.total != 0u ? 1 : 0)) : 0;

@@ -166,7 +166,7 @@ __device__ __forceinline__ bool long_epilogue(const simple_row_params& par, int 
 
 LdsLayout make_layout(int64_t V, int64_t max_nnz, bool with_history);
 // Layout of the single-pass kernel; total = 0 when the call cannot use it.
-FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_history, bool vec, int lds_limit,
+FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_history, bool elem, int lds_limit,
                             int64_t B, int n_cu);
 hipError_t launch_sample(const SampleArgs& a, int dtype, bool vec, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_fast(const SampleArgs& a, int dtype, hipStream_t st);

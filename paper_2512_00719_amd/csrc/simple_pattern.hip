@@ -137,7 +137,7 @@ __device__ __forceinline__ void tile_load(TileRegs& R, const uint16_t* rowp, con
     R.r[h] = u32x4{FILL, FILL, FILL, FILL};
     R.hq[h] = 0u;
     if (g < n_groups) {
-      R.r[h] = *as_global(reinterpret_cast<const u32x4*>(rowp) + g);
+      R.r[h] = ((GlobalU4)rowp)[g];
       if (USE_HOT) R.hq[h] = (as_global(hot_bits)[g >> 2] >> ((g & 3) * 8)) & 0xFFu;
     }
   }
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
   const int n_tiles = (V + TILE - 1) / TILE;
   const float tau = par.temperature;
   unsigned char* tabb = reinterpret_cast<unsigned char*>(tab);
-  const u32x4* rp = reinterpret_cast<const u32x4*>(rowp);
+  const GlobalU4 rp = (GlobalU4)rowp;
   auto hand_back = [&]() { if (tid == 0) a.out[row] = NOT_TAKEN; };
 
   // ---- first pass: columns per pattern ----
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
     for (int u = 0; u < UN; ++u) {
       const int g = g0 + u * PT + tid;
       R[u] = u32x4{0u, 0u, 0u, 0u};
-      if (g < n_groups) R[u] = *as_global(rp + g);
+      if (g < n_groups) R[u] = rp[g];
     }
   };
   fetch(A, 0);
