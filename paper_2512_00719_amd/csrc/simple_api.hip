@@ -76,15 +76,16 @@ LdsLayout make_layout(int64_t V, int64_t max_nnz, bool with_history) {
   return L;
 }
 
-// The single-pass kernel needs rows that start at an element's boundary (`elem`), a vocabulary whose
-// columns fit 18 bits, 16-bit token counts and at least two tiles per wave.  Its row state is sized so that four workgroups of
+// The single-pass kernel needs rows that start at an element's boundary (`elem`), fewer than FAST_MAX_V
+// columns, 16-bit token counts and at least two tiles per wave.  (The limit was 2^18 columns: 128 bfloat16
+// rows of 262,144 took 1045 us in the general kernel, 139 us here.)  Its row state is sized so that four workgroups of
 // 256 threads share a compute unit when the history tables allow it, else 512 threads are used.  A
 // batch with fewer rows than that many workgroups gets more threads per row (up to 1024: sixteen
 // waves, what a compute unit holds of this kernel), so that the compute units it reaches are full.
 FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_history, bool elem, int lds_limit,
                             int64_t B, int n_cu) {
   FastLayout F{};
-  if (!elem || V >= ((int64_t)1 << 18) || max_nnz > 65535) return F;
+  if (!elem || V >= (int64_t)FAST_MAX_V || max_nnz > 65535) return F;
   const int64_t tile = 64 * 4 * ((dtype == SIMPLE_F32) ? 4 : 8);
   const uint32_t n_words = (uint32_t)((V + 31) / 32), n_pairs = (n_words + 1u) / 2u;
   uint32_t off = 0;
@@ -101,6 +102,7 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   F.samp = body;
   // the sample merge area holds SPW keys per wave
   F.threads = ((int64_t)body + 2048 <= (int64_t)lds_limit / 4) ? 256 : 512;  // four workgroups per compute unit, static LDS included
+  if (V >= ((int64_t)1 << 18)) F.threads = 512;  // a sample of two tiles per wave: four waves' is too small a share of such rows
   if (B <= (int64_t)n_cu) F.threads = 1024;
   else if (B <= 2 * (int64_t)n_cu) F.threads = 512;
   while (F.threads > 256 && V / tile < 2 * (F.threads / 64)) F.threads /= 2;  // two tiles per wave
@@ -124,8 +126,10 @@ CtxLayout ctx_layout(int64_t max_V, int64_t max_nnz, int slots, int lds_limit, i
   L.order = off;     off = align256(off + (size_t)slots * 4u);  // the order in which the single-pass kernel takes a launch's rows
   L.wq = off;        off = align256(off + 64u + 64u * (size_t)slots);  // head, then one 64-byte record per slot
   // a slot holds the fixed part and the largest history tables the single-pass kernel can have
-  const FastLayout Fm = make_fast_layout(max_V < ((int64_t)1 << 18) ? max_V : ((int64_t)1 << 18) - 1, SIMPLE_F32,
-                                         max_nnz, max_nnz > 0, true, lds_limit, (int64_t)1 << 30, n_cu);
+  // (where FAST_MAX_V columns and max_nnz ids outgrow the LDS, tables for fewer columns still fit)
+  FastLayout Fm{};
+  for (const int64_t lim : {(int64_t)FAST_MAX_V, (int64_t)1 << 18})
+    if (!Fm.total) Fm = make_fast_layout(max_V < lim ? max_V : lim - 1, SIMPLE_F32, max_nnz, max_nnz > 0, true, lds_limit, (int64_t)1 << 30, n_cu);
   const uint32_t tables = (max_nnz > 0 && Fm.total) ? Fm.cnt + (uint32_t)((max_nnz + 3) / 2) * 4u + 16u : 0u;
   L.ws_stride = (WIDE_SLOT_FIXED + tables + 255u) & ~255u;
   L.wws = off;       off = align256(off + (size_t)L.ws_stride * (size_t)slots);
@@ -364,7 +368,7 @@ static int sample_impl(simple_ctx* ctx, const simple_state* state, const int32_t
   a.F = simple::make_fast_layout(V, dtype, with_hist ? ctx->max_nnz : 0, with_hist, elem, ctx->lds_limit,
                                  B < per_launch ? B : per_launch, ctx->n_cu);
   a.gated = (a.F.total != 0u || tail) ? 1 : 0;
-  a.pattern_on = (dtype == SIMPLE_BF16 && V < ((int64_t)1 << 18)) ? (tail ? 2 : (a.F.total != 0u ? 1 : 0)) : 0;
+  a.pattern_on = (dtype == SIMPLE_BF16 && V < (int64_t)simple::FAST_MAX_V) ? (tail ? 2 : (a.F.total != 0u ? 1 : 0)) : 0;
   for (int64_t b0 = 0; b0 < B; b0 += per_launch) {
     const int64_t nb = (B - b0 < per_launch) ? (B - b0) : per_launch;
     a.B = (int)nb;

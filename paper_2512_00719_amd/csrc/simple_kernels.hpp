@@ -36,6 +36,8 @@ struct FastLayout {
 constexpr int SAMPLE_PER_WAVE = 48;   // keys of the threshold sample a wave hands to the merge (sizes the merge area)
 constexpr int CAPF_PER_THREAD = 12;  // candidate-list entries per thread the single-pass kernel's epilogue holds in registers
 constexpr int KMAXF = 1024;   // largest top-k its list certifies
+constexpr int FAST_MAX_V = 1 << 19;  // columns from which only the general kernel serves a call: the 2^44 fixed-point masses of a
+                                     // row stay below 2^63, and a row is at most 128 slices of the sliced kernels
 constexpr int32_t PENDING = -2;  // id left by the single-pass kernel on rows the general kernel completes
 constexpr int32_t NOT_TAKEN = -3;  // id left by the pattern-count kernel on every row that the single-pass kernel still has to do
 constexpr int PEND_ROWS = 65536; // rows per launch (capacity of the pending-row queue)

@@ -51,7 +51,7 @@ constexpr int BPT = NB / PT;   // bins per thread in the cut phase
 static_assert(NB % PT == 0, "bins divide among the threads");
 constexpr int TG = 4;          // 16-byte groups per lane and tile
 constexpr int TILE = 64 * 8 * TG;  // columns per tile of the second pass, one wave each
-constexpr int NTILE = (1 << 18) / TILE;  // V < 2^18
+constexpr int NTILE = FAST_MAX_V / TILE;
 static_assert(NTILE <= PT, "one tile per thread in the scans over tiles");
 constexpr int UN = 4;          // 16-byte loads in flight per lane, twice (two register sets take turns)
 constexpr uint32_t FILL = 0xFF80FF80u;  // two patterns (-inf) of the last bin, whose columns have no mass

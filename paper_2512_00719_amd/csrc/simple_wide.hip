@@ -33,7 +33,7 @@
 //
 // Rows without truncation skip the first kernel and have no cut; rows with a min-p cut use the first
 // kernel for the row maximum only (the cut is a value).  Rows with top-k alone run the same three
-// kernels by count instead of mass: a bin also counts its columns, the cut's bin is the one in which
+// kernels by count instead of mass: a bin counts its columns, the cut's bin is the one in which
 // the count from the top reaches k, and the descent inside it weighs every column as one.
 //
 // Penalties (section 2.2) are applied on the fly: the single-pass kernel leaves the row's history
@@ -252,7 +252,6 @@ __device__ __forceinline__ void hist_columns(const SliceTabs& T, const WideRow& 
 
 // The bin that holds the cut, from the masses of the first pass: cumulative mass from the top
 // reaches top_p * total.  bstar < 0 if none.  Ends with a barrier.
-constexpr u64 MASS_BITS = (1ull << CNT_SHIFT) - 1ull;
 __device__ inline int find_cut(FS& S, const WideRow& W, u64& s_tot) {
   const int tid = threadIdx.x;
   constexpr int BPT = NBW / WT;
@@ -260,7 +259,7 @@ __device__ inline int find_cut(FS& S, const WideRow& W, u64& s_tot) {
   const u64 m_top = as_global(reinterpret_cast<const u64*>(W.ws + WS_SCAL))[0];
   u64 hm[BPT]; u64 loc = 0ull;
 #pragma unroll
-  for (int j = 0; j < BPT; ++j) { hm[j] = as_global(gh)[tid * BPT + j] & MASS_BITS; loc += hm[j]; }
+  for (int j = 0; j < BPT; ++j) { hm[j] = as_global(gh)[tid * BPT + j]; loc += hm[j]; }
   if (tid == 0) S.bk = -1;
   unsigned ce, ct; u64 me, mt;
   blk_excl_scan2<WNW>(S, 0u, loc, ce, me, ct, mt);
@@ -286,7 +285,7 @@ __device__ inline int find_cut_k(FS& S, const WideRow& W) {
   const unsigned n_top = as_global(reinterpret_cast<const uint32_t*>(W.ws + WS_SCAL))[7];
   unsigned hc[BPT], loc = 0u;
 #pragma unroll
-  for (int j = 0; j < BPT; ++j) { hc[j] = (unsigned)(as_global(gh)[tid * BPT + j] >> CNT_SHIFT); loc += hc[j]; }
+  for (int j = 0; j < BPT; ++j) { hc[j] = (unsigned)as_global(gh)[tid * BPT + j]; loc += hc[j]; }
   if (tid == 0) S.bk = -1;
   unsigned ce, ct; u64 me, mt;
   blk_excl_scan2<WNW>(S, loc, 0ull, ce, me, ct, mt);
@@ -519,8 +518,8 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
       int b; float y;
       const float w = mass_term(z, W.C, b, y);
       ymax = fmaxf(ymax, y);
-      // top-k route: a bin also counts its columns, above its mass
-      if (z < W.C.g) atomicAdd(&lh[b], mass_fix_below(w) | (W.mode == WIDE_TOP_K ? 1ull << CNT_SHIFT : 0ull));
+      // top-k route: a bin counts its columns
+      if (z < W.C.g) atomicAdd(&lh[b], W.mode == WIDE_TOP_K ? 1ull : mass_fix_below(w));
       else { mtop += mass_fix(fminf(w, W_LIMIT)); ++ntop; }
     };
     if (W.mode == WIDE_MIN_P) {  // the row maximum is all a value cut needs
@@ -563,8 +562,8 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
               float_to_parts(fminf(w, W_LIMIT) * MSCALE, hi, lo);
               const bool below = z[e] < W.C.g;
               u64 v = parts_to_u64(hi, lo);
-              if (TOPK) {  // the bin counts the column too (not the history columns, handled below)
-                v |= (below && !((nib >> e) & 1u)) ? 1ull << CNT_SHIFT : 0ull;
+              if (TOPK) {  // the bin counts the column instead (not the history columns, handled below)
+                v = (below && !((nib >> e) & 1u)) ? 1ull : 0ull;
                 ntop += below ? 0u : 1u;
               }
               atomicAdd(&lh[below ? b : NBW], v);
@@ -802,7 +801,10 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
       if (use_hot) { const u64 s1 = wave_sum(acc1); if (lane == 0 && s1) atomicAdd(&ltile[1], s1); }
     }
     __syncthreads();  // the tile sums and this slice's appends are complete
-    if (tid < 2 && sl < 256) reinterpret_cast<u64*>(W.ws + WS_TILES)[tid * 256 + sl] = ltile[tid];
+    if (tid < 2 && sl < 256) {
+      reinterpret_cast<u64*>(W.ws + WS_TILES)[tid * 256 + sl] = ltile[tid];
+      if (ltile[tid] >> 55) bad = true;  // 128 tiles of two classes below 2^55 sum below 2^63; more mass in one is not carried
+    }
     // every slice may add ICAP boundary columns before the stage has to be written out
     if (l_n > (unsigned)(LCAP - ICAP)) list_out();
   }
