@@ -523,8 +523,8 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   // ... and rows with top-k alone beyond the list's reach (any penalties).
   const bool big_k = !R.greedy && R.k_on && par.top_k > KMAXF && !R.p_on && !R.minp_on;
   const bool straight = no_trunc || big_k || (!R.greedy && !R.k_on && !R.p_le0 && h_active && !lowering);
-  const uint32_t straight_mode = no_trunc ? (uint32_t)WIDE_ALL : big_k ? (uint32_t)WIDE_TOP_K
-                                          : (R.p_on ? (uint32_t)WIDE_TOP_P : (uint32_t)WIDE_MIN_P);
+  const uint32_t straight_mode = big_k ? (uint32_t)WIDE_TOP_K
+                                       : (R.p_on ? (uint32_t)WIDE_TOP_P : (uint32_t)WIDE_MIN_P);
   const bool eligible = straight ? (!bad_par && !too_long)
                                  : (!bad_par && !too_long && (!h_active || lowering) &&
                                     (R.greedy || !R.k_on || par.top_k <= KMAXF));
@@ -579,71 +579,8 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
   }
   const uint32_t* hot_bits = R.greedy ? nullptr : a.hot_bits;
-
-  // ---- threshold from the sample: three largest penalised values per lane, wave select, merge ----
-  float a1 = -INFINITY, a2 = -INFINITY, a3 = -INFINITY;  // branch-free insertion; a NaN is ignored here
-#define SIMPLE_TAKE3(v) do { const float v_ = (v); const float m1_ = fmaxf(a1, v_), l1_ = fminf(a1, v_); \
-    const float m2_ = fmaxf(a2, l1_), l2_ = fminf(a2, l1_); a3 = fmaxf(a3, l2_); a2 = m2_; a1 = m1_; } while (0)
-#pragma unroll
-  for (int u = 0; u < UNR; ++u) {
-    float z[EPL];
-    sample_group<DT>(A[u], t0 * T + u * 64 * EPL + lane * EPL, H, z);
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) SIMPLE_TAKE3(z[e]);
-    sample_group<DT>(Bf[u], (t0 + 1) * T + u * 64 * EPL + lane * EPL, H, z);
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) SIMPLE_TAKE3(z[e]);
-  }
-#undef SIMPLE_TAKE3
-  // rank in the sample whose value leaves, with high probability, >= k_sel columns above it in the row
-  const float m_exp = (float)k_sel * (float)(NWV * 2 * T) / (float)V;
-  const unsigned r_samp = (unsigned)ceilf(1.15f * m_exp + 3.2f * sqrtf(m_exp) + 3.5f);
-  {
-    const float r_w = (float)r_samp / (float)NWV;
-    const unsigned q = min((unsigned)(SPW * 3 / 4), (unsigned)ceilf(r_w + 3.0f * sqrtf(r_w) + 2.0f));
-    const uint32_t k3[3] = {fkey(a1), fkey(a2), fkey(a3)};
-    // every lane's largest is >= the smallest of the lanes' largest: at least 64 >= q keys qualify
-    const uint32_t Kw = wave_threshold<3>(k3, q, q / 4u + 1u, wave_min_u32(k3[0]), wave_max_u32(k3[0]));
-    if (lane < SPW) samp[wave * SPW + lane] = 0u;
-    unsigned have = 0;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const u64 m = __ballot(k3[j] >= Kw);
-      const unsigned p = have + lanes_before(m);
-      if (((m >> lane) & 1ull) && p < (unsigned)SPW) samp[wave * SPW + p] = k3[j];
-      have = min(have + (unsigned)__popcll(m), (unsigned)SPW);
-    }
-    const float wp = wave_max(a1);
-    if (lane == 0) { S.wmax[wave] = wp; S.wcnt[wave] = have; }
-  }
-  __syncthreads();
   StreamCtx C;
-  {
-    constexpr int NS = (NWV * SPW) / 64;
-    uint32_t ks[NS];
-    unsigned total = 0;
-    float Mp = S.wmax[0];
-#pragma unroll
-    for (int w = 0; w < NWV; ++w) { total += S.wcnt[w]; Mp = fmaxf(Mp, S.wmax[w]); }
-    uint32_t kmn = 0xFFFFFFFFu, kmx = 0u;
-#pragma unroll
-    for (int j = 0; j < NS; ++j) { ks[j] = samp[j * 64 + lane]; kmx = max(kmx, ks[j]); if (ks[j]) kmn = min(kmn, ks[j]); }
-    kmn = wave_min_u32(kmn); kmx = wave_max_u32(kmx);
-    const unsigned need = max(1u, min(r_samp, total));
-    float g = keyf(wave_threshold<NS>(ks, need, need / 8u + 1u, min(kmn, kmx), kmx));
-    if (!R.greedy && !R.k_on && R.minp_on) {
-      // min-p survivors lie within ln(min_p) of the row maximum, which is at least the sample's
-      const float thr_lb = Mp / R.tau + (float)log((double)R.min_p);
-      float gm = thr_lb * R.tau;
-      gm = gm - fabsf(gm) * 1e-6f - 1e-30f;
-      g = fmaxf(g, gm);
-    }
-    C.g = g;
-    C.y_g = R.greedy ? g : g / R.tau;
-    C.inv_tau = 1.0 / (double)R.tau;
-    C.need_sum = R.need_sum;
-    C.l2e_tau = (float)(1.4426950408889634 / (double)R.tau);
-  }
+  C.g = 0.0f;
   // Hands the row to the kernels of the whole-vocabulary routes: a queue record, a cleared workspace
   // slot and the row's history tables (rebuilt first if the region no longer holds them).  False if
   // no slot is free.  All threads call.
@@ -682,7 +619,75 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
     return true;
   };
-  if (straight) {  // nothing to select here (without truncation every column survives)
+  if (no_trunc) {  // every column survives: no threshold to look for
+    if (!queue_wide(WIDE_ALL, true) && tid == 0) queue_pending(a, row);
+    return;
+  }
+
+  // ---- threshold from the sample: three largest penalised values per lane, wave select, merge ----
+  float a1 = -INFINITY, a2 = -INFINITY, a3 = -INFINITY;  // branch-free insertion; a NaN is ignored here
+#define SIMPLE_TAKE3(v) do { const float v_ = (v); const float m1_ = fmaxf(a1, v_), l1_ = fminf(a1, v_); \
+    const float m2_ = fmaxf(a2, l1_), l2_ = fminf(a2, l1_); a3 = fmaxf(a3, l2_); a2 = m2_; a1 = m1_; } while (0)
+#pragma unroll
+  for (int u = 0; u < UNR; ++u) {
+    float z[EPL];
+    sample_group<DT>(A[u], t0 * T + u * 64 * EPL + lane * EPL, H, z);
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) SIMPLE_TAKE3(z[e]);
+    sample_group<DT>(Bf[u], (t0 + 1) * T + u * 64 * EPL + lane * EPL, H, z);
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) SIMPLE_TAKE3(z[e]);
+  }
+#undef SIMPLE_TAKE3
+  // rank in the sample whose value leaves, with high probability, >= k_sel columns above it in the row
+  const float m_exp = (float)k_sel * (float)(NWV * 2 * T) / (float)V;
+  const unsigned r_samp = (unsigned)ceilf(1.15f * m_exp + 3.2f * sqrtf(m_exp) + 3.5f);
+  {
+    const float r_w = (float)r_samp / (float)NWV;
+    const unsigned q = min((unsigned)(SPW * 3 / 4), (unsigned)ceilf(r_w + 3.0f * sqrtf(r_w) + 2.0f));
+    const uint32_t k3[3] = {fkey(a1), fkey(a2), fkey(a3)};
+    // every lane's largest is >= the smallest of the lanes' largest: at least 64 >= q keys qualify
+    const uint32_t Kw = wave_threshold<3>(k3, q, q / 4u + 1u, wave_min_u32(k3[0]), wave_max_u32(k3[0]));
+    if (lane < SPW) samp[wave * SPW + lane] = 0u;
+    unsigned have = 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const u64 m = __ballot(k3[j] >= Kw);
+      const unsigned p = have + lanes_before(m);
+      if (((m >> lane) & 1ull) && p < (unsigned)SPW) samp[wave * SPW + p] = k3[j];
+      have = min(have + (unsigned)__popcll(m), (unsigned)SPW);
+    }
+    const float wp = wave_max(a1);
+    if (lane == 0) { S.wmax[wave] = wp; S.wcnt[wave] = have; }
+  }
+  __syncthreads();
+  {
+    constexpr int NS = (NWV * SPW) / 64;
+    uint32_t ks[NS];
+    unsigned total = 0;
+    float Mp = S.wmax[0];
+#pragma unroll
+    for (int w = 0; w < NWV; ++w) { total += S.wcnt[w]; Mp = fmaxf(Mp, S.wmax[w]); }
+    uint32_t kmn = 0xFFFFFFFFu, kmx = 0u;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) { ks[j] = samp[j * 64 + lane]; kmx = max(kmx, ks[j]); if (ks[j]) kmn = min(kmn, ks[j]); }
+    kmn = wave_min_u32(kmn); kmx = wave_max_u32(kmx);
+    const unsigned need = max(1u, min(r_samp, total));
+    float g = keyf(wave_threshold<NS>(ks, need, need / 8u + 1u, min(kmn, kmx), kmx));
+    if (!R.greedy && !R.k_on && R.minp_on) {
+      // min-p survivors lie within ln(min_p) of the row maximum, which is at least the sample's
+      const float thr_lb = Mp / R.tau + (float)log((double)R.min_p);
+      float gm = thr_lb * R.tau;
+      gm = gm - fabsf(gm) * 1e-6f - 1e-30f;
+      g = fmaxf(g, gm);
+    }
+    C.g = g;
+    C.y_g = R.greedy ? g : g / R.tau;
+    C.inv_tau = 1.0 / (double)R.tau;
+    C.need_sum = R.need_sum;
+    C.l2e_tau = (float)(1.4426950408889634 / (double)R.tau);
+  }
+  if (straight) {
     if (!queue_wide(straight_mode, true) && tid == 0) queue_pending(a, row);
     return;
   }

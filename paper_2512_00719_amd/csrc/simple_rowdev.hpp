@@ -332,12 +332,17 @@ enum { WIDE_TOP_P = 0,   // the shortest prefix whose mass reaches top_p of the 
        WIDE_TOP_K = 3 }; // the first top_k columns of the order (top-k alone, beyond the candidate list's reach)
 constexpr int WQ_HEAD = 16;             // words before the records
 constexpr uint32_t WS_HIST = 0u;        // u64[NBW]: mass of the columns below g, by bin (top-k route: their number)
+                                        // (rows without truncation: AllPart[128][4], per slice and wave)
 constexpr uint32_t WS_TILES = 16384u;   // u64[2][256]: survivors' mass per tile, tail class then hot class
 constexpr uint32_t WS_SCAL = 20480u;    // u64 mass at or above g; u32 sure survivors; u32 boundary columns; u64 exact mass
                                         // of the row; u32 largest key of a tempered value; u32 columns at or above g
 constexpr uint32_t WS_RL = 20544u;      // u64[RCAP]: columns of the boundary bin (value bits << 32 | id)
 constexpr uint32_t WS_HT = 53312u;      // the row's history tables as the single-pass kernel laid them out in LDS
 // [0, WS_RL) must be zero when a row is queued
+// A wave's share of a slice of a row without truncation: masses relative to the largest tempered value
+// among them (double sums of float32 exponentials), the hot columns' part, and that value.
+struct AllPart { double s, h; float m; uint32_t unused; };
+static_assert(sizeof(AllPart) == 24 && (FAST_MAX_V / 4096) * 4 * sizeof(AllPart) <= 16384, "the parts of a row fit the bins' place");
 
 // Mass of one column relative to the mass at y_g, w = exp(y - y_g) with y = fl32(z / tau), and the
 // bin of y (linear in y, so columns of equal y share a bin).  y is formed as fl32(double(z) * fl64(1 /

@@ -31,7 +31,9 @@
 // before its main line runs, so that no trip through memory is waited for in full.  Loads return in
 // order: what is needed first is requested first.
 //
-// Rows without truncation skip the first kernel and have no cut; rows with a min-p cut use the first
+// Rows without truncation have no cut and are read once, by the first kernel: per slice and wave it leaves
+// the columns' mass relative to the largest of them (so any dynamic range is carried: one column may
+// hold almost the whole mass), from which the third kernel draws.  Rows with a min-p cut use the first
 // kernel for the row maximum only (the cut is a value).  Rows with top-k alone run the same three
 // kernels by count instead of mass: a bin counts its columns, the cut's bin is the one in which
 // the count from the top reaches k, and the descent inside it weighs every column as one.
@@ -227,6 +229,21 @@ __device__ __forceinline__ void hist_stage(SliceTabs& T, const HistPre<DT>& P, c
     }
   }
 }
+// f(z', idx) for each history column of the slice behind the HCAP staged ones, by its mask word's thread.
+template <typename DT, typename F>
+__device__ __forceinline__ void hist_beyond(const SliceTabs& T, const WideRow& W, const DT* rowp, int c0, int V, F&& f) {
+  const int tid = fresh_tid();
+  if (tid >= SLC / 32) return;
+  uint32_t word = T.bm[tid];
+  unsigned r = T.dir[tid >> 1] - T.dir[0] + ((tid & 1) ? (unsigned)__popc(T.bm[tid - 1]) : 0u);
+  while (word) {
+    const int idx = c0 + 32 * tid + (__ffs((int)word) - 1);
+    word &= word - 1u;
+    if (r >= (unsigned)HCAP && idx < V)
+      f(apply_penalties(Io<DT>::one(rowp + idx), (uint32_t)T.cnt[min(r, (unsigned)SLC - 1u)], W.rep, W.inv_rep, W.freq, W.pres), idx);
+    ++r;
+  }
+}
 // f(z', idx) for each history column of the slice, with its penalised value: the staged ones one per
 // thread, the rest (a slice with more than HCAP of them) by their mask word's thread.
 template <typename DT, typename F>
@@ -237,17 +254,7 @@ __device__ __forceinline__ void hist_columns(const SliceTabs& T, const WideRow& 
     const int idx = c0 + (int)T.hcol[j];
     if (idx < V) f(apply_penalties(T.hz[j], (uint32_t)T.cnt[j], W.rep, W.inv_rep, W.freq, W.pres), idx);
   }
-  if (nc > (unsigned)HCAP && tid < SLC / 32) {
-    uint32_t word = T.bm[tid];
-    unsigned r = T.dir[tid >> 1] - T.dir[0] + ((tid & 1) ? (unsigned)__popc(T.bm[tid - 1]) : 0u);
-    while (word) {
-      const int idx = c0 + 32 * tid + (__ffs((int)word) - 1);
-      word &= word - 1u;
-      if (r >= (unsigned)HCAP && idx < V)
-        f(apply_penalties(Io<DT>::one(rowp + idx), (uint32_t)T.cnt[min(r, (unsigned)SLC - 1u)], W.rep, W.inv_rep, W.freq, W.pres), idx);
-      ++r;
-    }
-  }
+  if (nc > (unsigned)HCAP) hist_beyond<DT>(T, W, rowp, c0, V, f);
 }
 
 // The bin that holds the cut, from the masses of the first pass: cumulative mass from the top
@@ -311,7 +318,7 @@ __device__ inline RowCut row_cut(FS& S, const WideRow& W) {  // every thread cal
   if (W.mode == WIDE_TOP_P) { c.bstar = find_cut(S, W, c.s_tot); c.valid = c.bstar >= 0; }
   else if (W.mode == WIDE_TOP_K) { c.bstar = find_cut_k(S, W); c.valid = c.bstar >= 0; }
   else c.bstar = NBW;  // no bin holds a cut
-  if (W.mode != WIDE_ALL && W.min_p > 0.0f) {  // min-p, alone or on top of top-p: the shorter prefix wins
+  if (W.min_p > 0.0f) {  // min-p, alone or on top of top-p: the shorter prefix wins
     const uint32_t kmax = as_global(reinterpret_cast<const uint32_t*>(W.ws + WS_SCAL))[6];
     c.valid = c.valid && kmax > KEY_NEG_INF;
     c.thr_y = keyf(kmax) + (float)log((double)W.min_p);  // fl(y_max + fl(ln min_p)), as in the list's epilogue
@@ -414,8 +421,8 @@ struct SlotIds {
   __device__ __forceinline__ void settle() { row_c = uni(row_c); act_c = uni(act_c); row_n = uni(row_n); act_n = uni(act_n); }
 };
 static_assert(offsetof(WideRec, row) == 0 && offsetof(WideRec, mode) == 8 && offsetof(WideRec, h_active) == 44, "record words read by SlotIds");
-// skip_all: rows without truncation need nothing from this pass (the bins kernel)
-template <typename DT, bool use_hot, bool skip_all = false>
+// classify: rows without truncation need nothing from this pass; else (the bins kernel) only they need the hot bits
+template <typename DT, bool use_hot, bool classify>
 __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a, unsigned item, unsigned n_sl, int cur_slot, const SlotIds& ids) {
   constexpr int EPL = Io<DT>::EPL;
   const int tid = threadIdx.x;
@@ -423,7 +430,7 @@ __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a
   const uint32_t row = slot == cur_slot ? ids.row_c : ids.row_n;  // scalars (SlotIds::settle)
   const uint32_t actw = slot == cur_slot ? ids.act_c : ids.act_n;
   const bool act = (actw & 1u) != 0u;
-  if (skip_all && (actw & 2u)) return;
+  if (classify && (actw & 2u)) return;
   const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride;
   L.pre = act ? slice_fetch(a.wws + (size_t)slot * a.ws_stride, a, c0) : 0u;
 #pragma unroll
@@ -432,12 +439,102 @@ __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a
     L.hq[j] = 0u;
     L.A[j] = typename Io<DT>::Raw();
     if (idx0 + EPL <= a.V) L.A[j] = Io<DT>::load(rowp + idx0);
-    if (use_hot && idx0 < a.V) L.hq[j] = (as_global(a.hot_bits)[idx0 >> 5] >> ((unsigned)idx0 & 31u)) & ((1u << EPL) - 1u);
+    if (use_hot && (classify || (actw & 2u)) && idx0 < a.V) L.hq[j] = (as_global(a.hot_bits)[idx0 >> 5] >> ((unsigned)idx0 & 31u)) & ((1u << EPL) - 1u);
+  }
+}
+
+// ---------------------------------------------------------------- no truncation ---------------
+constexpr float LOWEST = -3.4028234663852886e38f;
+// exp(y - m) for y <= m (float32, split log2(e)); a NaN stays one
+__device__ __forceinline__ float mass_rel(float y, float m) {
+  const float d = y - m;
+  return __builtin_amdgcn_exp2f(fmaf(d, L2E_HI, d * L2E_LO));
+}
+// One slice of a row without truncation: every wave leaves the mass of its columns, relative to the
+// largest of them.  A column costs a double product, three conversions, an exponential and a double
+// sum, less than the time its bytes take; the row is read once.  (128,256 float32 columns x 256 rows:
+// the call 173 us with the mass taken relative to a threshold, up to 229 with a row it could not carry; 55 us so.)
+template <typename DT, bool use_hot>
+__device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<DT>& HP, SliceTabs& Tb, const WideRow& W, const SampleArgs& a,
+                                          const DT* rowp, int c0, int sl) {
+  constexpr int EPL = Io<DT>::EPL, G = ItemLoads<DT>::G;
+  const int tid = fresh_tid(), V = a.V;
+  float y[G][EPL];
+  float m = LOWEST;
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+    const int o = (j * WT + tid) * EPL;
+    Io<DT>::unpack(L.A[j], y[j]);
+    if (c0 + o + EPL > V) {  // the ragged end of the row
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) y[j][e] = c0 + o + e < V ? Io<DT>::one(rowp + c0 + o + e) : -INFINITY;
+    }
+    const uint32_t nib = W.h_active ? Tb.bm[o >> 5] >> ((unsigned)o & 31u) : 0u;  // history columns: below
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      y[j][e] = ((nib >> e) & 1u) ? -INFINITY : tempered(y[j][e], W.C);
+      m = fmaxf(m, y[j][e]);
+    }
+  }
+  float yh[HCAP / WT];  // this thread's share of the staged history columns, and their hot bits
+  uint32_t hh = 0u;
+  unsigned nc = 0u;
+  if (W.h_active) {
+    hist_stage<DT>(Tb, HP, W.ws, a, rowp, c0, V);
+    __syncthreads();
+    nc = min(Tb.dir[SLC / 64] - Tb.dir[0], (unsigned)SLC);
+#pragma unroll
+    for (int k = 0; k < HCAP / WT; ++k) {
+      const unsigned j = (unsigned)(k * WT + tid);
+      yh[k] = -INFINITY;
+      if (j < min(nc, (unsigned)HCAP)) {
+        const int idx = c0 + (int)Tb.hcol[j];
+        if (idx < V) {
+          yh[k] = tempered(apply_penalties(Tb.hz[j], (uint32_t)Tb.cnt[j], W.rep, W.inv_rep, W.freq, W.pres), W.C);
+          if (use_hot) hh |= hot_bit(a.hot_bits, (uint32_t)idx) << k;
+        }
+      }
+      m = fmaxf(m, yh[k]);
+    }
+    // (a slice with more history columns than the stage holds: the rest by their mask word's thread, twice)
+    if (nc > (unsigned)HCAP) hist_beyond<DT>(Tb, W, rowp, c0, V, [&](float z, int) { m = fmaxf(m, tempered(z, W.C)); });
+  }
+  const float M = wave_max(m);
+  double s = 0.0, h = 0.0;
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      const float w = mass_rel(y[j][e], M);
+      s += (double)w;
+      if (use_hot) h += ((L.hq[j] >> e) & 1u) ? (double)w : 0.0;
+    }
+  }
+  if (W.h_active) {
+#pragma unroll
+    for (int k = 0; k < HCAP / WT; ++k) {
+      const float w = mass_rel(yh[k], M);
+      s += (double)w;
+      if (use_hot) h += ((hh >> k) & 1u) ? (double)w : 0.0;
+    }
+    if (nc > (unsigned)HCAP)
+      hist_beyond<DT>(Tb, W, rowp, c0, V, [&](float z, int idx) {
+        const float w = mass_rel(tempered(z, W.C), M);
+        s += (double)w;
+        if (use_hot && hot_bit(a.hot_bits, (uint32_t)idx)) h += (double)w;
+      });
+    __syncthreads();  // the tables are rewritten by the next item
+  }
+  s = wave_sum(s);
+  if (use_hot) h = wave_sum(h);
+  if ((tid & 63) == 0) {
+    AllPart* part = reinterpret_cast<AllPart*>(W.ws + WS_HIST) + sl * WNW + (tid >> 6);
+    part->s = s; part->h = h; part->m = M;
   }
 }
 
 // ---------------------------------------------------------------- bins ------------------------
-template <typename DT>
+template <typename DT, bool use_hot>
 __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kernel(const SampleArgs a) {
   constexpr int EPL = Io<DT>::EPL;
   constexpr int G = ItemLoads<DT>::G;
@@ -459,12 +556,8 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
   ids.request(a, (unsigned)cur + 1u, n_wide, ids.row_n, ids.act_n);
   WideRow W = load_row(a, (unsigned)cur);
   ids.settle();
-  {  // nothing to do for rows without truncation (a workgroup's items lie in at most two slots)
-    const int last = (int)((I.i1 - 1u) / I.n_sl);
-    if ((ids.act_c & 2u) && (last == cur || (last == cur + 1 && (ids.act_n & 2u)))) return;
-  }
   ItemLoads<DT> N;  // the next item's loads
-  item_fetch<DT, false, true>(N, a, I.i0, I.n_sl, cur, ids);
+  item_fetch<DT, use_hot, false>(N, a, I.i0, I.n_sl, cur, ids);
   for (int b = tid; b <= NBW; b += WT) lh[b] = 0ull;
   u64 mtop = 0ull;
   unsigned ntop = 0u;      // top-k route: columns at or above g seen by this thread
@@ -501,10 +594,6 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
       ids.settle();
       for (int b = tid; b <= NBW; b += WT) lh[b] = 0ull;
     }
-    if (W.mode == WIDE_ALL) {  // every column survives: nothing to find in a first pass
-      if (more) item_fetch<DT, false, true>(N, a, it + 1u, I.n_sl, cur, ids);
-      continue;
-    }
     const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
     HistPre<DT> HP;
     if (W.h_active) {
@@ -512,7 +601,11 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
       __syncthreads();
       hist_fetch<DT>(HP, Tb, W.ws, a, rowp, c0, V);  // this item's own loads go first: loads return in order
     } else __syncthreads();  // the zeroed bins are visible
-    if (more) item_fetch<DT, false, true>(N, a, it + 1u, I.n_sl, cur, ids);
+    if (more) item_fetch<DT, use_hot, false>(N, a, it + 1u, I.n_sl, cur, ids);
+    if (W.mode == WIDE_ALL) {  // every column survives: this wave's masses
+      all_slice<DT, use_hot>(L, HP, Tb, W, a, rowp, c0, sl);
+      continue;
+    }
     auto one = [&](float z, int) {
       if (W.mode == WIDE_MIN_P) { ymax = fmaxf(ymax, tempered(z, W.C)); return; }
       int b; float y;
@@ -622,8 +715,12 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
   ids.request(a, (unsigned)cur, n_wide, ids.row_c, ids.act_c);
   ids.request(a, (unsigned)cur + 1u, n_wide, ids.row_n, ids.act_n);
   ids.settle();
+  {  // nothing to do for rows without truncation (a workgroup's items lie in at most two slots, or the first is one of them)
+    const int last = (int)((I.i1 - 1u) / I.n_sl);
+    if ((ids.act_c & 2u) && (last == cur || (last == cur + 1 && (ids.act_n & 2u)))) return;
+  }
   ItemLoads<DT> N;  // the next item's loads
-  item_fetch<DT, use_hot>(N, a, I.i0, I.n_sl, cur, ids);
+  item_fetch<DT, use_hot, true>(N, a, I.i0, I.n_sl, cur, ids);
   WideRow W;
   int bstar = -1;
   float thr_y = -INFINITY;
@@ -634,6 +731,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     ids.settle();
     const RowCut rc = row_cut(S, W);
     bstar = rc.bstar; thr_y = rc.thr_y; valid = rc.valid;
+    valid = valid && W.mode != WIDE_ALL;  // (done by the bins kernel)
     if (valid) zc = z_cut(W, bstar, thr_y);
   };
   // What a thread gathers over this workgroup's slices of one row, reduced when the row ends:
@@ -688,7 +786,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
       enter_row(slot);
     }
     if (!valid) {  // the finishing kernel hands the row on
-      if (more) item_fetch<DT, use_hot>(N, a, it + 1u, I.n_sl, cur, ids);
+      if (more) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
       continue;
     }
     const int c0 = sl * SLC;
@@ -698,7 +796,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     __syncthreads();
     HistPre<DT> HP;
     if (W.h_active) hist_fetch<DT>(HP, Tb, W.ws, a, rowp, c0, V);  // this item's own loads go first: loads return in order
-    if (more) item_fetch<DT, use_hot>(N, a, it + 1u, I.n_sl, cur, ids);
+    if (more) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
     u64 acc_s = 0ull, acc1 = 0ull;  // this slice: mass of the sure columns, and of the hot ones among them
     // one column the slow way: history columns and the ragged end of the row
     auto one = [&](float z, int idx) {
@@ -721,9 +819,9 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     };
     // The main line: every column's mass, and its class by the logit alone; boundary columns follow
     // under a wave-wide test.
-    auto sweep = [&](auto unit_tau_c, auto want_all_c, auto all_sure_c) {
-      // UT: tau == 1; WANT_ALL: the row's mass is summed here (no bins); ALL_SURE: no truncation, every column survives
-      constexpr bool UT = decltype(unit_tau_c)::value, WANT_ALL = decltype(want_all_c)::value, ALL_SURE = decltype(all_sure_c)::value;
+    auto sweep = [&](auto unit_tau_c, auto want_all_c) {
+      // UT: tau == 1; WANT_ALL: the row's mass is summed here (no bins)
+      constexpr bool UT = decltype(unit_tau_c)::value, WANT_ALL = decltype(want_all_c)::value;
 #pragma unroll
       for (int j = 0; j < G; ++j) {
         const int idx0 = c0 + (j * WT + tid) * EPL;
@@ -737,7 +835,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
 #pragma unroll
             for (int e = 0; e < EPL; ++e) z[e] = ((live >> e) & 1u) ? z[e] : -INFINITY;
             // ... but -inf counts as sure when every value does
-            if (ALL_SURE || zc.z_sure == -INFINITY) n_sure -= (unsigned)__popc(~live & EMASK);
+            if (zc.z_sure == -INFINITY) n_sure -= (unsigned)__popc(~live & EMASK);
           }
           // group sums of the masses' two parts (units of 2^24, and the rest): <= 8 terms of <= 2^25
           uint32_t sh = 0u, sl_ = 0u, hh = 0u, hl = 0u, ah = 0u, al = 0u;
@@ -749,23 +847,17 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
             uint32_t hi, lo;
             float_to_parts(w * MSCALE, hi, lo);
             ymax = fmaxf(ymax, y);
-            if (ALL_SURE) {
-              sh += hi; sl_ += lo;
-              if (use_hot) { const uint32_t hm = (uint32_t)(-(int32_t)((L.hq[j] >> e) & 1u)); hh += hi & hm; hl += lo & hm; }
-            } else {
-              const bool sure = z[e] >= zc.z_sure;
-              const uint32_t his = sure ? hi : 0u, los = sure ? lo : 0u;
-              sh += his; sl_ += los;
-              if (use_hot) { const uint32_t hm = (uint32_t)(-(int32_t)((L.hq[j] >> e) & 1u)); hh += his & hm; hl += los & hm; }
-              if (WANT_ALL) { ah += hi; al += lo; }
-              n_sure += sure ? 1u : 0u;
-              any_edge = any_edge || (z[e] >= zc.z_edge && !sure);
-            }
+            const bool sure = z[e] >= zc.z_sure;
+            const uint32_t his = sure ? hi : 0u, los = sure ? lo : 0u;
+            sh += his; sl_ += los;
+            if (use_hot) { const uint32_t hm = (uint32_t)(-(int32_t)((L.hq[j] >> e) & 1u)); hh += his & hm; hl += los & hm; }
+            if (WANT_ALL) { ah += hi; al += lo; }
+            n_sure += sure ? 1u : 0u;
+            any_edge = any_edge || (z[e] >= zc.z_edge && !sure);
           }
           acc_s += parts_to_u64(sh, sl_);
           if (use_hot) acc1 += parts_to_u64(hh, hl);
-          if (ALL_SURE) { acc_all += parts_to_u64(sh, sl_); n_sure += (unsigned)EPL; }
-          else if (WANT_ALL) acc_all += parts_to_u64(ah, al);
+          if (WANT_ALL) acc_all += parts_to_u64(ah, al);
           if (__ballot(any_edge)) {  // boundary columns: few per wave, element by element
 #pragma unroll
             for (int e = 0; e < EPL; ++e) {
@@ -786,9 +878,9 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     const std::true_type yes{};
     const std::false_type no{};
     if (W.tau == 1.0f) {
-      if (W.mode == WIDE_TOP_P || W.mode == WIDE_TOP_K) sweep(yes, no, no); else if (W.mode == WIDE_ALL) sweep(yes, yes, yes); else sweep(yes, yes, no);
+      if (W.mode == WIDE_TOP_P || W.mode == WIDE_TOP_K) sweep(yes, no); else sweep(yes, yes);
     } else {
-      if (W.mode == WIDE_TOP_P || W.mode == WIDE_TOP_K) sweep(no, no, no); else if (W.mode == WIDE_ALL) sweep(no, yes, yes); else sweep(no, yes, no);
+      if (W.mode == WIDE_TOP_P || W.mode == WIDE_TOP_K) sweep(no, no); else sweep(no, yes);
     }
     if (W.h_active) {  // the history columns, whose logits and counts were requested before the main line
       hist_stage<DT>(Tb, HP, W.ws, a, rowp, c0, V);
@@ -1010,6 +1102,115 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   return S.out_id >= 0;
 }
 
+// A row without truncation, from its waves' parts: 2^44 fixed-point masses of the slices relative to the row
+// maximum, acceptance (section 5.3), the slice that holds the draw, and that slice's columns once more.
+template <typename DT>
+__device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS& S, SliceTabs& Tb, simple_row_diag& dg) {
+  constexpr int EPT = SLC / WT;
+  const int tid = threadIdx.x, V = a.V;
+  const int n_sl = (V + SLC - 1) / SLC;
+  static_assert(FAST_MAX_V / SLC <= WT, "a slice per thread");
+  const uint32_t* hot_bits = a.hot_bits;
+  const bool use_hot = hot_bits != nullptr;
+  const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
+  const AllPart* parts = reinterpret_cast<const AllPart*>(W.ws + WS_HIST);
+  double ps[WNW], ph[WNW];
+  float pm[WNW], m = LOWEST;
+#pragma unroll
+  for (int k = 0; k < WNW; ++k) {
+    ps[k] = 0.0; ph[k] = 0.0; pm[k] = LOWEST;
+    if (tid < n_sl) {
+      const AllPart* q = parts + tid * WNW + k;
+      ps[k] = as_global(q)->s; ph[k] = as_global(q)->h; pm[k] = as_global(q)->m;
+    }
+  }
+  double u3[3];
+  row_uniforms(a.seed, a.row_offset + (uint64_t)W.row, a.step, u3);
+  if (tid == 0) { S.bd = -1; S.out_id = -1; S.flags = 0u; }
+#pragma unroll
+  for (int k = 0; k < WNW; ++k) m = fmaxf(m, pm[k]);
+  {
+    const float wm = wave_max(m);
+    if ((tid & 63) == 0) S.wmax[tid >> 6] = wm;
+  }
+  __syncthreads();
+  float y_max = S.wmax[0];
+#pragma unroll
+  for (int w = 1; w < WNW; ++w) y_max = fmaxf(y_max, S.wmax[w]);
+  double s = 0.0, h = 0.0;
+#pragma unroll
+  for (int k = 0; k < WNW; ++k) {
+    const double f = exp((double)pm[k] - (double)y_max) * WSCALE;
+    s += ps[k] * f; h += ph[k] * f;
+  }
+  if (!(s >= 0.0)) atomicOr(&S.flags, 1u);  // a NaN, or +inf less itself
+  const u64 m_all = s >= 0.0 ? (u64)__double2ull_rn(s) : 0ull;
+  const u64 m_hot = (use_hot && s >= 0.0) ? min(m_all, (u64)__double2ull_rn(h)) : 0ull;
+  unsigned near = (tid < n_sl && m >= y_max - 88.0f) ? 1u : 0u, finite = (tid < n_sl && m > LOWEST) ? 1u : 0u;
+  u64 S_K = m_all, mx = 0ull;
+  blk_reduce<WNW>(S, near, finite, mx, S_K);  // barriers inside
+  const u64 S_H = use_hot ? blk_sum_u64<WNW>(S, m_hot) : 0ull;
+  // one slice so far above all others that their exponentials leave float32's range: the general kernel's
+  if (near == 1u && finite > 1u) return false;
+  if (S.flags || !(y_max > LOWEST) || y_max == INFINITY) return false;
+  bool pick_hot = false;
+  if (use_hot) {
+    pick_hot = (S_H > 0ull) && (u3[1] * (double)S_K <= (double)S_H);
+    dg.alpha = (double)S_H / (double)S_K;
+    dg.flags |= SIMPLE_DIAG_SHVS | (pick_hot ? SIMPLE_DIAG_ACCEPTED : 0u);
+  }
+  const u64 S_cls = use_hot ? (pick_hot ? S_H : S_K - S_H) : S_K;
+  const double u = use_hot ? (pick_hot ? u3[0] : u3[2]) : u3[0];
+  if (S_cls == 0ull) return false;
+  u64 tfix = (u64)__double2ull_rd(u * (double)S_cls);
+  if (tfix >= S_cls) tfix = S_cls - 1ull;
+  {
+    const u64 mc = use_hot ? (pick_hot ? m_hot : m_all - m_hot) : m_all;
+    unsigned ce, ct; u64 me, mt;
+    blk_excl_scan2<WNW>(S, 0u, mc, ce, me, ct, mt);
+    if (mc > 0ull && me <= tfix && tfix < me + mc) { S.bd = tid; S.mab_d = tfix - me; S.mab_k = mc; S.wmax[15] = m; }
+  }
+  __syncthreads();
+  const int t = S.bd;
+  if (t < 0) return false;
+  // the columns' shares of the slice, relative to its largest, in ascending id
+  const int c0 = t * SLC;
+  const float M = S.wmax[15];
+  const double place = (double)S.mab_d / (double)S.mab_k;
+  float zv[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) { const int idx = c0 + tid * EPT + e; zv[e] = (idx < V) ? Io<DT>::one(rowp + idx) : -INFINITY; }
+  if (W.h_active) load_slice(Tb, W, a, c0);
+  u64 q[EPT], lsum = 0ull;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const int o = tid * EPT + e;
+    q[e] = 0ull;
+    if (c0 + o < V) {
+      float z = zv[e];
+      if (W.h_active && slice_bit(o, Tb)) z = slice_value(z, o, Tb, W);
+      zv[e] = mass_rel(tempered(z, W.C), M);
+      if (!use_hot || (hot_bit(hot_bits, (uint32_t)(c0 + o)) != 0u) == pick_hot) q[e] = (u64)__double2ull_rn((double)zv[e] * WSCALE);
+    }
+    lsum += q[e];
+  }
+  unsigned ce, ct; u64 me, Q;
+  blk_excl_scan2<WNW>(S, 0u, lsum, ce, me, ct, Q);
+  u64 rq = (u64)__double2ull_rd(place * (double)Q);
+  if (Q > 0ull && rq >= Q) rq = Q - 1ull;
+  u64 run = me;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    if (q[e] > 0ull && run <= rq && rq < run + q[e]) { S.out_id = c0 + tid * EPT + e; S.wmax[0] = zv[e]; }
+    run += q[e];
+  }
+  __syncthreads();
+  dg.n_survivors = V;
+  dg.s_k = (double)S_K / WSCALE;
+  dg.p_chosen = (float)((double)S.wmax[0] * exp((double)M - (double)y_max) * WSCALE / (double)S_K);
+  return S.out_id >= 0;
+}
+
 template <typename DT>
 __global__ __launch_bounds__(WT) void wide_finish_kernel(const SampleArgs a) {
   __shared__ SliceTabs Tb;
@@ -1028,7 +1229,7 @@ __global__ __launch_bounds__(WT) void wide_finish_kernel(const SampleArgs a) {
     dg.s_k = 0.0; dg.p_chosen = 0.0f; dg.n_survivors = 0; dg.reserved = 0u;
     dg.flags = SIMPLE_DIAG_WIDE | W.flags;
     if (a.hot_bits && a.hot_flags && *a.hot_flags) dg.flags |= SIMPLE_DIAG_BAD_HOT_SET;
-    const bool ok = finish_row<DT>(a, W, S, Tb, rcmp, rl, dmass, tiles, dg);
+    const bool ok = W.mode == WIDE_ALL ? finish_all_row<DT>(a, W, S, Tb, dg) : finish_row<DT>(a, W, S, Tb, rcmp, rl, dmass, tiles, dg);
     if (tid == 0) {
       if (!ok) hand_on(a, W.row);
       else {
@@ -1049,12 +1250,14 @@ hipError_t launch_wide(const SampleArgs& a, int dtype, hipStream_t st) {
   // registers and LDS; a workgroup then takes a contiguous run of slices, mostly of one row.
   const dim3 bins((unsigned)a.n_cu * 5u), cls((unsigned)a.n_cu * 4u), fin(1024), blk(fast::WT);
   if (dtype == SIMPLE_F32) {
-    hipLaunchKernelGGL((fast::wide_bins_kernel<float>), cls, blk, 0, st, a);  // (float32: four workgroups per compute unit, no spilled register)
+    if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<float, true>), cls, blk, 0, st, a);
+    else hipLaunchKernelGGL((fast::wide_bins_kernel<float, false>), cls, blk, 0, st, a);  // (float32: four workgroups per compute unit, no spilled register)
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_classify_kernel<float, true>), cls, blk, 0, st, a);
     else hipLaunchKernelGGL((fast::wide_classify_kernel<float, false>), cls, blk, 0, st, a);
     hipLaunchKernelGGL((fast::wide_finish_kernel<float>), fin, blk, 0, st, a);
   } else {
-    hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t>), bins, blk, 0, st, a);
+    if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, true>), bins, blk, 0, st, a);
+    else hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, false>), bins, blk, 0, st, a);
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_classify_kernel<uint16_t, true>), cls, blk, 0, st, a);
     else hipLaunchKernelGGL((fast::wide_classify_kernel<uint16_t, false>), cls, blk, 0, st, a);
     hipLaunchKernelGGL((fast::wide_finish_kernel<uint16_t>), fin, blk, 0, st, a);
