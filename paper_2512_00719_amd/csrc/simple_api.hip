@@ -88,6 +88,11 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   if (!elem || V >= (int64_t)FAST_MAX_V || max_nnz > 65535) return F;
   const int64_t tile = 64 * 4 * ((dtype == SIMPLE_F32) ? 4 : 8);
   const uint32_t n_words = (uint32_t)((V + 31) / 32), n_pairs = (n_words + 1u) / 2u;
+  // A vocabulary that the list holds whole (registers: CAPF_WHOLE columns per thread; LDS: 8 bytes a
+  // column and the long-list tables): every column is listed.  Beyond that a sample needs its two tiles
+  // per wave; between the two (bfloat16 rows of 12,289 to 16,383 columns) the general kernel serves the call.
+  // Four float32 rows of 1024 columns: 51 us in the general kernel, 23 us listed whole.
+  const bool whole = V <= (int64_t)CAPF_WHOLE * 1024 && V / tile < 8;
   uint32_t off = 0;
   F.bitmap = 0;
   if (with_history) {
@@ -98,19 +103,29 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   }
   const uint32_t tables = 256u * 12u + 256u * 16u;           // bucket tables of the long-list epilogue
   uint32_t body = off < 28672u ? 28672u : off;               // >= 14 KB of sorted-epilogue arrays, >= 3072-entry list
-  F.long_cap = (body - tables) / 8u;
-  F.samp = body;
-  // the sample merge area holds SPW keys per wave
+  if (whole && body < align16((uint32_t)V * 8u + tables)) body = align16((uint32_t)V * 8u + tables);
   F.threads = ((int64_t)body + 2048 <= (int64_t)lds_limit / 4) ? 256 : 512;  // four workgroups per compute unit, static LDS included
   if (V >= ((int64_t)1 << 18)) F.threads = 512;  // a sample of two tiles per wave: four waves' is too small a share of such rows
   if (B <= (int64_t)n_cu) F.threads = 1024;
   else if (B <= 2 * (int64_t)n_cu) F.threads = 512;
   while (F.threads > 256 && V / tile < 2 * (F.threads / 64)) F.threads /= 2;  // two tiles per wave
+  if (whole) {
+    F.whole = 1u;
+    F.threads = 256;
+    while (V > (int64_t)CAPF_WHOLE * F.threads) F.threads *= 2;
+  }
+  // Room for as many long-list entries as the epilogue's registers hold, where the compute unit's LDS has it
+  // at the occupancy chosen (a sample that admits a few hundred columns too many otherwise sends its row to
+  // the general kernel: 1024 float32 rows of 128,256 columns 207 us, 260 with one such row).
+  const uint32_t roomy = F.threads == 256 ? 36864u : align16((uint32_t)(capf_per_thread(F.threads, whole) * F.threads) * 8u + tables);
+  if (!whole && body < roomy) body = roomy;
+  F.long_cap = (body - tables) / 8u;
+  F.samp = body;  // the sample merge area holds SPW keys per wave
   const uint32_t total = body + align16((uint32_t)(F.threads / 64) * (uint32_t)SAMPLE_PER_WAVE * 4u);
-  const uint32_t reg_cap = (uint32_t)(CAPF_PER_THREAD * F.threads);  // the epilogue moves the list to registers
+  const uint32_t reg_cap = (uint32_t)(capf_per_thread(F.threads, whole) * F.threads);  // the epilogue moves the list to registers
   F.list_cap = body / 8u < reg_cap ? body / 8u : reg_cap;
   if ((int64_t)total + 1024 > (int64_t)lds_limit) return F;  // total stays 0
-  if (V / tile < 2 * (F.threads / 64)) return F;
+  if (!whole && V / tile < 2 * (F.threads / 64)) return F;
   F.total = total;
   return F;
 }
@@ -368,7 +383,7 @@ static int sample_impl(simple_ctx* ctx, const simple_state* state, const int32_t
   a.F = simple::make_fast_layout(V, dtype, with_hist ? ctx->max_nnz : 0, with_hist, elem, ctx->lds_limit,
                                  B < per_launch ? B : per_launch, ctx->n_cu);
   a.gated = (a.F.total != 0u || tail) ? 1 : 0;
-  a.pattern_on = (dtype == SIMPLE_BF16 && V < (int64_t)simple::FAST_MAX_V) ? (tail ? 2 : (a.F.total != 0u ? 1 : 0)) : 0;
+  a.pattern_on = (dtype == SIMPLE_BF16 && V < (int64_t)simple::FAST_MAX_V) ? (tail ? 2 : (a.F.total != 0u && !a.F.whole ? 1 : 0)) : 0;
   for (int64_t b0 = 0; b0 < B; b0 += per_launch) {
     const int64_t nb = (B - b0 < per_launch) ? (B - b0) : per_launch;
     a.B = (int)nb;
@@ -382,7 +397,7 @@ static int sample_impl(simple_ctx* ctx, const simple_state* state, const int32_t
     a.diag = diag_dev ? diag_dev + b0 : nullptr;
     a.logprobs = ctx->logprobs ? ctx->logprobs + b0 : nullptr;
     a.eos_out = ctx->eos_out ? ctx->eos_out + b0 : nullptr;
-    a.order = (a.F.total != 0u && !tail && nb > (int64_t)ctx->n_cu) ? ctx->order : nullptr;
+    a.order = (a.F.total != 0u && !a.F.whole && !tail && nb > (int64_t)ctx->n_cu) ? ctx->order : nullptr;
     a.parity = ctx->parity;
     if (a.gated) ctx->parity ^= 1;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;

@@ -125,6 +125,7 @@ __device__ __forceinline__ void stream_tile(const typename Io<DT>::Raw (&A)[UNR]
 }
 
 // ---------------------------------------------------------------- epilogue --------------------
+constexpr unsigned SHORT_WAVE = 1u << 16;  // mark beside a wave's sample count: fewer finite columns than asked for
 enum { FIN_DONE = 0, FIN_PENDING = 1, FIN_WIDE = 2 };
 
 __device__ __forceinline__ u64 pick8(const u64 (&a)[8], int j) {
@@ -197,7 +198,7 @@ __device__ __forceinline__ int finalize_small(FS& S, const RowCfg& R, unsigned n
         key_thr = fkey(thr);
         m_cert = key_thr > key_g;
       }
-      const bool known = R.k_on || p_found || m_cert;
+      const bool known = R.k_on || p_found || m_cert || R.all;
       if (!known) rc = (R.need_sum || (!R.k_on && !R.p_on && R.minp_on)) ? FIN_WIDE : FIN_PENDING;
       // every cut is a prefix of the sorted order; the first entry always survives
       const bool use_hot = hot_bits != nullptr;
@@ -260,12 +261,14 @@ __device__ __forceinline__ int finalize_small(FS& S, const RowCfg& R, unsigned n
   return (S.out_id >= 0) ? FIN_DONE : FIN_PENDING;
 }
 
+constexpr float MAX_SPAN = 64.0f;  // a complete list may reach further down: what lies there shares the last bucket
+
 // Long lists (more than MEMB certified entries, in LDS as keys lk[] / ids li[]): bucket tables over
 // the key range locate each cut; only the bucket that holds a cut is resolved entry by entry.
 // Same decisions as finalize_small.
 template <int NTHR>
 __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n, unsigned n_unc, uint32_t kmax,
-                                             uint32_t key_g, float g, double S_below, const uint32_t* lk, const uint32_t* li,
+                                             uint32_t key_g, uint32_t key_lo, bool sliced, float g, double S_below, const uint32_t* lk, const uint32_t* li,
                                              unsigned char* tables, const uint32_t* __restrict__ hot_bits, simple_row_diag& dg) {
   constexpr int NWV = NTHR / 64;
   const int tid = threadIdx.x;
@@ -274,13 +277,20 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
   u64* mc = reinterpret_cast<u64*>(tables + NBF * 12);               // MEMB2 * 8
   u64* mw = reinterpret_cast<u64*>(tables + NBF * 12 + MEMB2 * 8);   // MEMB2 * 8
   const float y_max = keyf(kmax);
-  // buckets are linear in the tempered value (key space is logarithmic around zero); monotone in the key
-  const float bscale = (float)NBF / fmaxf(y_max - keyf(key_g), 1e-30f);
+  // buckets are linear in the tempered value (key space is logarithmic around zero), down to the list's
+  // lower end; monotone in the key
+  const float bscale = (float)NBF / fmaxf(fminf(y_max - keyf(key_lo), MAX_SPAN), 1e-30f);
   auto bucket_of = [&](uint32_t k) { return (unsigned)min((int)((y_max - keyf(k)) * bscale), NBF - 1); };
   u64 cl = 0ull;
   for (unsigned i = tid; i < n; i += NTHR) { const u64 c = composite(lk[i], li[i]); cl = (c > cl) ? c : cl; }
   unsigned da = 0, db = 0; u64 cmax = cl, dd = 0ull;
   blk_reduce<NWV>(S, da, db, cmax, dd);
+  if (R.greedy) {  // the first of the total order
+    if (tid == 0) S.out_id = (int)(0xFFFFFFFFu - (uint32_t)cmax);
+    __syncthreads();
+    dg.n_survivors = 1; dg.p_chosen = 1.0f;
+    return FIN_DONE;
+  }
   for (int i = tid; i < NBF; i += NTHR) { fcnt[i] = 0u; fmass[i] = 0ull; }
   __syncthreads();
   for (unsigned i = tid; i < n; i += NTHR) {
@@ -352,7 +362,11 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
       }
       __syncthreads();
       const unsigned nm = S.memb;
-      if (nm > (unsigned)MEMB2) return FIN_PENDING;
+      if (nm > (unsigned)MEMB2) {  // ties wider than the member table: the sliced kernels resolve them, from the bucket's upper end down
+        if (!sliced) return FIN_PENDING;
+        if (tid == 0) S.wmax[0] = y_max - (float)bp / bscale;
+        return FIN_WIDE;
+      }
       const u64 mab = S.mab_p;
       for (unsigned mi = tid; mi < nm; mi += NTHR) {
         const u64 cm = mc[mi], wm = mw[mi];
@@ -375,7 +389,7 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
     const uint32_t key_thr = fkey(thr);
     if (key_thr > key_g) { cut_m = (u64)key_thr << 32; m_cert = true; }
   }
-  const bool known = R.k_on || p_found || m_cert;
+  const bool known = R.k_on || p_found || m_cert || R.all;
   if (!known) return (R.need_sum || (!R.k_on && !R.p_on && R.minp_on)) ? FIN_WIDE : FIN_PENDING;
   if (R.k_on && R.p_on && !p_found) { return FIN_PENDING; }  // cannot happen: the top-k prefix holds its own mass
   u64 cut = cut_k;
@@ -465,12 +479,14 @@ __device__ inline void queue_pending(const SampleArgs& a, int row) {
 // workgroups of 256 threads, two of 512, one of 1024.)
 // STATEFUL: the rows' histories come from an incremental penalty state (its own instantiation, so
 // that the stateless kernel carries none of that code).
-template <typename DT, int NTHR, bool STATEFUL>
+// WHOLE: the list holds every column of a row (a.F.whole; its own instantiation, since with the test at run
+// time the sampled rows' prologue was 1 us slower: 8 bfloat16 rows of 151,936 columns 44.4 against 45.9 us).
+template <typename DT, int NTHR, bool STATEFUL, bool WHOLE>
 __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) {
   constexpr int NWV = NTHR / 64;
   constexpr int EPL = Io<DT>::EPL;
   constexpr int T = 64 * EPL * UNR;
-  constexpr int PER = CAPF_PER_THREAD;
+  constexpr int PER = capf_per_thread(NTHR, WHOLE);
   typedef typename Io<DT>::Raw Raw;
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ FS S;
@@ -484,13 +500,20 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     return;
   }
   // this wave's first two tiles (its threshold sample): issued before anything else
-  const int nfull = V / T;  // the host guarantees nfull >= 2 * NWV
+  // (a row that fits the list whole has at most one tile per wave and no sample)
+  const int nfull = V / T;  // else the host guarantees nfull >= 2 * NWV
   const int t0 = (int)(((long long)wave * nfull) / NWV);
+  const int t_end = (int)(((long long)(wave + 1) * nfull) / NWV);
+  constexpr bool whole = WHOLE;
   Raw A[UNR], Bf[UNR];
+  if (!whole || t0 < t_end) {
 #pragma unroll
-  for (int u = 0; u < UNR; ++u) A[u] = Io<DT>::load(rowp + (size_t)t0 * T + u * 64 * EPL + lane * EPL);
+    for (int u = 0; u < UNR; ++u) A[u] = Io<DT>::load(rowp + (size_t)t0 * T + u * 64 * EPL + lane * EPL);
+  }
+  if (!whole) {
 #pragma unroll
-  for (int u = 0; u < UNR; ++u) Bf[u] = Io<DT>::load(rowp + (size_t)(t0 + 1) * T + u * 64 * EPL + lane * EPL);
+    for (int u = 0; u < UNR; ++u) Bf[u] = Io<DT>::load(rowp + (size_t)(t0 + 1) * T + u * 64 * EPL + lane * EPL);
+  }
   const simple_row_params par = a.params[row];
   if (blockIdx.x == 0 && tid == 0) { a.pend[a.parity ^ 1] = 0u; a.wq[a.parity ^ 1] = 0u; }  // the previous launch's counts
   uint32_t* samp = reinterpret_cast<uint32_t*>(lds + a.F.samp);
@@ -522,12 +545,14 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   // raw logits would miss columns).
   // ... and rows with top-k alone beyond the list's reach (any penalties).
   const bool big_k = !R.greedy && R.k_on && par.top_k > KMAXF && !R.p_on && !R.minp_on;
-  const bool straight = no_trunc || big_k || (!R.greedy && !R.k_on && !R.p_le0 && h_active && !lowering);
+  // (a list that holds the whole row needs no threshold and decides all of these itself)
+  const bool straight = !whole && (no_trunc || big_k || (!R.greedy && !R.k_on && !R.p_le0 && h_active && !lowering));
+  R.all = whole && no_trunc;
   const uint32_t straight_mode = big_k ? (uint32_t)WIDE_TOP_K
                                        : (R.p_on ? (uint32_t)WIDE_TOP_P : (uint32_t)WIDE_MIN_P);
-  const bool eligible = straight ? (!bad_par && !too_long)
-                                 : (!bad_par && !too_long && (!h_active || lowering) &&
-                                    (R.greedy || !R.k_on || par.top_k <= KMAXF));
+  const bool eligible = (straight || whole) ? (!bad_par && !too_long)
+                                            : (!bad_par && !too_long && (!h_active || lowering) &&
+                                               (R.greedy || !R.k_on || par.top_k <= KMAXF));
   if (!eligible) {  // the general kernel takes the row (it also reports parameter errors)
     if (tid == 0) queue_pending(a, row);
     return;
@@ -537,7 +562,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   const int k_sel = R.greedy ? 1 : (R.k_on ? (big_k ? par.top_k / 4 : par.top_k) : (R.p_le0 ? 1 : KMAXF));
   if (tid == 0) {
     S.cand_count = 0u; S.flags = 0u; S.kmax = 0u; S.memb = 0u; S.bk = -1; S.bp = -1; S.bd = -1;
-    S.need_k = 0u; S.cut_k = 0ull; S.cut_p = 0ull; S.n_p = 0u; S.out_id = -1; S.out_w = 0ull;
+    S.need_k = 0u; S.cut_k = 0ull; S.cut_p = 0ull; S.n_p = 0u; S.out_id = -1; S.out_w = 0ull; S.kmin = 0xFFFFFFFFu;
     S.n2 = 0u; S.nunc = 0u; S.e_rc = FIN_PENDING; S.e_n = 0u; S.tile_ctr = 0u;
   }
   // ---- loads first: history ids, then this wave's two sample tiles ----
@@ -584,7 +609,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   // Hands the row to the kernels of the whole-vocabulary routes: a queue record, a cleared workspace
   // slot and the row's history tables (rebuilt first if the region no longer holds them).  False if
   // no slot is free.  All threads call.
-  auto queue_wide = [&](uint32_t mode, bool tables_live) -> bool {
+  auto queue_wide = [&](uint32_t mode, bool tables_live, float g_ref) -> bool {
     __syncthreads();
     if (H.active && !tables_live) {
       if (stateful) load_tables(true);
@@ -610,7 +635,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
     if (tid == 0) {
       WideRec rec;
-      rec.row = (uint32_t)row; rec.g = C.g; rec.mode = mode; rec.flags = S.flags & 0x3FFFFFFFu;
+      rec.row = (uint32_t)row; rec.g = g_ref; rec.mode = mode; rec.flags = S.flags & 0x3FFFFFFFu;
       rec.tau = R.tau; rec.top_p = R.top_p; rec.rep = par.rep_penalty; rec.freq = par.freq_penalty;
       rec.pres = par.pres_penalty; rec.nnz = nnz; rec.n_prompt = min(max(rh.n_prompt, 0), nnz); rec.h_active = h_active ? 1 : 0;
       rec.min_p = R.min_p; rec.top_k = par.top_k; rec.distinct = H.active ? S.distinct : 0u; rec.reserved1 = 0u;
@@ -619,11 +644,13 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
     return true;
   };
-  if (no_trunc) {  // every column survives: no threshold to look for
-    if (!queue_wide(WIDE_ALL, true) && tid == 0) queue_pending(a, row);
+  if (no_trunc && !whole) {  // every column survives: no threshold to look for
+    if (!queue_wide(WIDE_ALL, true, 0.0f) && tid == 0) queue_pending(a, row);
     return;
   }
 
+  bool complete = whole;  // the list takes every finite column
+  if (!whole) {
   // ---- threshold from the sample: three largest penalised values per lane, wave select, merge ----
   float a1 = -INFINITY, a2 = -INFINITY, a3 = -INFINITY;  // branch-free insertion; a NaN is ignored here
 #define SIMPLE_TAKE3(v) do { const float v_ = (v); const float m1_ = fmaxf(a1, v_), l1_ = fminf(a1, v_); \
@@ -647,7 +674,8 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     const unsigned q = min((unsigned)(SPW * 3 / 4), (unsigned)ceilf(r_w + 3.0f * sqrtf(r_w) + 2.0f));
     const uint32_t k3[3] = {fkey(a1), fkey(a2), fkey(a3)};
     // every lane's largest is >= the smallest of the lanes' largest: at least 64 >= q keys qualify
-    const uint32_t Kw = wave_threshold<3>(k3, q, q / 4u + 1u, wave_min_u32(k3[0]), wave_max_u32(k3[0]));
+    // (-inf is never kept: a wave short of q finite columns hands all of them on)
+    const uint32_t Kw = max(KEY_NEG_INF + 1u, wave_threshold<3>(k3, q, q / 4u + 1u, wave_min_u32(k3[0]), wave_max_u32(k3[0])));
     if (lane < SPW) samp[wave * SPW + lane] = 0u;
     unsigned have = 0;
 #pragma unroll
@@ -658,7 +686,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       have = min(have + (unsigned)__popcll(m), (unsigned)SPW);
     }
     const float wp = wave_max(a1);
-    if (lane == 0) { S.wmax[wave] = wp; S.wcnt[wave] = have; }
+    if (lane == 0) { S.wmax[wave] = wp; S.wcnt[wave] = have | (have < q ? SHORT_WAVE : 0u); }
   }
   __syncthreads();
   {
@@ -667,11 +695,17 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     unsigned total = 0;
     float Mp = S.wmax[0];
 #pragma unroll
-    for (int w = 0; w < NWV; ++w) { total += S.wcnt[w]; Mp = fmaxf(Mp, S.wmax[w]); }
+    for (int w = 0; w < NWV; ++w) { const unsigned c = S.wcnt[w]; total += c & (SHORT_WAVE - 1u); complete = complete || (c & SHORT_WAVE) != 0u; Mp = fmaxf(Mp, S.wmax[w]); }
     uint32_t kmn = 0xFFFFFFFFu, kmx = 0u;
 #pragma unroll
     for (int j = 0; j < NS; ++j) { ks[j] = samp[j * 64 + lane]; kmx = max(kmx, ks[j]); if (ks[j]) kmn = min(kmn, ks[j]); }
     kmn = wave_min_u32(kmn); kmx = wave_max_u32(kmx);
+    // Few finite columns in the sample (an allow-list masked the rest): the list takes all there are
+    // instead of a prefix of them.  Before, such rows admitted the masked columns too, overflowed the list
+    // and went to the general kernel (32 float32 rows of 128,256 columns, 8 of them with 2000 columns
+    // left: the call 451 to 536 us, 106 so).
+    // (the same in every lane: said so, the stream's tests on it stay scalar)
+    complete = __builtin_amdgcn_readfirstlane((complete && total < r_samp) ? 1 : 0) != 0;
     const unsigned need = max(1u, min(r_samp, total));
     float g = keyf(wave_threshold<NS>(ks, need, need / 8u + 1u, min(kmn, kmx), kmx));
     if (!R.greedy && !R.k_on && R.minp_on) {
@@ -683,12 +717,16 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
     C.g = g;
     C.y_g = R.greedy ? g : g / R.tau;
+  }
+  }
+  {
+    if (complete) { C.g = LOWEST; C.y_g = -INFINITY; }  // every finite column is listed, and certified
     C.inv_tau = 1.0 / (double)R.tau;
-    C.need_sum = R.need_sum;
+    C.need_sum = R.need_sum && !complete;  // (nothing lies below the list)
     C.l2e_tau = (float)(1.4426950408889634 / (double)R.tau);
   }
   if (straight) {
-    if (!queue_wide(straight_mode, true) && tid == 0) queue_pending(a, row);
+    if (!queue_wide(straight_mode, true, C.g) && tid == 0) queue_pending(a, row);
     return;
   }
   const bool minp_only = !R.greedy && !R.k_on && !R.p_on && R.minp_on;
@@ -705,8 +743,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   // 1 % slower at four waves, 1.5 to 3 % faster at eight).  No result depends on which wave took
   // which tile (the list is ranked by value and id, the masses are integers).
   constexpr bool HAND_OUT = NWV > 4;
-  const int t_end = (int)(((long long)(wave + 1) * nfull) / NWV);
-  const unsigned n_dyn = (unsigned)(nfull - 2 * NWV);
+  const unsigned n_dyn = (unsigned)max(nfull - 2 * NWV, 0);
   int t_own = t0 + 2;  // contiguous shares: this wave's next tile
   auto grab = [&]() -> int {  // the next tile for this wave, -1 if none; the same in every lane
     if constexpr (!HAND_OUT) {
@@ -728,7 +765,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     for (int u = 0; u < UNR; ++u) X[u] = Io<DT>::load(rowp + (size_t)t * T + u * 64 * EPL + lane * EPL);
   };
   {
-    int tA = t0, tB = t0 + 1;
+    int tA = (!whole || t0 < t_end) ? t0 : -1, tB = whole ? -1 : t0 + 1;
     int nx = grab();
     if constexpr (sizeof(DT) == 2) {
       // two buffers in turn, each refilled as soon as it has been consumed, so no registers are
@@ -744,7 +781,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
         if (tB >= 0) { fill(Bf, tB); nx = grab(); }
       }
     } else {
-      stream_tile<DT>(A, tA * T, C, S, lz, li, cap, below_mass);
+      if (!whole || tA >= 0) stream_tile<DT>(A, tA * T, C, S, lz, li, cap, below_mass);
       while (tB >= 0) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) A[u] = Bf[u];
@@ -779,10 +816,10 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   const unsigned n = S.cand_count;
   // the stream added 2^28 for every column at or above g: all of them were counted for the list
   if (C.need_sum && tid == 0) below_mass -= (u64)n << 28;
-  if (n > cap && (R.need_sum || minp_only)) {
+  if (n > cap && !complete && (R.need_sum || minp_only)) {
     // more columns at or above g than the list holds, and a cut that the whole-vocabulary routes
     // find without the list
-    if (queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, false)) return;
+    if (queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, false, C.g)) return;
   }
   if (n <= cap) {
     // the list moves to registers; the region takes the history tables again
@@ -803,7 +840,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
         const unsigned i = (unsigned)tid + (unsigned)j * NTHR;
         if (i < n) ez[j] = H.penalised_at(ez[j], (int)eid[j]);
       }
-      if (R.need_sum) {
+      if (C.need_sum) {
         // exact correction of the mass below g for the history columns (the stream summed their raw
         // values), once per distinct column: by the thread that first marked it when all ids sit in
         // registers, else by the thread that first claims the column's rank
@@ -868,7 +905,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
           if (y == INFINITY) err = true;
           else {
             key[j] = fkey(y);
-            if (R.need_sum) {
+            if (C.need_sum) {
               int b;
               const float w = mass_term(z, C, b);
               if (w > 2097152.0f) peaked = true;  // 2^21: far too peaked for a wide nucleus
@@ -876,31 +913,39 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
               if (key[j] > key_g) mcert += mass_fix(w);
             }
           }
-        } else if (R.need_sum) below_mass += (u64)below_term(z, C);
+        } else if (C.need_sum) below_mass += (u64)below_term(z, C);
       }
       kloc = max(kloc, key[j]);
     }
     if (kloc) atomicMax(&S.kmax, kloc);
+    if (complete) {
+      uint32_t kmin = 0xFFFFFFFFu;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) if (key[j] > key_g) kmin = min(kmin, key[j]);
+      if (kmin != 0xFFFFFFFFu) atomicMin(&S.kmin, kmin);
+    }
     if (err) atomicOr(&S.flags, SIMPLE_DIAG_ERROR | SIMPLE_DIAG_BAD_LOGIT);
     if (peaked) atomicOr(&S.flags, 1u << 30);
     __syncthreads();
     // mass below g (integer, exact) and the decision between the list and the kernels that follow
     u64 S_below_int = 0ull, M_list = 0ull, M_cert = 0ull;
     bool wide = false;
-    if (R.need_sum) {
+    if (C.need_sum) {
       S_below_int = blk_sum_u64<NWV>(S, below_mass);
       M_list = blk_sum_u64<NWV>(S, mlist);
       M_cert = blk_sum_u64<NWV>(S, mcert);
       const u64 target = (u64)__double2ull_ru((double)R.top_p * (double)(M_list + S_below_int));
-      wide = !R.minp_on && M_cert < target;
+      // (a column more than 2^21 above g: these sums say nothing, the sorted list does)
+      wide = !R.minp_on && M_cert < target && !((S.flags >> 30) & 1u);
     }
     const double S_below = (double)S_below_int / (double)MSCALE;
     const uint32_t kmax = S.kmax;
+    if (tid == 0) S.wmax[0] = -INFINITY;  // (lower end of what the sliced kernels may take as above their threshold)
     bool tables_live = false;  // the region still holds the history tables
     if (S.flags & SIMPLE_DIAG_ERROR) rc = FIN_DONE;
     else if (kmax <= key_g || kmax <= KEY_NEG_INF) rc = FIN_PENDING;
     else if (wide) {
-      rc = ((S.flags >> 30) & 1u) ? FIN_PENDING : FIN_WIDE;
+      rc = FIN_WIDE;
       tables_live = true;
     } else {
       // certified entries (tempered value strictly above fl(g / tau)) as composites
@@ -920,6 +965,8 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       if (nul) atomicAdd(&S.nunc, nul);
       __syncthreads();
       const unsigned n_cert = S.n2, n_unc = S.nunc;
+      const int k_asked = R.top_k;  // a complete list shorter than k: the rest of the prefix has no mass
+      if (complete && R.k_on) R.top_k = min(R.top_k, (int)n_cert);
       if (R.k_on && !R.greedy && n_cert < (unsigned)R.top_k) rc = FIN_PENDING;  // the sampled threshold admitted too few
       else if (n_cert <= (unsigned)MEMB) {
         rc = finalize_small<NTHR>(S, R, n_cert, n_unc, kmax, key_g, C.g, S_below, mc, sc, sw, sid, hot_bits, dg);
@@ -936,14 +983,19 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
           if (key[j]) { const unsigned slot = atomicAdd(&S.n2, 1u); lk[slot] = key[j]; lid[slot] = eid[j]; }
         }
         __syncthreads();
-        rc = finalize_long<NTHR>(S, R, n_cert, n_unc, kmax, key_g, C.g, S_below, lk, lid, lds + (size_t)lcap * 8u, hot_bits, dg);
+        rc = finalize_long<NTHR>(S, R, n_cert, n_unc, kmax, key_g, complete ? S.kmin : key_g, C.need_sum, C.g, S_below, lk, lid, lds + (size_t)lcap * 8u, hot_bits, dg);
       }
-      if (rc == FIN_WIDE && ((S.flags >> 30) & 1u)) rc = FIN_PENDING;
+      // -inf columns without mass among the survivors of a count alone, or where nothing is truncated
+      if (complete && !R.greedy && !R.p_on && !R.minp_on) dg.n_survivors = R.k_on ? k_asked : V;
     }
 
     // ---- a cut below the list's reach: the row goes to the kernels that follow ----
+    // (masses there are relative to the threshold and reach 2^21 above it: where the row maximum stands
+    // higher, the threshold is moved up to e^13.5 below it, and above a bucket of ties that holds the cut)
     if (rc == FIN_WIDE) {
-      if (queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, tables_live)) return;
+      __syncthreads();
+      const float y_ref = fmaxf(keyf(kmax) - 13.5f, S.wmax[0]);
+      if (queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, tables_live, fmaxf(C.g, y_ref * R.tau))) return;
       rc = FIN_PENDING;  // no free slot: the general kernel takes the row
     }
   }
@@ -968,20 +1020,18 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
 }  // namespace simple
 namespace simple {
 
-template <bool STATEFUL>
-static hipError_t launch_fast_instance(const SampleArgs& a, int dtype, hipStream_t st) {
+template <typename DT, bool STATEFUL, bool WHOLE>
+static hipError_t launch_fast_instance(const SampleArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)a.B);
-  if (a.F.threads == 256) {
-    if (dtype == SIMPLE_F32) hipLaunchKernelGGL((fast::fast_rows_kernel<float, 256, STATEFUL>), grid, dim3(256), a.F.total, st, a);
-    else hipLaunchKernelGGL((fast::fast_rows_kernel<uint16_t, 256, STATEFUL>), grid, dim3(256), a.F.total, st, a);
-  } else if (a.F.threads == 512) {
-    if (dtype == SIMPLE_F32) hipLaunchKernelGGL((fast::fast_rows_kernel<float, 512, STATEFUL>), grid, dim3(512), a.F.total, st, a);
-    else hipLaunchKernelGGL((fast::fast_rows_kernel<uint16_t, 512, STATEFUL>), grid, dim3(512), a.F.total, st, a);
-  } else {
-    if (dtype == SIMPLE_F32) hipLaunchKernelGGL((fast::fast_rows_kernel<float, 1024, STATEFUL>), grid, dim3(1024), a.F.total, st, a);
-    else hipLaunchKernelGGL((fast::fast_rows_kernel<uint16_t, 1024, STATEFUL>), grid, dim3(1024), a.F.total, st, a);
-  }
+  if (a.F.threads == 256) hipLaunchKernelGGL((fast::fast_rows_kernel<DT, 256, STATEFUL, WHOLE>), grid, dim3(256), a.F.total, st, a);
+  else if (a.F.threads == 512) hipLaunchKernelGGL((fast::fast_rows_kernel<DT, 512, STATEFUL, WHOLE>), grid, dim3(512), a.F.total, st, a);
+  else hipLaunchKernelGGL((fast::fast_rows_kernel<DT, 1024, STATEFUL, WHOLE>), grid, dim3(1024), a.F.total, st, a);
   return hipGetLastError();
+}
+template <typename DT>
+static hipError_t launch_fast_dtype(const SampleArgs& a, hipStream_t st) {
+  if (a.F.whole) return a.st_rec ? launch_fast_instance<DT, true, true>(a, st) : launch_fast_instance<DT, false, true>(a, st);
+  return a.st_rec ? launch_fast_instance<DT, true, false>(a, st) : launch_fast_instance<DT, false, false>(a, st);
 }
 // The order in which the single-pass kernel's workgroups take the rows of a launch: rows with long
 // epilogues first, the others behind them, each group in row order.  Workgroups are handed to the
@@ -1002,19 +1052,25 @@ hipError_t launch_order(const SampleArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_fast(const SampleArgs& a, int dtype, hipStream_t st) {
-  return a.st_rec ? launch_fast_instance<true>(a, dtype, st) : launch_fast_instance<false>(a, dtype, st);
+  return dtype == SIMPLE_F32 ? launch_fast_dtype<float>(a, st) : launch_fast_dtype<uint16_t>(a, st);
 }
 
+template <typename DT, int NTHR>
+static hipError_t set_max_lds_instances(unsigned bytes) {
+  const void* fns[4] = {
+    reinterpret_cast<const void*>(fast::fast_rows_kernel<DT, NTHR, false, false>), reinterpret_cast<const void*>(fast::fast_rows_kernel<DT, NTHR, true, false>),
+    reinterpret_cast<const void*>(fast::fast_rows_kernel<DT, NTHR, false, true>), reinterpret_cast<const void*>(fast::fast_rows_kernel<DT, NTHR, true, true>)};
+  for (const void* f : fns) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 hipError_t set_max_lds_fast(unsigned bytes) {
-  const void* fns[12] = {
-    reinterpret_cast<const void*>(fast::fast_rows_kernel<float, 256, false>), reinterpret_cast<const void*>(fast::fast_rows_kernel<uint16_t, 256, false>),
-    reinterpret_cast<const void*>(fast::fast_rows_kernel<float, 512, false>), reinterpret_cast<const void*>(fast::fast_rows_kernel<uint16_t, 512, false>),
-    reinterpret_cast<const void*>(fast::fast_rows_kernel<float, 1024, false>), reinterpret_cast<const void*>(fast::fast_rows_kernel<uint16_t, 1024, false>),
-    reinterpret_cast<const void*>(fast::fast_rows_kernel<float, 256, true>), reinterpret_cast<const void*>(fast::fast_rows_kernel<uint16_t, 256, true>),
-    reinterpret_cast<const void*>(fast::fast_rows_kernel<float, 512, true>), reinterpret_cast<const void*>(fast::fast_rows_kernel<uint16_t, 512, true>),
-    reinterpret_cast<const void*>(fast::fast_rows_kernel<float, 1024, true>), reinterpret_cast<const void*>(fast::fast_rows_kernel<uint16_t, 1024, true>)};
-  for (int i = 0; i < 12; ++i) {
-    const hipError_t e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  hipError_t (*const set[6])(unsigned) = {set_max_lds_instances<float, 256>, set_max_lds_instances<float, 512>, set_max_lds_instances<float, 1024>,
+                                          set_max_lds_instances<uint16_t, 256>, set_max_lds_instances<uint16_t, 512>, set_max_lds_instances<uint16_t, 1024>};
+  for (auto f : set) {
+    const hipError_t e = f(bytes);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -1611,7 +1611,7 @@ hipError_t launch_sample(const SampleArgs& a, int dtype, bool vec, hipStream_t s
     e = launch_fast(a, dtype, st);
     if (e != hipSuccess) return e;
     if (ev1 && hipEventRecord(ev1, st) != hipSuccess) return hipErrorUnknown;
-    e = launch_wide(a, dtype, st);  // rows whose nucleus spans more of the vocabulary than the list holds
+    e = a.F.whole ? hipSuccess : launch_wide(a, dtype, st);  // rows whose nucleus spans more of the vocabulary than the list holds
     if (e != hipSuccess) return e;
     if (dtype == SIMPLE_F32) return vec ? launch_pending<float, true>(a, st) : launch_pending<float, false>(a, st);
     return vec ? launch_pending<uint16_t, true>(a, st) : launch_pending<uint16_t, false>(a, st);

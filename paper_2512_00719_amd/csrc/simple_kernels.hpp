@@ -30,11 +30,15 @@ struct FastLayout {
   uint32_t long_cap;  // entries of a long certified list that fit beside its bucket tables
   uint32_t samp;      // threshold sample merge area
   uint32_t total;     // 0: the call cannot use the kernel
+  uint32_t whole;     // 1: the list holds every column of a row (short vocabularies): no sample, nothing for the sliced kernels
   int threads;        // workgroup size the layout was made for (256, 512 or 1024)
 };
 
 constexpr int SAMPLE_PER_WAVE = 48;   // keys of the threshold sample a wave hands to the merge (sizes the merge area)
-constexpr int CAPF_PER_THREAD = 12;  // candidate-list entries per thread the single-pass kernel's epilogue holds in registers
+// Candidate-list entries per thread that the single-pass kernel's epilogue holds in registers: 3584 to 8192 a row,
+// about twice and more what the threshold aims at.
+constexpr int CAPF_WHOLE = 12;
+constexpr int capf_per_thread(int threads, bool whole) { return whole ? CAPF_WHOLE : threads == 256 ? 14 : threads == 512 ? 12 : 8; }
 constexpr int KMAXF = 1024;   // largest top-k its list certifies
 constexpr int FAST_MAX_V = 1 << 19;  // columns from which only the general kernel serves a call: the 2^44 fixed-point masses of a
                                      // row stay below 2^63, and a row is at most 128 slices of the sliced kernels

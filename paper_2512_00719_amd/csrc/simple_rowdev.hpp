@@ -28,6 +28,7 @@ constexpr int NBW = 2048;               // bins of the mass histogram (whole-voc
 constexpr float BINS_PER_LOG2 = 64.0f;  // bin width: 1/64 of a factor two in probability
 constexpr float MSCALE = 268435456.0f;  // 2^28: fixed-point scale of masses relative to the one at g
 constexpr int RCAP = 4096;              // columns of the boundary bin that can be resolved exactly
+constexpr float LOWEST = -3.4028234663852886e38f;  // lowest finite float32
 constexpr float L2E_HI = 1.44269502162933349609375f, L2E_LO = 1.925963033500011e-8f;  // log2(e), split
 
 // Global-memory view of a pointer.  Inside out-of-line device functions the compiler cannot tell that
@@ -82,7 +83,7 @@ __device__ __forceinline__ unsigned lanes_before(u64 m) {
 
 // Row-wide state in static LDS.
 struct FS {
-  unsigned cand_count, flags, kmax, memb;
+  unsigned cand_count, flags, kmax, kmin, memb;
   int bk, bp, bd;
   unsigned need_k, cab_k, cab_p, n_p;
   u64 mab_k, mab_p, mab_d, cut_k, cut_p, out_w;
@@ -103,6 +104,7 @@ struct RowCfg {
   float tau, top_p, min_p;
   int top_k, V;
   bool greedy, k_on, p_on, p_le0, minp_on, need_sum;
+  bool all;  // no truncation, and the list holds the whole row
   double u_draw, u_acc, u_tail;
 };
 

@@ -444,7 +444,6 @@ __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a
 }
 
 // ---------------------------------------------------------------- no truncation ---------------
-constexpr float LOWEST = -3.4028234663852886e38f;
 // exp(y - m) for y <= m (float32, split log2(e)); a NaN stays one
 __device__ __forceinline__ float mass_rel(float y, float m) {
   const float d = y - m;
