@@ -487,6 +487,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   constexpr int EPL = Io<DT>::EPL;
   constexpr int T = 64 * EPL * UNR;
   constexpr int PER = capf_per_thread(NTHR, WHOLE);
+  constexpr int IDR = idr(NTHR);
   typedef typename Io<DT>::Raw Raw;
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ FS S;
@@ -548,8 +549,8 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   // (a list that holds the whole row needs no threshold and decides all of these itself)
   const bool straight = !whole && (no_trunc || big_k || (!R.greedy && !R.k_on && !R.p_le0 && h_active && !lowering));
   R.all = whole && no_trunc;
-  const uint32_t straight_mode = big_k ? (uint32_t)WIDE_TOP_K
-                                       : (R.p_on ? (uint32_t)WIDE_TOP_P : (uint32_t)WIDE_MIN_P);
+  const uint32_t straight_mode = no_trunc ? (uint32_t)WIDE_ALL : big_k ? (uint32_t)WIDE_TOP_K
+                                          : (R.p_on ? (uint32_t)WIDE_TOP_P : (uint32_t)WIDE_MIN_P);
   const bool eligible = (straight || whole) ? (!bad_par && !too_long)
                                             : (!bad_par && !too_long && (!h_active || lowering) &&
                                                (R.greedy || !R.k_on || par.top_k <= KMAXF));
@@ -644,10 +645,6 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
     return true;
   };
-  if (no_trunc && !whole) {  // every column survives: no threshold to look for
-    if (!queue_wide(WIDE_ALL, true, 0.0f) && tid == 0) queue_pending(a, row);
-    return;
-  }
 
   bool complete = whole;  // the list takes every finite column
   if (!whole) {
@@ -725,7 +722,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     C.need_sum = R.need_sum && !complete;  // (nothing lies below the list)
     C.l2e_tau = (float)(1.4426950408889634 / (double)R.tau);
   }
-  if (straight) {
+  if (straight) {  // (without truncation the threshold is only the reference of the masses)
     if (!queue_wide(straight_mode, true, C.g) && tid == 0) queue_pending(a, row);
     return;
   }
@@ -816,11 +813,11 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   const unsigned n = S.cand_count;
   // the stream added 2^28 for every column at or above g: all of them were counted for the list
   if (C.need_sum && tid == 0) below_mass -= (u64)n << 28;
-  if (n > cap && !complete && (R.need_sum || minp_only)) {
-    // more columns at or above g than the list holds, and a cut that the whole-vocabulary routes
-    // find without the list
-    if (queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, false, C.g)) return;
-  }
+  float g_ref = C.g;         // threshold for the sliced kernels
+  bool tables_live = false;  // the region holds the history tables
+  // more columns at or above g than the list holds, and a cut that the whole-vocabulary routes find
+  // without the list
+  if (n > cap && !complete && (R.need_sum || minp_only)) rc = FIN_WIDE;
   if (n <= cap) {
     // the list moves to registers; the region takes the history tables again
     float ez[PER]; uint32_t eid[PER];
@@ -941,7 +938,6 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     const double S_below = (double)S_below_int / (double)MSCALE;
     const uint32_t kmax = S.kmax;
     if (tid == 0) S.wmax[0] = -INFINITY;  // (lower end of what the sliced kernels may take as above their threshold)
-    bool tables_live = false;  // the region still holds the history tables
     if (S.flags & SIMPLE_DIAG_ERROR) rc = FIN_DONE;
     else if (kmax <= key_g || kmax <= KEY_NEG_INF) rc = FIN_PENDING;
     else if (wide) {
@@ -994,10 +990,12 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     // higher, the threshold is moved up to e^13.5 below it, and above a bucket of ties that holds the cut)
     if (rc == FIN_WIDE) {
       __syncthreads();
-      const float y_ref = fmaxf(keyf(kmax) - 13.5f, S.wmax[0]);
-      if (queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, tables_live, fmaxf(C.g, y_ref * R.tau))) return;
-      rc = FIN_PENDING;  // no free slot: the general kernel takes the row
+      g_ref = fmaxf(g_ref, fmaxf(keyf(kmax) - 13.5f, S.wmax[0]) * R.tau);
     }
+  }
+  if (rc == FIN_WIDE) {
+    if (queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, tables_live, g_ref)) return;
+    rc = FIN_PENDING;  // no free slot: the general kernel takes the row
   }
   if (tid == 0) {
     if (rc != FIN_DONE) {

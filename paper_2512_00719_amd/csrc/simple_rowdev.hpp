@@ -22,7 +22,7 @@ constexpr int SPW = SAMPLE_PER_WAVE;  // sample entries a wave hands to the merg
 constexpr int NBF = 256;     // buckets of the long-list tables
 constexpr int MEMB = 512;    // entries the sorted epilogue handles
 constexpr int MEMB2 = 256;   // members of one bucket the long-list path resolves exactly
-constexpr int IDR = 16;      // history ids a thread keeps in registers
+constexpr int idr(int threads) { return threads == 1024 ? 8 : 16; }  // history ids a thread keeps in registers (1024 threads have 128 each: no room for more)
 constexpr double WSCALE = 17592186044416.0;  // 2^44: fixed-point scale of probability mass
 constexpr int NBW = 2048;               // bins of the mass histogram (whole-vocabulary nucleus)
 constexpr float BINS_PER_LOG2 = 64.0f;  // bin width: 1/64 of a factor two in probability
@@ -223,18 +223,18 @@ __device__ __forceinline__ void zero16(void* p, int bytes, int tid, int nthr) {
 }
 
 // The presence mask alone (enough for the threshold sample): ids[j] is history entry tid + j * NTHR.
-template <int NTHR>
-__device__ inline void build_bitmap(FS& S, const Hist& H, const int (&ids)[IDR], const int32_t* __restrict__ hist, int nnz, int V) {
+template <int NTHR, int NID>
+__device__ inline void build_bitmap(FS& S, const Hist& H, const int (&ids)[NID], const int32_t* __restrict__ hist, int nnz, int V) {
   const int tid = threadIdx.x;
   const int n_pairs = (H.n_words + 1) >> 1;
   zero16(H.bm, n_pairs * 8, tid, NTHR);
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < IDR; ++j) {
+  for (int j = 0; j < NID; ++j) {
     const int i = tid + j * NTHR;
     if (i < nnz && (unsigned)ids[j] < (unsigned)V) atomicOr(&H.bm[ids[j] >> 5], 1u << (ids[j] & 31));
   }
-  for (int i = tid + IDR * NTHR; i < nnz; i += NTHR) {
+  for (int i = tid + NID * NTHR; i < nnz; i += NTHR) {
     const int id = hist[i];
     if ((unsigned)id < (unsigned)V) atomicOr(&H.bm[id >> 5], 1u << (id & 31));
   }
@@ -245,8 +245,8 @@ __device__ inline void build_bitmap(FS& S, const Hist& H, const int (&ids)[IDR],
 // (ids[j] is history entry tid + j * NTHR) and, beyond those, from global memory.  own gets bit j
 // set when this thread was the first to mark ids[j] (one owner per distinct id).  Out-of-range ids
 // are ignored and flagged.
-template <int NTHR>
-__device__ inline void build_history(FS& S, const Hist& H, const int (&ids)[IDR], const int32_t* __restrict__ hist,
+template <int NTHR, int NID>
+__device__ inline void build_history(FS& S, const Hist& H, const int (&ids)[NID], const int32_t* __restrict__ hist,
                                      int nnz, int n_prompt, int V, unsigned& own) {
   constexpr int NWV = NTHR / 64;
   const int tid = threadIdx.x;
@@ -257,7 +257,7 @@ __device__ inline void build_history(FS& S, const Hist& H, const int (&ids)[IDR]
   bool bad = false;
   own = 0u;
 #pragma unroll
-  for (int j = 0; j < IDR; ++j) {
+  for (int j = 0; j < NID; ++j) {
     const int i = tid + j * NTHR;
     if (i < nnz) {
       if ((unsigned)ids[j] < (unsigned)V) {
@@ -266,7 +266,7 @@ __device__ inline void build_history(FS& S, const Hist& H, const int (&ids)[IDR]
       } else bad = true;
     }
   }
-  for (int i = tid + IDR * NTHR; i < nnz; i += NTHR) {
+  for (int i = tid + NID * NTHR; i < nnz; i += NTHR) {
     const int id = hist[i];
     if ((unsigned)id < (unsigned)V) atomicOr(&H.bm[id >> 5], 1u << (id & 31)); else bad = true;
   }
@@ -304,8 +304,8 @@ __device__ inline void build_history(FS& S, const Hist& H, const int (&ids)[IDR]
     }
   };
 #pragma unroll
-  for (int j = 0; j < IDR; ++j) { const int i = tid + j * NTHR; if (i >= n_prompt && i < nnz) count_one(ids[j]); }
-  for (int i = tid + IDR * NTHR; i < nnz; i += NTHR) if (i >= n_prompt) count_one(hist[i]);
+  for (int j = 0; j < NID; ++j) { const int i = tid + j * NTHR; if (i >= n_prompt && i < nnz) count_one(ids[j]); }
+  for (int i = tid + NID * NTHR; i < nnz; i += NTHR) if (i >= n_prompt) count_one(hist[i]);
   __syncthreads();
 }
 
@@ -337,13 +337,15 @@ constexpr uint32_t WS_HIST = 0u;        // u64[NBW]: mass of the columns below g
                                         // (rows without truncation: AllPart[128][4], per slice and wave)
 constexpr uint32_t WS_TILES = 16384u;   // u64[2][256]: survivors' mass per tile, tail class then hot class
 constexpr uint32_t WS_SCAL = 20480u;    // u64 mass at or above g; u32 sure survivors; u32 boundary columns; u64 exact mass
-                                        // of the row; u32 largest key of a tempered value; u32 columns at or above g
+                                        // of the row; u32 largest key of a tempered value; u32 columns at or above g;
+                                        // u32 the cut's bin + 1 (0: none); (pad) u64 mass of the row by the bins
 constexpr uint32_t WS_RL = 20544u;      // u64[RCAP]: columns of the boundary bin (value bits << 32 | id)
 constexpr uint32_t WS_HT = 53312u;      // the row's history tables as the single-pass kernel laid them out in LDS
 // [0, WS_RL) must be zero when a row is queued
-// A wave's share of a slice of a row without truncation: masses relative to the largest tempered value
-// among them (double sums of float32 exponentials), the hot columns' part, and that value.
-struct AllPart { double s, h; float m; uint32_t unused; };
+// A wave's share of a slice of a row without truncation, all columns and the hot ones among them, and the
+// largest tempered value m: masses as integers relative to the one at g, or (rel) as doubles relative to m
+// where a column stands too far above g for the fixed point.
+struct AllPart { u64 s, h; float m; uint32_t rel; };
 static_assert(sizeof(AllPart) == 24 && (FAST_MAX_V / 4096) * 4 * sizeof(AllPart) <= 16384, "the parts of a row fit the bins' place");
 
 // Mass of one column relative to the mass at y_g, w = exp(y - y_g) with y = fl32(z / tau), and the

@@ -22,7 +22,7 @@ namespace state {
 
 using fast::FS;
 using fast::Hist;
-using fast::IDR;
+
 using fast::u32x4;
 
 constexpr int ST = 256;  // threads per sequence
@@ -63,6 +63,7 @@ __global__ __launch_bounds__(ST) void state_reset_kernel(const StateArgs st, con
   H.n_words = (st.V + 31) >> 5;
   H.rep = 1.0f; H.freq = 0.0f; H.pres = 0.0f; H.inv_rep = 1.0; H.active = true;
   if (tid == 0) { S.flags = 0u; S.distinct = 0u; }
+  constexpr int IDR = fast::idr(ST);
   int ids[IDR];
 #pragma unroll
   for (int j = 0; j < IDR; ++j) { const int k = tid + j * ST; ids[j] = (k < len) ? src[k] : -1; }

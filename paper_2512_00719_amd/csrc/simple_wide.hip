@@ -32,8 +32,9 @@
 // order: what is needed first is requested first.
 //
 // Rows without truncation have no cut and are read once, by the first kernel: per slice and wave it leaves
-// the columns' mass relative to the largest of them (so any dynamic range is carried: one column may
-// hold almost the whole mass), from which the third kernel draws.  Rows with a min-p cut use the first
+// the columns' mass, from which the third kernel draws; where one stands too far above g for the fixed
+// point, relative to the largest of them (so that any dynamic range is carried: one column may hold almost
+// the whole mass).  Rows with a min-p cut use the first
 // kernel for the row maximum only (the cut is a value).  Rows with top-k alone run the same three
 // kernels by count instead of mass: a bin counts its columns, the cut's bin is the one in which
 // the count from the top reaches k, and the descent inside it weighs every column as one.
@@ -229,21 +230,6 @@ __device__ __forceinline__ void hist_stage(SliceTabs& T, const HistPre<DT>& P, c
     }
   }
 }
-// f(z', idx) for each history column of the slice behind the HCAP staged ones, by its mask word's thread.
-template <typename DT, typename F>
-__device__ __forceinline__ void hist_beyond(const SliceTabs& T, const WideRow& W, const DT* rowp, int c0, int V, F&& f) {
-  const int tid = fresh_tid();
-  if (tid >= SLC / 32) return;
-  uint32_t word = T.bm[tid];
-  unsigned r = T.dir[tid >> 1] - T.dir[0] + ((tid & 1) ? (unsigned)__popc(T.bm[tid - 1]) : 0u);
-  while (word) {
-    const int idx = c0 + 32 * tid + (__ffs((int)word) - 1);
-    word &= word - 1u;
-    if (r >= (unsigned)HCAP && idx < V)
-      f(apply_penalties(Io<DT>::one(rowp + idx), (uint32_t)T.cnt[min(r, (unsigned)SLC - 1u)], W.rep, W.inv_rep, W.freq, W.pres), idx);
-    ++r;
-  }
-}
 // f(z', idx) for each history column of the slice, with its penalised value: the staged ones one per
 // thread, the rest (a slice with more than HCAP of them) by their mask word's thread.
 template <typename DT, typename F>
@@ -254,7 +240,17 @@ __device__ __forceinline__ void hist_columns(const SliceTabs& T, const WideRow& 
     const int idx = c0 + (int)T.hcol[j];
     if (idx < V) f(apply_penalties(T.hz[j], (uint32_t)T.cnt[j], W.rep, W.inv_rep, W.freq, W.pres), idx);
   }
-  if (nc > (unsigned)HCAP) hist_beyond<DT>(T, W, rowp, c0, V, f);
+  if (nc > (unsigned)HCAP && tid < SLC / 32) {
+    uint32_t word = T.bm[tid];
+    unsigned r = T.dir[tid >> 1] - T.dir[0] + ((tid & 1) ? (unsigned)__popc(T.bm[tid - 1]) : 0u);
+    while (word) {
+      const int idx = c0 + 32 * tid + (__ffs((int)word) - 1);
+      word &= word - 1u;
+      if (r >= (unsigned)HCAP && idx < V)
+        f(apply_penalties(Io<DT>::one(rowp + idx), (uint32_t)T.cnt[min(r, (unsigned)SLC - 1u)], W.rep, W.inv_rep, W.freq, W.pres), idx);
+      ++r;
+    }
+  }
 }
 
 // The bin that holds the cut, from the masses of the first pass: cumulative mass from the top
@@ -449,10 +445,10 @@ __device__ __forceinline__ float mass_rel(float y, float m) {
   const float d = y - m;
   return __builtin_amdgcn_exp2f(fmaf(d, L2E_HI, d * L2E_LO));
 }
-// One slice of a row without truncation: every wave leaves the mass of its columns, relative to the
-// largest of them.  A column costs a double product, three conversions, an exponential and a double
-// sum, less than the time its bytes take; the row is read once.  (128,256 float32 columns x 256 rows:
-// the call 173 us with the mass taken relative to a threshold, up to 229 with a row it could not carry; 55 us so.)
+// One slice of a row without truncation: every wave leaves the mass of its columns.  The row is read once;
+// bound: HBM, with about 25 vector instructions a column beside it.  (128,256 float32 columns x 256 rows:
+// classified in the second kernel, a column 2^21 above g sending the row to the general kernel, the call
+// took 120 us, 229 with three such rows; 64 so.)
 template <typename DT, bool use_hot>
 __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<DT>& HP, SliceTabs& Tb, const WideRow& W, const SampleArgs& a,
                                           const DT* rowp, int c0, int sl) {
@@ -460,6 +456,13 @@ __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<
   const int tid = fresh_tid(), V = a.V;
   float y[G][EPL];
   float m = LOWEST;
+  bool far = false;  // a mass the fixed point cannot carry, or a NaN
+  uint32_t sh = 0u, sl_ = 0u, hh = 0u, hl = 0u;  // sums of the masses' two parts (16 terms of <= 2^25 and < 2^24)
+  auto weigh = [&](float yv) {  // exp(y - y_g), as in mass_term
+    const float w = mass_rel(yv, W.C.y_g);
+    far = far || !(w <= W_LIMIT);
+    return w;
+  };
 #pragma unroll
   for (int j = 0; j < G; ++j) {
     const int o = (j * WT + tid) * EPL;
@@ -473,62 +476,50 @@ __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<
     for (int e = 0; e < EPL; ++e) {
       y[j][e] = ((nib >> e) & 1u) ? -INFINITY : tempered(y[j][e], W.C);
       m = fmaxf(m, y[j][e]);
+      uint32_t hi, lo;
+      float_to_parts(weigh(y[j][e]) * MSCALE, hi, lo);
+      sh += hi; sl_ += lo;
+      if (use_hot) { const uint32_t hm = (uint32_t)(-(int32_t)((L.hq[j] >> e) & 1u)); hh += hi & hm; hl += lo & hm; }
     }
   }
-  float yh[HCAP / WT];  // this thread's share of the staged history columns, and their hot bits
-  uint32_t hh = 0u;
-  unsigned nc = 0u;
+  u64 s = parts_to_u64(sh, sl_), h = use_hot ? parts_to_u64(hh, hl) : 0ull;
   if (W.h_active) {
     hist_stage<DT>(Tb, HP, W.ws, a, rowp, c0, V);
     __syncthreads();
-    nc = min(Tb.dir[SLC / 64] - Tb.dir[0], (unsigned)SLC);
-#pragma unroll
-    for (int k = 0; k < HCAP / WT; ++k) {
-      const unsigned j = (unsigned)(k * WT + tid);
-      yh[k] = -INFINITY;
-      if (j < min(nc, (unsigned)HCAP)) {
-        const int idx = c0 + (int)Tb.hcol[j];
-        if (idx < V) {
-          yh[k] = tempered(apply_penalties(Tb.hz[j], (uint32_t)Tb.cnt[j], W.rep, W.inv_rep, W.freq, W.pres), W.C);
-          if (use_hot) hh |= hot_bit(a.hot_bits, (uint32_t)idx) << k;
-        }
-      }
-      m = fmaxf(m, yh[k]);
-    }
-    // (a slice with more history columns than the stage holds: the rest by their mask word's thread, twice)
-    if (nc > (unsigned)HCAP) hist_beyond<DT>(Tb, W, rowp, c0, V, [&](float z, int) { m = fmaxf(m, tempered(z, W.C)); });
+    hist_columns<DT>(Tb, W, rowp, c0, V, [&](float z, int idx) {
+      const float yv = tempered(z, W.C);
+      m = fmaxf(m, yv);
+      const u64 f = mass_fix(weigh(yv));
+      s += f;
+      if (use_hot && hot_bit(a.hot_bits, (uint32_t)idx)) h += f;
+    });
   }
   const float M = wave_max(m);
-  double s = 0.0, h = 0.0;
+  const bool rel = __ballot(far) != 0ull;
+  if (rel) {  // once more, relative to the largest: double sums of float32 exponentials
+    double ds = 0.0, dh = 0.0;
+    auto add = [&](float yv, bool hot) {
+      const double w = (double)mass_rel(yv, M);
+      ds += w;
+      if (use_hot && hot) dh += w;
+    };
 #pragma unroll
-  for (int j = 0; j < G; ++j) {
+    for (int j = 0; j < G; ++j) {
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      const float w = mass_rel(y[j][e], M);
-      s += (double)w;
-      if (use_hot) h += ((L.hq[j] >> e) & 1u) ? (double)w : 0.0;
+      for (int e = 0; e < EPL; ++e) add(y[j][e], use_hot && ((L.hq[j] >> e) & 1u) != 0u);
     }
+    if (W.h_active)
+      hist_columns<DT>(Tb, W, rowp, c0, V, [&](float z, int idx) { add(tempered(z, W.C), use_hot && hot_bit(a.hot_bits, (uint32_t)idx) != 0u); });
+    s = (u64)__double_as_longlong(wave_sum(ds));
+    h = use_hot ? (u64)__double_as_longlong(wave_sum(dh)) : 0ull;
+  } else {
+    s = wave_sum(s);
+    if (use_hot) h = wave_sum(h);
   }
-  if (W.h_active) {
-#pragma unroll
-    for (int k = 0; k < HCAP / WT; ++k) {
-      const float w = mass_rel(yh[k], M);
-      s += (double)w;
-      if (use_hot) h += ((hh >> k) & 1u) ? (double)w : 0.0;
-    }
-    if (nc > (unsigned)HCAP)
-      hist_beyond<DT>(Tb, W, rowp, c0, V, [&](float z, int idx) {
-        const float w = mass_rel(tempered(z, W.C), M);
-        s += (double)w;
-        if (use_hot && hot_bit(a.hot_bits, (uint32_t)idx)) h += (double)w;
-      });
-    __syncthreads();  // the tables are rewritten by the next item
-  }
-  s = wave_sum(s);
-  if (use_hot) h = wave_sum(h);
+  if (W.h_active) __syncthreads();  // the tables are rewritten by the next item
   if ((tid & 63) == 0) {
     AllPart* part = reinterpret_cast<AllPart*>(W.ws + WS_HIST) + sl * WNW + (tid >> 6);
-    part->s = s; part->h = h; part->m = M;
+    part->s = s; part->h = h; part->m = M; part->rel = rel ? 1u : 0u;
   }
 }
 
@@ -725,12 +716,16 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
   float thr_y = -INFINITY;
   bool valid = false;
   ZCut zc = {INFINITY, INFINITY};
-  auto enter_row = [&](int slot) {  // barriers inside
+  auto enter_row = [&](int slot, bool first) {  // barriers inside; first: the item is the row's first slice
     W = load_row(a, (unsigned)slot);
     ids.settle();
     const RowCut rc = row_cut(S, W);
     bstar = rc.bstar; thr_y = rc.thr_y; valid = rc.valid;
     valid = valid && W.mode != WIDE_ALL;  // (done by the bins kernel)
+    if (first && tid == 0 && valid) {  // for the finishing kernel
+      reinterpret_cast<uint32_t*>(W.ws + WS_SCAL)[8] = (uint32_t)bstar + 1u;
+      reinterpret_cast<u64*>(W.ws + WS_SCAL)[5] = rc.s_tot;
+    }
     if (valid) zc = z_cut(W, bstar, thr_y);
   };
   // What a thread gathers over this workgroup's slices of one row, reduced when the row ends:
@@ -772,7 +767,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     n_sure = 0u; acc_all = 0ull; ymax = -INFINITY; bad = false;
   };
   if (tid == 0) l_n = 0u;
-  enter_row(cur);
+  enter_row(cur, I.i0 % I.n_sl == 0u);
   for (unsigned it = I.i0; it < I.i1; ++it) {
     const int slot = (int)(it / I.n_sl), sl = (int)(it % I.n_sl);
     const ItemLoads<DT> L = N;
@@ -782,7 +777,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
       cur = slot;
       ids.row_c = ids.row_n; ids.act_c = ids.act_n;
       ids.request(a, (unsigned)slot + 1u, n_wide, ids.row_n, ids.act_n);
-      enter_row(slot);
+      enter_row(slot, true);
     }
     if (!valid) {  // the finishing kernel hands the row on
       if (more) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
@@ -909,6 +904,32 @@ __device__ inline void hand_on(const SampleArgs& a, int row) {
   a.out[row] = PENDING;
 }
 
+// This thread's columns of the slice that starts at c0 (SLC / WT of them, contiguous; -inf behind the row's
+// end), and their hot bits.
+template <typename DT>
+__device__ __forceinline__ uint32_t slice_columns(float (&z)[SLC / WT], const SampleArgs& a, const DT* rowp, int c0) {
+  constexpr int EPT = SLC / WT, EPL = Io<DT>::EPL;
+  static_assert(EPT == 16, "a thread's hot bits lie in half a word");
+  const int first = c0 + (int)threadIdx.x * EPT;
+  if (first + EPT <= a.V) {
+    typename Io<DT>::Raw r[EPT / EPL];
+#pragma unroll
+    for (int k = 0; k < EPT / EPL; ++k) r[k] = Io<DT>::load(rowp + first + k * EPL);
+#pragma unroll
+    for (int k = 0; k < EPT / EPL; ++k) {
+      float v[EPL];
+      Io<DT>::unpack(r[k], v);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) z[k * EPL + e] = v[e];
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) z[e] = first + e < a.V ? Io<DT>::one(rowp + first + e) : -INFINITY;
+  }
+  return (a.hot_bits && first < a.V) ? as_global(a.hot_bits)[first >> 5] >> ((unsigned)first & 31u) : 0u;
+}
+
+constexpr int NBK_BITS = 10, NBK = 1 << NBK_BITS;  // buckets of the cut bin's columns
 template <typename DT>
 __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, SliceTabs& Tb, u64* rcmp, uint32_t* rl,
                                   u64* dmass, u64* tiles, simple_row_diag& dg) {
@@ -930,18 +951,19 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
 #pragma unroll
   for (int k = 0; k < 2; ++k) tv[k] = as_global(reinterpret_cast<const u64*>(W.ws + WS_TILES))[k * WT + tid];
   const uint32_t kmax = as_global(sc)[6];
-  const RowCut rcut = row_cut(S, W);
-  const int bstar = rcut.bstar;
-  const float thr_y = rcut.thr_y;
-  if (!rcut.valid) { return false; }
+  // the cut as the classifying kernel found it
+  const int bstar = (int)as_global(sc)[8] - 1;
+  const u64 s_bins = as_global(reinterpret_cast<const u64*>(W.ws + WS_SCAL))[5];
+  if (bstar < 0) { return false; }
+  const float thr_y = W.min_p > 0.0f ? keyf(kmax) + (float)log((double)W.min_p) : -INFINITY;
   const bool top_p_route = W.mode == WIDE_TOP_P, top_k_route = W.mode == WIDE_TOP_K;
   const bool cut_route = top_p_route || top_k_route;  // a cut inside a bin: by mass, or by count
-  const u64 S_tot = top_p_route ? rcut.s_tot : S_sum;  // exact mass of the row (from the bins where there are bins)
+  const u64 S_tot = top_p_route ? s_bins : S_sum;  // exact mass of the row (from the bins where there are bins)
   // a count past the limit is also how the classifying pass reports a row it could not handle; no
   // collected column on the top-p route means that a min-p cut ended the survivors above the bin
   const bool minp_too = top_p_route && W.min_p > 0.0f;
   if (n_r > (unsigned)RCAP || (!cut_route && n_r != 0u) || (cut_route && n_r == 0u && !minp_too)) { return false; }
-  if (tid == 0) { S.bd = -1; S.cut_k = 0ull; S.cut_p = ~0ull; S.out_id = -1; S.out_w = 0ull; }
+  if (tid == 0) { S.bd = -1; S.cut_k = 0ull; S.cut_p = ~0ull; S.e_tfix = 0ull; S.out_id = -1; S.out_w = 0ull; }
   tiles[tid] = tv[0]; tiles[WT + tid] = tv[1];
   const u64 msure = tv[0] + tv[1];
   u64 cut_found = 0ull;  // every collected column at or after it in the order survives; 0: no collected columns
@@ -969,7 +991,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
         const float z = __uint_as_float((uint32_t)(e[k] >> 32));
         int b;
         const float w = mass_term(z, C, b);
-        const u64 c = composite(fkey(z / W.tau), (uint32_t)e[k]);
+        const u64 c = composite(fkey(tempered(z, C)), (uint32_t)e[k]);
         rcmp[t] = c;
         rl[t] = (uint32_t)mass_fix_below(w);
         cmax_t = (c > cmax_t) ? c : cmax_t; cmin_t = (c < cmin_t) ? c : cmin_t;
@@ -980,40 +1002,69 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
     if ((tid & 63) == 0) { atomicMax(&S.cut_k, cmax_t); atomicMin(&S.cut_p, cmin_t); }
   }
   __syncthreads();
-  // Radix descent, eight bits at a time from the top of (key, ~id): among the columns that share the
-  // digits fixed so far, the digit whose mass carries the running total over the target is fixed
-  // next.  Digits on which all columns agree are skipped; after the last one the cut column is known.
+  // The columns between the largest and the smallest (key, ~id) go to 1024 buckets of equal width; the
+  // bucket whose mass carries the running total over the target holds the cut.  With at most a thread per
+  // member it is resolved at once, else (many ties) its members are spread again.  (A radix descent by eight bits
+  // took five levels of six barriers for the same; a kernel of 90 such rows 22.7 us, 17.1 so.)
   {
-    const u64 cmax = S.cut_k, differ = S.cut_k ^ S.cut_p;
-    u64 prefix = 0ull, mask = 0ull, acc = m_above;
+    u64 hi = S.cut_k, lo = S.cut_p, prefix = 0ull, acc = m_above;
     bool ok = true;
-    for (int shift = 56; shift >= 0; shift -= 8) {
-      if ((differ >> shift) == 0ull) {  // no column differs here or above
-        prefix |= cmax & (0xFFull << shift); mask |= 0xFFull << shift;
-        continue;
-      }
-      dmass[tid] = 0ull;
-      if (tid == 0) S.bp = -1;
+    for (;;) {
+      const int sh = max(0, 64 - NBK_BITS - (int)__clzll((long long)(hi - lo)));
+      for (int i = tid; i < NBK; i += WT) dmass[i] = 0ull;
+      if (tid == 0) { S.bp = -1; S.memb = 0u; }
       __syncthreads();
       for (unsigned t = tid; t < n_r; t += WT) {
         const u64 c = rcmp[t];
-        if ((c & mask) == prefix) atomicAdd(&dmass[(unsigned)(c >> shift) & 0xFFu], top_k_route ? 1ull : (u64)rl[t]);
+        if (c >= lo && c <= hi) atomicAdd(&dmass[(unsigned)((hi - c) >> sh)], top_k_route ? 1ull : (u64)rl[t]);
       }
       __syncthreads();
-      {  // thread i looks at digit 255 - i: the exclusive scan sums the digits above it
-        const u64 m = dmass[255 - tid];
+      {
+        constexpr int PT4 = NBK / WT;
+        u64 mb[PT4], m = 0ull;
+#pragma unroll
+        for (int k = 0; k < PT4; ++k) { mb[k] = dmass[tid * PT4 + k]; m += mb[k]; }
         unsigned ce2, ct2; u64 me2, mt2;
         blk_excl_scan2<WNW>(S, 0u, m, ce2, me2, ct2, mt2);
-        if (m > 0ull && acc + me2 < target && acc + me2 + m >= target) { S.bp = 255 - tid; S.mab_p = acc + me2; }
+        u64 run = acc + me2;
+#pragma unroll
+        for (int k = 0; k < PT4; ++k) {
+          if (run < target && run + mb[k] >= target) { S.bp = tid * PT4 + k; S.mab_p = run; }
+          run += mb[k];
+        }
       }
       __syncthreads();
       const int d = S.bp;
       if (d < 0) { ok = false; break; }  // the collected columns do not reach the target: the passes disagree
       acc = S.mab_p;
-      prefix |= (u64)(unsigned)d << shift; mask |= 0xFFull << shift;
+      const u64 width = 1ull << sh;
+      hi -= (u64)(unsigned)d << sh;
+      if (hi - lo >= width) lo = hi - (width - 1ull);
+      if (sh == 0) { prefix = hi; break; }
+      u64* mc = dmass;        // its members, and their masses
+      u64* mw = dmass + WT;
+      for (unsigned t = tid; t < n_r; t += WT) {
+        const u64 c = rcmp[t];
+        if (c >= lo && c <= hi) {
+          const unsigned slot = atomicAdd(&S.memb, 1u);
+          if (slot < (unsigned)WT) { mc[slot] = c; mw[slot] = top_k_route ? 1ull : (u64)rl[t]; }
+        }
+      }
       __syncthreads();
+      const unsigned nm = S.memb;
+      if (nm <= (unsigned)WT) {
+        if ((unsigned)tid < nm) {
+          const u64 c = mc[tid], w = mw[tid];
+          unsigned above;
+          const u64 G = acc + sum_where<true>(mc, mw, nm, c, above);
+          if (G >= target && G - w < target) S.e_tfix = c;
+        }
+        __syncthreads();
+        prefix = S.e_tfix;
+        break;
+      }
+      __syncthreads();  // every thread has read the member count
     }
-    if (differ == 0ull && m_above + (top_k_route ? 1ull : (u64)rl[0]) < target) ok = false;  // a single column, and it does not reach the target
     // the collected columns do not reach the target: with a min-p cut those below it were never
     // collected, and the min-p prefix is the shorter one (all collected columns survive)
     if (!ok && !minp_too) { return false; }
@@ -1030,14 +1081,24 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   }
   }  // a cut inside a bin
   const u64 cut_c = cut_found;
-  unsigned ns = r_in + (tid == 0 ? n_sure : 0u), dz = 0; u64 mx = 0ull, dsum = 0ull;
-  blk_reduce<WNW>(S, ns, dz, mx, dsum);  // barriers inside: the tile masses are complete after it
-  if (top_k_route && ns != (unsigned)W.top_k) { return false; }  // the passes disagree
+  __syncthreads();  // the tile masses are complete
   // -- masses of the classes, acceptance (section 5.3), the tile that holds the draw --
-  u64 p0 = 0ull, p1 = 0ull;
-  for (int i = tid; i < 256; i += WT) { p0 += tiles[i]; p1 += tiles[256 + i]; }
-  const u64 S0 = blk_sum_u64<WNW>(S, p0);
-  const u64 S1 = blk_sum_u64<WNW>(S, p1);
+  u64 S0, S1, t0 = tiles[tid], t1 = tiles[256 + tid], e0, e1;  // WT == 256: one tile of each class per thread
+  unsigned ns = r_in + (tid == 0 ? n_sure : 0u);
+  {
+    const u64 i0 = wave_incl_scan(t0), i1 = use_hot ? wave_incl_scan(t1) : 0ull;
+    ns = wave_sum(ns);
+    if (lane_id() == 63) { const int w = wave_id(); S.r64a[w] = i0; S.r64b[w] = i1; S.r32a[w] = ns; }
+    __syncthreads();
+    S0 = 0ull; S1 = 0ull; e0 = i0 - t0; e1 = i1 - t1; ns = 0u;
+#pragma unroll
+    for (int w = 0; w < WNW; ++w) {
+      const u64 x = S.r64a[w], y = S.r64b[w];
+      if (w < wave_id()) { e0 += x; e1 += y; }
+      S0 += x; S1 += y; ns += S.r32a[w];
+    }
+  }
+  if (top_k_route && ns != (unsigned)W.top_k) { return false; }  // the passes disagree
   const u64 S_K = S0 + S1;
   bool pick_hot = false;
   if (use_hot) {
@@ -1054,9 +1115,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   u64 tfix = (u64)__double2ull_rd(u * (double)S_cls);
   if (tfix >= S_cls) tfix = S_cls - 1ull;
   {
-    const u64 m2 = tiles[cls * 256u + (unsigned)tid];  // WT == 256: one tile per thread
-    unsigned ce2, ct2; u64 me2, tot2;
-    blk_excl_scan2<WNW>(S, 0u, m2, ce2, me2, ct2, tot2);
+    const u64 m2 = pick_hot ? t1 : t0, me2 = pick_hot ? e1 : e0;
     if (m2 > 0ull && me2 <= tfix && me2 + m2 > tfix) { S.bd = tid; S.mab_d = me2; }
   }
   __syncthreads();
@@ -1065,8 +1124,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   // -- the drawn id inside one tile --
   const int c0 = tstar * T;
   float zv[EPT];  // requested before the tables' barriers
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) { const int idx = c0 + tid * EPT + e; zv[e] = (idx < V) ? Io<DT>::one(rowp + idx) : 0.0f; }
+  const uint32_t hq = slice_columns<DT>(zv, a, rowp, c0);
   if (W.h_active) load_slice(Tb, W, a, c0);
   u64 mloc[EPT]; u64 lsum = 0ull;
 #pragma unroll
@@ -1076,13 +1134,12 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
     if (idx < V) {
       float z = zv[e];
       if (W.h_active && slice_bit(idx - c0, Tb)) z = slice_value(z, idx - c0, Tb, W);
-      const unsigned hot = use_hot ? hot_bit(hot_bits, (uint32_t)idx) : 0u;
-      if (!use_hot || hot == cls) {
+      if (!use_hot || ((hq >> e) & 1u) == cls) {
         int b; float y;
         const float w = mass_term(z, C, b, y);
         const bool below = z < C.g;
         bool in = !below || b < bstar;
-        if (!in && b == bstar) in = composite(fkey(z / W.tau), (uint32_t)idx) >= cut_c;
+        if (!in && b == bstar) in = composite(fkey(y), (uint32_t)idx) >= cut_c;
         if (in && y >= thr_y) mloc[e] = below ? mass_fix_below(w) : mass_fix(w);
       }
     }
@@ -1101,8 +1158,9 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   return S.out_id >= 0;
 }
 
-// A row without truncation, from its waves' parts: 2^44 fixed-point masses of the slices relative to the row
-// maximum, acceptance (section 5.3), the slice that holds the draw, and that slice's columns once more.
+// A row without truncation, from its waves' parts: acceptance (section 5.3), the slice that holds the draw, and
+// that slice's columns once more.  Where every wave kept integers, the slices' masses are their sums; else
+// they become 2^44 fixed point relative to the row maximum, and the draw's place inside its slice a fraction.
 template <typename DT>
 __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS& S, SliceTabs& Tb, simple_row_diag& dg) {
   constexpr int EPT = SLC / WT;
@@ -1113,45 +1171,60 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
   const bool use_hot = hot_bits != nullptr;
   const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
   const AllPart* parts = reinterpret_cast<const AllPart*>(W.ws + WS_HIST);
-  double ps[WNW], ph[WNW];
+  u64 ps[WNW], ph[WNW];
   float pm[WNW], m = LOWEST;
+  uint32_t prel[WNW];
+  unsigned rels = 0u;
 #pragma unroll
   for (int k = 0; k < WNW; ++k) {
-    ps[k] = 0.0; ph[k] = 0.0; pm[k] = LOWEST;
+    ps[k] = 0ull; ph[k] = 0ull; pm[k] = LOWEST; prel[k] = 0u;
     if (tid < n_sl) {
       const AllPart* q = parts + tid * WNW + k;
-      ps[k] = as_global(q)->s; ph[k] = as_global(q)->h; pm[k] = as_global(q)->m;
+      ps[k] = as_global(q)->s; ph[k] = as_global(q)->h; pm[k] = as_global(q)->m; prel[k] = as_global(q)->rel;
     }
   }
   double u3[3];
   row_uniforms(a.seed, a.row_offset + (uint64_t)W.row, a.step, u3);
-  if (tid == 0) { S.bd = -1; S.out_id = -1; S.flags = 0u; }
+  if (tid == 0) { S.bd = -1; S.out_id = -1; S.out_w = 0ull; S.flags = 0u; }
 #pragma unroll
-  for (int k = 0; k < WNW; ++k) m = fmaxf(m, pm[k]);
+  for (int k = 0; k < WNW; ++k) { m = fmaxf(m, pm[k]); rels |= prel[k]; }
   {
     const float wm = wave_max(m);
-    if ((tid & 63) == 0) S.wmax[tid >> 6] = wm;
+    const u64 any = __ballot(rels != 0u);
+    if ((tid & 63) == 0) { S.wmax[tid >> 6] = wm; S.wcnt[tid >> 6] = any ? 1u : 0u; }
   }
   __syncthreads();
   float y_max = S.wmax[0];
+  bool rel = S.wcnt[0] != 0u;
 #pragma unroll
-  for (int w = 1; w < WNW; ++w) y_max = fmaxf(y_max, S.wmax[w]);
-  double s = 0.0, h = 0.0;
+  for (int w = 1; w < WNW; ++w) { y_max = fmaxf(y_max, S.wmax[w]); rel = rel || S.wcnt[w] != 0u; }
+  if (!(y_max > LOWEST) || y_max == INFINITY) return false;
+  u64 m_all = 0ull, m_hot = 0ull;
+  bool lost = false;
+  if (!rel) {
 #pragma unroll
-  for (int k = 0; k < WNW; ++k) {
-    const double f = exp((double)pm[k] - (double)y_max) * WSCALE;
-    s += ps[k] * f; h += ph[k] * f;
+    for (int k = 0; k < WNW; ++k) { m_all += ps[k]; m_hot += ph[k]; }
+    lost = (m_all >> 56) != 0ull;  // 128 slices below 2^56 sum below 2^63
+  } else {
+    double s = 0.0, h = 0.0;
+#pragma unroll
+    for (int k = 0; k < WNW; ++k) {
+      const double f = prel[k] ? exp((double)pm[k] - (double)y_max) * WSCALE
+                               : exp((double)W.C.y_g - (double)y_max) * (WSCALE / (double)MSCALE);
+      s += (prel[k] ? __longlong_as_double((long long)ps[k]) : (double)ps[k]) * f;
+      h += (prel[k] ? __longlong_as_double((long long)ph[k]) : (double)ph[k]) * f;
+      if (tid >= n_sl) s = h = 0.0;
+    }
+    lost = !(s >= 0.0);  // a NaN, or +inf less itself
+    if (!lost) { m_all = (u64)__double2ull_rn(s); m_hot = min(m_all, (u64)__double2ull_rn(h)); }
   }
-  if (!(s >= 0.0)) atomicOr(&S.flags, 1u);  // a NaN, or +inf less itself
-  const u64 m_all = s >= 0.0 ? (u64)__double2ull_rn(s) : 0ull;
-  const u64 m_hot = (use_hot && s >= 0.0) ? min(m_all, (u64)__double2ull_rn(h)) : 0ull;
+  if (lost) atomicOr(&S.flags, 1u);
   unsigned near = (tid < n_sl && m >= y_max - 88.0f) ? 1u : 0u, finite = (tid < n_sl && m > LOWEST) ? 1u : 0u;
   u64 S_K = m_all, mx = 0ull;
   blk_reduce<WNW>(S, near, finite, mx, S_K);  // barriers inside
   const u64 S_H = use_hot ? blk_sum_u64<WNW>(S, m_hot) : 0ull;
   // one slice so far above all others that their exponentials leave float32's range: the general kernel's
-  if (near == 1u && finite > 1u) return false;
-  if (S.flags || !(y_max > LOWEST) || y_max == INFINITY) return false;
+  if (S.flags || (rel && near == 1u && finite > 1u)) return false;
   bool pick_hot = false;
   if (use_hot) {
     pick_hot = (S_H > 0ull) && (u3[1] * (double)S_K <= (double)S_H);
@@ -1172,13 +1245,14 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
   __syncthreads();
   const int t = S.bd;
   if (t < 0) return false;
-  // the columns' shares of the slice, relative to its largest, in ascending id
+  // the columns' masses in the slice, in ascending id
   const int c0 = t * SLC;
-  const float M = S.wmax[15];
+  const float y_ref = rel ? S.wmax[15] : W.C.y_g;
+  const float scale = rel ? (float)WSCALE : MSCALE;
+  u64 rq = S.mab_d;
   const double place = (double)S.mab_d / (double)S.mab_k;
   float zv[EPT];
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) { const int idx = c0 + tid * EPT + e; zv[e] = (idx < V) ? Io<DT>::one(rowp + idx) : -INFINITY; }
+  const uint32_t hq = slice_columns<DT>(zv, a, rowp, c0);
   if (W.h_active) load_slice(Tb, W, a, c0);
   u64 q[EPT], lsum = 0ull;
 #pragma unroll
@@ -1188,25 +1262,26 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
     if (c0 + o < V) {
       float z = zv[e];
       if (W.h_active && slice_bit(o, Tb)) z = slice_value(z, o, Tb, W);
-      zv[e] = mass_rel(tempered(z, W.C), M);
-      if (!use_hot || (hot_bit(hot_bits, (uint32_t)(c0 + o)) != 0u) == pick_hot) q[e] = (u64)__double2ull_rn((double)zv[e] * WSCALE);
+      if (!use_hot || (((hq >> e) & 1u) != 0u) == pick_hot) q[e] = float_to_u64(mass_rel(tempered(z, W.C), y_ref) * scale);
     }
     lsum += q[e];
   }
   unsigned ce, ct; u64 me, Q;
   blk_excl_scan2<WNW>(S, 0u, lsum, ce, me, ct, Q);
-  u64 rq = (u64)__double2ull_rd(place * (double)Q);
-  if (Q > 0ull && rq >= Q) rq = Q - 1ull;
+  if (rel) {
+    rq = (u64)__double2ull_rd(place * (double)Q);
+    if (Q > 0ull && rq >= Q) rq = Q - 1ull;
+  }
   u64 run = me;
 #pragma unroll
   for (int e = 0; e < EPT; ++e) {
-    if (q[e] > 0ull && run <= rq && rq < run + q[e]) { S.out_id = c0 + tid * EPT + e; S.wmax[0] = zv[e]; }
+    if (q[e] > 0ull && run <= rq && rq < run + q[e]) { S.out_id = c0 + tid * EPT + e; S.out_w = q[e]; }
     run += q[e];
   }
   __syncthreads();
   dg.n_survivors = V;
-  dg.s_k = (double)S_K / WSCALE;
-  dg.p_chosen = (float)((double)S.wmax[0] * exp((double)M - (double)y_max) * WSCALE / (double)S_K);
+  dg.s_k = rel ? (double)S_K / WSCALE : (double)S_K / (double)MSCALE * exp((double)W.C.y_g - (double)y_max);
+  dg.p_chosen = (float)((double)S.out_w * (rel ? exp((double)y_ref - (double)y_max) : 1.0) / (double)S_K);
   return S.out_id >= 0;
 }
 
@@ -1215,7 +1290,7 @@ __global__ __launch_bounds__(WT) void wide_finish_kernel(const SampleArgs a) {
   __shared__ SliceTabs Tb;
   __shared__ u64 rcmp[RCAP];
   __shared__ uint32_t rl[RCAP];
-  __shared__ u64 dmass[256];
+  __shared__ u64 dmass[NBK];
   __shared__ u64 tiles[512];
   __shared__ FS S;
   const int tid = threadIdx.x;
