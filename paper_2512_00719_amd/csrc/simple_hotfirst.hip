@@ -17,16 +17,17 @@
 // rows without penalties; the rest is queued for the general kernel.  So each row of the call gets
 // the ids of the speculative sampler as the definition over the whole row gives them.
 //
-// One workgroup per row.  Masses are relative to the row maximum (the stable softmax numerator of Eq.
+// One workgroup per row for the hot columns and the acceptance; a rejected row is queued, and its tail is cut
+// into tiles that spread over the whole chip (a kernel for the tile sums, one for the draw).  Masses are relative to the row maximum (the stable softmax numerator of Eq.
 // (2)); a 16-byte group of columns is summed in double precision in column order and rounded once to a
 // 2^44 fixed-point integer, and everything above a group adds integers, so no sum depends on the order
 // of the additions.  The inverse CDF runs in ascending token id: per tile of 2048 groups a sum, the
 // tile that holds the target, the group in it, the column in the group.
 //
 // What bounds it: an accepted row is one trip through memory for its hot columns and a chain of
-// barriers; a rejected row streams its tail through one compute unit, 12 vector instructions a column
-// (a double-precision add costs what a single-precision one does here, so the mass needs no conversion
-// to integers per column), and the launch ends with the rejected rows.
+// barriers.  A rejected row's tail, 12 vector instructions a column, took one compute unit 45 us, and the
+// launch ended with those rows while most of the chip was idle: 1024 rows of 201,088 bfloat16 columns with
+// H = 8192, 82 of them rejected, 68.6 us a call; 51.9 with the tails' tiles spread out (984 workgroups).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -204,6 +205,33 @@ __device__ __forceinline__ int locate(const Span<DT>& C, double inv_tau, float y
   return S.out_id;
 }
 
+// What the kernels behind this one need of a rejected row (a queue record), and its workspace slot.
+struct Rejected { uint32_t row, flags; float y_max; uint32_t unused; u64 s_h; double alpha; u64 pad[4]; };
+static_assert(sizeof(Rejected) == 64, "queue record size");
+struct TailSums { u64 tsum[MAX_TILES]; uint32_t bad[MAX_TILES]; };  // per tile of the tail; bad: a NaN or +inf among its columns
+static_assert(sizeof(TailSums) <= WIDE_SLOT_FIXED, "workspace slot size");
+__device__ __forceinline__ Rejected* rejected(const SampleArgs& a) { return reinterpret_cast<Rejected*>(a.wq + fast::WQ_HEAD); }
+__device__ __forceinline__ TailSums* tail_sums(const SampleArgs& a, unsigned slot) { return reinterpret_cast<TailSums*>(a.wws + (size_t)slot * a.ws_stride); }
+
+// The results of a row decided here.
+__device__ __forceinline__ void write_row(const SampleArgs& a, int row, int id, uint32_t flags, double alpha, u64 w_id, u64 S_K) {
+  const bool err = (flags & SIMPLE_DIAG_ERROR) != 0u;
+  simple_row_diag dg;
+  dg.alpha = alpha; dg.s_k = 0.0; dg.n_survivors = err ? 0 : a.V; dg.reserved = 0u;
+  dg.flags = flags;
+  if (a.hot_flags && *a.hot_flags) dg.flags |= SIMPLE_DIAG_BAD_HOT_SET;
+  dg.p_chosen = err ? 0.0f : (float)((double)w_id / (double)S_K);
+  a.out[row] = err ? -1 : id;
+  if (a.diag) a.diag[row] = dg;
+  if (a.stats) stats_add(a.stats, dg.flags, dg.alpha);
+  write_decision(a, row, err ? -1 : id, dg.p_chosen, false);
+}
+__device__ __forceinline__ void leave_pending(const SampleArgs& a, int row) {
+  const unsigned slot = atomicAdd(&a.pend[a.parity], 1u);
+  a.pend[2 + slot] = (uint32_t)row;
+  a.out[row] = PENDING;
+}
+
 template <typename DT>
 __global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs a, int H, const simple_tail_stats* __restrict__ tail) {
   constexpr int EPL = Io<DT>::EPL;
@@ -221,7 +249,7 @@ __global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs 
   if (a.pattern_on && a.out[row] != NOT_TAKEN) return;
   const bool plain = hot_first_plain(par, V);
   if (!plain) {  // truncated, penalised, greedy or invalid rows: the general kernel, with [0, H) as the hot set
-    if (tid == 0) { const unsigned slot = atomicAdd(&a.pend[a.parity], 1u); a.pend[2 + slot] = (uint32_t)row; a.out[row] = PENDING; }
+    if (tid == 0) leave_pending(a, row);
     return;
   }
   Tile<DT> T0;  // the first tile of the hot columns (all of them up to 8192 or 16,384): read once, used for the maximum and the masses
@@ -260,9 +288,8 @@ __global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs 
   const u64 S_H = tile_masses<DT>(T0, hot, inv_tau, y_max, tsum, S, bad);
   if (bad) atomicOr(&S.flags, SIMPLE_DIAG_ERROR | SIMPLE_DIAG_BAD_LOGIT);
   __syncthreads();
-  simple_row_diag dg;
-  dg.alpha = __longlong_as_double(0x7FF8000000000000ll);
-  dg.s_k = 0.0; dg.p_chosen = 0.0f; dg.n_survivors = V; dg.flags = SIMPLE_DIAG_SHVS; dg.reserved = 0u;
+  uint32_t flags = SIMPLE_DIAG_SHVS;
+  double alpha = __longlong_as_double(0x7FF8000000000000ll);
   int id = -1;
   u64 w_id = 0ull, S_K = 0ull;
   if (!(S.flags & SIMPLE_DIAG_ERROR)) {
@@ -270,42 +297,93 @@ __global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs 
     if (has_tail && ts.tail_sum > 0.0) S_T = (u64)__double2ull_rn(ts.tail_sum * exp((double)y_tmax - (double)y_max) * fast::WSCALE);
     S_K = S_H + S_T;
     const bool pick_hot = (S_H > 0ull) && (u[1] * (double)S_K <= (double)S_H);   // accept iff u <= alpha_b (Eq. (8))
-    dg.alpha = S_K ? (double)S_H / (double)S_K : 0.0;
+    alpha = S_K ? (double)S_H / (double)S_K : 0.0;
     if (pick_hot) {
-      dg.flags |= SIMPLE_DIAG_ACCEPTED;
+      flags |= SIMPLE_DIAG_ACCEPTED;
       u64 tfix = (u64)__double2ull_rd(u[0] * (double)S_H);
       if (tfix >= S_H) tfix = S_H - 1ull;
       id = locate<DT>(hot, inv_tau, y_max, tsum, tfix, S, part, w_id);
-    } else {
-      // rejected: the tail proposal r of Eq. (8), over the columns the kernel has not read yet
-      bool bad_t = false;
-      const Span<DT> rest(rowp, H, V);
-      tile_load<DT>(T0, rest, 0);
-      const u64 S_T_exact = tile_masses<DT>(T0, rest, inv_tau, y_max, tsum, S, bad_t);
-      if (bad_t) atomicOr(&S.flags, SIMPLE_DIAG_ERROR | SIMPLE_DIAG_BAD_LOGIT);
-      __syncthreads();
-      if (!(S.flags & SIMPLE_DIAG_ERROR) && S_T_exact > 0ull) {
-        u64 tfix = (u64)__double2ull_rd(u[2] * (double)S_T_exact);
-        if (tfix >= S_T_exact) tfix = S_T_exact - 1ull;
-        id = locate<DT>(rest, inv_tau, y_max, tsum, tfix, S, part, w_id);
-        S_K = S_H + S_T_exact;  // p~ of the drawn id over the masses as summed here
+    } else if (has_tail) {  // rejected: the tail proposal r of Eq. (8), over the columns not read yet
+      if (tid == 0) {
+        const unsigned slot = atomicAdd(&a.wq[a.parity], 1u);  // a launch has a slot for every row
+        Rejected* r = rejected(a) + slot;
+        r->row = (uint32_t)row; r->flags = flags | S.flags; r->y_max = y_max; r->s_h = S_H; r->alpha = alpha;
+        a.out[row] = PENDING;
       }
+      return;
     }
   }
-  const bool err = (S.flags & SIMPLE_DIAG_ERROR) != 0u;
-  if (!err && id < 0) {  // nothing could be located (a class without mass): the general kernel decides
-    if (tid == 0) { const unsigned slot = atomicAdd(&a.pend[a.parity], 1u); a.pend[2 + slot] = (uint32_t)row; a.out[row] = PENDING; }
-    return;
+  if (tid != 0) return;
+  flags |= S.flags;
+  if (!(flags & SIMPLE_DIAG_ERROR) && id < 0) leave_pending(a, row);  // nothing could be located (a class without mass): the general kernel decides
+  else write_row(a, row, id, flags, alpha, w_id, S_K);
+}
+
+// The tile sums of the rejected rows' tails: items are (queued row, tile) pairs, taken in turn.
+template <typename DT>
+__global__ __launch_bounds__(HT, 4) void hot_tail_sums_kernel(const SampleArgs a, int H) {
+  __shared__ FS S;
+  const int V = a.V;
+  const unsigned n = min(fast::as_global(a.wq)[a.parity], (unsigned)a.wide_slots);
+  const int n_tiles = ((V - H + Io<DT>::EPL - 1) / Io<DT>::EPL + HT * HU - 1) / (HT * HU);
+  for (unsigned it = blockIdx.x; it < n * (unsigned)n_tiles; it += gridDim.x) {
+    const unsigned slot = it / (unsigned)n_tiles;
+    const int tile = (int)(it % (unsigned)n_tiles);
+    const Rejected* r = rejected(a) + slot;
+    const int row = (int)r->row;
+    const float y_max = r->y_max;
+    const Span<DT> rest(reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride, H, V);
+    Tile<DT> T;
+    tile_load<DT>(T, rest, tile);
+    const double inv_tau = 1.0 / (double)a.params[row].temperature;
+    u64 m = 0ull, mx = 0ull;
+    double check = 0.0;
+#pragma unroll
+    for (int u = 0; u < HU; ++u) {
+      double s;
+      m += group_mass<DT>(T.r[u], inv_tau, y_max, s);
+      check += s;
+      __builtin_amdgcn_sched_barrier(0);  // one group at a time
+    }
+    unsigned bad = !(check < (double)INFINITY) ? 1u : 0u, none = 0u;
+    fast::blk_reduce<HWV>(S, bad, none, mx, m);  // barriers inside
+    if (threadIdx.x == 0) { TailSums* t = tail_sums(a, slot); t->tsum[tile] = m; t->bad[tile] = bad; }
   }
-  if (tid == 0) {
-    dg.flags |= S.flags;
-    if (a.hot_flags && *a.hot_flags) dg.flags |= SIMPLE_DIAG_BAD_HOT_SET;
-    dg.p_chosen = err ? 0.0f : (float)((double)w_id / (double)S_K);
-    if (err) dg.n_survivors = 0;
-    a.out[row] = err ? -1 : id;
-    if (a.diag) a.diag[row] = dg;
-    if (a.stats) stats_add(a.stats, dg.flags, dg.alpha);
-    write_decision(a, row, err ? -1 : id, dg.p_chosen, false);
+}
+
+// The draw from a rejected row's tail, one workgroup per row.
+template <typename DT>
+__global__ __launch_bounds__(HT, 4) void hot_tail_draw_kernel(const SampleArgs a, int H) {
+  __shared__ FS S;
+  __shared__ u64 tsum[MAX_TILES];
+  __shared__ u64 part[HU][HWV];
+  const int tid = threadIdx.x;
+  const int V = a.V;
+  const unsigned n = min(fast::as_global(a.wq)[a.parity], (unsigned)a.wide_slots);
+  for (unsigned slot = blockIdx.x; slot < n; slot += gridDim.x) {
+    __syncthreads();
+    const Rejected r = rejected(a)[slot];
+    const int row = (int)r.row;
+    const Span<DT> rest(reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride, H, V);
+    const TailSums* t = tail_sums(a, slot);
+    u64 S_T = 0ull, mx = 0ull;
+    unsigned bad = 0u, none = 0u;
+    if (tid < rest.n_tiles) { S_T = t->tsum[tid]; bad = t->bad[tid]; tsum[tid] = S_T; }
+    double u[3];
+    row_uniforms(a.seed, a.row_offset + (uint64_t)row, a.step, u);
+    fast::blk_reduce<HWV>(S, bad, none, mx, S_T);  // barriers inside: the tile sums are in place after it
+    int id = -1;
+    u64 w_id = 0ull;
+    uint32_t flags = r.flags | (bad ? SIMPLE_DIAG_ERROR | SIMPLE_DIAG_BAD_LOGIT : 0u);
+    if (!bad && S_T > 0ull) {
+      u64 tfix = (u64)__double2ull_rd(u[2] * (double)S_T);
+      if (tfix >= S_T) tfix = S_T - 1ull;
+      id = locate<DT>(rest, 1.0 / (double)a.params[row].temperature, r.y_max, tsum, tfix, S, part, w_id);
+    }
+    if (tid == 0) {
+      if (!bad && id < 0) leave_pending(a, row);  // a class without mass: the general kernel decides
+      else write_row(a, row, id, flags, r.alpha, w_id, r.s_h + S_T);  // p~ of the drawn id over the masses as summed here
+    }
   }
 }
 
@@ -327,10 +405,19 @@ hipError_t launch_hot_range(uint32_t* bits, uint32_t* flags, int V, int H, hipSt
   return hipGetLastError();
 }
 
+template <typename DT>
+static void launch_hot_first_dtype(const SampleArgs& a, int H, const simple_tail_stats* tail, hipStream_t st) {
+  // Two workgroups of 512 threads a compute unit fit: one resident round for the tails' tiles and draws.
+  const unsigned round = 2u * (unsigned)a.n_cu, rows = (unsigned)a.B;
+  hipLaunchKernelGGL((hotfirst::hot_first_rows_kernel<DT>), dim3(rows), dim3(hotfirst::HT), 0, st, a, H, tail);
+  if (H >= a.V) return;  // no tail to reject into
+  hipLaunchKernelGGL((hotfirst::hot_tail_sums_kernel<DT>), dim3(round), dim3(hotfirst::HT), 0, st, a, H);
+  hipLaunchKernelGGL((hotfirst::hot_tail_draw_kernel<DT>), dim3(rows < round ? rows : round), dim3(hotfirst::HT), 0, st, a, H);
+}
+
 hipError_t launch_hot_first(const SampleArgs& a, int dtype, int H, const simple_tail_stats* tail, hipStream_t st) {
-  const dim3 grid((unsigned)a.B);
-  if (dtype == SIMPLE_F32) hipLaunchKernelGGL((hotfirst::hot_first_rows_kernel<float>), grid, dim3(hotfirst::HT), 0, st, a, H, tail);
-  else hipLaunchKernelGGL((hotfirst::hot_first_rows_kernel<uint16_t>), grid, dim3(hotfirst::HT), 0, st, a, H, tail);
+  if (dtype == SIMPLE_F32) launch_hot_first_dtype<float>(a, H, tail, st);
+  else launch_hot_first_dtype<uint16_t>(a, H, tail, st);
   return hipGetLastError();
 }
 
