@@ -88,11 +88,11 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   if (!elem || V >= (int64_t)FAST_MAX_V || max_nnz > 65535) return F;
   const int64_t tile = 64 * 4 * ((dtype == SIMPLE_F32) ? 4 : 8);
   const uint32_t n_words = (uint32_t)((V + 31) / 32), n_pairs = (n_words + 1u) / 2u;
-  // A vocabulary that the list holds whole (registers: CAPF_WHOLE columns per thread; LDS: 8 bytes a
-  // column and the long-list tables): every column is listed.  Beyond that a sample needs its two tiles
-  // per wave; between the two (bfloat16 rows of 12,289 to 16,383 columns) the general kernel serves the call.
-  // Four float32 rows of 1024 columns: 51 us in the general kernel, 23 us listed whole.
-  const bool whole = V <= (int64_t)CAPF_WHOLE * 1024 && V / tile < 8;
+  // A short vocabulary is listed whole (beyond it a sample needs its two tiles per wave; bfloat16 rows of 8,193
+  // to 16,383 columns have neither, and the general kernel serves them: listed whole, 4000 rows of 12,000
+  // columns took 907 us against its 874).  4 float32 rows of 1024 columns: 51 us in the general kernel, 23
+  // here; 1000 of 7000: 226 and 169.
+  const bool whole = V <= (int64_t)MAX_WHOLE && V / tile < 8;
   uint32_t off = 0;
   F.bitmap = 0;
   if (with_history) {
@@ -112,7 +112,7 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   if (whole) {
     F.whole = 1u;
     F.threads = 256;
-    while (V > (int64_t)CAPF_WHOLE * F.threads) F.threads *= 2;
+    while (V > (int64_t)capf_per_thread(F.threads, true) * F.threads) F.threads *= 2;
   }
   // Room for as many long-list entries as the epilogue's registers hold, where the compute unit's LDS has it
   // at the occupancy chosen (a sample that admits a few hundred columns too many otherwise sends its row to

@@ -37,8 +37,9 @@ struct FastLayout {
 constexpr int SAMPLE_PER_WAVE = 48;   // keys of the threshold sample a wave hands to the merge (sizes the merge area)
 // Candidate-list entries per thread that the single-pass kernel's epilogue holds in registers: 3584 to 8192 a row,
 // about twice and more what the threshold aims at.
-constexpr int CAPF_WHOLE = 12;
-constexpr int capf_per_thread(int threads, bool whole) { return whole ? CAPF_WHOLE : threads == 256 ? 14 : threads == 512 ? 12 : 8; }
+constexpr int capf_per_thread(int threads, bool whole) { return threads == 256 ? (whole ? 12 : 14) : threads == 512 ? 12 : 8; }
+constexpr int MAX_WHOLE = 8192;  // columns of a row that is listed whole
+static_assert(MAX_WHOLE <= 1024 * capf_per_thread(1024, true), "a row that is listed whole fits the registers");
 constexpr int KMAXF = 1024;   // largest top-k its list certifies
 constexpr int FAST_MAX_V = 1 << 19;  // columns from which only the general kernel serves a call: the 2^44 fixed-point masses of a
                                      // row stay below 2^63, and a row is at most 128 slices of the sliced kernels
