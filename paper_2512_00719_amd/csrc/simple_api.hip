@@ -101,7 +101,7 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
     F.cnt = off; off = align16(off + (uint32_t)((max_nnz + 3) / 2) * 4u);
     F.claim = off; off = align16(off + (uint32_t)((max_nnz + 31) / 32) * 4u);
   }
-  const uint32_t tables = 256u * 12u + 256u * 16u;           // bucket tables of the long-list epilogue
+  const uint32_t tables = NBF * 12u + MEMB2 * 16u;           // bucket tables of the long-list epilogue
   uint32_t body = off < 28672u ? 28672u : off;               // >= 14 KB of sorted-epilogue arrays, >= 3072-entry list
   if (whole && body < align16((uint32_t)V * 8u + tables)) body = align16((uint32_t)V * 8u + tables);
   F.threads = ((int64_t)body + 2048 <= (int64_t)lds_limit / 4) ? 256 : 512;  // four workgroups per compute unit, static LDS included

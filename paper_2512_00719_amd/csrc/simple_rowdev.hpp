@@ -19,9 +19,7 @@ typedef unsigned long long u64;
 
 constexpr int UNR = 4;       // 16-byte loads per lane and tile
 constexpr int SPW = SAMPLE_PER_WAVE;  // sample entries a wave hands to the merge
-constexpr int NBF = 256;     // buckets of the long-list tables
 constexpr int MEMB = 512;    // entries the sorted epilogue handles
-constexpr int MEMB2 = 256;   // members of one bucket the long-list path resolves exactly
 constexpr int idr(int threads) { return threads == 1024 ? 8 : 16; }  // history ids a thread keeps in registers (1024 threads have 128 each: no room for more)
 constexpr double WSCALE = 17592186044416.0;  // 2^44: fixed-point scale of probability mass
 constexpr int NBW = 2048;               // bins of the mass histogram (whole-vocabulary nucleus)
