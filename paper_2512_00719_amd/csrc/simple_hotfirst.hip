@@ -27,7 +27,7 @@
 // What bounds it: an accepted row is one trip through memory for its hot columns and a chain of
 // barriers.  A rejected row's tail, 12 vector instructions a column, took one compute unit 45 us, and the
 // launch ended with those rows while most of the chip was idle: 1024 rows of 201,088 bfloat16 columns with
-// H = 8192, 82 of them rejected, 68.6 us a call; 51.9 with the tails' tiles spread out (984 workgroups).
+// H = 8192, 82 of them rejected, 68.6 us a call; 41 with the tails' tiles spread out (984 workgroups).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -42,13 +42,20 @@ using fast::Io;
 using fast::u32x4;
 using fast::u64;
 
-constexpr int HT = 512;            // threads per row
-constexpr int HWV = HT / 64;
+// Threads of a workgroup.  A row's hot columns: 256, so that six rows share a compute unit and hide each
+// other's barriers (3548 bfloat16 rows, H = 8192: 108 us a call with 512, 63 so).  A tail's tile: 512.
+constexpr int ROW_T = 256, TAIL_T = 512;
 constexpr int HU = 4;              // 16-byte groups per thread and tile
 constexpr int STEP = 256;          // the hot set is a whole number of steps of 256 groups
 constexpr int MAX_STEPS = 1024;    // steps of hot set or tail (V below 2^20 with float32, 2^21 with bfloat16)
-constexpr int MAX_TILES = MAX_STEPS * STEP / (HT * HU) + 1;
-static_assert(MAX_TILES <= HT, "one tile per thread in the scan over tiles");
+constexpr int max_tiles(int threads) { return MAX_STEPS * STEP / (threads * HU); }  // of whole steps
+constexpr int MAX_TAIL_TILES = max_tiles(TAIL_T) + 1;                              // (a tail may end in part of one)
+static_assert(max_tiles(ROW_T) <= ROW_T && MAX_TAIL_TILES <= TAIL_T, "one tile per thread in the scan over tiles");
+// A tail of up to 128 KB is streamed by its row's own workgroup, and so is any tail of a batch of up to three rows:
+// there the two launches for the tails' tiles cost more than the 10 us they save now and then.
+constexpr int OWN_TAIL_BYTES = 128 << 10, OWN_TAIL_ROWS = 3;
+constexpr int64_t OWN_TAIL_MAX = (int64_t)(max_tiles(ROW_T) - 1) * ROW_T * HU * 16;  // tiles that a row's workgroup can index
+static_assert(OWN_TAIL_BYTES < OWN_TAIL_MAX, "a short tail fits the tile sums");
 
 // Tempered value (the IEEE quotient z / tau) and mass exp(y - y_max) of a column: float32 exponential
 // with a split log2(e).
@@ -61,7 +68,7 @@ __device__ __forceinline__ u64 to_fix(double m) { return (u64)__double2ull_rn(m 
 
 // The columns [c0, c1) of a row as 16-byte groups (c0 is a whole number of them); the columns behind the
 // last whole group make one more, filled up with -inf (no mass).
-template <typename DT>
+template <typename DT, int HT>
 struct Span {
   static constexpr int EPL = Io<DT>::EPL;
   static constexpr uint32_t NONE = sizeof(DT) == 4 ? 0xFF800000u : 0xFF80FF80u;  // -inf
@@ -87,15 +94,15 @@ struct Span {
 // A thread's groups of one tile: group tile * HT * HU + u * HT + tid.
 template <typename DT>
 struct Tile { Raw<DT> r[HU]; };
-template <typename DT>
-__device__ __forceinline__ void tile_load(Tile<DT>& T, const Span<DT>& C, int tile) {
+template <typename DT, int HT>
+__device__ __forceinline__ void tile_load(Tile<DT>& T, const Span<DT, HT>& C, int tile) {
   const int g0 = tile * HU * HT + (int)threadIdx.x;
   const Raw<DT>* q = reinterpret_cast<const Raw<DT>*>(C.p);
   if ((tile + 1) * HU * HT <= C.whole) {
 #pragma unroll
     for (int u = 0; u < HU; ++u) T.r[u] = fast::as_global(q)[g0 + u * HT];
   } else {
-    const Raw<DT> none = __builtin_bit_cast(Raw<DT>, u32x4{Span<DT>::NONE, Span<DT>::NONE, Span<DT>::NONE, Span<DT>::NONE});
+    const Raw<DT> none = __builtin_bit_cast(Raw<DT>, u32x4{Span<DT, HT>::NONE, Span<DT, HT>::NONE, Span<DT, HT>::NONE, Span<DT, HT>::NONE});
 #pragma unroll
     for (int u = 0; u < HU; ++u) {
       const int g = g0 + u * HT;
@@ -117,8 +124,8 @@ __device__ __forceinline__ u64 group_mass(const Raw<DT>& r, double inv_tau, floa
 // Sums of the masses of columns [c0, c1) by tile into tsum[]; returns (all threads) their total.  bad is
 // raised for a NaN or +inf tempered value.  `first`: the first tile, already loaded; the next tile is
 // in flight while one is summed.
-template <typename DT>
-__device__ __forceinline__ u64 tile_masses(const Tile<DT>& first, const Span<DT>& C, double inv_tau, float y_max, u64* tsum, FS& S, bool& bad) {
+template <typename DT, int HT>
+__device__ __forceinline__ u64 tile_masses(const Tile<DT>& first, const Span<DT, HT>& C, double inv_tau, float y_max, u64* tsum, FS& S, bool& bad) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int n_tiles = C.n_tiles;
   for (int i = tid; i < n_tiles; i += HT) tsum[i] = 0ull;
@@ -128,7 +135,7 @@ __device__ __forceinline__ u64 tile_masses(const Tile<DT>& first, const Span<DT>
   Tile<DT> T = first;
   for (int i = 0; i < n_tiles; ++i) {
     Tile<DT> N = T;
-    if (i + 1 < n_tiles) tile_load<DT>(N, C, i + 1);
+    if (i + 1 < n_tiles) tile_load<DT, HT>(N, C, i + 1);
     u64 m = 0ull;
 #pragma unroll
     for (int u = 0; u < HU; ++u) {
@@ -143,12 +150,13 @@ __device__ __forceinline__ u64 tile_masses(const Tile<DT>& first, const Span<DT>
     T = N;
   }
   bad = bad || !(check < (double)INFINITY);
-  return fast::blk_sum_u64<HWV>(S, total);  // barriers inside: the tile sums are complete after it
+  return fast::blk_sum_u64<HT / 64>(S, total);  // barriers inside: the tile sums are complete after it
 }
 
 // The column of [c0, c1) at which the running mass (ascending id) first exceeds tfix; its mass in w_out.
-template <typename DT>
-__device__ __forceinline__ int locate(const Span<DT>& C, double inv_tau, float y_max, const u64* tsum, u64 tfix, FS& S, u64 (&part)[HU][HWV], u64& w_out) {
+template <typename DT, int HT>
+__device__ __forceinline__ int locate(const Span<DT, HT>& C, double inv_tau, float y_max, const u64* tsum, u64 tfix, FS& S, u64 (&part)[HU][HT / 64], u64& w_out) {
+  constexpr int HWV = HT / 64;
   constexpr int EPL = Io<DT>::EPL;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n_tiles = C.n_tiles;
@@ -164,7 +172,7 @@ __device__ __forceinline__ int locate(const Span<DT>& C, double inv_tau, float y
   const int tile = S.bd;
   if (tile < 0) return -1;
   Tile<DT> T;
-  tile_load<DT>(T, C, tile);
+  tile_load<DT, HT>(T, C, tile);
   u64 g[HU], incl[HU];
 #pragma unroll
   for (int u = 0; u < HU; ++u) {
@@ -208,7 +216,7 @@ __device__ __forceinline__ int locate(const Span<DT>& C, double inv_tau, float y
 // What the kernels behind this one need of a rejected row (a queue record), and its workspace slot.
 struct Rejected { uint32_t row, flags; float y_max; uint32_t unused; u64 s_h; double alpha; u64 pad[4]; };
 static_assert(sizeof(Rejected) == 64, "queue record size");
-struct TailSums { u64 tsum[MAX_TILES]; uint32_t bad[MAX_TILES]; };  // per tile of the tail; bad: a NaN or +inf among its columns
+struct TailSums { u64 tsum[MAX_TAIL_TILES]; uint32_t bad[MAX_TAIL_TILES]; };  // per tile of the tail; bad: a NaN or +inf among its columns
 static_assert(sizeof(TailSums) <= WIDE_SLOT_FIXED, "workspace slot size");
 __device__ __forceinline__ Rejected* rejected(const SampleArgs& a) { return reinterpret_cast<Rejected*>(a.wq + fast::WQ_HEAD); }
 __device__ __forceinline__ TailSums* tail_sums(const SampleArgs& a, unsigned slot) { return reinterpret_cast<TailSums*>(a.wws + (size_t)slot * a.ws_stride); }
@@ -233,10 +241,10 @@ __device__ __forceinline__ void leave_pending(const SampleArgs& a, int row) {
 }
 
 template <typename DT>
-__global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs a, int H, const simple_tail_stats* __restrict__ tail) {
-  constexpr int EPL = Io<DT>::EPL;
+__global__ __launch_bounds__(ROW_T, 6) void hot_first_rows_kernel(const SampleArgs a, int H, const simple_tail_stats* __restrict__ tail, bool own_tail) {
+  constexpr int EPL = Io<DT>::EPL, HT = ROW_T, HWV = HT / 64;
   __shared__ FS S;
-  __shared__ u64 tsum[MAX_TILES];
+  __shared__ u64 tsum[max_tiles(ROW_T)];
   __shared__ u64 part[HU][HWV];
   const int tid = threadIdx.x;
   const int row = blockIdx.x;
@@ -253,8 +261,8 @@ __global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs 
     return;
   }
   Tile<DT> T0;  // the first tile of the hot columns (all of them up to 8192 or 16,384): read once, used for the maximum and the masses
-  const Span<DT> hot(rowp, 0, H);
-  tile_load<DT>(T0, hot, 0);
+  const Span<DT, HT> hot(rowp, 0, H);
+  tile_load<DT, HT>(T0, hot, 0);
   const double inv_tau = 1.0 / (double)par.temperature;
   double u[3];
   row_uniforms(a.seed, a.row_offset + (uint64_t)row, a.step, u);
@@ -271,7 +279,7 @@ __global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs 
     }
   };
   take_max(T0);
-  for (int i = 1; i < hot.n_tiles; ++i) { Tile<DT> T; tile_load<DT>(T, hot, i); take_max(T); }
+  for (int i = 1; i < hot.n_tiles; ++i) { Tile<DT> T; tile_load<DT, HT>(T, hot, i); take_max(T); }
   kmax = fast::wave_max_u32(kmax);
   if (tid == 0) { S.kmax = KEY_NEG_INF; S.flags = 0u; }
   __syncthreads();
@@ -285,7 +293,7 @@ __global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs 
   if (has_tail && (ts.tail_max != ts.tail_max || ts.tail_max == INFINITY || !(ts.tail_sum >= 0.0) || ts.tail_sum == (double)INFINITY)) bad = true;
   if (y_max == INFINITY || z_top == -INFINITY) bad = true;               // overflow of z / tau, or nothing to draw
   // ---- hot mass by tile, tail mass from the caller's statistics (Eq. (7)) ----
-  const u64 S_H = tile_masses<DT>(T0, hot, inv_tau, y_max, tsum, S, bad);
+  const u64 S_H = tile_masses<DT, HT>(T0, hot, inv_tau, y_max, tsum, S, bad);
   if (bad) atomicOr(&S.flags, SIMPLE_DIAG_ERROR | SIMPLE_DIAG_BAD_LOGIT);
   __syncthreads();
   uint32_t flags = SIMPLE_DIAG_SHVS;
@@ -302,8 +310,21 @@ __global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs 
       flags |= SIMPLE_DIAG_ACCEPTED;
       u64 tfix = (u64)__double2ull_rd(u[0] * (double)S_H);
       if (tfix >= S_H) tfix = S_H - 1ull;
-      id = locate<DT>(hot, inv_tau, y_max, tsum, tfix, S, part, w_id);
-    } else if (has_tail) {  // rejected: the tail proposal r of Eq. (8), over the columns not read yet
+      id = locate<DT, HT>(hot, inv_tau, y_max, tsum, tfix, S, part, w_id);
+    } else if (own_tail) {  // rejected: the tail proposal r of Eq. (8), over the columns not read yet
+      bool bad_t = false;
+      const Span<DT, HT> rest(rowp, H, V);
+      tile_load<DT, HT>(T0, rest, 0);
+      const u64 S_T_exact = tile_masses<DT, HT>(T0, rest, inv_tau, y_max, tsum, S, bad_t);
+      if (bad_t) atomicOr(&S.flags, SIMPLE_DIAG_ERROR | SIMPLE_DIAG_BAD_LOGIT);
+      __syncthreads();
+      if (!(S.flags & SIMPLE_DIAG_ERROR) && S_T_exact > 0ull) {
+        u64 tfix = (u64)__double2ull_rd(u[2] * (double)S_T_exact);
+        if (tfix >= S_T_exact) tfix = S_T_exact - 1ull;
+        id = locate<DT, HT>(rest, inv_tau, y_max, tsum, tfix, S, part, w_id);
+        S_K = S_H + S_T_exact;  // p~ of the drawn id over the masses as summed here
+      }
+    } else if (has_tail) {
       if (tid == 0) {
         const unsigned slot = atomicAdd(&a.wq[a.parity], 1u);  // a launch has a slot for every row
         Rejected* r = rejected(a) + slot;
@@ -321,7 +342,8 @@ __global__ __launch_bounds__(HT, 4) void hot_first_rows_kernel(const SampleArgs 
 
 // The tile sums of the rejected rows' tails: items are (queued row, tile) pairs, taken in turn.
 template <typename DT>
-__global__ __launch_bounds__(HT, 4) void hot_tail_sums_kernel(const SampleArgs a, int H) {
+__global__ __launch_bounds__(TAIL_T, 4) void hot_tail_sums_kernel(const SampleArgs a, int H) {
+  constexpr int HT = TAIL_T, HWV = HT / 64;
   __shared__ FS S;
   const int V = a.V;
   const unsigned n = min(fast::as_global(a.wq)[a.parity], (unsigned)a.wide_slots);
@@ -332,9 +354,9 @@ __global__ __launch_bounds__(HT, 4) void hot_tail_sums_kernel(const SampleArgs a
     const Rejected* r = rejected(a) + slot;
     const int row = (int)r->row;
     const float y_max = r->y_max;
-    const Span<DT> rest(reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride, H, V);
+    const Span<DT, HT> rest(reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride, H, V);
     Tile<DT> T;
-    tile_load<DT>(T, rest, tile);
+    tile_load<DT, HT>(T, rest, tile);
     const double inv_tau = 1.0 / (double)a.params[row].temperature;
     u64 m = 0ull, mx = 0ull;
     double check = 0.0;
@@ -353,9 +375,10 @@ __global__ __launch_bounds__(HT, 4) void hot_tail_sums_kernel(const SampleArgs a
 
 // The draw from a rejected row's tail, one workgroup per row.
 template <typename DT>
-__global__ __launch_bounds__(HT, 4) void hot_tail_draw_kernel(const SampleArgs a, int H) {
+__global__ __launch_bounds__(TAIL_T, 4) void hot_tail_draw_kernel(const SampleArgs a, int H) {
+  constexpr int HT = TAIL_T, HWV = HT / 64;
   __shared__ FS S;
-  __shared__ u64 tsum[MAX_TILES];
+  __shared__ u64 tsum[MAX_TAIL_TILES];
   __shared__ u64 part[HU][HWV];
   const int tid = threadIdx.x;
   const int V = a.V;
@@ -364,7 +387,7 @@ __global__ __launch_bounds__(HT, 4) void hot_tail_draw_kernel(const SampleArgs a
     __syncthreads();
     const Rejected r = rejected(a)[slot];
     const int row = (int)r.row;
-    const Span<DT> rest(reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride, H, V);
+    const Span<DT, HT> rest(reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride, H, V);
     const TailSums* t = tail_sums(a, slot);
     u64 S_T = 0ull, mx = 0ull;
     unsigned bad = 0u, none = 0u;
@@ -378,7 +401,7 @@ __global__ __launch_bounds__(HT, 4) void hot_tail_draw_kernel(const SampleArgs a
     if (!bad && S_T > 0ull) {
       u64 tfix = (u64)__double2ull_rd(u[2] * (double)S_T);
       if (tfix >= S_T) tfix = S_T - 1ull;
-      id = locate<DT>(rest, 1.0 / (double)a.params[row].temperature, r.y_max, tsum, tfix, S, part, w_id);
+      id = locate<DT, HT>(rest, 1.0 / (double)a.params[row].temperature, r.y_max, tsum, tfix, S, part, w_id);
     }
     if (tid == 0) {
       if (!bad && id < 0) leave_pending(a, row);  // a class without mass: the general kernel decides
@@ -409,10 +432,12 @@ template <typename DT>
 static void launch_hot_first_dtype(const SampleArgs& a, int H, const simple_tail_stats* tail, hipStream_t st) {
   // Two workgroups of 512 threads a compute unit fit: one resident round for the tails' tiles and draws.
   const unsigned round = 2u * (unsigned)a.n_cu, rows = (unsigned)a.B;
-  hipLaunchKernelGGL((hotfirst::hot_first_rows_kernel<DT>), dim3(rows), dim3(hotfirst::HT), 0, st, a, H, tail);
-  if (H >= a.V) return;  // no tail to reject into
-  hipLaunchKernelGGL((hotfirst::hot_tail_sums_kernel<DT>), dim3(round), dim3(hotfirst::HT), 0, st, a, H);
-  hipLaunchKernelGGL((hotfirst::hot_tail_draw_kernel<DT>), dim3(rows < round ? rows : round), dim3(hotfirst::HT), 0, st, a, H);
+  const int64_t tail_bytes = (int64_t)(a.V - H) * (int64_t)sizeof(DT);
+  const bool own_tail = tail_bytes <= hotfirst::OWN_TAIL_BYTES || (rows <= (unsigned)hotfirst::OWN_TAIL_ROWS && tail_bytes < hotfirst::OWN_TAIL_MAX);
+  hipLaunchKernelGGL((hotfirst::hot_first_rows_kernel<DT>), dim3(rows), dim3(hotfirst::ROW_T), 0, st, a, H, tail, own_tail);
+  if (own_tail) return;
+  hipLaunchKernelGGL((hotfirst::hot_tail_sums_kernel<DT>), dim3(round), dim3(hotfirst::TAIL_T), 0, st, a, H);
+  hipLaunchKernelGGL((hotfirst::hot_tail_draw_kernel<DT>), dim3(rows < round ? rows : round), dim3(hotfirst::TAIL_T), 0, st, a, H);
 }
 
 hipError_t launch_hot_first(const SampleArgs& a, int dtype, int H, const simple_tail_stats* tail, hipStream_t st) {
