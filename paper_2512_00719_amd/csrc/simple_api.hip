@@ -26,7 +26,6 @@ struct simple_ctx {
   unsigned char* wws;   // device: their workspace, `slots` slots
   uint32_t ws_stride;   // bytes per slot
   int slots;            // rows per launch: every row of a launch can be queued, with a slot
-  int parity;           // which queue counters the next launch uses
   hipEvent_t* prof_ev;  // 2 * PROF_MAX events while profiling is enabled, else null
   int prof_n;           // launches recorded so far
   void* base;           // device allocation that holds all of the above (null: not owned)
@@ -51,7 +50,7 @@ struct simple_state {
 namespace simple {
 
 // Device memory of a context, carved from one block: hot-set bitmap (max_V bits), one flag word, the
-// pending-row queue (two counters, then one entry per row of a launch), the wide-row queue (a head,
+// pending-row queue (two words, then one entry per row of a launch), the wide-row queue (a head,
 // then one 64-byte record per slot) and the slots.  Every part starts on a 256-byte boundary.
 struct CtxLayout { size_t hot_bits, hot_flags, pend, order, wq, wws, total; uint32_t ws_stride; };
 // Maxima of simple_sample_static, whose context lives in a static device array.
@@ -199,7 +198,7 @@ int simple_create(simple_ctx** out, int device, int64_t max_B, int64_t max_V, in
   simple_ctx* c = new (std::nothrow) simple_ctx();
   if (!c) return SIMPLE_ENOMEM;
   c->device = device; c->max_V = max_V; c->max_nnz = max_nnz_per_row; c->lds_limit = lds; c->n_cu = n_cu;
-  c->hot_V = 0; c->hot_H = 0; c->hot_is_range = false; c->hot_bits = nullptr; c->hot_flags = nullptr; c->pend = nullptr; c->order = nullptr; c->wq = nullptr; c->wws = nullptr; c->ws_stride = 0; c->parity = 0;
+  c->hot_V = 0; c->hot_H = 0; c->hot_is_range = false; c->hot_bits = nullptr; c->hot_flags = nullptr; c->pend = nullptr; c->order = nullptr; c->wq = nullptr; c->wws = nullptr; c->ws_stride = 0;
   c->prof_ev = nullptr; c->prof_n = 0; c->base = nullptr; c->slots = 0; c->stats = nullptr;
   c->logprobs = nullptr; c->eos_out = nullptr; c->n_eos = 0;
   c->slots = (int)(max_B < (int64_t)simple::WIDE_SLOTS ? max_B : (int64_t)simple::WIDE_SLOTS);
@@ -398,8 +397,6 @@ static int sample_impl(simple_ctx* ctx, const simple_state* state, const int32_t
     a.logprobs = ctx->logprobs ? ctx->logprobs + b0 : nullptr;
     a.eos_out = ctx->eos_out ? ctx->eos_out + b0 : nullptr;
     a.order = (a.F.total != 0u && !a.F.whole && !tail && nb > (int64_t)ctx->n_cu) ? ctx->order : nullptr;
-    a.parity = ctx->parity;
-    if (a.gated) ctx->parity ^= 1;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (ctx->prof_ev && ctx->prof_n < PROF_MAX) { ev0 = ctx->prof_ev[2 * ctx->prof_n]; ev1 = ctx->prof_ev[2 * ctx->prof_n + 1]; ++ctx->prof_n; }
     if (tail) {  // the hot-first kernel, then the general kernel on the rows it left
@@ -556,7 +553,7 @@ static simple_ctx* static_ctx(int* err) {
   c->ws_stride = L.ws_stride;
   c->slots = STATIC_SLOTS;
   // The array is zero when the code object is loaded, which is what the queue counters need at the
-  // first launch; afterwards every launch clears the pair of counters the previous one used, the
+  // first launch; afterwards the last kernel of every launch clears them again, the
   // hot-set bitmap is rebuilt by the call that passes a hot set, and a slot is cleared by the row
   // that takes it.
   g_static_ready[device] = true;

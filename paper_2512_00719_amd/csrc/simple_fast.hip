@@ -468,7 +468,7 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
 }
 
 __device__ inline void queue_pending(const SampleArgs& a, int row) {
-  const unsigned slot = atomicAdd(&a.pend[a.parity], 1u);
+  const unsigned slot = atomicAdd(&a.pend[0], 1u);
   a.pend[2 + slot] = (uint32_t)row;
   a.out[row] = PENDING;
 }
@@ -496,10 +496,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   const int V = a.V;
   const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride;
   // the pattern-count kernel, when it ran before this one, has left NOT_TAKEN on every row that is still to do
-  if (a.pattern_on && a.out[row] != NOT_TAKEN) {
-    if (blockIdx.x == 0 && tid == 0) { a.pend[a.parity ^ 1] = 0u; a.wq[a.parity ^ 1] = 0u; }  // the previous launch's counts
-    return;
-  }
+  if (a.pattern_on && a.out[row] != NOT_TAKEN) return;
   // this wave's first two tiles (its threshold sample): issued before anything else
   // (a row that fits the list whole has at most one tile per wave and no sample)
   const int nfull = V / T;  // else the host guarantees nfull >= 2 * NWV
@@ -516,7 +513,6 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     for (int u = 0; u < UNR; ++u) Bf[u] = Io<DT>::load(rowp + (size_t)(t0 + 1) * T + u * 64 * EPL + lane * EPL);
   }
   const simple_row_params par = a.params[row];
-  if (blockIdx.x == 0 && tid == 0) { a.pend[a.parity ^ 1] = 0u; a.wq[a.parity ^ 1] = 0u; }  // the previous launch's counts
   uint32_t* samp = reinterpret_cast<uint32_t*>(lds + a.F.samp);
 
   // ---- row configuration (identical in every thread) ----
@@ -590,7 +586,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   {
     int ids[IDR];
 #pragma unroll
-    for (int j = 0; j < IDR; ++j) { const int i = tid + j * NTHR; ids[j] = (h_active && !stateful && i < nnz) ? hist[i] : -1; }
+    for (int j = 0; j < IDR; ++j) { const int i = tid + j * NTHR; ids[j] = (!whole && h_active && !stateful && i < nnz) ? hist[i] : -1; }
     {
       double u[3];
       row_uniforms(a.seed, a.row_offset + (uint64_t)row, a.step, u);
@@ -598,7 +594,8 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
     __syncthreads();
     // ---- presence mask of the history (in the shared region); all tables for a row that leaves early ----
-    if (H.active) {
+    // (a row that is listed whole has no sample to keep the history out of)
+    if (!whole && H.active) {
       if (stateful) load_tables(straight);
       else if (straight) { unsigned own; build_history<NTHR>(S, H, ids, hist, nnz, rh.n_prompt, V, own); }
       else build_bitmap<NTHR>(S, H, ids, hist, nnz, V);
@@ -622,7 +619,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
         build_history<NTHR>(S, H, ids2, hist, nnz, rh.n_prompt, V, own);
       }
     }
-    if (tid == 0) S.e_n = atomicAdd(&a.wq[a.parity], 1u);
+    if (tid == 0) S.e_n = atomicAdd(&a.wq[0], 1u);
     __syncthreads();
     const unsigned slot = S.e_n;
     const unsigned hb = H.active ? (a.F.cnt + (unsigned)((nnz + 3) / 2) * 4u + 15u) / 16u : 0u;  // 16-byte units of history tables
@@ -914,6 +911,10 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       }
       kloc = max(kloc, key[j]);
     }
+    // What the branches below derive from an entry is formed there: carried across them all, it cost the instances
+    // for rows listed whole 40 to 150 spilled registers (4 rows of 1024 columns 27.7 us, 22.4 so).
+#pragma unroll
+    for (int j = 0; j < PER; ++j) asm volatile("" : "+v"(key[j]), "+v"(eid[j]));
     if (kloc) atomicMax(&S.kmax, kloc);
     if (complete) {
       uint32_t kmin = 0xFFFFFFFFu;
@@ -994,7 +995,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
   }
   if (rc == FIN_WIDE) {
-    if (queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, tables_live, g_ref)) return;
+    if (!whole && queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, tables_live, g_ref)) return;  // (no such kernel runs behind rows listed whole)
     rc = FIN_PENDING;  // no free slot: the general kernel takes the row
   }
   if (tid == 0) {

@@ -235,7 +235,7 @@ __device__ __forceinline__ void write_row(const SampleArgs& a, int row, int id, 
   write_decision(a, row, err ? -1 : id, dg.p_chosen, false);
 }
 __device__ __forceinline__ void leave_pending(const SampleArgs& a, int row) {
-  const unsigned slot = atomicAdd(&a.pend[a.parity], 1u);
+  const unsigned slot = atomicAdd(&a.pend[0], 1u);
   a.pend[2 + slot] = (uint32_t)row;
   a.out[row] = PENDING;
 }
@@ -252,7 +252,6 @@ __global__ __launch_bounds__(ROW_T, 6) void hot_first_rows_kernel(const SampleAr
   const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride;
   const simple_row_params par = a.params[row];
   const simple_tail_stats ts = tail[row];
-  if (row == 0 && tid == 0) { a.pend[a.parity ^ 1] = 0u; a.wq[a.parity ^ 1] = 0u; }  // the previous launch's counts
   // the pattern-count kernel, when it ran before this one, has left NOT_TAKEN on every row that is still to do
   if (a.pattern_on && a.out[row] != NOT_TAKEN) return;
   const bool plain = hot_first_plain(par, V);
@@ -326,7 +325,7 @@ __global__ __launch_bounds__(ROW_T, 6) void hot_first_rows_kernel(const SampleAr
       }
     } else if (has_tail) {
       if (tid == 0) {
-        const unsigned slot = atomicAdd(&a.wq[a.parity], 1u);  // a launch has a slot for every row
+        const unsigned slot = atomicAdd(&a.wq[0], 1u);  // a launch has a slot for every row
         Rejected* r = rejected(a) + slot;
         r->row = (uint32_t)row; r->flags = flags | S.flags; r->y_max = y_max; r->s_h = S_H; r->alpha = alpha;
         a.out[row] = PENDING;
@@ -346,7 +345,7 @@ __global__ __launch_bounds__(TAIL_T, 4) void hot_tail_sums_kernel(const SampleAr
   constexpr int HT = TAIL_T, HWV = HT / 64;
   __shared__ FS S;
   const int V = a.V;
-  const unsigned n = min(fast::as_global(a.wq)[a.parity], (unsigned)a.wide_slots);
+  const unsigned n = min(fast::as_global(a.wq)[0], (unsigned)a.wide_slots);
   const int n_tiles = ((V - H + Io<DT>::EPL - 1) / Io<DT>::EPL + HT * HU - 1) / (HT * HU);
   for (unsigned it = blockIdx.x; it < n * (unsigned)n_tiles; it += gridDim.x) {
     const unsigned slot = it / (unsigned)n_tiles;
@@ -382,7 +381,7 @@ __global__ __launch_bounds__(TAIL_T, 4) void hot_tail_draw_kernel(const SampleAr
   __shared__ u64 part[HU][HWV];
   const int tid = threadIdx.x;
   const int V = a.V;
-  const unsigned n = min(fast::as_global(a.wq)[a.parity], (unsigned)a.wide_slots);
+  const unsigned n = min(fast::as_global(a.wq)[0], (unsigned)a.wide_slots);
   for (unsigned slot = blockIdx.x; slot < n; slot += gridDim.x) {
     __syncthreads();
     const Rejected r = rejected(a)[slot];

@@ -1529,8 +1529,9 @@ __global__ __launch_bounds__(NT, 4) void sample_rows_kernel(const SampleArgs a) 
 }
 
 // Completes the rows the single-pass kernel queued: workgroup i takes queue entries i, i + grid, ...
-// The next launch's single-pass kernel clears the count.  The queue is empty in the common case, so
-// the count is looked at first.  The row body takes the arguments by reference; handing it the
+// The queue is empty in the common case, so the count is looked at first.  Both queues' counts are zero
+// again when the launch has ended: the sliced kernels, which read wq's, are done, and pend's is cleared
+// by the last workgroup to have read it.  The row body takes the arguments by reference; handing it the
 // by-value parameter would make every lane of every launch copy the whole record to scratch memory
 // at the kernel's entry (220 bytes a lane, 28 MB a launch), so it gets the record where the launch
 // placed it, in the kernel-argument segment (the record is the kernel's only parameter).
@@ -1546,7 +1547,11 @@ template <typename DT, bool VEC>
 __global__ __launch_bounds__(NT, 4) void pending_rows_kernel(const SampleArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ Shared S;
-  const unsigned n = min(__hip_atomic_load(&a.pend[a.parity], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), (unsigned)a.B);
+  const unsigned n = min(__hip_atomic_load(&a.pend[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), (unsigned)a.B);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && a.wq[0] != 0u) a.wq[0] = 0u;
+  if (n == 0u) return;
+  __syncthreads();  // every thread has read the count
+  if (threadIdx.x == 0 && atomicAdd(&a.pend[1], 1u) == gridDim.x - 1u) { a.pend[0] = 0u; a.pend[1] = 0u; }
   if (blockIdx.x >= n) return;
   const SampleArgs* in_place = (const SampleArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   pending_rows_body<DT, VEC>(*in_place, n, lds, S);

@@ -91,16 +91,15 @@ struct SampleArgs {
   int gated;       // 1: the single-pass kernel runs first and queues the rows it leaves
   int pattern_on;  // the pattern-count kernel (bfloat16 rows without penalties and without a short top-k) ran first: 1 before the
                    // single-pass kernel, 2 before the hot-first kernel (it then leaves that kernel's own rows alone)
-  // Queues filled by the single-pass kernel.  Word [parity] counts the entries of this launch; the
-  // single-pass kernel clears word [parity ^ 1], which the previous launch on the stream used.
-  uint32_t* pend;  // rows left to the general kernel: [0], [1] counts, [2 ..] row indices
+  // Queues of the rows that a kernel leaves to a later one of the same launch.  The counts are zero between
+  // launches: the general kernel, the last one, clears them, so that a captured launch can be replayed.
+  uint32_t* pend;  // rows left to the general kernel: [0] count, [1] its workgroups that have read the count, [2 ..] row indices
   int32_t* order;  // row of each workgroup of the single-pass kernel (written by the ordering kernel of a launch with more rows
                    // than compute units), or nullptr: workgroup b takes row b
-  uint32_t* wq;    // rows with a whole-vocabulary nucleus wider than the list: [0], [1] counts, records from word 16
+  uint32_t* wq;    // rows with a whole-vocabulary nucleus wider than the list: [0] count, records from word 16
   unsigned char* wws;  // one workspace slot per queued row
   int wide_slots;
   uint32_t ws_stride;  // bytes per slot: fixed part, then the row's history tables
-  int parity;
   int n_cu;        // compute units of the device (sizes the grids of the sliced kernels)
   LdsLayout L;
   FastLayout F;

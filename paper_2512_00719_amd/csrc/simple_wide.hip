@@ -383,7 +383,7 @@ __device__ __forceinline__ ZCut z_cut(const WideRow& W, int bstar, float thr_y) 
 struct Items { unsigned i0, i1, n_sl; };
 __device__ __forceinline__ Items my_items(const SampleArgs& a) {
   Items I;
-  const unsigned n_wide = min(as_global(a.wq)[a.parity], (unsigned)a.wide_slots);
+  const unsigned n_wide = min(as_global(a.wq)[0], (unsigned)a.wide_slots);
   I.n_sl = (unsigned)((a.V + SLC - 1) / SLC);
   const unsigned items = n_wide * I.n_sl;
   const unsigned chunk = (items + gridDim.x - 1u) / gridDim.x;
@@ -539,7 +539,7 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
   static_assert((WT * EPL) % 32 == 0, "group stride in mask words");
   const Items I = my_items(a);
   if (I.i0 >= I.i1) return;
-  const unsigned n_wide = min(as_global(a.wq)[a.parity], (unsigned)a.wide_slots);
+  const unsigned n_wide = min(as_global(a.wq)[0], (unsigned)a.wide_slots);
   int cur = (int)(I.i0 / I.n_sl);
   SlotIds ids;
   ids.request(a, (unsigned)cur, n_wide, ids.row_c, ids.act_c);
@@ -699,7 +699,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
   const Items I = my_items(a);
   if (I.i0 >= I.i1) return;
   const uint32_t* hot_bits = a.hot_bits;
-  const unsigned n_wide = min(as_global(a.wq)[a.parity], (unsigned)a.wide_slots);
+  const unsigned n_wide = min(as_global(a.wq)[0], (unsigned)a.wide_slots);
   int cur = (int)(I.i0 / I.n_sl);
   SlotIds ids;
   ids.request(a, (unsigned)cur, n_wide, ids.row_c, ids.act_c);
@@ -899,7 +899,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
 
 // ---------------------------------------------------------------- finish ----------------------
 __device__ inline void hand_on(const SampleArgs& a, int row) {
-  const unsigned slot = atomicAdd(&a.pend[a.parity], 1u);
+  const unsigned slot = atomicAdd(&a.pend[0], 1u);
   a.pend[2 + slot] = (uint32_t)row;
   a.out[row] = PENDING;
 }
@@ -1294,7 +1294,7 @@ __global__ __launch_bounds__(WT) void wide_finish_kernel(const SampleArgs a) {
   __shared__ u64 tiles[512];
   __shared__ FS S;
   const int tid = threadIdx.x;
-  const unsigned n_wide = min(as_global(a.wq)[a.parity], (unsigned)a.wide_slots);
+  const unsigned n_wide = min(as_global(a.wq)[0], (unsigned)a.wide_slots);
   for (unsigned slot = blockIdx.x; slot < n_wide; slot += gridDim.x) {
     __syncthreads();
     const WideRow W = load_row(a, slot);
