@@ -56,14 +56,10 @@ __device__ __forceinline__ uint32_t wave_threshold(const uint32_t (&k)[N], unsig
   return lo;
 }
 
-// Fixed-point weight exp(y - y_max) * 2^44 (stable softmax numerator, section 2.1 Eq. (2)).  The
-// exponential is float32 with a split log2(e): relative error about 1e-7, far inside the 1e-5
-// tolerance on probabilities; the sums are exact integers.
-__device__ __forceinline__ u64 wfix(uint32_t key, float y_max) {
-  const float d = keyf(key) - y_max;
-  const float t = fmaf(d, L2E_HI, d * L2E_LO);
-  return float_to_u64(__builtin_amdgcn_exp2f(t) * 0x1p44f);  // the scaling is exact
-}
+// Fixed-point weight exp(y - y_max) * 2^44 (stable softmax numerator, section 2.1 Eq. (2)); the sums are
+// exact integers.  In double precision, as the general kernel weighs a row: with a float32 exponential
+// p~ was up to 4e-7 off, here it is the float32 nearest to the exact one.
+__device__ __forceinline__ u64 wfix(uint32_t key, float y_max) { return exp_fix<44>(keyf(key), y_max); }
 
 // Unpacks one 16-byte group of a sample tile; columns that are in the history are masked out, so
 // the threshold comes from unpenalised columns only (history columns can only add to the prefix).
@@ -396,21 +392,27 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
   if (p_found && cut_p > cut) cut = cut_p;
   if (m_cert && cut_m > cut) cut = cut_m;
   if (cut > cmax) cut = cmax;  // never empty
-  // ---- survivors K_b, their mass, the hot split (Eq. (7)) ----
+  // ---- survivors K_b by ranges of ids, all and the hot ones: their masses (Eq. (7)) and where the draw lies ----
+  // (one weighing of the list for both)
   const bool use_hot = hot_bits != nullptr;
-  unsigned ns = 0, nh = 0; u64 sk = 0ull, sh = 0ull, cdum = 0ull;
+  const int ishift = max(0, 32 - (int)__clz((unsigned)(R.V - 1) | 1u) - 8);
+  u64* hmass = mc;  // the member table is free here
+  for (int i = tid; i < NBF; i += NTHR) { fmass[i] = 0ull; if (use_hot) hmass[i] = 0ull; }
+  __syncthreads();
+  unsigned ns = 0;
   for (unsigned i = tid; i < n; i += NTHR) {
-    const uint32_t k = lk[i];
-    if (composite(k, li[i]) >= cut) {
+    const uint32_t k = lk[i], id = li[i];
+    if (composite(k, id) >= cut) {
       const u64 w = wfix(k, y_max);
-      ++ns; sk += w;
-      if (use_hot && hot_bit(hot_bits, li[i])) { ++nh; sh += w; }
+      ++ns;
+      atomicAdd(&fmass[id >> ishift], w);
+      if (use_hot && hot_bit(hot_bits, id)) atomicAdd(&hmass[id >> ishift], w);
     }
   }
-  blk_reduce<NWV>(S, ns, nh, cdum, sk);
-  const u64 S_K = sk;
-  u64 S_H = 0ull;
-  if (use_hot) S_H = blk_sum_u64<NWV>(S, sh);
+  __syncthreads();
+  unsigned n_before, n_surv; u64 ea, eh = 0ull, S_K, S_H = 0ull;
+  blk_excl_scan2<NWV>(S, ns, (tid < NBF) ? fmass[tid] : 0ull, n_before, ea, n_surv, S_K);
+  if (use_hot) { unsigned c2, ct2; blk_excl_scan2<NWV>(S, 0u, (tid < NBF) ? hmass[tid] : 0ull, c2, eh, ct2, S_H); }
   bool pick_hot = false;
   if (use_hot) {
     pick_hot = (S_H > 0ull) && (R.u_acc * (double)S_K <= (double)S_H);
@@ -418,28 +420,23 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
     dg.flags |= SIMPLE_DIAG_SHVS | (pick_hot ? SIMPLE_DIAG_ACCEPTED : 0u);
   }
   const u64 S_cls = use_hot ? (pick_hot ? S_H : S_K - S_H) : S_K;
-  const double u = use_hot ? (pick_hot ? R.u_draw : R.u_tail) : R.u_draw;
-  dg.n_survivors = (int)ns;
+  const double u_first = R.u_draw, u_rest = R.u_tail;  // (by value: a choice between R's fields put all of R in memory)
+  const double u = (use_hot && !pick_hot) ? u_rest : u_first;
+  dg.n_survivors = (int)n_surv;
   dg.s_k = (double)S_k_fix / WSCALE;
   if (S_cls == 0ull) { return FIN_PENDING; }  // the chosen class holds no mass here: general kernel
   // ---- inverse CDF in ascending token id: first id whose running mass exceeds u * S ----
   u64 tfix = (u64)__double2ull_rd(u * (double)S_cls);
   if (tfix >= S_cls) tfix = S_cls - 1ull;
-  const int ishift = max(0, 32 - (int)__clz((unsigned)(R.V - 1) | 1u) - 8);
-  for (int i = tid; i < NBF; i += NTHR) fmass[i] = 0ull;
-  __syncthreads();
   auto in_class = [&](uint32_t k, uint32_t id) {
     if (composite(k, id) < cut) return false;
     if (!use_hot) return true;
     return (hot_bit(hot_bits, id) != 0u) == pick_hot;
   };
-  for (unsigned i = tid; i < n; i += NTHR) if (in_class(lk[i], li[i])) atomicAdd(&fmass[li[i] >> ishift], wfix(lk[i], y_max));
-  __syncthreads();
-  {
-    const u64 m2 = (tid < NBF) ? fmass[tid] : 0ull;
-    unsigned ce2, ct2; u64 me2, mt2;
-    blk_excl_scan2<NWV>(S, 0u, m2, ce2, me2, ct2, mt2);
-    if (tid < NBF && m2 > 0ull && me2 <= tfix && me2 + m2 > tfix) { S.bd = tid; S.mab_d = me2; }
+  if (tid < NBF) {
+    const u64 mh = use_hot ? hmass[tid] : 0ull;
+    const u64 m2 = pick_hot ? mh : fmass[tid] - mh, me2 = pick_hot ? eh : ea - eh;
+    if (m2 > 0ull && me2 <= tfix && me2 + m2 > tfix) { S.bd = tid; S.mab_d = me2; }
   }
   __syncthreads();
   const int bd = S.bd;

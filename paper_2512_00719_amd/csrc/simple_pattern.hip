@@ -96,27 +96,6 @@ __device__ __forceinline__ uint32_t raw_of(int d) {
 }
 __device__ __forceinline__ bool merged_bin(int d) { return d == NMAG - 1 || d == NMAG; }
 __device__ __forceinline__ float value_of(uint32_t raw) { return __uint_as_float(raw << 16); }
-// Nearest integer to exp(y - y_max) * 2^44: 2^n * 2^f with n = rint(x log2 e) and the Taylor
-// polynomial of degree 10 for 2^f on [-1/2, 1/2] (relative error below 1e-12).
-__device__ __forceinline__ u64 mass_fix44(float y, float y_max) {
-  const double x = (double)y - (double)y_max;
-  if (!(x >= -44.0)) return 0ull;
-  const double t = x * 1.4426950408889634;
-  const double n = rint(t), f = t - n;
-  double p = 7.054911620801121e-09;
-  p = fma(p, f, 1.0178086009239696e-07);
-  p = fma(p, f, 1.3215486790144305e-06);
-  p = fma(p, f, 1.5252733804059838e-05);
-  p = fma(p, f, 0.00015403530393381606);
-  p = fma(p, f, 0.0013333558146428441);
-  p = fma(p, f, 0.009618129107628477);
-  p = fma(p, f, 0.055504108664821576);
-  p = fma(p, f, 0.2402265069591007);
-  p = fma(p, f, 0.6931471805599453);
-  p = fma(p, f, 1.0);
-  return (u64)__double2ull_rn(ldexp(p, (int)n + 44));
-}
-
 // Sum over the wave, the same in every lane (data-parallel primitives: no LDS, no waiting).
 template <typename T>
 __device__ __forceinline__ T wave_total(T v) { return wave_sum(v); }
@@ -264,7 +243,7 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
     mb[j] = 0ull;
     if (ca[j] && d_first + j < NB - 1) {
       const float y = value_of(raw_of(d_first + j)) / tau;
-      mb[j] = mass_fix44(y, y_max);
+      mb[j] = exp_fix<44>(y, y_max);
       ge_thr |= (y >= thr_y) ? (1u << j) : 0u;
       if (merged_bin(d_first + j)) { atomicAdd(&P.merged_n, ca[j]); P.m_merged = mb[j]; }
     }
@@ -554,7 +533,7 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
       if (id < 0) a.out[row] = NOT_TAKEN;
       else {
         // a column of a merged bin was walked with the bin's mass; its own is reported
-        if (merged_bin(bin_of(raw_id))) w_id = mass_fix44(value_of(raw_id) / tau, y_max);
+        if (merged_bin(bin_of(raw_id))) w_id = exp_fix<44>(value_of(raw_id) / tau, y_max);
         simple_row_diag dg;
         dg.alpha = USE_HOT ? (double)S_H / (double)S_K : __longlong_as_double(0x7FF8000000000000ll);
         dg.s_k = (double)s_k / WSCALE;

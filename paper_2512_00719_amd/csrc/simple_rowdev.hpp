@@ -74,6 +74,32 @@ template <> struct Io<uint16_t> {  // bfloat16 bit patterns; the upcast to float
   __device__ static __forceinline__ float cvt(Elem v) { return __uint_as_float(v << 16); }
 };
 
+// Nearest integer to exp(y - y_ref) * 2^BITS, for y up to (51 - BITS) ln 2 above y_ref: 2^n * 2^f with
+// n = rint(x log2 e) and the Taylor polynomial of degree 10 for 2^f on [-1/2, 1/2] (relative error
+// below 1e-12).  Far below y_ref (and for a NaN) it is zero.
+template <int BITS>
+__device__ __forceinline__ u64 exp_fix(float y, float y_ref) {
+  static_assert(BITS <= 51, "the integer takes the low 52 bits of a double");
+  const double x = (double)y - (double)y_ref;
+  if (!(x >= -44.0)) return 0ull;
+  const double t = x * 1.4426950408889634;
+  const double n = rint(t), f = t - n;
+  double p = 7.054911620801121e-09;
+  p = fma(p, f, 1.0178086009239696e-07);
+  p = fma(p, f, 1.3215486790144305e-06);
+  p = fma(p, f, 1.5252733804059838e-05);
+  p = fma(p, f, 0.00015403530393381606);
+  p = fma(p, f, 0.0013333558146428441);
+  p = fma(p, f, 0.009618129107628477);
+  p = fma(p, f, 0.055504108664821576);
+  p = fma(p, f, 0.2402265069591007);
+  p = fma(p, f, 0.6931471805599453);
+  p = fma(p, f, 1.0);
+  // adding 2^52 rounds to the nearest integer and leaves it in the low 52 bits of the sum
+  const double v = ldexp(p, (int)n + BITS) + 0x1p52;
+  return (u64)__double_as_longlong(v) & 0x000FFFFFFFFFFFFFull;
+}
+
 __device__ __forceinline__ u64 composite(uint32_t key, uint32_t id) { return ((u64)key << 32) | (u64)(0xFFFFFFFFu - id); }
 __device__ __forceinline__ unsigned lanes_before(u64 m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -134,7 +160,7 @@ __device__ inline void blk_excl_scan2(FS& S, unsigned c, u64 m, unsigned& ce, u6
   if (lane_id() == 63) { S.r32a[wave_id()] = ci; S.r64a[wave_id()] = mi; }
   __syncthreads();
   unsigned cb = 0, ctt = 0; u64 mb = 0, mtt = 0;
-#pragma unroll
+#pragma unroll (NWV > 8 ? 8 : NWV)
   for (int w = 0; w < NWV; ++w) {
     const unsigned x = S.r32a[w]; const u64 y = S.r64a[w];
     if (w < wave_id()) { cb += x; mb += y; }
