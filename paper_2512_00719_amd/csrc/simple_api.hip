@@ -381,6 +381,7 @@ static int sample_impl(simple_ctx* ctx, const simple_state* state, const int32_t
   const int64_t per_launch = ctx->slots;
   a.F = simple::make_fast_layout(V, dtype, with_hist ? ctx->max_nnz : 0, with_hist, elem, ctx->lds_limit,
                                  B < per_launch ? B : per_launch, ctx->n_cu);
+  a.f64 = (!vec || V >= ((int64_t)1 << 18)) ? 1 : 0;
   a.gated = (a.F.total != 0u || tail) ? 1 : 0;
   a.pattern_on = (dtype == SIMPLE_BF16 && V < (int64_t)simple::FAST_MAX_V) ? (tail ? 2 : (a.F.total != 0u && !a.F.whole ? 1 : 0)) : 0;
   for (int64_t b0 = 0; b0 < B; b0 += per_launch) {

@@ -633,7 +633,8 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       rec.row = (uint32_t)row; rec.g = g_ref; rec.mode = mode; rec.flags = S.flags & 0x3FFFFFFFu;
       rec.tau = R.tau; rec.top_p = R.top_p; rec.rep = par.rep_penalty; rec.freq = par.freq_penalty;
       rec.pres = par.pres_penalty; rec.nnz = nnz; rec.n_prompt = min(max(rh.n_prompt, 0), nnz); rec.h_active = h_active ? 1 : 0;
-      rec.min_p = R.min_p; rec.top_k = par.top_k; rec.distinct = H.active ? S.distinct : 0u; rec.reserved1 = 0u;
+      rec.min_p = R.min_p; rec.top_k = par.top_k; rec.distinct = H.active ? S.distinct : 0u;
+      rec.f64 = (a.f64 || g_ref > C.g) ? 1u : 0u;
       reinterpret_cast<WideRec*>(a.wq + WQ_HEAD)[slot] = rec;
       a.out[row] = PENDING;
     }
@@ -716,8 +717,16 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     C.need_sum = R.need_sum && !complete;  // (nothing lies below the list)
     C.l2e_tau = (float)(1.4426950408889634 / (double)R.tau);
   }
+  // A threshold within the double-precision masses' reach of the row's maximum, as far as the sample knows it.
+  // (Only where such a row is queued: taken with the threshold, it cost every row of a call 1 us.)
+  auto below_sample_top = [&]() -> float {
+    float g = C.g;
+#pragma unroll 1
+    for (int w = 0; w < NWV; ++w) g = fmaxf(g, S.wmax[w] - F64_MARGIN * R.tau);
+    return g;
+  };
   if (straight) {  // (without truncation the threshold is only the reference of the masses)
-    if (!queue_wide(straight_mode, true, C.g) && tid == 0) queue_pending(a, row);
+    if (!queue_wide(straight_mode, true, a.f64 ? below_sample_top() : C.g) && tid == 0) queue_pending(a, row);
     return;
   }
   const bool minp_only = !R.greedy && !R.k_on && !R.p_on && R.minp_on;
@@ -811,7 +820,10 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   bool tables_live = false;  // the region holds the history tables
   // more columns at or above g than the list holds, and a cut that the whole-vocabulary routes find
   // without the list
-  if (n > cap && !complete && (R.need_sum || minp_only)) rc = FIN_WIDE;
+  if (n > cap && !complete && (R.need_sum || minp_only)) {
+    rc = FIN_WIDE;
+    if (a.f64) g_ref = below_sample_top();
+  }
   if (n <= cap) {
     // the list moves to registers; the region takes the history tables again
     float ez[PER]; uint32_t eid[PER];
@@ -985,10 +997,12 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
 
     // ---- a cut below the list's reach: the row goes to the kernels that follow ----
     // (masses there are relative to the threshold and reach 2^21 above it: where the row maximum stands
-    // higher, the threshold is moved up to e^13.5 below it, and above a bucket of ties that holds the cut)
+    // higher, the threshold is moved up to e^10 below it, and above a bucket of ties that holds the cut)
     if (rc == FIN_WIDE) {
       __syncthreads();
-      g_ref = fmaxf(g_ref, fmaxf(keyf(kmax) - 13.5f, S.wmax[0]) * R.tau);
+      const float y_m = keyf(kmax);
+      const float y_ref = fmaxf((a.f64 || y_m - C.y_g > 13.5f || S.wmax[0] > -INFINITY) ? y_m - F64_MARGIN : -INFINITY, S.wmax[0]);
+      g_ref = fmaxf(g_ref, y_ref * R.tau);
     }
   }
   if (rc == FIN_WIDE) {

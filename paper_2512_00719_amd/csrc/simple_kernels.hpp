@@ -88,6 +88,7 @@ struct SampleArgs {
   int st_lmax, st_nslots, st_slot0;
   uint32_t st_stride;
   int max_nnz;
+  int f64;         // rows that the sliced kernels weigh in double precision throughout (see mass_fix64)
   int gated;       // 1: the single-pass kernel runs first and queues the rows it leaves
   int pattern_on;  // the pattern-count kernel (bfloat16 rows without penalties and without a short top-k) ran first: 1 before the
                    // single-pass kernel, 2 before the hot-first kernel (it then leaves that kernel's own rows alone)

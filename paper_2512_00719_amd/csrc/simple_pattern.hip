@@ -282,7 +282,8 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
   if (P.merged_n) {
     const double err = (double)P.merged_n * (double)P.m_merged * (6.2e-5 / (double)tau);
     const bool near_thr = minp_on && fabsf(thr_y) * tau <= 1.3e-4f;
-    if (err > (double)s_k * 0x1p-24 || near_thr) { hand_back(); return; }
+    // (calls that the general kernel served before: far below the float32 rounding of p~)
+    if (err > (double)s_k * (a.f64 ? 0x1p-28 : 0x1p-24) || near_thr) { hand_back(); return; }
   }
   unsigned n = k_on ? (unsigned)par.top_k : (unsigned)V;
   if (minp_on) n = min(n, P.pos_m);

@@ -74,31 +74,42 @@ template <> struct Io<uint16_t> {  // bfloat16 bit patterns; the upcast to float
   __device__ static __forceinline__ float cvt(Elem v) { return __uint_as_float(v << 16); }
 };
 
+// Taylor coefficients of 2^f, from the tenth power down to the first.  A kernel whose registers are short
+// where the weights are formed reads them from memory there (from_memory): as literals the compiler
+// keeps them in registers through the whole of its outermost loop.
+struct Exp2Poly { double c[10]; };
+constexpr Exp2Poly EXP2_POLY = {{7.054911620801121e-09, 1.0178086009239696e-07, 1.3215486790144305e-06, 1.5252733804059838e-05,
+                                 0.00015403530393381606, 0.0013333558146428441, 0.009618129107628477, 0.055504108664821576,
+                                 0.2402265069591007, 0.6931471805599453}};
+static __device__ const Exp2Poly EXP2_POLY_MEM = EXP2_POLY;
+__device__ __forceinline__ Exp2Poly exp2_poly_from_memory() {
+  const Exp2Poly* q = &EXP2_POLY_MEM;
+  asm volatile("" : "+v"(q));
+  Exp2Poly P;
+#pragma unroll
+  for (int i = 0; i < 10; ++i) P.c[i] = as_global(q->c)[i];
+  return P;
+}
 // Nearest integer to exp(y - y_ref) * 2^BITS, for y up to (51 - BITS) ln 2 above y_ref: 2^n * 2^f with
 // n = rint(x log2 e) and the Taylor polynomial of degree 10 for 2^f on [-1/2, 1/2] (relative error
 // below 1e-12).  Far below y_ref (and for a NaN) it is zero.
 template <int BITS>
-__device__ __forceinline__ u64 exp_fix(float y, float y_ref) {
+__device__ __forceinline__ u64 exp_fix(float y, float y_ref, const Exp2Poly& P) {
   static_assert(BITS <= 51, "the integer takes the low 52 bits of a double");
   const double x = (double)y - (double)y_ref;
   if (!(x >= -44.0)) return 0ull;
   const double t = x * 1.4426950408889634;
   const double n = rint(t), f = t - n;
-  double p = 7.054911620801121e-09;
-  p = fma(p, f, 1.0178086009239696e-07);
-  p = fma(p, f, 1.3215486790144305e-06);
-  p = fma(p, f, 1.5252733804059838e-05);
-  p = fma(p, f, 0.00015403530393381606);
-  p = fma(p, f, 0.0013333558146428441);
-  p = fma(p, f, 0.009618129107628477);
-  p = fma(p, f, 0.055504108664821576);
-  p = fma(p, f, 0.2402265069591007);
-  p = fma(p, f, 0.6931471805599453);
+  double p = P.c[0];
+#pragma unroll
+  for (int i = 1; i < 10; ++i) p = fma(p, f, P.c[i]);
   p = fma(p, f, 1.0);
   // adding 2^52 rounds to the nearest integer and leaves it in the low 52 bits of the sum
   const double v = ldexp(p, (int)n + BITS) + 0x1p52;
   return (u64)__double_as_longlong(v) & 0x000FFFFFFFFFFFFFull;
 }
+template <int BITS>
+__device__ __forceinline__ u64 exp_fix(float y, float y_ref) { constexpr Exp2Poly P = EXP2_POLY; return exp_fix<BITS>(y, y_ref, P); }
 
 __device__ __forceinline__ u64 composite(uint32_t key, uint32_t id) { return ((u64)key << 32) | (u64)(0xFFFFFFFFu - id); }
 __device__ __forceinline__ unsigned lanes_before(u64 m) {
@@ -349,7 +360,7 @@ struct WideRec {  // 64 bytes: everything the later kernels need to know about t
   uint32_t row; float g; uint32_t mode, flags;
   float tau, top_p, rep, freq;
   float pres; int nnz, n_prompt, h_active;
-  float min_p; int32_t top_k; uint32_t distinct, reserved1;
+  float min_p; int32_t top_k; uint32_t distinct, f64;  // f64: weigh the columns in double precision
 };
 // What delimits the survivors of a queued row (each is a prefix of the total order, section 5.2):
 enum { WIDE_TOP_P = 0,   // the shortest prefix whose mass reaches top_p of the row's mass
@@ -388,6 +399,18 @@ __device__ __forceinline__ float mass_term(float z, const StreamCtx& C, int& bin
 template <bool UNIT_TAU = false>
 __device__ __forceinline__ float mass_term(float z, const StreamCtx& C, int& bin) { float y; return mass_term<UNIT_TAU>(z, C, bin, y); }
 constexpr float W_LIMIT = 2097152.0f;  // 2^21: largest mass relative to the one at g that the 2^28 fixed point carries
+// Masses relative to the one at g in double precision: 2^36 fixed point, for columns up to 2^15 above it (a
+// slice's 4096 then sum below 2^63).  For the rows that only the general kernel, which weighs them so, served
+// before these kernels took them: calls with rows off a 16-byte boundary or 2^18 columns and more, and rows
+// whose threshold was moved up.  The others are weighed in float32 (28 bits, 2^21 above): a third of the
+// instructions.
+constexpr int F64_BITS = 36;
+constexpr float F64_REACH = 10.39f;    // below 15 ln 2
+constexpr float F64_MARGIN = 10.0f;    // where a threshold is put below the row's maximum
+__device__ __forceinline__ u64 mass_fix64(float y, const StreamCtx& C, const Exp2Poly& P) {
+  return exp_fix<F64_BITS>(fminf(y, C.y_g + F64_REACH), C.y_g, P);
+}
+__device__ __forceinline__ u64 mass_fix64(float y, const StreamCtx& C) { constexpr Exp2Poly P = EXP2_POLY; return mass_fix64(y, C, P); }
 // Nearest integer of a float in [0, 2^52) as 64 bits, in two 32-bit conversions (the split is exact:
 // a float has 24 significant bits): hi counts units of 2^24.  The two parts of several values can
 // be summed separately in 32 bits and combined once.

@@ -71,6 +71,7 @@ struct WideRow {
   double inv_rep;
   uint32_t distinct;
   int top_k;
+  bool f64;
   unsigned char* ws;
 };
 
@@ -96,6 +97,7 @@ __device__ __forceinline__ WideRow load_row(const SampleArgs& a, unsigned slot) 
   W.h_active = uni(rec.h_active) != 0;
   W.distinct = uni(rec.distinct);
   W.top_k = uni(rec.top_k);
+  W.f64 = uni(rec.f64) != 0u;
   W.ws = a.wws + (size_t)slot * a.ws_stride;
   return W;
 }
@@ -250,6 +252,34 @@ __device__ __forceinline__ void hist_columns(const SliceTabs& T, const WideRow& 
         f(apply_penalties(Io<DT>::one(rowp + idx), (uint32_t)T.cnt[min(r, (unsigned)SLC - 1u)], W.rep, W.inv_rep, W.freq, W.pres), idx);
       ++r;
     }
+  }
+}
+
+// f(z', idx) for every column of the slice that starts at c0, one at a time: rows that are weighed in double
+// precision.  (The slice was requested in 16-byte groups already and is read from the cache here: the
+// groups' unrolled form with double weights, or the next slice's groups in flight beside this loop, took
+// more registers than there are.)
+template <typename DT, typename F>
+__device__ __forceinline__ void weighed_columns(SliceTabs& T, const HistPre<DT>& HP, const WideRow& W, const SampleArgs& a, const DT* rowp,
+                                                int c0, int V, F&& f) {
+  const int tid = fresh_tid();
+  const int n = min(V - c0, SLC);
+  const DT* p = rowp + c0;
+  const Exp2Poly P = exp2_poly_from_memory();
+#pragma unroll 1
+  for (int o = tid; o < n; o += 4 * WT) {
+    typename Io<DT>::Elem z0 = Io<DT>::raw(p + o), z1 = Io<DT>::raw(p + min(o + WT, n - 1)), z2 = Io<DT>::raw(p + min(o + 2 * WT, n - 1)),
+                          z3 = Io<DT>::raw(p + min(o + 3 * WT, n - 1));
+#pragma unroll 1
+    for (int i = o; i < min(o + 4 * WT, n); i += WT) {
+      if (!(W.h_active && slice_bit(i, T))) f(Io<DT>::cvt(z0), c0 + i, P);
+      z0 = z1; z1 = z2; z2 = z3;
+    }
+  }
+  if (W.h_active) {
+    hist_stage<DT>(T, HP, W.ws, a, rowp, c0, V);
+    __syncthreads();
+    hist_columns<DT>(T, W, rowp, c0, V, [&](float z, int idx) { f(z, idx, P); });
   }
 }
 
@@ -591,6 +621,18 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
       __syncthreads();
       hist_fetch<DT>(HP, Tb, W.ws, a, rowp, c0, V);  // this item's own loads go first: loads return in order
     } else __syncthreads();  // the zeroed bins are visible
+    if (W.f64 && W.mode == WIDE_TOP_P) {
+      weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int, const Exp2Poly& P) {
+        int b; float y;
+        (void)mass_term(z, W.C, b, y);
+        ymax = fmaxf(ymax, y);
+        const u64 m = mass_fix64(y, W.C, P);
+        if (z < W.C.g) atomicAdd(&lh[b], m); else mtop += m;
+      });
+      if (W.h_active) __syncthreads();  // the tables are rewritten by the next item
+      if (more) item_fetch<DT, use_hot, false>(N, a, it + 1u, I.n_sl, cur, ids);
+      continue;
+    }
     if (more) item_fetch<DT, use_hot, false>(N, a, it + 1u, I.n_sl, cur, ids);
     if (W.mode == WIDE_ALL) {  // every column survives: this wave's masses
       all_slice<DT, use_hot>(L, HP, Tb, W, a, rowp, c0, sl);
@@ -790,7 +832,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     __syncthreads();
     HistPre<DT> HP;
     if (W.h_active) hist_fetch<DT>(HP, Tb, W.ws, a, rowp, c0, V);  // this item's own loads go first: loads return in order
-    if (more) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
+    if (more && !W.f64) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
     u64 acc_s = 0ull, acc1 = 0ull;  // this slice: mass of the sure columns, and of the hot ones among them
     // one column the slow way: history columns and the ragged end of the row
     auto one = [&](float z, int idx) {
@@ -811,6 +853,26 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
         if (s < (unsigned)LCAP) lrl[s] = ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx;
       }
     };
+    if (W.f64) {
+      weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int idx, const Exp2Poly& P) {
+        int b; float y;
+        (void)mass_term(z, W.C, b, y);
+        bad = bad || !(y - W.C.y_g <= F64_REACH);  // a mass the fixed point cannot carry, or a NaN
+        const u64 m = mass_fix64(y, W.C, P);
+        acc_all += m;
+        ymax = fmaxf(ymax, y);
+        if (!(y >= thr_y)) return;
+        if (!(z < W.C.g) || b < bstar) {
+          acc_s += m;
+          if (use_hot && hot_bit(hot_bits, (uint32_t)idx)) acc1 += m;
+          ++n_sure;
+        } else if (b == bstar) {
+          const unsigned s = atomicAdd(&l_n, 1u);
+          if (s < (unsigned)LCAP) lrl[s] = ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx;
+        }
+      });
+      if (more) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
+    } else {
     // The main line: every column's mass, and its class by the logit alone; boundary columns follow
     // under a wave-wide test.
     auto sweep = [&](auto unit_tau_c, auto want_all_c) {
@@ -880,6 +942,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
       hist_stage<DT>(Tb, HP, W.ws, a, rowp, c0, V);
       __syncthreads();
       hist_columns<DT>(Tb, W, rowp, c0, V, one);
+    }
     }
     {
       const u64 s0 = wave_sum(acc_s - acc1);
@@ -973,6 +1036,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   // exact masses (top-k: counts) from here: the columns surely inside must stay below the target, the
   // collected bin must reach it
   const u64 m_sure = blk_sum_u64<WNW>(S, msure);  // barriers inside
+  auto mass_at = [&](unsigned t) -> u64 { return W.f64 ? mass_fix64(keyf((uint32_t)(rcmp[t] >> 32)), C) : (u64)rl[t]; };
   const u64 m_above = top_k_route ? (u64)n_sure : m_sure;
   const u64 target = top_k_route ? (u64)W.top_k : (u64)__double2ull_ru((double)W.top_p * (double)S_tot);
   if (m_above >= target) { return false; }
@@ -989,9 +1053,9 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
         const unsigned t = t0 + (unsigned)(k * WT + tid);
         if (t >= n_r) continue;
         const float z = __uint_as_float((uint32_t)(e[k] >> 32));
-        int b;
-        const float w = mass_term(z, C, b);
-        const u64 c = composite(fkey(tempered(z, C)), (uint32_t)e[k]);
+        int b; float y;
+        const float w = mass_term(z, C, b, y);
+        const u64 c = composite(fkey(y), (uint32_t)e[k]);
         rcmp[t] = c;
         rl[t] = (uint32_t)mass_fix_below(w);
         cmax_t = (c > cmax_t) ? c : cmax_t; cmin_t = (c < cmin_t) ? c : cmin_t;
@@ -1016,7 +1080,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
       __syncthreads();
       for (unsigned t = tid; t < n_r; t += WT) {
         const u64 c = rcmp[t];
-        if (c >= lo && c <= hi) atomicAdd(&dmass[(unsigned)((hi - c) >> sh)], top_k_route ? 1ull : (u64)rl[t]);
+        if (c >= lo && c <= hi) atomicAdd(&dmass[(unsigned)((hi - c) >> sh)], top_k_route ? 1ull : mass_at(t));
       }
       __syncthreads();
       {
@@ -1047,7 +1111,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
         const u64 c = rcmp[t];
         if (c >= lo && c <= hi) {
           const unsigned slot = atomicAdd(&S.memb, 1u);
-          if (slot < (unsigned)WT) { mc[slot] = c; mw[slot] = top_k_route ? 1ull : (u64)rl[t]; }
+          if (slot < (unsigned)WT) { mc[slot] = c; mw[slot] = top_k_route ? 1ull : mass_at(t); }
         }
       }
       __syncthreads();
@@ -1075,7 +1139,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
     if (rcmp[t] >= cut_found) {
       const uint32_t id = 0xFFFFFFFFu - (uint32_t)rcmp[t];
       const unsigned hot = use_hot ? hot_bit(hot_bits, id) : 0u;
-      atomicAdd(&tiles[hot * 256u + id / (unsigned)T], (u64)rl[t]);
+      atomicAdd(&tiles[hot * 256u + id / (unsigned)T], mass_at(t));
       ++r_in;
     }
   }
@@ -1110,7 +1174,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   const u64 S_cls = use_hot ? (pick_hot ? S1 : S0) : S_K;
   const double u = use_hot ? (pick_hot ? u3[0] : u3[2]) : u3[0];
   dg.n_survivors = (int)ns;
-  dg.s_k = (double)(top_k_route ? S_K : S_tot) / (double)MSCALE * exp((double)C.y_g - (double)keyf(kmax));
+  dg.s_k = (double)(top_k_route ? S_K : S_tot) / (W.f64 ? (double)(1ull << F64_BITS) : (double)MSCALE) * exp((double)C.y_g - (double)keyf(kmax));
   if (S_cls == 0ull) { return false; }
   u64 tfix = (u64)__double2ull_rd(u * (double)S_cls);
   if (tfix >= S_cls) tfix = S_cls - 1ull;
@@ -1140,7 +1204,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
         const bool below = z < C.g;
         bool in = !below || b < bstar;
         if (!in && b == bstar) in = composite(fkey(y), (uint32_t)idx) >= cut_c;
-        if (in && y >= thr_y) mloc[e] = below ? mass_fix_below(w) : mass_fix(w);
+        if (in && y >= thr_y) mloc[e] = W.f64 ? mass_fix64(y, C) : below ? mass_fix_below(w) : mass_fix(w);
       }
     }
     lsum += mloc[e];

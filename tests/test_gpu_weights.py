@@ -18,7 +18,7 @@ def _params(controls, B, temperature):
                              min_p=cols["min_p"].astype(np.float32))
 
 
-def _errors(w, dev, dg_want, steps=4):
+def _errors(w, dev, dg_want, steps=4, check_s_k=False):
     """Checks ids and p~ of `steps` calls; returns the number of rows per diagnostics flag of dg_want."""
     seen = np.zeros(len(dg_want), int)
     for step in range(steps):
@@ -30,6 +30,8 @@ def _errors(w, dev, dg_want, steps=4):
                 continue
             got = float(dg["p_chosen"][r])
             bad = [abs(got - p) - p * (1.001 * 2.0 ** -24 + o.n * 2.0 ** -45) - 2.0 ** -45 for p in (o.p_chosen, *o.alt_p)]
+            if check_s_k and dg["flags"][r] & (binding.DIAG_WIDE | binding.DIAG_PATTERN) == binding.DIAG_WIDE and o.S_k_used:  # the mass of the row relative to its maximum
+                assert abs(float(dg["s_k"][r]) - o.S_k) <= 1e-9 * o.S_k, (step, r, hex(int(dg["flags"][r])), float(dg["s_k"][r]) / o.S_k - 1.0)
             assert min(bad) <= 0.0, (step, r, hex(int(dg["flags"][r])), got, o.p_chosen, abs(got - o.p_chosen) / o.p_chosen)
         for i, f in enumerate(dg_want):
             seen[i] += int(((dg["flags"] & f) > 0).sum())
@@ -56,3 +58,29 @@ def test_listed_columns(kind, dtype, V):
     w = _workload(f"weights-{kind}", z, dtype, _params(controls, B, np.resize([0.6, 0.8, 1.0], B).astype(np.float32)))
     wide, general = _errors(w, P.to_device(w), (binding.DIAG_WIDE, binding.DIAG_GENERAL))
     assert general <= 4 and (kind != "short" or wide == 0 or V < 8192)
+
+
+@pytest.mark.parametrize("kind,dtype,V", [("unaligned", "f32", 50_001), ("unaligned", "bf16", 50_001), ("large", "f32", 270_000),
+                                          ("large", "bf16", 270_000), ("high", "f32", 50_048), ("high", "f32", 270_000)])
+@pytest.mark.parametrize("hot_set,history", [(False, False), (True, False), (True, True)])
+def test_survivors_beyond_the_list(kind, dtype, V, hot_set, history):
+    """Rows of the sliced kernels that the general kernel used to serve: a nucleus wider than the list, a min-p
+    cut below it, top-k above it, and ("high") wide nuclei under a maximum that holds nearly all of the mass."""
+    rng = np.random.default_rng(V + 3 * hot_set + history)
+    B = 18
+    z = (rng.standard_normal((B, V)) * rng.choice([0.3, 1.0], B)[:, None]).astype(np.float32)
+    if kind == "high":
+        z[np.arange(B), rng.integers(0, V, B)] = 16.5 + rng.random(B).astype(np.float32)
+        params = _params([dict(top_p=0.9995), dict(top_p=0.9999), dict(top_p=0.9992, min_p=1e-9)], B, 1.0)
+    else:
+        params = _params([dict(top_p=0.9), dict(top_k=5000), dict(min_p=0.01), dict(top_p=0.95, min_p=0.001), dict(top_p=0.7), dict(top_k=20_000)], B,
+                         np.resize([1.0, 0.8, 1.2], B).astype(np.float32))
+    n = 200 if history else 0
+    if history:
+        params["rep_penalty"], params["freq_penalty"], params["n_prompt"] = 1.1, 0.2, 50
+        params["rep_penalty"][4::6] = 0.9  # raises logits: no list
+    w = synth.Workload(f"weights-{kind}", B, V, dtype, synth.f32_to_bf16_bits(z) if dtype == "bf16" else z, params,
+                       np.arange(B + 1, dtype=np.int64) * n, rng.integers(0, V, B * n).astype(np.int32),
+                       hot_ids=np.sort(rng.choice(V, V // 10, replace=False)).astype(np.int32) if hot_set else None)
+    wide, general, pattern = _errors(w, P.to_device(w), (binding.DIAG_WIDE, binding.DIAG_GENERAL, binding.DIAG_PATTERN), steps=2, check_s_k=True)
+    assert wide + pattern >= (B if kind != "high" else 4) and (general <= 6 or kind != "unaligned")
