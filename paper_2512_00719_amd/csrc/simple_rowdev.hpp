@@ -367,6 +367,7 @@ enum { WIDE_TOP_P = 0,   // the shortest prefix whose mass reaches top_p of the 
        WIDE_ALL = 1,     // no truncation: every column
        WIDE_MIN_P = 2,   // tempered value >= fl(y_max + fl(ln min_p))
        WIDE_TOP_K = 3 }; // the first top_k columns of the order (top-k alone, beyond the candidate list's reach)
+constexpr uint32_t WIDE_FAR = 16u;      // beside WIDE_ALL: a column stands too far above g for the integer masses, or the row is weighed in double
 constexpr int WQ_HEAD = 16;             // words before the records
 constexpr uint32_t WS_HIST = 0u;        // u64[NBW]: mass of the columns below g, by bin (top-k route: their number)
                                         // (rows without truncation: AllPart[128][4], per slice and wave)
@@ -378,9 +379,9 @@ constexpr uint32_t WS_RL = 20544u;      // u64[RCAP]: columns of the boundary bi
 constexpr uint32_t WS_HT = 53312u;      // the row's history tables as the single-pass kernel laid them out in LDS
 // [0, WS_RL) must be zero when a row is queued
 // A wave's share of a slice of a row without truncation, all columns and the hot ones among them, and the
-// largest tempered value m: masses as integers relative to the one at g, or (rel) as doubles relative to m
-// where a column stands too far above g for the fixed point.
-struct AllPart { u64 s, h; float m; uint32_t rel; };
+// largest tempered value m: masses as integers relative to the one at g, or (WIDE_FAR) the slice's in the
+// first of its four parts, weighed in double precision, as 2^44 fixed point relative to m.
+struct AllPart { u64 s, h; float m; uint32_t unused; };
 static_assert(sizeof(AllPart) == 24 && (FAST_MAX_V / 4096) * 4 * sizeof(AllPart) <= 16384, "the parts of a row fit the bins' place");
 
 // Mass of one column relative to the mass at y_g, w = exp(y - y_g) with y = fl32(z / tau), and the

@@ -32,9 +32,10 @@
 // order: what is needed first is requested first.
 //
 // Rows without truncation have no cut and are read once, by the first kernel: per slice and wave it leaves
-// the columns' mass, from which the third kernel draws; where one stands too far above g for the fixed
-// point, relative to the largest of them (so that any dynamic range is carried: one column may hold almost
-// the whole mass).  Rows with a min-p cut use the first
+// the columns' mass, from which the third kernel draws.  Where a column stands too far above g for the fixed
+// point, the second kernel weighs the row again, in double precision and each slice relative to its largest
+// column (so that any dynamic range is carried: one column may hold almost the whole mass).  Rows with a
+// min-p cut use the first
 // kernel for the row maximum only (the cut is a value).  Rows with top-k alone run the same three
 // kernels by count instead of mass: a bin counts its columns, the cut's bin is the one in which
 // the count from the top reaches k, and the descent inside it weighs every column as one.
@@ -71,7 +72,7 @@ struct WideRow {
   double inv_rep;
   uint32_t distinct;
   int top_k;
-  bool f64;
+  bool f64, far;
   unsigned char* ws;
 };
 
@@ -88,7 +89,7 @@ __device__ __forceinline__ WideRow load_row(const SampleArgs& a, unsigned slot) 
   WideRow W;
   slot = uni(slot);
   const WideRec rec = reinterpret_cast<const WideRec*>(a.wq + WQ_HEAD)[slot];
-  W.row = uni((int)rec.row); W.mode = uni(rec.mode); W.flags = uni(rec.flags);
+  W.row = uni((int)rec.row); W.mode = uni(rec.mode & 15u); W.far = (uni(rec.mode) & WIDE_FAR) != 0u; W.flags = uni(rec.flags);
   W.tau = uni(rec.tau); W.top_p = uni(rec.top_p); W.min_p = uni(rec.min_p);
   W.C.g = uni(rec.g); W.C.y_g = uni(rec.g / rec.tau); W.C.inv_tau = uni(1.0 / (double)rec.tau); W.C.need_sum = true;
   W.C.l2e_tau = 0.0f;
@@ -255,10 +256,10 @@ __device__ __forceinline__ void hist_columns(const SliceTabs& T, const WideRow& 
   }
 }
 
-// f(z', idx) for every column of the slice that starts at c0, one at a time: rows that are weighed in double
-// precision.  (The slice was requested in 16-byte groups already and is read from the cache here: the
-// groups' unrolled form with double weights, or the next slice's groups in flight beside this loop, took
-// more registers than there are.)
+// f(z', idx) for every column of the slice that starts at c0, one at a time and from the cache (barriers inside if
+// the row has a history): rows that are weighed in double precision.  (The slice was requested in 16-byte
+// groups already: the groups' unrolled form with double weights, or the next slice's groups in flight
+// beside this loop, took more registers than there are.)
 template <typename DT, typename F>
 __device__ __forceinline__ void weighed_columns(SliceTabs& T, const HistPre<DT>& HP, const WideRow& W, const SampleArgs& a, const DT* rowp,
                                                 int c0, int V, F&& f) {
@@ -266,20 +267,17 @@ __device__ __forceinline__ void weighed_columns(SliceTabs& T, const HistPre<DT>&
   const int n = min(V - c0, SLC);
   const DT* p = rowp + c0;
   const Exp2Poly P = exp2_poly_from_memory();
+  typename Io<DT>::Elem z = tid < n ? Io<DT>::raw(p + tid) : typename Io<DT>::Elem();
 #pragma unroll 1
-  for (int o = tid; o < n; o += 4 * WT) {
-    typename Io<DT>::Elem z0 = Io<DT>::raw(p + o), z1 = Io<DT>::raw(p + min(o + WT, n - 1)), z2 = Io<DT>::raw(p + min(o + 2 * WT, n - 1)),
-                          z3 = Io<DT>::raw(p + min(o + 3 * WT, n - 1));
-#pragma unroll 1
-    for (int i = o; i < min(o + 4 * WT, n); i += WT) {
-      if (!(W.h_active && slice_bit(i, T))) f(Io<DT>::cvt(z0), c0 + i, P);
-      z0 = z1; z1 = z2; z2 = z3;
-    }
+  for (int i = tid; i < n; i += WT) {
+    const typename Io<DT>::Elem next = Io<DT>::raw(p + min(i + WT, n - 1));
+    if (!(W.h_active && slice_bit(i, T))) f(Io<DT>::cvt(z), c0 + i, P);
+    z = next;
   }
   if (W.h_active) {
     hist_stage<DT>(T, HP, W.ws, a, rowp, c0, V);
     __syncthreads();
-    hist_columns<DT>(T, W, rowp, c0, V, [&](float z, int idx) { f(z, idx, P); });
+    hist_columns<DT>(T, W, rowp, c0, V, [&](float z1, int idx) { f(z1, idx, P); });
   }
 }
 
@@ -433,21 +431,24 @@ struct ItemLoads {
   uint32_t pre;    // this thread's mask word or directory entry
 };
 struct SlotIds {
-  uint32_t row_c, act_c, row_n, act_n;  // current slot, next slot; act: bit 0 history in force, bit 1 no truncation
+  uint32_t row_c, act_c, row_n, act_n;  // current slot, next slot; act: bit 0 history in force, bit 1 no truncation, bit 2 (with it) WIDE_FAR
   __device__ __forceinline__ void request(const SampleArgs& a, unsigned slot, unsigned n_wide, uint32_t& row, uint32_t& act) {
     row = 0u; act = 0u;
     if (slot < n_wide) {
       const uint32_t* rec = reinterpret_cast<const uint32_t*>(reinterpret_cast<const WideRec*>(a.wq + WQ_HEAD) + slot);
       row = as_global(rec)[0];
-      act = (as_global(rec)[11] != 0u ? 1u : 0u) | (as_global(rec)[2] == (uint32_t)WIDE_ALL ? 2u : 0u);
+      const uint32_t mode = as_global(rec)[2];
+      act = (as_global(rec)[11] != 0u ? 1u : 0u) | ((mode & 15u) == (uint32_t)WIDE_ALL ? 2u : 0u) | (mode & WIDE_FAR ? 4u : 0u);
     }
   }
+  // nothing to do for the classifying kernel: the bins kernel has the masses of a row without truncation
+  static __device__ __forceinline__ bool idle(uint32_t act) { return (act & 6u) == 2u; }
   // The record is the same in every lane: scalars from here on.  Called where the workgroup waits
   // for its loads anyway (a row's record), so that no later use has to wait for loads in flight.
   __device__ __forceinline__ void settle() { row_c = uni(row_c); act_c = uni(act_c); row_n = uni(row_n); act_n = uni(act_n); }
 };
 static_assert(offsetof(WideRec, row) == 0 && offsetof(WideRec, mode) == 8 && offsetof(WideRec, h_active) == 44, "record words read by SlotIds");
-// classify: rows without truncation need nothing from this pass; else (the bins kernel) only they need the hot bits
+// classify: most rows without truncation need nothing from this pass; else (the bins kernel) only they need the hot bits
 template <typename DT, bool use_hot, bool classify>
 __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a, unsigned item, unsigned n_sl, int cur_slot, const SlotIds& ids) {
   constexpr int EPL = Io<DT>::EPL;
@@ -456,7 +457,7 @@ __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a
   const uint32_t row = slot == cur_slot ? ids.row_c : ids.row_n;  // scalars (SlotIds::settle)
   const uint32_t actw = slot == cur_slot ? ids.act_c : ids.act_n;
   const bool act = (actw & 1u) != 0u;
-  if (classify && (actw & 2u)) return;
+  if (classify && SlotIds::idle(actw)) return;
   const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride;
   L.pre = act ? slice_fetch(a.wws + (size_t)slot * a.ws_stride, a, c0) : 0u;
 #pragma unroll
@@ -481,7 +482,7 @@ __device__ __forceinline__ float mass_rel(float y, float m) {
 // took 120 us, 229 with three such rows; 64 so.)
 template <typename DT, bool use_hot>
 __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<DT>& HP, SliceTabs& Tb, const WideRow& W, const SampleArgs& a,
-                                          const DT* rowp, int c0, int sl) {
+                                          const DT* rowp, int c0, int sl, int slot) {
   constexpr int EPL = Io<DT>::EPL, G = ItemLoads<DT>::G;
   const int tid = fresh_tid(), V = a.V;
   float y[G][EPL];
@@ -525,31 +526,14 @@ __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<
     });
   }
   const float M = wave_max(m);
-  const bool rel = __ballot(far) != 0ull;
-  if (rel) {  // once more, relative to the largest: double sums of float32 exponentials
-    double ds = 0.0, dh = 0.0;
-    auto add = [&](float yv, bool hot) {
-      const double w = (double)mass_rel(yv, M);
-      ds += w;
-      if (use_hot && hot) dh += w;
-    };
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) add(y[j][e], use_hot && ((L.hq[j] >> e) & 1u) != 0u);
-    }
-    if (W.h_active)
-      hist_columns<DT>(Tb, W, rowp, c0, V, [&](float z, int idx) { add(tempered(z, W.C), use_hot && hot_bit(a.hot_bits, (uint32_t)idx) != 0u); });
-    s = (u64)__double_as_longlong(wave_sum(ds));
-    h = use_hot ? (u64)__double_as_longlong(wave_sum(dh)) : 0ull;
-  } else {
-    s = wave_sum(s);
-    if (use_hot) h = wave_sum(h);
-  }
+  s = wave_sum(s);
+  if (use_hot) h = wave_sum(h);
   if (W.h_active) __syncthreads();  // the tables are rewritten by the next item
+  const bool any_far = __ballot(far) != 0ull;
   if ((tid & 63) == 0) {
     AllPart* part = reinterpret_cast<AllPart*>(W.ws + WS_HIST) + sl * WNW + (tid >> 6);
-    part->s = s; part->h = h; part->m = M; part->rel = rel ? 1u : 0u;
+    part->s = s; part->h = h; part->m = M;
+    if (any_far) atomicOr(&(reinterpret_cast<WideRec*>(a.wq + WQ_HEAD) + slot)->mode, WIDE_FAR);  // the second kernel weighs the row again
   }
 }
 
@@ -635,7 +619,7 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
     }
     if (more) item_fetch<DT, use_hot, false>(N, a, it + 1u, I.n_sl, cur, ids);
     if (W.mode == WIDE_ALL) {  // every column survives: this wave's masses
-      all_slice<DT, use_hot>(L, HP, Tb, W, a, rowp, c0, sl);
+      all_slice<DT, use_hot>(L, HP, Tb, W, a, rowp, c0, sl, slot);
       continue;
     }
     auto one = [&](float z, int) {
@@ -747,9 +731,9 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
   ids.request(a, (unsigned)cur, n_wide, ids.row_c, ids.act_c);
   ids.request(a, (unsigned)cur + 1u, n_wide, ids.row_n, ids.act_n);
   ids.settle();
-  {  // nothing to do for rows without truncation (a workgroup's items lie in at most two slots, or the first is one of them)
+  {  // nothing to do for such rows (a workgroup's items lie in at most two slots, or the first is one of them)
     const int last = (int)((I.i1 - 1u) / I.n_sl);
-    if ((ids.act_c & 2u) && (last == cur || (last == cur + 1 && (ids.act_n & 2u)))) return;
+    if (SlotIds::idle(ids.act_c) && (last == cur || (last == cur + 1 && SlotIds::idle(ids.act_n)))) return;
   }
   ItemLoads<DT> N;  // the next item's loads
   item_fetch<DT, use_hot, true>(N, a, I.i0, I.n_sl, cur, ids);
@@ -763,7 +747,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     ids.settle();
     const RowCut rc = row_cut(S, W);
     bstar = rc.bstar; thr_y = rc.thr_y; valid = rc.valid;
-    valid = valid && W.mode != WIDE_ALL;  // (done by the bins kernel)
+    valid = valid && (W.mode != WIDE_ALL || W.far);  // (else done by the bins kernel)
     if (first && tid == 0 && valid) {  // for the finishing kernel
       reinterpret_cast<uint32_t*>(W.ws + WS_SCAL)[8] = (uint32_t)bstar + 1u;
       reinterpret_cast<u64*>(W.ws + WS_SCAL)[5] = rc.s_tot;
@@ -832,7 +816,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     __syncthreads();
     HistPre<DT> HP;
     if (W.h_active) hist_fetch<DT>(HP, Tb, W.ws, a, rowp, c0, V);  // this item's own loads go first: loads return in order
-    if (more && !W.f64) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
+    if (more && !W.f64 && W.mode != WIDE_ALL) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
     u64 acc_s = 0ull, acc1 = 0ull;  // this slice: mass of the sure columns, and of the hot ones among them
     // one column the slow way: history columns and the ragged end of the row
     auto one = [&](float z, int idx) {
@@ -853,6 +837,29 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
         if (s < (unsigned)LCAP) lrl[s] = ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx;
       }
     };
+    if (W.mode == WIDE_ALL) {  // the masses of an untruncated row again, relative to the slice's largest
+      AllPart* part = reinterpret_cast<AllPart*>(W.ws + WS_HIST) + sl * WNW;
+      float M = LOWEST;
+#pragma unroll
+      for (int k = 0; k < WNW; ++k) M = fmaxf(M, part[k].m);
+      weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int idx, const Exp2Poly& P) {
+        const float y = tempered(z, W.C);
+        bad = bad || y != y;
+        const u64 m = exp_fix<44>(y, M, P);
+        acc_s += m;
+        if (use_hot && hot_bit(hot_bits, (uint32_t)idx)) acc1 += m;
+      });
+      unsigned n_bad = bad ? 1u : 0u, dz = 0u; u64 mx = 0ull;
+      blk_reduce<WNW>(S, n_bad, dz, mx, acc_s);  // barriers inside
+      acc1 = use_hot ? blk_sum_u64<WNW>(S, acc1) : 0ull;
+      if (tid < WNW) {
+        part[tid].s = tid == 0 ? acc_s : 0ull; part[tid].h = tid == 0 ? acc1 : 0ull;
+        part[tid].m = n_bad ? INFINITY : M;  // (a NaN: the finishing kernel hands the row on)
+      }
+      bad = false;
+      if (more) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
+      continue;
+    }
     if (W.f64) {
       weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int idx, const Exp2Poly& P) {
         int b; float y;
@@ -1223,8 +1230,9 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
 }
 
 // A row without truncation, from its waves' parts: acceptance (section 5.3), the slice that holds the draw, and
-// that slice's columns once more.  Where every wave kept integers, the slices' masses are their sums; else
-// they become 2^44 fixed point relative to the row maximum, and the draw's place inside its slice a fraction.
+// that slice's columns once more.  Where the bins kernel's integers hold, the slices' masses are their sums;
+// else (WIDE_FAR) they are scaled to the row maximum, and the draw's place inside its slice is a fraction of
+// the slice's mass.
 template <typename DT>
 __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS& S, SliceTabs& Tb, simple_row_diag& dg) {
   constexpr int EPT = SLC / WT;
@@ -1237,31 +1245,28 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
   const AllPart* parts = reinterpret_cast<const AllPart*>(W.ws + WS_HIST);
   u64 ps[WNW], ph[WNW];
   float pm[WNW], m = LOWEST;
-  uint32_t prel[WNW];
-  unsigned rels = 0u;
 #pragma unroll
   for (int k = 0; k < WNW; ++k) {
-    ps[k] = 0ull; ph[k] = 0ull; pm[k] = LOWEST; prel[k] = 0u;
+    ps[k] = 0ull; ph[k] = 0ull; pm[k] = LOWEST;
     if (tid < n_sl) {
       const AllPart* q = parts + tid * WNW + k;
-      ps[k] = as_global(q)->s; ph[k] = as_global(q)->h; pm[k] = as_global(q)->m; prel[k] = as_global(q)->rel;
+      ps[k] = as_global(q)->s; ph[k] = as_global(q)->h; pm[k] = as_global(q)->m;
     }
   }
   double u3[3];
   row_uniforms(a.seed, a.row_offset + (uint64_t)W.row, a.step, u3);
   if (tid == 0) { S.bd = -1; S.out_id = -1; S.out_w = 0ull; S.flags = 0u; }
 #pragma unroll
-  for (int k = 0; k < WNW; ++k) { m = fmaxf(m, pm[k]); rels |= prel[k]; }
+  for (int k = 0; k < WNW; ++k) m = fmaxf(m, pm[k]);
   {
     const float wm = wave_max(m);
-    const u64 any = __ballot(rels != 0u);
-    if ((tid & 63) == 0) { S.wmax[tid >> 6] = wm; S.wcnt[tid >> 6] = any ? 1u : 0u; }
+    if ((tid & 63) == 0) S.wmax[tid >> 6] = wm;
   }
   __syncthreads();
   float y_max = S.wmax[0];
-  bool rel = S.wcnt[0] != 0u;
+  const bool rel = W.far;
 #pragma unroll
-  for (int w = 1; w < WNW; ++w) { y_max = fmaxf(y_max, S.wmax[w]); rel = rel || S.wcnt[w] != 0u; }
+  for (int w = 1; w < WNW; ++w) y_max = fmaxf(y_max, S.wmax[w]);
   if (!(y_max > LOWEST) || y_max == INFINITY) return false;
   u64 m_all = 0ull, m_hot = 0ull;
   bool lost = false;
@@ -1270,25 +1275,13 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
     for (int k = 0; k < WNW; ++k) { m_all += ps[k]; m_hot += ph[k]; }
     lost = (m_all >> 56) != 0ull;  // 128 slices below 2^56 sum below 2^63
   } else {
-    double s = 0.0, h = 0.0;
-#pragma unroll
-    for (int k = 0; k < WNW; ++k) {
-      const double f = prel[k] ? exp((double)pm[k] - (double)y_max) * WSCALE
-                               : exp((double)W.C.y_g - (double)y_max) * (WSCALE / (double)MSCALE);
-      s += (prel[k] ? __longlong_as_double((long long)ps[k]) : (double)ps[k]) * f;
-      h += (prel[k] ? __longlong_as_double((long long)ph[k]) : (double)ph[k]) * f;
-      if (tid >= n_sl) s = h = 0.0;
-    }
-    lost = !(s >= 0.0);  // a NaN, or +inf less itself
-    if (!lost) { m_all = (u64)__double2ull_rn(s); m_hot = min(m_all, (u64)__double2ull_rn(h)); }
+    const double f = tid < n_sl ? exp((double)m - (double)y_max) : 0.0;
+    m_all = (u64)__double2ull_rn((double)ps[0] * f); m_hot = min(m_all, (u64)__double2ull_rn((double)ph[0] * f));
   }
   if (lost) atomicOr(&S.flags, 1u);
-  unsigned near = (tid < n_sl && m >= y_max - 88.0f) ? 1u : 0u, finite = (tid < n_sl && m > LOWEST) ? 1u : 0u;
-  u64 S_K = m_all, mx = 0ull;
-  blk_reduce<WNW>(S, near, finite, mx, S_K);  // barriers inside
+  const u64 S_K = blk_sum_u64<WNW>(S, m_all);  // barriers inside
   const u64 S_H = use_hot ? blk_sum_u64<WNW>(S, m_hot) : 0ull;
-  // one slice so far above all others that their exponentials leave float32's range: the general kernel's
-  if (S.flags || (rel && near == 1u && finite > 1u)) return false;
+  if (S.flags) return false;
   bool pick_hot = false;
   if (use_hot) {
     pick_hot = (S_H > 0ull) && (u3[1] * (double)S_K <= (double)S_H);
@@ -1312,7 +1305,6 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
   // the columns' masses in the slice, in ascending id
   const int c0 = t * SLC;
   const float y_ref = rel ? S.wmax[15] : W.C.y_g;
-  const float scale = rel ? (float)WSCALE : MSCALE;
   u64 rq = S.mab_d;
   const double place = (double)S.mab_d / (double)S.mab_k;
   float zv[EPT];
@@ -1326,7 +1318,10 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
     if (c0 + o < V) {
       float z = zv[e];
       if (W.h_active && slice_bit(o, Tb)) z = slice_value(z, o, Tb, W);
-      if (!use_hot || (((hq >> e) & 1u) != 0u) == pick_hot) q[e] = float_to_u64(mass_rel(tempered(z, W.C), y_ref) * scale);
+      if (!use_hot || (((hq >> e) & 1u) != 0u) == pick_hot) {
+        const float y = tempered(z, W.C);
+        q[e] = rel ? exp_fix<44>(y, y_ref) : float_to_u64(mass_rel(y, y_ref) * MSCALE);
+      }
     }
     lsum += q[e];
   }

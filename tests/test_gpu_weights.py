@@ -84,3 +84,33 @@ def test_survivors_beyond_the_list(kind, dtype, V, hot_set, history):
                        hot_ids=np.sort(rng.choice(V, V // 10, replace=False)).astype(np.int32) if hot_set else None)
     wide, general, pattern = _errors(w, P.to_device(w), (binding.DIAG_WIDE, binding.DIAG_GENERAL, binding.DIAG_PATTERN), steps=2, check_s_k=True)
     assert wide + pattern >= (B if kind != "high" else 4) and (general <= 6 or kind != "unaligned")
+
+
+@pytest.mark.parametrize("dtype,V,offset", [("f32", 50_048, 0), ("bf16", 50_048, 0), ("f32", 50_001, 0), ("f32", 270_000, 0), ("f32", 8193, 3)])
+@pytest.mark.parametrize("hot_set,history", [(False, False), (True, False), (True, True)])
+def test_untruncated_rows_of_any_range(dtype, V, offset, hot_set, history):
+    """Rows beyond the float32 weights' reach: a few columns hold much of the mass, one holds all but a trace (more
+    than 88 above the rest), a spread of hundreds, masked columns."""
+    rng = np.random.default_rng(V + 3 * hot_set + history)
+    B = 20
+    z = (rng.standard_normal((B, V)) * 0.7).astype(np.float32)
+    z[0::5, rng.choice(V, 3, replace=False)] = 25.0 + rng.random(3).astype(np.float32)
+    z[1::5, rng.integers(0, V)] = 120.0
+    z[2::5] *= 60.0
+    z[3::5] *= 60.0
+    z[3::5, rng.permutation(V)[: V - 400]] = -np.inf
+    z[4::5, rng.choice(V, 40, replace=False)] += 30.0
+    params = _params([dict()], B, np.resize([1.0, 0.5, 1.3], B).astype(np.float32))
+    n = 300 if history else 0
+    if history:
+        params["rep_penalty"], params["freq_penalty"], params["n_prompt"] = 1.1, 0.2, 50
+    w = synth.Workload("weights-all", B, V, dtype, synth.f32_to_bf16_bits(z) if dtype == "bf16" else z, params, np.arange(B + 1, dtype=np.int64) * n,
+                       rng.integers(0, V, B * n).astype(np.int32), hot_ids=np.sort(rng.choice(V, V // 10, replace=False)).astype(np.int32) if hot_set else None)
+    dev = P.to_device(w)
+    if offset:
+        import torch
+        buf = torch.zeros(B * V + 16, dtype=dev["logits"].dtype, device="cuda:0")
+        buf[offset:offset + B * V] = dev["logits"].reshape(-1)
+        dev["logits"] = buf[offset:offset + B * V].view(B, V)
+    wide, general = _errors(w, dev, (binding.DIAG_WIDE, binding.DIAG_GENERAL))
+    assert general == 0 and wide == 4 * B
