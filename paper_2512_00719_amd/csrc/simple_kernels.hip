@@ -1392,7 +1392,7 @@ __device__ inline void sample_row_body(const SampleArgs& a, const int row, unsig
 
   simple_row_diag dg;
   dg.alpha = __longlong_as_double(0x7FF8000000000000ll);
-  dg.s_k = 0.0; dg.p_chosen = 0.0f; dg.n_survivors = 0; dg.flags = (a.gated && V < (1 << 18)) ? SIMPLE_DIAG_GENERAL : 0u; dg.reserved = 0u;
+  dg.s_k = 0.0; dg.p_chosen = 0.0f; dg.n_survivors = 0; dg.flags = a.gated ? SIMPLE_DIAG_GENERAL : 0u; dg.reserved = 0u;
 
   // ---- row configuration (identical in every thread) ----
   const bool bad_par = !(par.temperature >= 0.0f) || !(par.rep_penalty > 0.0f);

@@ -52,4 +52,29 @@ def test_routes_on_large_vocabularies(dtype, V, B, hot_share):
         for step in (0, 1):
             ids, dg = P.run_gpu(w, step)
             P.compare(ids, dg, P.run_oracle(w, step), range(B))
-    assert not (dg["flags"] & binding.DIAG_ERROR).any()
+    flags = dg["flags"]
+    assert not (flags & binding.DIAG_ERROR).any()
+    if V >= 1 << 19:
+        assert not (flags & binding.DIAG_GENERAL).any()  # (says that another kernel handed the row on)
+        return
+    # the routes complete their rows: nuclei wider than the list and top-k above it, the pattern counts of rows without
+    # penalties and top-k; the general kernel is left the rows with thousands of ties at a cut and a few that miss
+    handed = (flags & binding.DIAG_GENERAL) > 0
+    assert handed[kind != 4].mean() <= 0.1, np.bincount(kind[handed], minlength=n_kinds)
+    assert ((flags & binding.DIAG_WIDE) > 0)[np.isin(kind, (1, 7))].all()
+    if dtype == "bf16":
+        assert ((flags & binding.DIAG_PATTERN) > 0)[kind == 0].all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_handed_to_the_general_kernel_say_so(dtype):
+    """Top-k under penalties that raise logits is the general kernel's at every size."""
+    rng = np.random.default_rng(3)
+    B, V = 4, 1 << 18
+    z = rng.standard_normal((B, V)).astype(np.float32)
+    w = synth.Workload("handed-on", B, V, dtype, synth.f32_to_bf16_bits(z) if dtype == "bf16" else z,
+                       synth.make_params(B, temperature=1.0, top_k=20, rep_penalty=np.array([1.1, 0.8, 1.1, 0.8], np.float32), n_prompt=5),
+                       np.arange(B + 1, dtype=np.int64) * 10, rng.integers(0, V, B * 10).astype(np.int32))
+    ids, dg = P.run_gpu(w, 0)
+    P.compare(ids, dg, P.run_oracle(w, 0), range(B))
+    assert (((dg["flags"] & binding.DIAG_GENERAL) > 0) == [False, True, False, True]).all()

@@ -339,9 +339,9 @@ def test_single_best_token_among_thousands_of_ties_in_the_general_kernel():
             assert np.array_equal(ids, np.argmax(z, axis=1)) and (dg["n_survivors"] == 1).all()
 
 
-@pytest.mark.parametrize("V,dtype", [(1 << 18, "f32"), ((1 << 18) + 1000, "bf16"), (300_001, "f32"), ((1 << 18) + 8, "bf16")])
-def test_vocabularies_of_two_to_the_eighteen_columns_and_more(V, dtype):
-    """From 2^18 columns on the general kernel serves the whole batch (the single-pass kernel's fixed
+@pytest.mark.parametrize("V,dtype", [(1 << 19, "f32"), ((1 << 19) + 1000, "bf16"), (600_001, "f32"), ((1 << 19) + 8, "bf16")])
+def test_vocabularies_of_two_to_the_nineteen_columns_and_more(V, dtype):
+    """From 2^19 columns on the general kernel serves the whole batch (the single-pass kernel's fixed
     point is sized for fewer); whole-vocabulary nuclei, large top-k and min-p rows take its multi-pass
     route: aligned rows in 16-byte loads (a row length that is and is not a multiple of the stream's
     group of 1024 columns), the odd float32 length element by element."""
@@ -365,7 +365,7 @@ def test_vocabularies_of_two_to_the_eighteen_columns_and_more(V, dtype):
     w = synth.Workload(f"large-V-{V}", B, V, dtype, logits, params, hist_ptr, hist_ids, hot_ids=hot)
     res = _check(w, steps=(0, 1))
     flags = res[0][1]["flags"]
-    assert not (flags & 128).any()       # no row came through the single-pass kernel's queue
+    assert not (flags & 128).any()       # no row came through another kernel's queue
     assert (flags & 4).sum() >= 6        # the whole-vocabulary and large-k rows: multi-pass route
 
 
