@@ -993,6 +993,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       }
       // -inf columns without mass among the survivors of a count alone, or where nothing is truncated
       if (complete && !R.greedy && !R.p_on && !R.minp_on) dg.n_survivors = R.k_on ? k_asked : V;
+      if (R.all && V > KMAXF) dg.flags |= SIMPLE_DIAG_WIDE;  // (K_b is all of V)
     }
 
     // ---- a cut below the list's reach: the row goes to the kernels that follow ----

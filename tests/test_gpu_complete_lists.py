@@ -67,6 +67,8 @@ def test_short_vocabularies(dtype, V, history):
     z[13:26, rng.permutation(V)[: V // 2]] = -np.inf
     z[26:, V - 1] = 25.0
     out = _check(f"short-{V}", z, dtype, rng, history, hot_share=0.2 if V > 100 and history else 0.0)
+    untruncated = np.isin(np.arange(39) % len(CONTROLS), (0, 11))
+    assert all((((dg["flags"] & binding.DIAG_WIDE) > 0)[untruncated] == (V > 1024)).all() for dg in out)
     if dtype == "f32" and 1023 <= V <= 3073:  # (rows with very many equal values may still be handed on)
         assert all(((dg["flags"] & binding.DIAG_GENERAL) > 0).sum() <= 4 for dg in out)
 
