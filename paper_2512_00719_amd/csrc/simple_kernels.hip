@@ -1548,7 +1548,7 @@ __global__ __launch_bounds__(NT, 4) void pending_rows_kernel(const SampleArgs a)
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ Shared S;
   const unsigned n = min(__hip_atomic_load(&a.pend[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), (unsigned)a.B);
-  if (blockIdx.x == 0 && threadIdx.x == 0 && a.wq[0] != 0u) a.wq[0] = 0u;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && a.wq[0] != 0u) { a.wq[0] = 0u; a.wq[1] = 0u; }
   if (n == 0u) return;
   __syncthreads();  // every thread has read the count
   if (threadIdx.x == 0 && atomicAdd(&a.pend[1], 1u) == gridDim.x - 1u) { a.pend[0] = 0u; a.pend[1] = 0u; }

@@ -97,7 +97,7 @@ struct SampleArgs {
   uint32_t* pend;  // rows left to the general kernel: [0] count, [1] its workgroups that have read the count, [2 ..] row indices
   int32_t* order;  // row of each workgroup of the single-pass kernel (written by the ordering kernel of a launch with more rows
                    // than compute units), or nullptr: workgroup b takes row b
-  uint32_t* wq;    // rows with a whole-vocabulary nucleus wider than the list: [0] count, records from word 16
+  uint32_t* wq;    // rows with a whole-vocabulary nucleus wider than the list: [0], [1] counts, records from word 16
   unsigned char* wws;  // one workspace slot per queued row
   int wide_slots;
   uint32_t ws_stride;  // bytes per slot: fixed part, then the row's history tables

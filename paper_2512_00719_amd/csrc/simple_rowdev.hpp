@@ -360,15 +360,18 @@ struct WideRec {  // 64 bytes: everything the later kernels need to know about t
   uint32_t row; float g; uint32_t mode, flags;
   float tau, top_p, rep, freq;
   float pres; int nnz, n_prompt, h_active;
-  float min_p; int32_t top_k; uint32_t distinct, f64;  // f64: weigh the columns in double precision
+  float min_p; int32_t top_k; uint32_t distinct;
+  uint32_t far_slot;  // not this row's: the k-th record holds the slot of the k-th far row
 };
 // What delimits the survivors of a queued row (each is a prefix of the total order, section 5.2):
 enum { WIDE_TOP_P = 0,   // the shortest prefix whose mass reaches top_p of the row's mass
        WIDE_ALL = 1,     // no truncation: every column
        WIDE_MIN_P = 2,   // tempered value >= fl(y_max + fl(ln min_p))
        WIDE_TOP_K = 3 }; // the first top_k columns of the order (top-k alone, beyond the candidate list's reach)
-constexpr uint32_t WIDE_FAR = 16u;      // beside WIDE_ALL: a column stands too far above g for the integer masses, or the row is weighed in double
-constexpr int WQ_HEAD = 16;             // words before the records
+constexpr uint32_t WIDE_MODE = 15u;     // the mode's bits of WideRec::mode; beside them:
+constexpr uint32_t WIDE_F64 = 16u;      // the row's columns are weighed in double precision
+constexpr uint32_t WIDE_FAR = 32u;      // (with WIDE_ALL) ... or a column stands too far above g for the integer masses
+constexpr int WQ_HEAD = 16;             // words before the records: [0] their number, [1] the number of far rows
 constexpr uint32_t WS_HIST = 0u;        // u64[NBW]: mass of the columns below g, by bin (top-k route: their number)
                                         // (rows without truncation: AllPart[128][4], per slice and wave)
 constexpr uint32_t WS_TILES = 16384u;   // u64[2][256]: survivors' mass per tile, tail class then hot class
@@ -382,6 +385,11 @@ constexpr uint32_t WS_HT = 53312u;      // the row's history tables as the singl
 // largest tempered value m: masses as integers relative to the one at g, or (WIDE_FAR) the slice's in the
 // first of its four parts, weighed in double precision, as 2^44 fixed point relative to m.
 struct AllPart { u64 s, h; float m; uint32_t unused; };
+// Marks the untruncated row in `slot` for the second kernel, which weighs it (one thread calls; once per row counts).
+__device__ __forceinline__ void mark_far(uint32_t* wq, unsigned slot) {
+  WideRec* recs = reinterpret_cast<WideRec*>(wq + WQ_HEAD);
+  if (!(atomicOr(&recs[slot].mode, WIDE_FAR) & WIDE_FAR)) recs[atomicAdd(&wq[1], 1u)].far_slot = slot;
+}
 static_assert(sizeof(AllPart) == 24 && (FAST_MAX_V / 4096) * 4 * sizeof(AllPart) <= 16384, "the parts of a row fit the bins' place");
 
 // Mass of one column relative to the mass at y_g, w = exp(y - y_g) with y = fl32(z / tau), and the

@@ -34,8 +34,8 @@
 // Rows without truncation have no cut and are read once, by the first kernel: per slice and wave it leaves
 // the columns' mass, from which the third kernel draws.  Where a column stands too far above g for the fixed
 // point, the second kernel weighs the row again, in double precision and each slice relative to its largest
-// column (so that any dynamic range is carried: one column may hold almost the whole mass).  Rows with a
-// min-p cut use the first
+// column (one column may hold almost the whole mass; only a slice more than FAR_LIMIT above all others sends the
+// row to the general kernel).  Rows with a min-p cut use the first
 // kernel for the row maximum only (the cut is a value).  Rows with top-k alone run the same three
 // kernels by count instead of mass: a bin counts its columns, the cut's bin is the one in which
 // the count from the top reaches k, and the descent inside it weighs every column as one.
@@ -89,7 +89,7 @@ __device__ __forceinline__ WideRow load_row(const SampleArgs& a, unsigned slot) 
   WideRow W;
   slot = uni(slot);
   const WideRec rec = reinterpret_cast<const WideRec*>(a.wq + WQ_HEAD)[slot];
-  W.row = uni((int)rec.row); W.mode = uni(rec.mode & 15u); W.far = (uni(rec.mode) & WIDE_FAR) != 0u; W.flags = uni(rec.flags);
+  W.row = uni((int)rec.row); W.mode = uni(rec.mode & WIDE_MODE); W.far = (uni(rec.mode) & WIDE_FAR) != 0u; W.f64 = (uni(rec.mode) & WIDE_F64) != 0u; W.flags = uni(rec.flags);
   W.tau = uni(rec.tau); W.top_p = uni(rec.top_p); W.min_p = uni(rec.min_p);
   W.C.g = uni(rec.g); W.C.y_g = uni(rec.g / rec.tau); W.C.inv_tau = uni(1.0 / (double)rec.tau); W.C.need_sum = true;
   W.C.l2e_tau = 0.0f;
@@ -98,7 +98,6 @@ __device__ __forceinline__ WideRow load_row(const SampleArgs& a, unsigned slot) 
   W.h_active = uni(rec.h_active) != 0;
   W.distinct = uni(rec.distinct);
   W.top_k = uni(rec.top_k);
-  W.f64 = uni(rec.f64) != 0u;
   W.ws = a.wws + (size_t)slot * a.ws_stride;
   return W;
 }
@@ -431,24 +430,21 @@ struct ItemLoads {
   uint32_t pre;    // this thread's mask word or directory entry
 };
 struct SlotIds {
-  uint32_t row_c, act_c, row_n, act_n;  // current slot, next slot; act: bit 0 history in force, bit 1 no truncation, bit 2 (with it) WIDE_FAR
+  uint32_t row_c, act_c, row_n, act_n;  // current slot, next slot; act: bit 0 history in force, bit 1 no truncation
   __device__ __forceinline__ void request(const SampleArgs& a, unsigned slot, unsigned n_wide, uint32_t& row, uint32_t& act) {
     row = 0u; act = 0u;
     if (slot < n_wide) {
       const uint32_t* rec = reinterpret_cast<const uint32_t*>(reinterpret_cast<const WideRec*>(a.wq + WQ_HEAD) + slot);
       row = as_global(rec)[0];
-      const uint32_t mode = as_global(rec)[2];
-      act = (as_global(rec)[11] != 0u ? 1u : 0u) | ((mode & 15u) == (uint32_t)WIDE_ALL ? 2u : 0u) | (mode & WIDE_FAR ? 4u : 0u);
+      act = (as_global(rec)[11] != 0u ? 1u : 0u) | ((as_global(rec)[2] & WIDE_MODE) == (uint32_t)WIDE_ALL ? 2u : 0u);
     }
   }
-  // nothing to do for the classifying kernel: the bins kernel has the masses of a row without truncation
-  static __device__ __forceinline__ bool idle(uint32_t act) { return (act & 6u) == 2u; }
   // The record is the same in every lane: scalars from here on.  Called where the workgroup waits
   // for its loads anyway (a row's record), so that no later use has to wait for loads in flight.
   __device__ __forceinline__ void settle() { row_c = uni(row_c); act_c = uni(act_c); row_n = uni(row_n); act_n = uni(act_n); }
 };
 static_assert(offsetof(WideRec, row) == 0 && offsetof(WideRec, mode) == 8 && offsetof(WideRec, h_active) == 44, "record words read by SlotIds");
-// classify: most rows without truncation need nothing from this pass; else (the bins kernel) only they need the hot bits
+// classify: rows without truncation need nothing from this loop; else (the bins kernel) only they need the hot bits
 template <typename DT, bool use_hot, bool classify>
 __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a, unsigned item, unsigned n_sl, int cur_slot, const SlotIds& ids) {
   constexpr int EPL = Io<DT>::EPL;
@@ -457,7 +453,7 @@ __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a
   const uint32_t row = slot == cur_slot ? ids.row_c : ids.row_n;  // scalars (SlotIds::settle)
   const uint32_t actw = slot == cur_slot ? ids.act_c : ids.act_n;
   const bool act = (actw & 1u) != 0u;
-  if (classify && SlotIds::idle(actw)) return;
+  if (classify && (actw & 2u)) return;
   const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride;
   L.pre = act ? slice_fetch(a.wws + (size_t)slot * a.ws_stride, a, c0) : 0u;
 #pragma unroll
@@ -533,7 +529,7 @@ __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<
   if ((tid & 63) == 0) {
     AllPart* part = reinterpret_cast<AllPart*>(W.ws + WS_HIST) + sl * WNW + (tid >> 6);
     part->s = s; part->h = h; part->m = M;
-    if (any_far) atomicOr(&(reinterpret_cast<WideRec*>(a.wq + WQ_HEAD) + slot)->mode, WIDE_FAR);  // the second kernel weighs the row again
+    if (any_far || (W.f64 && sl == 0)) mark_far(a.wq, (unsigned)slot);  // the second kernel weighs the row again
   }
 }
 
@@ -706,6 +702,44 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
 }
 
 // ---------------------------------------------------------------- classify --------------------
+// The far rows: the masses of their slices again, in double precision and relative to the slice's largest column.
+// The slices of all of them are dealt out over the workgroups (with each row's to the few that hold it, as the
+// other rows' are, one such row among 256 untruncated ones took 26 us).
+template <typename DT, bool use_hot>
+__device__ __forceinline__ void far_rows(SliceTabs& Tb, FS& S, const SampleArgs& a) {
+  const int tid = threadIdx.x, V = a.V;
+  const unsigned n_sl = (unsigned)((V + SLC - 1) / SLC), n = min(as_global(a.wq)[1], (unsigned)a.wide_slots) * n_sl;
+  for (unsigned it = blockIdx.x; it < n; it += gridDim.x) {
+    const int sl = (int)(it % n_sl), c0 = sl * SLC;
+    const WideRow W = load_row(a, uni(reinterpret_cast<const WideRec*>(a.wq + WQ_HEAD)[it / n_sl].far_slot));
+    const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
+    AllPart* part = reinterpret_cast<AllPart*>(W.ws + WS_HIST) + sl * WNW;
+    float M = LOWEST;
+#pragma unroll
+    for (int k = 0; k < WNW; ++k) M = fmaxf(M, part[k].m);
+    HistPre<DT> HP;
+    if (W.h_active) {
+      slice_store(Tb, slice_fetch(W.ws, a, c0), a, c0, W.distinct);
+      __syncthreads();
+      hist_fetch<DT>(HP, Tb, W.ws, a, rowp, c0, V);
+    }
+    u64 s = 0ull, h = 0ull, mx = 0ull;
+    unsigned bad = 0u, none = 0u;
+    weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int idx, const Exp2Poly& P) {
+      const float y = tempered(z, W.C);
+      bad |= y != y ? 1u : 0u;
+      const u64 m = exp_fix<44>(y, M, P);
+      s += m;
+      if (use_hot && hot_bit(a.hot_bits, (uint32_t)idx)) h += m;
+    });
+    blk_reduce<WNW>(S, bad, none, mx, s);  // barriers inside: the parts' maxima and the tables have been read
+    if (use_hot) h = blk_sum_u64<WNW>(S, h);
+    if (tid < WNW) {
+      part[tid].s = tid == 0 ? s : 0ull; part[tid].h = tid == 0 ? h : 0ull;
+      part[tid].m = bad ? INFINITY : M;  // (a NaN: the finishing kernel hands the row on)
+    }
+  }
+}
 template <typename DT, bool use_hot>  // use_hot: a hot set is installed (section 5.3): masses are split by class
 __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a) {
   constexpr int EPL = Io<DT>::EPL;
@@ -722,18 +756,19 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
   const int wbase = (tid * EPL) >> 5;
   const unsigned wsh = (unsigned)(tid * EPL) & 31u;
   static_assert((WT * EPL) % 32 == 0, "group stride in mask words");
+  const uint32_t* hot_bits = a.hot_bits;
+  far_rows<DT, use_hot>(Tb, S, a);
   const Items I = my_items(a);
   if (I.i0 >= I.i1) return;
-  const uint32_t* hot_bits = a.hot_bits;
   const unsigned n_wide = min(as_global(a.wq)[0], (unsigned)a.wide_slots);
   int cur = (int)(I.i0 / I.n_sl);
   SlotIds ids;
   ids.request(a, (unsigned)cur, n_wide, ids.row_c, ids.act_c);
   ids.request(a, (unsigned)cur + 1u, n_wide, ids.row_n, ids.act_n);
   ids.settle();
-  {  // nothing to do for such rows (a workgroup's items lie in at most two slots, or the first is one of them)
+  {  // nothing to do for rows without truncation (a workgroup's items lie in at most two slots, or the first is one of them)
     const int last = (int)((I.i1 - 1u) / I.n_sl);
-    if (SlotIds::idle(ids.act_c) && (last == cur || (last == cur + 1 && SlotIds::idle(ids.act_n)))) return;
+    if ((ids.act_c & 2u) && (last == cur || (last == cur + 1 && (ids.act_n & 2u)))) return;
   }
   ItemLoads<DT> N;  // the next item's loads
   item_fetch<DT, use_hot, true>(N, a, I.i0, I.n_sl, cur, ids);
@@ -747,7 +782,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     ids.settle();
     const RowCut rc = row_cut(S, W);
     bstar = rc.bstar; thr_y = rc.thr_y; valid = rc.valid;
-    valid = valid && (W.mode != WIDE_ALL || W.far);  // (else done by the bins kernel)
+    valid = valid && W.mode != WIDE_ALL;  // (done by the bins kernel, or above)
     if (first && tid == 0 && valid) {  // for the finishing kernel
       reinterpret_cast<uint32_t*>(W.ws + WS_SCAL)[8] = (uint32_t)bstar + 1u;
       reinterpret_cast<u64*>(W.ws + WS_SCAL)[5] = rc.s_tot;
@@ -816,7 +851,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     __syncthreads();
     HistPre<DT> HP;
     if (W.h_active) hist_fetch<DT>(HP, Tb, W.ws, a, rowp, c0, V);  // this item's own loads go first: loads return in order
-    if (more && !W.f64 && W.mode != WIDE_ALL) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
+    if (more && !W.f64) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
     u64 acc_s = 0ull, acc1 = 0ull;  // this slice: mass of the sure columns, and of the hot ones among them
     // one column the slow way: history columns and the ragged end of the row
     auto one = [&](float z, int idx) {
@@ -837,29 +872,6 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
         if (s < (unsigned)LCAP) lrl[s] = ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx;
       }
     };
-    if (W.mode == WIDE_ALL) {  // the masses of an untruncated row again, relative to the slice's largest
-      AllPart* part = reinterpret_cast<AllPart*>(W.ws + WS_HIST) + sl * WNW;
-      float M = LOWEST;
-#pragma unroll
-      for (int k = 0; k < WNW; ++k) M = fmaxf(M, part[k].m);
-      weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int idx, const Exp2Poly& P) {
-        const float y = tempered(z, W.C);
-        bad = bad || y != y;
-        const u64 m = exp_fix<44>(y, M, P);
-        acc_s += m;
-        if (use_hot && hot_bit(hot_bits, (uint32_t)idx)) acc1 += m;
-      });
-      unsigned n_bad = bad ? 1u : 0u, dz = 0u; u64 mx = 0ull;
-      blk_reduce<WNW>(S, n_bad, dz, mx, acc_s);  // barriers inside
-      acc1 = use_hot ? blk_sum_u64<WNW>(S, acc1) : 0ull;
-      if (tid < WNW) {
-        part[tid].s = tid == 0 ? acc_s : 0ull; part[tid].h = tid == 0 ? acc1 : 0ull;
-        part[tid].m = n_bad ? INFINITY : M;  // (a NaN: the finishing kernel hands the row on)
-      }
-      bad = false;
-      if (more) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
-      continue;
-    }
     if (W.f64) {
       weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int idx, const Exp2Poly& P) {
         int b; float y;
@@ -1229,6 +1241,8 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   return S.out_id >= 0;
 }
 
+// A slice that stands this far above all others holds the row's whole mass; such rows are left to the general kernel.
+constexpr float FAR_LIMIT = 88.0f;
 // A row without truncation, from its waves' parts: acceptance (section 5.3), the slice that holds the draw, and
 // that slice's columns once more.  Where the bins kernel's integers hold, the slices' masses are their sums;
 // else (WIDE_FAR) they are scaled to the row maximum, and the draw's place inside its slice is a fraction of
@@ -1279,9 +1293,11 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
     m_all = (u64)__double2ull_rn((double)ps[0] * f); m_hot = min(m_all, (u64)__double2ull_rn((double)ph[0] * f));
   }
   if (lost) atomicOr(&S.flags, 1u);
-  const u64 S_K = blk_sum_u64<WNW>(S, m_all);  // barriers inside
+  unsigned near = (tid < n_sl && m >= y_max - FAR_LIMIT) ? 1u : 0u, finite = (tid < n_sl && m > LOWEST) ? 1u : 0u;
+  u64 S_K = m_all, mx = 0ull;
+  blk_reduce<WNW>(S, near, finite, mx, S_K);  // barriers inside
   const u64 S_H = use_hot ? blk_sum_u64<WNW>(S, m_hot) : 0ull;
-  if (S.flags) return false;
+  if (S.flags || (rel && near == 1u && finite > 1u)) return false;
   bool pick_hot = false;
   if (use_hot) {
     pick_hot = (S_H > 0ull) && (u3[1] * (double)S_K <= (double)S_H);

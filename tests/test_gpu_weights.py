@@ -89,8 +89,8 @@ def test_survivors_beyond_the_list(kind, dtype, V, hot_set, history):
 @pytest.mark.parametrize("dtype,V,offset", [("f32", 50_048, 0), ("bf16", 50_048, 0), ("f32", 50_001, 0), ("f32", 270_000, 0), ("f32", 8193, 3)])
 @pytest.mark.parametrize("hot_set,history", [(False, False), (True, False), (True, True)])
 def test_untruncated_rows_of_any_range(dtype, V, offset, hot_set, history):
-    """Rows beyond the float32 weights' reach: a few columns hold much of the mass, one holds all but a trace (more
-    than 88 above the rest), a spread of hundreds, masked columns."""
+    """Rows beyond the float32 weights' reach: a few columns hold much of the mass, one holds all but a trace, a spread
+    of hundreds, masked columns.  Only a column more than 88 above the rest is the general kernel's."""
     rng = np.random.default_rng(V + 3 * hot_set + history)
     B = 20
     z = (rng.standard_normal((B, V)) * 0.7).astype(np.float32)
@@ -113,4 +113,4 @@ def test_untruncated_rows_of_any_range(dtype, V, offset, hot_set, history):
         buf[offset:offset + B * V] = dev["logits"].reshape(-1)
         dev["logits"] = buf[offset:offset + B * V].view(B, V)
     wide, general = _errors(w, dev, (binding.DIAG_WIDE, binding.DIAG_GENERAL))
-    assert general == 0 and wide == 4 * B
+    assert (general > 0 or dtype == "bf16") and general <= 4 * 4 and wide == 4 * B  # (bfloat16: the pattern counts carry any range)
