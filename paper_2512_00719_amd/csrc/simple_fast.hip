@@ -257,7 +257,7 @@ __device__ __forceinline__ int finalize_small(FS& S, const RowCfg& R, unsigned n
   return (S.out_id >= 0) ? FIN_DONE : FIN_PENDING;
 }
 
-constexpr float MAX_SPAN = 64.0f;  // a complete list may reach further down: what lies there shares the last bucket
+constexpr float MAX_SPAN = 64.0f;  // a complete list may reach further down: what lies there has no mass and shares the last bucket
 
 // Long lists (more than MEMB certified entries, in LDS as keys lk[] / ids li[]): bucket tables over
 // the key range locate each cut; only the bucket that holds a cut is resolved entry by entry.
@@ -274,8 +274,10 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
   u64* mw = reinterpret_cast<u64*>(tables + NBF * 12 + MEMB2 * 8);   // MEMB2 * 8
   const float y_max = keyf(kmax);
   // buckets are linear in the tempered value (key space is logarithmic around zero), down to the list's
-  // lower end; monotone in the key
-  const float bscale = (float)NBF / fmaxf(fminf(y_max - keyf(key_lo), MAX_SPAN), 1e-30f);
+  // lower end; monotone in the key.  A sampled list (key_lo is its threshold) ends a little below the cut, however
+  // far that is from the maximum: at a low temperature a long top-k reaches hundreds down.
+  const float span = y_max - keyf(key_lo);
+  const float bscale = (float)NBF / fmaxf(key_lo == key_g ? span : fminf(span, MAX_SPAN), 1e-30f);
   auto bucket_of = [&](uint32_t k) { return (unsigned)min((int)((y_max - keyf(k)) * bscale), NBF - 1); };
   u64 cl = 0ull;
   for (unsigned i = tid; i < n; i += NTHR) { const u64 c = composite(lk[i], li[i]); cl = (c > cl) ? c : cl; }

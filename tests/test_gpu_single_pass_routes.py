@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 import parity_util as P
-from paper_2512_00719_amd import synth
+from paper_2512_00719_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -426,3 +426,21 @@ def test_top_k_alone_beyond_the_list_with_a_hot_set():
         f = dg["flags"]
         assert ((f & WIDE) > 0).all() and ((f & SHVS) > 0).all() and not ((f & GENERAL) > 0).any()
         assert np.array_equal(dg["n_survivors"], params["top_k"])
+
+
+@pytest.mark.parametrize("dtype,B,V", [("f32", 40, 128_256), ("f32", 600, 50_048), ("bf16", 300, 200_000)])
+@pytest.mark.parametrize("temperature", [0.02, 0.05, 0.1])
+def test_long_top_k_at_low_temperatures(dtype, B, V, temperature):
+    """A list of up to thousands of columns that spans hundreds of nats: its buckets follow, and the list decides."""
+    rng = np.random.default_rng(B + V)
+    z = synth.zipf_profile_logits(B, V, 1.1, 1.5, rng, "f32", rng.permutation(V))
+    z += (rng.random((B, V)) * 1e-3).astype(np.float32)
+    params = synth.make_params(B, temperature=temperature, top_k=np.resize([1000, 600, 900], B).astype(np.int32),
+                               top_p=np.resize([1.0, 0.999999], B).astype(np.float32))
+    hot = np.sort(rng.choice(V, V // 5, replace=False)).astype(np.int32)
+    w = synth.Workload("low-temperature", B, V, dtype, synth.f32_to_bf16_bits(z) if dtype == "bf16" else z, params, np.zeros(B + 1, np.int64),
+                       np.zeros(0, np.int32), hot_ids=hot if temperature == 0.05 else None)
+    ids, dg = P.run_gpu(w, 0)
+    rows = sorted(rng.choice(B, 24, replace=False).tolist())
+    P.compare(ids, dg, P.run_oracle(w, 0, rows=rows), rows)
+    assert ((dg["flags"] & binding.DIAG_GENERAL) > 0).mean() <= 0.01
