@@ -707,7 +707,9 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       const float thr_lb = Mp / R.tau + (float)log((double)R.min_p);
       float gm = thr_lb * R.tau;
       gm = gm - fabsf(gm) * 1e-6f - 1e-30f;
-      g = fmaxf(g, gm);
+      // (a row with few finite columns: the bound, and what lies below it need not be listed)
+      if (complete && gm > LOWEST) { complete = false; g = gm; }
+      else g = fmaxf(g, gm);
     }
     C.g = g;
     C.y_g = R.greedy ? g : g / R.tau;

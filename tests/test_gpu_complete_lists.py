@@ -97,3 +97,27 @@ def test_wide_nuclei_under_a_high_maximum(V):
         assert (dg["n_survivors"] > 5000).any()
         # (a cut inside the list, where a thousand columns share a few buckets, is the general kernel's)
         assert not (dg["flags"] & binding.DIAG_GENERAL)[dg["n_survivors"] > 2000].any()
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", 128_256), ("bf16", 200_000)])
+@pytest.mark.parametrize("allowed", [1, 40, 2000, 20_000])
+def test_min_p_on_masked_rows(dtype, V, allowed):
+    """Few finite columns where the threshold is sampled (two tiles at the start of each sixteenth of a row), more than a
+    list holds elsewhere; min-p leaves some of them, and its bound is the threshold."""
+    rng = np.random.default_rng(V + allowed)
+    B, T = 12, 1024 if dtype == "f32" else 2048
+    col = np.arange(V)
+    sampled = np.isin(col // T, [w * (V // T) // 16 + k for w in range(16) for k in (0, 1)])
+    z = np.full((B, V), -np.inf, np.float32)
+    for b in range(B):
+        ids = np.concatenate([rng.choice(col[~sampled], allowed, replace=False), rng.choice(col[sampled], 20, replace=False)])
+        z[b, ids] = rng.standard_normal(ids.size) * 2.0
+    n = 30
+    hist_ids = rng.integers(0, V, B * n).astype(np.int32)
+    params = synth.make_params(B, temperature=np.resize([1.0, 0.7], B).astype(np.float32), min_p=np.resize([0.05, 0.2, 0.5], B).astype(np.float32),
+                               top_p=np.resize([1.0, 1.0, 1.0, 0.9], B).astype(np.float32), rep_penalty=1.1, n_prompt=10)
+    w = synth.Workload(f"min-p-{allowed}", B, V, dtype, synth.f32_to_bf16_bits(z) if dtype == "bf16" else z, params,
+                       np.arange(B + 1, dtype=np.int64) * n, hist_ids)
+    ids, dg = P.run_gpu(w, 0)
+    P.compare(ids, dg, P.run_oracle(w, 0), range(B))
+    assert not (dg["flags"] & binding.DIAG_GENERAL).any()
