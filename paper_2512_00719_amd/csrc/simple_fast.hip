@@ -261,8 +261,9 @@ constexpr float MAX_SPAN = 64.0f;  // a complete list may reach further down: wh
 
 // Long lists (more than MEMB certified entries, in LDS as keys lk[] / ids li[]): bucket tables over
 // the key range locate each cut; only the bucket that holds a cut is resolved entry by entry.
-// Same decisions as finalize_small.
-template <int NTHR>
+// Same decisions as finalize_small.  SPREAD (rows listed whole): a bucket with more members than are resolved
+// at once is spread again; a sampled list leaves its row to the kernels that follow.
+template <int NTHR, bool SPREAD>
 __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n, unsigned n_unc, uint32_t kmax,
                                              uint32_t key_g, uint32_t key_lo, bool sliced, float g, double S_below, const uint32_t* lk, const uint32_t* li,
                                              unsigned char* tables, const uint32_t* __restrict__ hot_bits, simple_row_diag& dg) {
@@ -289,6 +290,78 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
     dg.n_survivors = 1; dg.p_chosen = 1.0f;
     return FIN_DONE;
   }
+  constexpr u64 MANY = ~0ull;
+  // Among the entries that `in` selects, in descending order of their (distinct) values: the one at which the
+  // running mass (or count), `acc` before the first, reaches the target (its value; 0 if none does).  Up to MEMB2 of
+  // them are resolved at once; more (ties, most often) are spread over the buckets of their range of values
+  // until the bucket that holds the place has no more (without SPREAD: MANY).  If they were not spread
+  // (direct), e_SK is the mass of the entries down to the one returned.
+  bool direct = true;
+  auto mass_of = [&](unsigned i) { return wfix(lk[i], y_max); };
+  auto resolve = [&](auto&& in, auto&& value, const bool by_count, u64 acc, u64 target) -> u64 {
+    direct = true;
+    u64 lo = 0ull, hi = ~0ull;
+    for (;;) {
+      if (tid == 0) { S.memb = 0u; S.e_tfix = 0ull; }
+      __syncthreads();
+      for (unsigned i = tid; i < n; i += NTHR) {
+        if (!in(i)) continue;
+        const u64 v = value(i);
+        if (v < lo || v > hi) continue;
+        const unsigned slot = atomicAdd(&S.memb, 1u);
+        if (slot < (unsigned)MEMB2) { mc[slot] = v; mw[slot] = mass_of(i); }
+      }
+      __syncthreads();
+      const unsigned nm = S.memb;
+      if (nm <= (unsigned)MEMB2) {
+        for (unsigned mi = tid; mi < nm; mi += NTHR) {
+          unsigned r;
+          const u64 mass = sum_where<true>(mc, mw, nm, mc[mi], r);
+          const u64 G = acc + (by_count ? (u64)r + 1ull : mass), w = by_count ? 1ull : mw[mi];
+          if (G >= target && G - w < target) { S.e_tfix = mc[mi]; S.e_SK = mass; }
+        }
+        __syncthreads();
+        return S.e_tfix;
+      }
+      if constexpr (!SPREAD) return MANY;
+      direct = false;
+      if (hi == ~0ull) {  // the range of their values
+        u64 vmax = 0ull, nmin = 0ull, none = 0ull;
+        unsigned z0 = 0u, z1 = 0u;
+        for (unsigned i = tid; i < n; i += NTHR) {
+          if (!in(i)) continue;
+          const u64 v = value(i);
+          vmax = v > vmax ? v : vmax; nmin = ~v > nmin ? ~v : nmin;
+        }
+        blk_reduce<NWV>(S, z0, z1, vmax, none);
+        blk_reduce<NWV>(S, z0, z1, nmin, none);
+        hi = vmax; lo = ~nmin;
+      }
+      const int sh = max(0, 64 - NBF_BITS - (int)__clzll((long long)(hi - lo)));
+      for (int i = tid; i < NBF; i += NTHR) fmass[i] = 0ull;
+      if (tid == 0) S.bk = -1;
+      __syncthreads();
+      for (unsigned i = tid; i < n; i += NTHR) {
+        if (!in(i)) continue;
+        const u64 v = value(i);
+        if (v >= lo && v <= hi) atomicAdd(&fmass[(unsigned)((hi - v) >> sh)], by_count ? 1ull : mass_of(i));
+      }
+      __syncthreads();
+      const u64 m = (tid < NBF) ? fmass[tid] : 0ull;
+      unsigned c0, c1; u64 me, mt;
+      blk_excl_scan2<NWV>(S, 0u, m, c0, me, c1, mt);
+      if (acc + me < target && acc + me + m >= target) { S.bk = tid; S.mab_p = acc + me; }
+      __syncthreads();
+      const int d = S.bk;
+      if (d < 0) return 0ull;
+      acc = S.mab_p;
+      const u64 width = 1ull << sh;
+      hi -= (u64)(unsigned)d << sh;
+      if (hi - lo >= width) lo = hi - (width - 1ull);
+      if (sh == 0) return hi;
+    }
+  };
+  auto comp_of = [&](unsigned i) { return composite(lk[i], li[i]); };
   for (int i = tid; i < NBF; i += NTHR) { fcnt[i] = 0u; fmass[i] = 0ull; }
   __syncthreads();
   for (unsigned i = tid; i < n; i += NTHR) {
@@ -305,34 +378,21 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
   const unsigned n_k = R.k_on ? (unsigned)R.top_k : (unsigned)R.V;
   // ---- top-k cut: the bucket that holds the n_k-th entry, then its members exactly ----
   const bool kcut = R.k_on && n > n_k;
-  if (kcut && tid < NBF && c > 0u && ce < n_k && n_k <= ce + c) { S.bk = tid; S.need_k = n_k - ce; S.cab_k = ce; S.mab_k = me; }
+  if (kcut && tid < NBF && c > 0u && ce < n_k && n_k <= ce + c) { S.bk = tid; S.cab_k = ce; S.mab_k = me; }
   __syncthreads();
   u64 cut_k = 0ull, S_klist = total_m;
   int bk = -1;
   if (kcut) {
     bk = S.bk;
-    for (unsigned i = tid; i < n; i += NTHR) {
-      const uint32_t k = lk[i];
-      if ((int)bucket_of(k) == bk) {
-        const unsigned slot = atomicAdd(&S.memb, 1u);
-        if (slot < (unsigned)MEMB2) { mc[slot] = composite(k, li[i]); mw[slot] = wfix(k, y_max); }
-      }
+    const u64 above = S.mab_k;
+    cut_k = resolve([&](unsigned i) { return (int)bucket_of(lk[i]) == bk; }, comp_of, true, (u64)S.cab_k, (u64)n_k);
+    if (cut_k == 0ull || cut_k == MANY) return FIN_PENDING;
+    S_klist = above + S.e_SK;
+    if (!direct) {
+      u64 part = 0ull;
+      for (unsigned i = tid; i < n; i += NTHR) if ((int)bucket_of(lk[i]) == bk && comp_of(i) >= cut_k) part += mass_of(i);
+      S_klist = above + blk_sum_u64<NWV>(S, part);
     }
-    __syncthreads();
-    const unsigned nm = S.memb;
-    if (nm > (unsigned)MEMB2) return FIN_PENDING;  // ties wider than the member table
-    const unsigned need = S.need_k;
-    for (unsigned mi = tid; mi < nm; mi += NTHR) {
-      const u64 cm = mc[mi];
-      const unsigned r = count_greater(mc, nm, cm);
-      if (r == need - 1u) S.cut_k = cm;
-    }
-    __syncthreads();
-    cut_k = S.cut_k;
-    u64 part = 0ull;
-    for (unsigned mi = tid; mi < nm; mi += NTHR) if (mc[mi] >= cut_k) part += mw[mi];
-    S_klist = S.mab_k + blk_sum_u64<NWV>(S, part);
-    if (tid == 0) S.memb = 0u;
     __syncthreads();
   }
   // ---- mass of the top-k prefix (all of V when top-k is off) ----
@@ -346,37 +406,19 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
     if (target == 0ull) target = 1ull;
     if (tid < NBF && c > 0u && (bk < 0 || tid <= bk)) {
       const u64 incl = (tid == bk) ? S_klist : me + m;
-      if (me < target && incl >= target) { S.bp = tid; S.mab_p = me; S.cab_p = ce; }
+      if (me < target && incl >= target) { S.bp = tid; S.mab_p = me; }
     }
     __syncthreads();
     const int bp = S.bp;
     if (bp >= 0) {
-      for (unsigned i = tid; i < n; i += NTHR) {
-        const uint32_t k = lk[i];
-        if ((int)bucket_of(k) == bp && composite(k, li[i]) >= cut_k) {
-          const unsigned slot = atomicAdd(&S.memb, 1u);
-          if (slot < (unsigned)MEMB2) { mc[slot] = composite(k, li[i]); mw[slot] = wfix(k, y_max); }
-        }
-      }
-      __syncthreads();
-      const unsigned nm = S.memb;
-      if (nm > (unsigned)MEMB2) {  // ties wider than the member table: the sliced kernels resolve them, from the bucket's upper end down
+      cut_p = resolve([&](unsigned i) { return (int)bucket_of(lk[i]) == bp && comp_of(i) >= cut_k; }, comp_of, false, S.mab_p, target);
+      if (cut_p == MANY) {  // the sliced kernels resolve them, from the bucket's upper end down
         if (!sliced) return FIN_PENDING;
         if (tid == 0) S.wmax[0] = y_max - (float)bp / bscale;
         return FIN_WIDE;
       }
-      const u64 mab = S.mab_p;
-      for (unsigned mi = tid; mi < nm; mi += NTHR) {
-        const u64 cm = mc[mi], wm = mw[mi];
-        unsigned r;
-        const u64 G = mab + sum_where<true>(mc, mw, nm, cm, r);
-        if (G >= target && G - wm < target) { S.cut_p = cm; S.n_p = S.cab_p + r + 1u; }
-      }
-      __syncthreads();
-      cut_p = S.cut_p;
+      if (cut_p == 0ull) return FIN_PENDING;  // cannot happen: the bucket's mass reaches the target
       p_found = true;
-      if (tid == 0) S.memb = 0u;
-      __syncthreads();
     }
   }
   // ---- min-p cut: y >= fl32(y_max + fl32(ln min_p)) ----
@@ -443,23 +485,12 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
   __syncthreads();
   const int bd = S.bd;
   if (bd < 0) { return FIN_PENDING; }  // cannot happen: tfix < S_cls
-  for (unsigned i = tid; i < n; i += NTHR) {
-    if (in_class(lk[i], li[i]) && (int)(li[i] >> ishift) == bd) {
-      const unsigned slot = atomicAdd(&S.memb, 1u);
-      if (slot < (unsigned)MEMB2) { mc[slot] = (u64)li[i]; mw[slot] = wfix(lk[i], y_max); }
-    }
-  }
-  __syncthreads();
   {
-    const unsigned nm = S.memb;
-    if (nm > (unsigned)MEMB2) return FIN_PENDING;
-    const u64 mab = S.mab_d;
-    for (unsigned mi = tid; mi < nm; mi += NTHR) {
-      const u64 im = mc[mi], wm = mw[mi];
-      unsigned dummy;
-      const u64 C = mab + sum_where<false>(mc, mw, nm, im, dummy);
-      if (C > tfix && C - wm <= tfix) { S.out_id = (int)im; S.out_w = wm; }
-    }
+    const u64 v = resolve([&](unsigned i) { return in_class(lk[i], li[i]) && (int)(li[i] >> ishift) == bd; },
+                          [&](unsigned i) { return (u64)(0xFFFFFFFFu - li[i]); }, false, S.mab_d, tfix + 1ull);
+    if (v == MANY) return FIN_PENDING;
+    const uint32_t id = 0xFFFFFFFFu - (uint32_t)v;  // (distinct ids below 2^31: no value is zero)
+    for (unsigned i = tid; i < n; i += NTHR) if (v != 0ull && li[i] == id) { S.out_id = (int)id; S.out_w = mass_of(i); }
   }
   __syncthreads();
   dg.p_chosen = (float)((double)S.out_w / (double)S_K);
@@ -558,7 +589,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   const int k_sel = R.greedy ? 1 : (R.k_on ? (big_k ? par.top_k / 4 : par.top_k) : (R.p_le0 ? 1 : KMAXF));
   if (tid == 0) {
     S.cand_count = 0u; S.flags = 0u; S.kmax = 0u; S.memb = 0u; S.bk = -1; S.bp = -1; S.bd = -1;
-    S.need_k = 0u; S.cut_k = 0ull; S.cut_p = 0ull; S.n_p = 0u; S.out_id = -1; S.out_w = 0ull; S.kmin = 0xFFFFFFFFu;
+    S.cut_k = 0ull; S.cut_p = 0ull; S.out_id = -1; S.out_w = 0ull; S.kmin = 0xFFFFFFFFu;
     S.n2 = 0u; S.nunc = 0u; S.e_rc = FIN_PENDING; S.e_n = 0u; S.tile_ctr = 0u;
   }
   // ---- loads first: history ids, then this wave's two sample tiles ----
@@ -993,7 +1024,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
           if (key[j]) { const unsigned slot = atomicAdd(&S.n2, 1u); lk[slot] = key[j]; lid[slot] = eid[j]; }
         }
         __syncthreads();
-        rc = finalize_long<NTHR>(S, R, n_cert, n_unc, kmax, key_g, complete ? S.kmin : key_g, C.need_sum, C.g, S_below, lk, lid, lds + (size_t)lcap * 8u, hot_bits, dg);
+        rc = finalize_long<NTHR, WHOLE>(S, R, n_cert, n_unc, kmax, key_g, complete ? S.kmin : key_g, C.need_sum, C.g, S_below, lk, lid, lds + (size_t)lcap * 8u, hot_bits, dg);
       }
       // -inf columns without mass among the survivors of a count alone, or where nothing is truncated
       if (complete && !R.greedy && !R.p_on && !R.minp_on) dg.n_survivors = R.k_on ? k_asked : V;

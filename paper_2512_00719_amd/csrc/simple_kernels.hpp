@@ -40,9 +40,8 @@ constexpr int SAMPLE_PER_WAVE = 48;   // keys of the threshold sample a wave han
 constexpr int capf_per_thread(int threads, bool whole) { return threads == 256 ? (whole ? 12 : 14) : threads == 512 ? 12 : 8; }
 constexpr int MAX_WHOLE = 8192;  // columns of a row that is listed whole
 static_assert(MAX_WHOLE <= 1024 * capf_per_thread(1024, true), "a row that is listed whole fits the registers");
-constexpr int NBF = 256;      // buckets of the long-list epilogue's tables
-constexpr int MEMB2 = 512;    // members of one bucket that it resolves exactly (with 256, rows of 5865 columns listed whole, their values
-                              // spread by penalties, went to the general kernel after all: 2126 rows 1576 us, 329 so)
+constexpr int NBF_BITS = 8, NBF = 1 << NBF_BITS;  // buckets of the long-list epilogue's tables
+constexpr int MEMB2 = 256;    // members of one bucket that it resolves at once (more are spread over the buckets again)
 constexpr int KMAXF = 1024;   // largest top-k its list certifies
 constexpr int FAST_MAX_V = 1 << 19;  // columns from which only the general kernel serves a call: the 2^44 fixed-point masses of a
                                      // row stay below 2^63, and a row is at most 128 slices of the sliced kernels

@@ -120,7 +120,7 @@ __device__ __forceinline__ unsigned lanes_before(u64 m) {
 struct FS {
   unsigned cand_count, flags, kmax, kmin, memb;
   int bk, bp, bd;
-  unsigned need_k, cab_k, cab_p, n_p;
+  unsigned cab_k;
   u64 mab_k, mab_p, mab_d, cut_k, cut_p, out_w;
   int out_id;
   unsigned n2, nunc;           // certified / uncertified entries of the list

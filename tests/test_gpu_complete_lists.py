@@ -121,3 +121,25 @@ def test_min_p_on_masked_rows(dtype, V, allowed):
     ids, dg = P.run_gpu(w, 0)
     P.compare(ids, dg, P.run_oracle(w, 0), range(B))
     assert not (dg["flags"] & binding.DIAG_GENERAL).any()
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", 1500), ("f32", 5865), ("f32", 8191), ("bf16", 7189), ("f32", 128_256)])
+@pytest.mark.parametrize("values", [1, 3, 40])
+@pytest.mark.parametrize("hot_share", [0.0, 0.3])
+def test_cuts_among_many_ties(dtype, V, values, hot_share):
+    """Lists whose columns share a few values: the bucket that holds a cut, or the draw's range of ids (an allow-list of
+    neighbours), has more members than are resolved at once."""
+    rng = np.random.default_rng(V + values)
+    B = 26
+    if V > 10_000:  # an allow-list of neighbouring ids
+        z = np.full((B, V), -np.inf, np.float32)
+        z[:, 70_000:73_000] = rng.integers(0, values, (B, 3000)) * np.float32(0.25)
+    else:
+        z = (rng.integers(0, values, (B, V)) * np.float32(0.25)).astype(np.float32)
+        z[::2] += (rng.random((z[::2].shape[0], V)) < 0.01) * np.float32(3.0)
+    pool = [np.arange(70_000, 73_000) if V > 10_000 else np.arange(V)] * B
+    for history in (False, True):
+        for dg in _check(f"ties-{values}", z, dtype, rng, history, hot_share, steps=(0,), id_pool=pool):
+            handed = (dg["flags"] & binding.DIAG_GENERAL) > 0
+            # (a sampled list whose threshold is one of the tied values certifies none of them)
+            assert V > 10_000 or not handed.any(), np.flatnonzero(handed)
