@@ -733,6 +733,13 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     complete = __builtin_amdgcn_readfirstlane((complete && total < r_samp) ? 1 : 0) != 0;
     const unsigned need = max(1u, min(r_samp, total));
     float g = keyf(wave_threshold<NS>(ks, need, need / 8u + 1u, min(kmn, kmx), kmx));
+    // A rank beyond what the waves hand over (a long top-k on a short row): the value there, from the slope between
+    // the sample's largest value and the last one handed over, with a margin.  (Without, such rows were streamed
+    // with a threshold that admits too few, and went to the general kernel after all.)
+    if (R.k_on && !complete && r_samp > total && total >= 8u) {
+      const float l2 = __builtin_amdgcn_logf((float)total);
+      g -= 1.35f * (Mp - g) * (__builtin_amdgcn_logf((float)r_samp) - l2) / l2;
+    }
     if (!R.greedy && !R.k_on && R.minp_on) {
       // min-p survivors lie within ln(min_p) of the row maximum, which is at least the sample's
       const float thr_lb = Mp / R.tau + (float)log((double)R.min_p);

@@ -42,4 +42,27 @@ def test_rows_at_any_element(dtype, V, offset, B, history):
     ids, dg = P.run_gpu(w, 3, dev=dev)
     P.compare(ids, dg, P.run_oracle(w, 3, rows=rows), rows)
     assert not (dg["flags"] & binding.DIAG_ERROR).any()
-    assert ((dg["flags"] & binding.DIAG_GENERAL) > 0).mean() <= 0.25  # the general kernel only completes what the others hand on
+    # the general kernel only completes what the others hand on (one row of nine: top-k 3000 or a sampled threshold that missed)
+    assert ((dg["flags"] & binding.DIAG_GENERAL) > 0).mean() <= 0.12
+
+
+@pytest.mark.parametrize("dtype,V,offset,B", [("f32", 20_001, 1, 8), ("f32", 20_000, 0, 300), ("f32", 17_500, 0, 700), ("bf16", 33_001, 3, 8),
+                                              ("bf16", 50_048, 0, 700)])
+@pytest.mark.parametrize("gaussian", [False, True])
+def test_long_top_k_on_short_rows(dtype, V, offset, B, gaussian):
+    """Top-k 600 to 1000 on rows whose sample hands over fewer values than the threshold's rank."""
+    import torch
+    rng = np.random.default_rng(V + gaussian)
+    z = rng.standard_normal((B, V)).astype(np.float32) if gaussian else synth.zipf_profile_logits(B, V, 1.1, 1.5, rng, "f32", rng.permutation(V))
+    params = synth.make_params(B, temperature=0.9, top_k=np.resize([1000, 600, 800], B).astype(np.int32), top_p=0.99)
+    w = synth.Workload("long-k", B, V, dtype, synth.f32_to_bf16_bits(z) if dtype == "bf16" else z, params, np.zeros(B + 1, np.int64), np.zeros(0, np.int32))
+    dev = P.to_device(w)
+    if offset:
+        buf = torch.zeros(B * V + 16, dtype=dev["logits"].dtype, device="cuda:0")
+        buf[offset:offset + B * V] = dev["logits"].reshape(-1)
+        dev["logits"] = buf[offset:offset + B * V].view(B, V)
+    ids, dg = P.run_gpu(w, 0, dev=dev)
+    rows = sorted(rng.choice(B, min(B, 24), replace=False).tolist())
+    P.compare(ids, dg, P.run_oracle(w, 0, rows=rows), rows)
+    print((V, gaussian), "general:", ((dg["flags"] & binding.DIAG_GENERAL) > 0).mean(), flush=True)
+    assert ((dg["flags"] & binding.DIAG_GENERAL) > 0).mean() <= 0.05
