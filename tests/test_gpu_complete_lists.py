@@ -143,3 +143,21 @@ def test_cuts_among_many_ties(dtype, V, values, hot_share):
             handed = (dg["flags"] & binding.DIAG_GENERAL) > 0
             # (a sampled list whose threshold is one of the tied values certifies none of them)
             assert V > 10_000 or not handed.any(), np.flatnonzero(handed)
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", 900), ("f32", 6000), ("bf16", 7000), ("f32", 40_960), ("f32", 128_256), ("bf16", 128_256), ("f32", 270_001)])
+@pytest.mark.parametrize("allowed,hot_share", [(1, 0.0), (50, 0.2), (700, 0.0)])
+@pytest.mark.parametrize("history", [False, True])
+def test_masks_of_the_types_lowest_value(dtype, V, allowed, hot_share, history):
+    """Columns masked with the lowest finite value instead of -inf: finite logits without mass, which a temperature below
+    one takes to -inf."""
+    rng = np.random.default_rng(V + allowed)
+    B = 26
+    lowest = np.float32(np.finfo(np.float32).min) if dtype == "f32" else synth.bf16_bits_to_f32(np.array([0xFF7F], np.uint16))[0]
+    z = np.full((B, V), lowest, np.float32)
+    pool = []
+    for b in range(B):
+        ids = rng.choice(V, allowed, replace=False)
+        z[b, ids] = rng.standard_normal(allowed) * 2.0
+        pool.append(ids)
+    _check(f"lowest-{allowed}", z, dtype, rng, history, hot_share, steps=(0,), id_pool=pool)

@@ -175,17 +175,22 @@ def test_hot_first_at_the_size_of_the_shvs_configuration():
 
 
 @pytest.mark.parametrize("dtype,H,n_tail", [("f32", 1024, 1), ("f32", 1024, 8191), ("f32", 9216, 8192), ("f32", 1024, 16_389),
-                                            ("bf16", 2048, 3), ("bf16", 2048, 16_384), ("bf16", 18_432, 16_385), ("bf16", 2048, 40_007)])
+                                            ("bf16", 2048, 3), ("bf16", 2048, 16_384), ("bf16", 18_432, 16_385), ("bf16", 2048, 40_007),
+                                            ("f32", 1024, 40_960), ("f32", 1024, 40_961), ("f32", 9216, 49_159), ("f32", 2048, 65_534),
+                                            ("bf16", 2048, 81_920), ("bf16", 2048, 81_921), ("bf16", 18_432, 98_311), ("bf16", 2048, 131_070)])
 def test_hot_first_row_ends_around_a_tile(dtype, H, n_tail):
     """Tails that end inside a 16-byte group, with one, exactly one tile, or one column more than a tile of
     2048 groups, and a hot set longer than the tile the kernel keeps in registers; rows whose draw is
-    rejected (a tail as heavy as the hot set) and rows whose draw is accepted."""
+    rejected (a tail as heavy as the hot set) and rows whose draw is accepted.  Tails of up to 128 KB are
+    summed by their row's workgroup, longer ones in tiles over the chip."""
     import torch
     rng = np.random.default_rng(n_tail)
     B, V = 24, H + n_tail
     stride = (V + 7) // 8 * 8
     z = rng.standard_normal((B, V)).astype(np.float32)
     z[::2, H:] += np.float32(np.log(max(H / n_tail, 1.0)) + 1.0)
+    if n_tail * (4 if dtype == "f32" else 2) > 128 << 10:  # (so long a tail outweighs the hot set by itself)
+        z[1::2, H:] -= np.float32(np.log(n_tail / H))
     bits = synth.f32_to_bf16_bits(z)
     if dtype == "bf16":
         z = synth.bf16_bits_to_f32(bits)
@@ -212,4 +217,39 @@ def test_hot_first_row_ends_around_a_tile(dtype, H, n_tail):
         assert not (dg["flags"] & binding.DIAG_GENERAL).any()
         accepted += int(((dg["flags"] & binding.DIAG_ACCEPTED) > 0).sum())
     assert 0 < accepted < 3 * B
+    s.close()
+
+
+@pytest.mark.parametrize("dtype,H,n_tail", [("f32", 1024, 20_003), ("f32", 1024, 60_003), ("bf16", 2048, 40_003), ("bf16", 2048, 120_005)])
+def test_a_nan_that_only_the_tail_holds(dtype, H, n_tail):
+    """The statistics know nothing of a NaN among the tail's columns: rows that draw from the tail report it, whichever
+    kernel reads the tail, rows that accept the hot draw never see it."""
+    import torch
+    rng = np.random.default_rng(n_tail)
+    B, V = 16, H + n_tail
+    stride = (V + 7) // 8 * 8
+    z = rng.standard_normal((B, stride)).astype(np.float32)
+    params = synth.make_params(B, temperature=1.0)
+    z = synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(z)) if dtype == "bf16" else z
+    ts = tail_stats(z[:, :V], params, H)
+    where = H + rng.integers(0, n_tail, B)
+    where[0], where[1] = V - 1, H
+    z[np.arange(B), where] = np.nan
+    lg = _dev(synth.f32_to_bf16_bits(z).view(np.int16) if dtype == "bf16" else z)
+    tsd, par = _dev(ts.view(np.uint8).reshape(B, 16)), _dev(params.view(np.uint8).reshape(B, 32))
+    s = binding.Sampler(V, 0, max_B=B)
+    seen = 0
+    for step in range(3):
+        out = torch.full((B,), -9, dtype=torch.int32, device="cuda:0")
+        diag = torch.zeros(B * 32, dtype=torch.uint8, device="cuda:0")
+        assert binding.simple_sample_hot_first(s.ctx, lg.data_ptr(), B, V, binding.SIMPLE_F32 if dtype == "f32" else binding.SIMPLE_BF16, stride,
+                                               par.data_ptr(), H, tsd.data_ptr(), 5, step, 0, out.data_ptr(), diag.data_ptr(),
+                                               torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        ids, dg = out.cpu().numpy(), diag.cpu().numpy().view(binding.ROW_DIAG_DTYPE)
+        accepted = (dg["flags"] & binding.DIAG_ACCEPTED) > 0
+        assert (ids[accepted] >= 0).all() and (ids[accepted] < H).all() and (ids[~accepted] == -1).all()
+        assert ((dg["flags"] & binding.DIAG_BAD_LOGIT) > 0).tolist() == (~accepted).tolist()
+        seen += int((~accepted).sum())
+    assert seen > 2 * B  # (the tail holds most of the mass)
     s.close()

@@ -2,9 +2,10 @@
 has served other shapes, with and without a diagnostics buffer.  The ids are a function of the
 inputs, the seed, the step and the row index alone (paper section 5.1, deterministic random
 numbers), so any difference between two calls is a race or a read of stale on-chip memory in a
-kernel; the workloads here send many rows through the multi-pass route of the general kernel (large
-top-k with penalties on rows that are not 16-byte aligned), through the sliced whole-vocabulary
-kernels and through the pattern-count kernel, the routes with the most hand-offs between waves."""
+kernel; the workloads here send many rows through the multi-pass route of the general kernel (wide
+nuclei and large top-k on vocabularies of 2^19 columns, which it serves alone), through the sliced
+whole-vocabulary kernels and through the pattern-count kernel, the routes with the most hand-offs
+between waves."""
 import numpy as np
 import pytest
 
@@ -76,3 +77,26 @@ def test_one_sampler_repeats_the_ids_across_routes():
             assert d.size == 0, (w.name, i, d[:10])
     s.close()
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", (1 << 19) + 3), ("bf16", 1 << 19)])
+def test_the_general_kernels_multi_pass_route_repeats_the_ids(dtype, V):
+    rng = np.random.default_rng(V)
+    B = 24
+    z = synth.zipf_profile_logits(B, V, 1.0, 1.5, rng, "f32", rng.permutation(V))
+    n = 500
+    w = synth.Workload("general", B, V, dtype, synth.f32_to_bf16_bits(z) if dtype == "bf16" else z,
+                       synth.make_params(B, temperature=1.0, top_k=np.resize([0, 20_000, 3000], B).astype(np.int32),
+                                         top_p=np.resize([0.97, 0.9, 1.0, 0.999], B).astype(np.float32), rep_penalty=1.1, freq_penalty=0.2, n_prompt=100),
+                       np.arange(B + 1, dtype=np.int64) * n, rng.integers(0, V, B * n).astype(np.int32))
+    other = M._random_workload(9)
+    ref = None
+    for rnd in range(12):
+        _ids(other, P.to_device(other), rnd % 2 == 0)
+        ids = _ids(w, P.to_device(w), rnd % 3 == 0)
+        ref = ids if ref is None else ref
+        assert np.array_equal(ids, ref), (rnd, np.flatnonzero(ids != ref)[:10])
+    rows = [0, 1, 2, 3]
+    _, dg = P.run_gpu(w, 0)
+    P.compare(ref, dg, P.run_oracle(w, 0, rows=rows), rows)
+    assert ((dg["flags"] & binding.DIAG_WIDE) > 0).sum() >= B // 2

@@ -179,3 +179,52 @@ def test_state_argument_errors_on_the_device_side():
     for s in (st, other):
         binding.simple_state_destroy(s)
     ctx.close(); small.close()
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", 900), ("f32", 3072), ("f32", 5000), ("f32", 8191), ("bf16", 700), ("bf16", 4500), ("bf16", 8192)])
+def test_short_vocabularies_on_a_state(dtype, V):
+    """Rows that are listed whole, at every workgroup size: the state's ids and p~ equal the stateless call's and the
+    oracle's over steps that append what was drawn."""
+    import torch
+    rng = np.random.default_rng(V)
+    B, L_max, steps = 12, 120, 6
+    z = (rng.standard_normal((B, V)) * 1.5).astype(np.float32)
+    bits = synth.f32_to_bf16_bits(z)
+    z = synth.bf16_bits_to_f32(bits) if dtype == "bf16" else z
+    lg = _dev(bits.view(np.int16)).view(torch.bfloat16) if dtype == "bf16" else _dev(z)
+    prompts = [rng.integers(0, V, int(n)).astype(np.int32) for n in rng.integers(1, 90, B)]
+    gen = [[] for _ in range(B)]
+    params = synth.make_params(B, temperature=np.resize([0.8, 1.0, 0.0, 1.2], B).astype(np.float32), top_k=np.resize([50, 0, 0, 700, 0, 3000], B).astype(np.int32),
+                               top_p=np.resize([0.9, 0.95, 1.0, 1.0], B).astype(np.float32), rep_penalty=np.resize([1.1, 0.9], B).astype(np.float32),
+                               freq_penalty=0.2, pres_penalty=0.1)
+    params["n_prompt"] = [p.size for p in prompts]
+    par = _dev(params.view(np.uint8).reshape(B, 32))
+    hot = np.sort(rng.choice(V, V // 4, replace=False)).astype(np.int32)
+    ctx = binding.Sampler(V, L_max, max_B=B)
+    st = binding.simple_state_create(0, B, V, L_max)
+    stream = torch.cuda.current_stream().cuda_stream
+    ptr, ids0 = _csr(prompts, gen)
+    p_d, i_d = _dev(ptr), _dev(ids0)
+    assert binding.simple_state_restart(st, 0, B, p_d.data_ptr(), i_d.data_ptr(), 0, stream) == 0
+    for step in range(steps):
+        use_hot = step % 2 == 1
+        hot_d = _dev(hot) if use_hot else None
+        out = torch.full((B,), -9, dtype=torch.int32, device="cuda:0")
+        diag, diag_c = (torch.zeros(B * 32, dtype=torch.uint8, device="cuda:0") for _ in range(2))
+        assert binding.simple_sample_state(ctx.ctx, st, 0, lg.data_ptr(), B, V, binding.SIMPLE_F32 if dtype == "f32" else binding.SIMPLE_BF16, V,
+                                           par.data_ptr(), hot_d.data_ptr() if use_hot else 0, hot.size if use_hot else 0, 7, step, 0,
+                                           out.data_ptr(), diag.data_ptr(), stream) == 0
+        ptr, ids = _csr(prompts, gen)
+        out_c = ctx.sample(lg, par, _dev(ptr), _dev(ids), hot_d, seed=7, step=step, diag=diag_c, V=V)
+        torch.cuda.synchronize()
+        dg, dg_c = (d.cpu().numpy().view(binding.ROW_DIAG_DTYPE) for d in (diag, diag_c))
+        got = out.cpu().numpy()
+        assert np.array_equal(got, out_c.cpu().numpy()) and np.array_equal(dg["p_chosen"], dg_c["p_chosen"])
+        assert np.array_equal(dg["flags"], dg_c["flags"]) and not (dg["flags"] & binding.DIAG_GENERAL).any()
+        P.compare(got, dg, O.sample(z, params, ptr, ids, hot if use_hot else None, 7, step), range(B))
+        assert binding.simple_state_append(st, 0, out.data_ptr(), B, stream) == 0
+        torch.cuda.synchronize()
+        for b in range(B):
+            gen[b].append(int(got[b]))
+    binding.simple_state_destroy(st)
+    ctx.close()
