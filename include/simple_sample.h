@@ -253,7 +253,7 @@ int simple_sample_hot_first(simple_ctx* ctx, const void* logits_dev, int64_t B, 
  * strides are equal.  A call without constraints never needs this pass; one with them pays one more
  * read and one write of its logits.  No context, nothing allocated; enqueued on hip_stream.
  * SIMPLE_EINVAL for NULL / negative / inconsistent arguments (offsets without their arrays, strides
- * below V, unknown dtype), SIMPLE_ECAPACITY if an allow-list's V-bit mask exceeds 96 KB of LDS.
+ * below V, unknown dtype), SIMPLE_ECAPACITY for allow-lists on more than 786,432 columns.
  */
 int simple_apply_logit_constraints(const void* logits_dev, int64_t B, int64_t V, int dtype, int64_t row_stride_elems,
                                    const int64_t* bias_ptr_dev, const int32_t* bias_ids_dev, const float* bias_vals_dev,

@@ -77,7 +77,7 @@ LdsLayout make_layout(int64_t V, int64_t max_nnz, bool with_history) {
 
 // The single-pass kernel needs rows that start at an element's boundary (`elem`), fewer than FAST_MAX_V
 // columns, 16-bit token counts and at least two tiles per wave.  (The limit was 2^18 columns: 128 bfloat16
-// rows of 262,144 took 1045 us in the general kernel, 139 us here.)  Its row state is sized so that four workgroups of
+// rows of 262,144 took 1047 us in the general kernel, 151 us here.)  Its row state is sized so that four workgroups of
 // 256 threads share a compute unit when the history tables allow it, else 512 threads are used.  A
 // batch with fewer rows than that many workgroups gets more threads per row (up to 1024: sixteen
 // waves, what a compute unit holds of this kernel), so that the compute units it reaches are full.
@@ -139,11 +139,10 @@ CtxLayout ctx_layout(int64_t max_V, int64_t max_nnz, int slots, int lds_limit, i
   L.pend = off;      off = align256(off + (2u + (size_t)slots) * 4u);
   L.order = off;     off = align256(off + (size_t)slots * 4u);  // the order in which the single-pass kernel takes a launch's rows
   L.wq = off;        off = align256(off + 64u + 64u * (size_t)slots);  // head, then one 64-byte record per slot
-  // a slot holds the fixed part and the largest history tables the single-pass kernel can have
-  // (where FAST_MAX_V columns and max_nnz ids outgrow the LDS, tables for fewer columns still fit)
-  FastLayout Fm{};
-  for (const int64_t lim : {(int64_t)FAST_MAX_V, (int64_t)1 << 18})
-    if (!Fm.total) Fm = make_fast_layout(max_V < lim ? max_V : lim - 1, SIMPLE_F32, max_nnz, max_nnz > 0, true, lds_limit, (int64_t)1 << 30, n_cu);
+  // a slot holds the fixed part and the largest history tables the single-pass kernel can have (they fit the LDS
+  // whenever the general kernel's, which simple_create asks for, do)
+  const FastLayout Fm = make_fast_layout(max_V < (int64_t)FAST_MAX_V ? max_V : (int64_t)FAST_MAX_V - 1, SIMPLE_F32, max_nnz, max_nnz > 0, true,
+                                         lds_limit, (int64_t)1 << 30, n_cu);
   const uint32_t tables = (max_nnz > 0 && Fm.total) ? Fm.cnt + (uint32_t)((max_nnz + 3) / 2) * 4u + 16u : 0u;
   L.ws_stride = (WIDE_SLOT_FIXED + tables + 255u) & ~255u;
   L.wws = off;       off = align256(off + (size_t)L.ws_stride * (size_t)slots);

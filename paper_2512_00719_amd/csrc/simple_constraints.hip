@@ -17,6 +17,7 @@ constexpr int CSL = 8192;      // columns per slice of a row, one workgroup each
 constexpr int CG = CSL / 4 / CT;  // 4-column groups per thread and slice, all of them in flight at once
 constexpr int AG = 4;          // allow-list ids in flight per thread
 constexpr int BCAP = 2048;     // bias ids of a row that are staged in LDS; a longer list is read from memory
+constexpr int64_t MAX_ALLOW_V = 96 * 1024 * 8;  // the boundary's limit for allow-lists (a V-bit mask of 96 KB once; the slices need none)
 constexpr int HEAD_BITS = 4;   // mask bits ahead of the slice's groups: the up to three columns before a row's first aligned group
 
 template <typename T> __device__ __forceinline__ float up(T v);
@@ -152,8 +153,7 @@ extern "C" int simple_apply_logit_constraints(const void* logits_dev, int64_t B,
   if (B == 0) return SIMPLE_OK;
   if (!logits_dev || !out_dev) return SIMPLE_EINVAL;
   if (B > (int64_t)0x7FFFFFFF) return SIMPLE_EINVAL;
-  const size_t lds = allow_ptr_dev ? (size_t)((V + 31) / 32) * 4u : 0u;  // the allow-list's mask
-  if (lds > (size_t)96 * 1024) return SIMPLE_ECAPACITY;
+  if (allow_ptr_dev && V > MAX_ALLOW_V) return SIMPLE_ECAPACITY;
   hipStream_t st = (hipStream_t)hip_stream;
   const int64_t n_sl = (V + CSL - 1) / CSL;  // (a row's slices start up to three columns in: the last one still covers its end)
   const dim3 grid((unsigned)B, (unsigned)(n_sl < 65535 ? n_sl : 65535));

@@ -42,7 +42,7 @@ __device__ __forceinline__ unsigned hot_bit(const uint32_t* __restrict__ hot_bit
 
 // Sixteen bytes of a row at any element's address: the same load instruction as at a 16-byte boundary, so
 // that rows of an odd vocabulary stored without padding take the same kernels (128 float32 rows of 50,001
-// columns: 336 us through the general kernel, 95 us here; aligned rows as before).
+// columns: 337 us through the general kernel, 93 us here; aligned rows as before).
 typedef f32x4 f32x4_any __attribute__((aligned(4)));
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
 typedef const __attribute__((address_space(1))) f32x4_any* GlobalF4;

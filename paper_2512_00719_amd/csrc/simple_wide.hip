@@ -19,9 +19,9 @@
 //             surely inside are summed by class (tail / hot) and the columns of the cut's bin are
 //             collected.
 //   finish    one workgroup per row checks that the cut does lie in the collected bin (else the
-//             general kernel takes the row), finds it exactly among those columns by a radix
-//             descent over (value, id) weighted by mass, however many of them tie (total order:
-//             value descending, id ascending), applies the SHVS acceptance test (section 5.3), walks
+//             general kernel takes the row), finds it exactly among those columns by buckets of equal
+//             width over (value, id), weighted by mass, spread again inside the bucket that holds it
+//             while many share that (total order: value descending, id ascending), applies the SHVS acceptance test (section 5.3), walks
 //             the per-tile masses of the drawn class in ascending id and reads one tile a last time
 //             to locate the drawn id (inverse CDF, step (3) of section 2.1).
 //
@@ -38,12 +38,12 @@
 // row to the general kernel).  Rows with a min-p cut use the first
 // kernel for the row maximum only (the cut is a value).  Rows with top-k alone run the same three
 // kernels by count instead of mass: a bin counts its columns, the cut's bin is the one in which
-// the count from the top reaches k, and the descent inside it weighs every column as one.
+// the count from the top reaches k, and the buckets inside it weigh every column as one.
 //
 // Penalties (section 2.2) are applied on the fly: the single-pass kernel leaves the row's history
 // tables (presence mask, rank directory, counts by rank) in the row's workspace slot, and a slice
-// loads its part of them into LDS.  All masses are
-// integers, so no result depends on the order of the additions.  A row for which a table overflows
+// loads its part of them into LDS.  All masses are integers (far untruncated rows: per slice, scaled and added
+// in a fixed order), so no result depends on the order of the additions.  A row for which a table overflows
 // or the passes disagree is handed to the general kernel.
 #include <type_traits>
 
