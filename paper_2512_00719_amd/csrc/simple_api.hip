@@ -101,7 +101,7 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
     F.claim = off; off = align16(off + (uint32_t)((max_nnz + 31) / 32) * 4u);
   }
   const uint32_t tables = NBF * 12u + MEMB2 * 16u;           // bucket tables of the long-list epilogue
-  uint32_t body = off < 28672u ? 28672u : off;               // >= 14 KB of sorted-epilogue arrays, >= 3072-entry list
+  uint32_t body = off < FAST_REGION_MIN ? FAST_REGION_MIN : off;
   if (whole && body < align16((uint32_t)V * 8u + tables)) body = align16((uint32_t)V * 8u + tables);
   F.threads = ((int64_t)body + 2048 <= (int64_t)lds_limit / 4) ? 256 : 512;  // four workgroups per compute unit, static LDS included
   if (V >= ((int64_t)1 << 18)) F.threads = 512;  // a sample of two tiles per wave: four waves' is too small a share of such rows
@@ -116,7 +116,7 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   // Room for as many long-list entries as the epilogue's registers hold, where the compute unit's LDS has it
   // at the occupancy chosen (a sample that admits a few hundred columns too many otherwise sends its row to
   // the general kernel: 1024 float32 rows of 128,256 columns 207 us, 260 with one such row).
-  const uint32_t roomy = F.threads == 256 ? 36864u : align16((uint32_t)(capf_per_thread(F.threads, whole) * F.threads) * 8u + tables);
+  const uint32_t roomy = F.threads == 256 ? FAST_REGION_MIN : align16((uint32_t)(capf_per_thread(F.threads, whole) * F.threads) * 8u + tables);
   if (!whole && body < roomy) body = roomy;
   F.long_cap = (body - tables) / 8u;
   F.samp = body;  // the sample merge area holds SPW keys per wave

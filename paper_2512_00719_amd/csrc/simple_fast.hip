@@ -124,13 +124,6 @@ __device__ __forceinline__ void stream_tile(const typename Io<DT>::Raw (&A)[UNR]
 constexpr unsigned SHORT_WAVE = 1u << 16;  // mark beside a wave's sample count: fewer finite columns than asked for
 enum { FIN_DONE = 0, FIN_PENDING = 1, FIN_WIDE = 2 };
 
-__device__ __forceinline__ u64 pick8(const u64 (&a)[8], int j) {
-  u64 v = 0ull;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) v = (i == j) ? a[i] : v;
-  return v;
-}
-
 // Mass of the top-k prefix when top-k is off: the whole row (list, uncertified entries, below g).
 __device__ __forceinline__ u64 whole_row_mass(u64 total_m, unsigned n_unc, uint32_t key_g, float y_max, float g, float tau,
                                               double S_below) {
@@ -139,129 +132,268 @@ __device__ __forceinline__ u64 whole_row_mass(u64 total_m, unsigned n_unc, uint3
   return total_m + (u64)n_unc * wfix(key_g, y_max) + (u64)__double2ull_rn(S_below * f0 * WSCALE);
 }
 
-// Survivors, masses and the draw for at most MEMB certified entries (the usual case).  The entries
-// arrive as composites in mc[0, n); they are ranked by counting, laid out in sorted order and one
-// wave takes every decision of Eq. (2) on that order; then all threads locate the drawn id.
+// ---- the certified entries in the total order ----
+// What follows needs them sorted (value descending, id ascending), and only as many as the survivors can be: with
+// top-k the first k.  Short lists are ranked by counting, longer ones go to buckets linear in the tempered value and are
+// ranked among their bucket's members; no place depends on the order in which the waves appended.  A sorted entry is its
+// weight and its id in one word.  Bound: the latency of LDS and barriers, so their number is what was cut down: with the
+// longer lists in bucket tables of masses and counts and the others' decisions on eight entries per lane, 4 float32 rows of
+// 1024 columns (top-k 50, top-p) took 22.8 us a call, 17.3 so; 4096 bfloat16 rows of 256,000 1011 and 973.
+constexpr int COUNT_MAX = 128;   // entries ranked by counting (several threads share an entry's comparisons)
+constexpr int SORT_BITS = 10, SORT_NB = 1 << SORT_BITS;  // buckets
+constexpr int SORT_MAX = 2048;   // entries that are sorted
+constexpr int SORT_CROWD = 512;  // members of a bucket that are ranked by counting; a list with more (ties) is left to finalize_long
+constexpr float MASS_SPAN = 44.0f;  // this far below the maximum an entry has no mass (exp_fix): its place does not matter
+constexpr uint32_t SORT_OUT = SORT_MAX * 8, SORT_BASE = 2 * SORT_MAX * 8, SORT_END = SORT_BASE + SORT_NB * 4;  // offsets in the shared region
+static_assert(SORT_END <= FAST_REGION_MIN, "the epilogue's arrays fit the smallest region");
+static_assert(COUNT_MAX <= SORT_MAX && NBF * 16 + MEMB2 * 12 <= SORT_MAX * 8, "and so do those that take the unsorted entries' place");
+constexpr int ID_BITS = 19;
+static_assert(FAST_MAX_V <= (1 << ID_BITS) && 44 + 1 + ID_BITS <= 64, "a weight of up to 2^44 and an id in one word");
+__device__ __forceinline__ u64 pack_entry(u64 c, float y_max) {  // from the composite of a key and an id
+  return (wfix((uint32_t)(c >> 32), y_max) << ID_BITS) | (u64)(0xFFFFFFFFu - (uint32_t)c);
+}
+__device__ __forceinline__ u64 entry_mass(u64 e) { return e >> ID_BITS; }
+__device__ __forceinline__ uint32_t entry_id(u64 e) { return (uint32_t)e & ((1u << ID_BITS) - 1u); }
+
+// n composites at the start of the region to sorted entries at SORT_OUT: an entry's place is the number of entries before
+// it, counted by 16, 4 or 2 neighbouring lanes.  S.memb counts those at or above key_thr.
 template <int NTHR>
-__device__ __forceinline__ int finalize_small(FS& S, const RowCfg& R, unsigned n, unsigned n_unc, uint32_t kmax, uint32_t key_g,
-                                              float g, double S_below, const u64* mc, u64* sc, u64* sw, uint32_t* sid,
-                                              const uint32_t* __restrict__ hot_bits, simple_row_diag& dg) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const float y_max = keyf(kmax);
-  for (unsigned t = tid; t < n; t += NTHR) {
-    const u64 c = mc[t];
-    const unsigned r = count_greater(mc, n, c);
-    sc[r] = c;
-    sw[r] = R.greedy ? 0ull : wfix((uint32_t)(c >> 32), y_max);
+__device__ __forceinline__ void sort_by_counting(FS& S, unsigned n, float y_max, uint32_t key_thr, unsigned char* region) {
+  static_assert(2 * COUNT_MAX <= NTHR, "two threads per entry at least");
+  const u64* mc = reinterpret_cast<const u64*>(region);
+  const unsigned tid = threadIdx.x;
+  const unsigned sh = n * 16u <= (unsigned)NTHR ? 4u : n * 4u <= (unsigned)NTHR ? 2u : 1u, P = 1u << sh;
+  if ((tid & ~63u) >> sh >= n) return;  // (whole waves)
+  const unsigned e = tid >> sh;
+  const u64 c = e < n ? mc[e] : 0ull;
+  unsigned r = 0u;
+#pragma unroll 4
+  for (unsigned q = tid & (P - 1u); q < n; q += P) r += mc[q] > c ? 1u : 0u;
+  r += dpp_move<DPP_XOR1, 0xF>(0u, r);
+  if (sh > 1u) r += dpp_move<DPP_XOR2, 0xF>(0u, r);
+  if (sh > 2u) { r += dpp_move<DPP_HALF_MIRROR, 0xF>(0u, r); r += dpp_move<DPP_MIRROR, 0xF>(0u, r); }
+  const bool first = e < n && (tid & (P - 1u)) == 0u;
+  const u64 m = __ballot(first && (uint32_t)(c >> 32) >= key_thr);
+  if (lane_id() == 0 && m) atomicAdd(&S.memb, (unsigned)__popcll(m));
+  if (first) reinterpret_cast<u64*>(region + SORT_OUT)[r] = pack_entry(c, y_max);
+}
+
+// The same from this thread's entries (key 0: none; S.memb is n_all, the number of all threads'); with top-k only the
+// buckets down to the one that holds the k-th.  Returns the number of sorted entries, or 0 if they are too many or
+// too crowded.  The counters at SORT_BASE are zero.  Barriers inside.
+template <int NTHR, int PER>
+__device__ __forceinline__ unsigned sort_by_buckets(FS& S, const RowCfg& R, const uint32_t (&key)[PER], const uint32_t (&eid)[PER], unsigned n_all,
+                                                    float y_max, uint32_t key_lo, uint32_t key_thr, unsigned char* region) {
+  constexpr int NWV = NTHR / 64, BPT = SORT_NB / NTHR;
+  const int tid = threadIdx.x;
+  u64* sc = reinterpret_cast<u64*>(region);
+  uint32_t* base = reinterpret_cast<uint32_t*>(region + SORT_BASE);
+  const float span = y_max - keyf(key_lo);
+  const bool zero_tail = span > MASS_SPAN;  // the last bucket holds all entries without mass
+  const float scale = (float)(zero_tail ? SORT_NB - 1 : SORT_NB) / fmaxf(zero_tail ? MASS_SPAN : span, 1e-30f);
+  auto bucket_of = [&](uint32_t k) { return (int)fminf((y_max - keyf(k)) * scale, (float)(SORT_NB - 1)); };
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    if (key[j]) atomicAdd(&base[bucket_of(key[j])], 1u);
+    __builtin_amdgcn_sched_barrier(0);
   }
   __syncthreads();
-  if (wave == 0) {
-    int rc = FIN_DONE;
-    if (R.greedy) {
-      if (lane == 0) { S.out_id = (int)(0xFFFFFFFFu - (uint32_t)sc[0]); S.out_w = 0ull; S.e_n = 1u; S.e_SK = 1ull; S.e_skfix = 0ull; S.e_SH = 0ull; S.e_acc = 0; }
-    } else {
-      u64 wl[8], cum[8];
-      uint32_t kl[8], il[8];
-      u64 loc = 0ull;
+  unsigned c[BPT], loc = 0u;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const unsigned r = (unsigned)lane * 8u + (unsigned)j;
-        const u64 c = (r < n) ? sc[r] : 0ull;
-        wl[j] = (r < n) ? sw[r] : 0ull;
-        kl[j] = (uint32_t)(c >> 32); il[j] = 0xFFFFFFFFu - (uint32_t)c;
-        loc += wl[j];
-      }
-      const u64 incl = wave_incl_scan(loc);
-      const u64 total_m = read_lane(incl, 63);
-      u64 run = incl - loc;
+  for (int j = 0; j < BPT; ++j) { c[j] = base[tid * BPT + j]; loc += c[j]; }
+  const unsigned incl = wave_incl_scan(loc);
+  if (lane_id() == 63) S.r32a[wave_id()] = incl;
+  __syncthreads();
+  unsigned run = incl - loc;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) { run += wl[j]; cum[j] = run; }
-      const unsigned n_k = R.k_on ? (unsigned)R.top_k : n;  // n >= top_k was checked by the caller
-      const u64 S_klist = __shfl(pick8(cum, (int)((n_k - 1u) & 7u)), (int)((n_k - 1u) >> 3), 64);
-      const u64 S_k_fix = R.k_on ? S_klist : whole_row_mass(total_m, n_unc, key_g, y_max, g, R.tau, S_below);
-      u64 target = 0ull;
-      bool p_found = false;
-      if (R.p_le0) p_found = true;
-      else if (R.p_on) {
-        target = (u64)__double2ull_ru((double)R.top_p * (double)S_k_fix);
-        if (target == 0ull) target = 1ull;
-        p_found = S_klist >= target;
-      }
-      uint32_t key_thr = 0u;
-      bool m_cert = false;
-      if (R.minp_on) {
-        const float thr = y_max + (float)log((double)R.min_p);
-        key_thr = fkey(thr);
-        m_cert = key_thr > key_g;
-      }
-      const bool known = R.k_on || p_found || m_cert || R.all;
-      if (!known) rc = (R.need_sum || (!R.k_on && !R.p_on && R.minp_on)) ? FIN_WIDE : FIN_PENDING;
-      // every cut is a prefix of the sorted order; the first entry always survives
-      const bool use_hot = hot_bits != nullptr;
-      unsigned okm = 0u, hotm = 0u;
-      unsigned cl = 0; u64 ml = 0ull, hl = 0ull;
+  for (int w = 0; w < NWV; ++w) { const unsigned x = S.r32a[w]; if (w < wave_id()) run += x; }
+  const unsigned want = R.k_on ? (unsigned)R.top_k : n_all;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const unsigned r = (unsigned)lane * 8u + (unsigned)j;
-        bool o = r < n_k;
-        if (R.p_le0) o = o && (r == 0u);
-        else if (R.p_on && p_found) o = o && (cum[j] - wl[j] < target);
-        if (m_cert) o = o && (kl[j] >= key_thr);
-        o = (o || r == 0u) && (r < n);
-        if (o) {
-          okm |= 1u << j; ++cl; ml += wl[j];
-          if (use_hot && hot_bit(hot_bits, il[j])) { hotm |= 1u << j; hl += wl[j]; }
-        }
-      }
-      const unsigned ns = wave_sum(cl);
-      const u64 S_K = wave_sum(ml);
-      const u64 S_H = use_hot ? wave_sum(hl) : 0ull;
-      bool pick_hot = false;
-      if (use_hot) pick_hot = (S_H > 0ull) && (R.u_acc * (double)S_K <= (double)S_H);
-      const u64 S_cls = use_hot ? (pick_hot ? S_H : S_K - S_H) : S_K;
-      const double u = use_hot ? (pick_hot ? R.u_draw : R.u_tail) : R.u_draw;
-      if (rc == FIN_DONE && S_cls == 0ull) rc = FIN_PENDING;  // the chosen class holds no mass here: general kernel
-      u64 tfix = (u64)__double2ull_rd(u * (double)S_cls);
-      if (S_cls > 0ull && tfix >= S_cls) tfix = S_cls - 1ull;
+  for (int j = 0; j < BPT; ++j) {
+    const int b = tid * BPT + j;
+    base[b] = run;
+    if (run < want && c[j] > (unsigned)SORT_CROWD && !(zero_tail && b == SORT_NB - 1)) S.bp = 0;
+    if (run < want && want <= run + c[j]) { S.e_n = run + c[j]; S.bk = b; }
+    run += c[j];
+  }
+  __syncthreads();
+  const unsigned n_sort = S.e_n;
+  const int last = S.bk;
+  if (S.bp == 0 || n_sort > (unsigned)SORT_MAX) return 0u;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const unsigned r = (unsigned)lane * 8u + (unsigned)j;
-        const bool in_cls = ((okm >> j) & 1u) && (!use_hot || (((hotm >> j) & 1u) != 0u) == pick_hot);
-        if (r < n) sid[r] = in_cls ? il[j] : 0xFFFFFFFFu;
-      }
-      if (lane == 0) { S.e_n = ns; S.e_SK = S_K; S.e_SH = S_H; S.e_tfix = tfix; S.e_skfix = S_k_fix; S.e_acc = pick_hot ? 1 : 0; }
+  for (int j = 0; j < PER; ++j) {
+    if (key[j]) {
+      const int b = bucket_of(key[j]);
+      if (b <= last) sc[atomicAdd(&base[b], 1u)] = composite(key[j], eid[j]);
     }
-    if (lane == 0) S.e_rc = rc;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();  // base[b] is the end of bucket b now
+  unsigned above = 0u;
+#pragma unroll 1
+  for (unsigned i = tid; i < n_sort; i += NTHR) {
+    const u64 e = sc[i];
+    const int b = bucket_of((uint32_t)(e >> 32));
+    unsigned r = i;
+    if (!(zero_tail && b == SORT_NB - 1)) {
+      const unsigned from = b ? base[b - 1] : 0u, to = base[b];
+      r = from;
+      for (unsigned q = from; q < to; ++q) r += sc[q] > e ? 1u : 0u;
+    }
+    above += (uint32_t)(e >> 32) >= key_thr ? 1u : 0u;
+    reinterpret_cast<u64*>(region + SORT_OUT)[r] = pack_entry(e, y_max);
+  }
+  above = wave_sum(above);
+  if (lane_id() == 0 && above) atomicAdd(&S.memb, above);
+  return n_sort;
+}
+
+// Where the sorted prefix ends (section 2.1): what both deciding functions below share.  total_m: the mass of the list,
+// with top-k of its first k entries.
+struct Cuts { u64 S_k_fix, target; bool p_found, known; };
+__device__ __forceinline__ Cuts list_cuts(const RowCfg& R, u64 total_m, unsigned n_unc, uint32_t key_g, float y_max, float g, double S_below, bool m_cert) {
+  Cuts c;
+  c.S_k_fix = R.k_on ? total_m : whole_row_mass(total_m, n_unc, key_g, y_max, g, R.tau, S_below);
+  c.target = 0ull;
+  c.p_found = R.p_le0;
+  if (!R.p_le0 && R.p_on) {
+    c.target = (u64)__double2ull_ru((double)R.top_p * (double)c.S_k_fix);
+    if (c.target == 0ull) c.target = 1ull;
+    c.p_found = total_m >= c.target;
+  }
+  c.known = R.k_on || c.p_found || m_cert || R.all;
+  return c;
+}
+// A cut below the list's reach: the sliced kernels find it, or the general kernel.
+__device__ __forceinline__ int beyond_list(const RowCfg& R) {
+  return (R.need_sum || (!R.k_on && !R.p_on && R.minp_on)) ? FIN_WIDE : FIN_PENDING;
+}
+// What the sorted entries are decided from: their number and that of the listed columns that are not certified, the
+// row maximum, the threshold, the mass below it, and with a min-p bound above the threshold (m_cert) the entries at or above it.
+struct Listed { unsigned n, n_unc; float y_max; uint32_t key_g; float g; double S_below; bool m_cert; unsigned n_minp; };
+
+// Survivors, masses and the draw (Eq. (2), step (3)) from n <= 64 sorted entries: one per lane of one wave, no
+// barrier and no LDS on the way.  The other waves wait.
+__device__ __forceinline__ void decide_wave(FS& S, const RowCfg& R, const Listed& L, const u64* entries, const uint32_t* __restrict__ hot_bits) {
+  const unsigned lane = lane_id(), n = L.n;
+  const bool in = lane < n;
+  const u64 e = in ? entries[lane] : 0ull;
+  const uint32_t id = entry_id(e);
+  const bool use_hot = hot_bits != nullptr;
+  const bool hot = use_hot && in && hot_bit(hot_bits, id);
+  const u64 w = entry_mass(e);
+  const u64 cum = wave_incl_scan(w);
+  const Cuts cut = list_cuts(R, read_lane(cum, 63), L.n_unc, L.key_g, L.y_max, L.g, L.S_below, L.m_cert);
+  int rc = cut.known ? FIN_DONE : beyond_list(R);
+  bool o = in;  // (every cut ends a prefix of the order; the first entry always survives)
+  if (R.p_le0) o = lane == 0u;
+  else if (R.p_on && cut.p_found) o = o && (cum - w < cut.target);
+  if (L.m_cert) o = o && lane < L.n_minp;
+  o = o || lane == 0u;
+  const unsigned ns = (unsigned)__popcll(__ballot(o));
+  const u64 S_K = read_lane(cum, (int)ns - 1);
+  const u64 S_H = use_hot ? wave_sum(o && hot ? w : 0ull) : 0ull;
+  bool pick_hot = false;
+  if (use_hot) pick_hot = (S_H > 0ull) && (S.u[1] * (double)S_K <= (double)S_H);
+  const u64 S_cls = use_hot ? (pick_hot ? S_H : S_K - S_H) : S_K;
+  const double u = S.u[use_hot && !pick_hot ? 2 : 0];
+  if (rc == FIN_DONE && S_cls == 0ull) rc = FIN_PENDING;  // the chosen class holds no mass here: general kernel
+  u64 tfix = (u64)__double2ull_rd(u * (double)S_cls);
+  if (S_cls > 0ull && tfix >= S_cls) tfix = S_cls - 1ull;
+  // inverse CDF in ascending token id over the survivors of the chosen class: the lanes in the order of their ids
+  const u64 m = (o && (!use_hot || hot == pick_hot)) ? w : 0ull;
+  unsigned r = in ? 0u : lane;
+#pragma unroll 4
+  for (unsigned q = 0; q < n; ++q) r += (in && read_lane(id, (int)q) < id) ? 1u : 0u;
+  const int to = (int)(r * 4u);
+  const u64 m2 = ((u64)(uint32_t)__builtin_amdgcn_ds_permute(to, (int)(uint32_t)(m >> 32)) << 32) | (u64)(uint32_t)__builtin_amdgcn_ds_permute(to, (int)(uint32_t)m);
+  const uint32_t id2 = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)id);
+  const u64 run = wave_incl_scan(m2);
+  if (lane == 0u) { S.e_rc = rc; S.e_n = ns; S.e_SK = S_K; S.e_SH = S_H; S.e_skfix = cut.S_k_fix; S.e_acc = pick_hot ? 1 : 0; }
+  if (rc == FIN_DONE && run > tfix && run - m2 <= tfix) { S.out_id = (int)id2; S.out_w = m2; }
+}
+
+// The same for up to SORT_MAX entries, a thread's lie side by side.  Barriers inside.
+template <int NTHR>
+__device__ __forceinline__ void decide_block(FS& S, const RowCfg& R, const Listed& L, unsigned char* region, const uint32_t* __restrict__ hot_bits) {
+  constexpr int NWV = NTHR / 64;
+  const int tid = threadIdx.x;
+  const u64* entries = reinterpret_cast<const u64*>(region + SORT_OUT);
+  u64* fmass = reinterpret_cast<u64*>(region);  // masses of the survivors by ranges of ids, all and the hot ones
+  u64* hmass = fmass + NBF;
+  u64* mw = hmass + NBF;  // members of the range that holds the draw
+  uint32_t* mid = reinterpret_cast<uint32_t*>(mw + MEMB2);
+  const bool use_hot = hot_bits != nullptr;
+  const unsigned per = (L.n + NTHR - 1u) / NTHR, p0 = min((unsigned)tid * per, L.n), p1 = min(p0 + per, L.n);
+  for (int i = tid; i < NBF; i += NTHR) { fmass[i] = 0ull; hmass[i] = 0ull; }
+  if (tid == 0) { S.bp = -1; S.bd = -1; }
+  u64 loc = 0ull;
+  for (unsigned r = p0; r < p1; ++r) loc += entry_mass(entries[r]);
+  unsigned z0, z1; u64 me, total_m;
+  blk_excl_scan2<NWV>(S, 0u, loc, z0, me, z1, total_m);
+  const Cuts cut = list_cuts(R, total_m, L.n_unc, L.key_g, L.y_max, L.g, L.S_below, L.m_cert);
+  const bool by_p = R.p_on && cut.p_found && !R.p_le0;
+  if (tid == 0) S.memb = 0u;
+  if (by_p) {
+    u64 run = me;
+    for (unsigned r = p0; r < p1; ++r) {
+      const u64 w = entry_mass(entries[r]);
+      if (run < cut.target && run + w >= cut.target) S.bp = (int)r + 1;
+      run += w;
+    }
+    __syncthreads();
+  }
+  unsigned ns = R.p_le0 ? 1u : by_p ? (unsigned)S.bp : L.n;
+  if (L.m_cert) ns = min(ns, L.n_minp);
+  ns = max(ns, 1u);
+  const int ishift = max(0, 32 - (int)__clz((unsigned)(R.V - 1) | 1u) - NBF_BITS);
+  for (unsigned r = p0; r < min(p1, ns); ++r) {
+    const u64 e = entries[r];
+    atomicAdd(&fmass[entry_id(e) >> ishift], entry_mass(e));
+    if (use_hot && hot_bit(hot_bits, entry_id(e))) atomicAdd(&hmass[entry_id(e) >> ishift], entry_mass(e));
   }
   __syncthreads();
-  if (S.e_rc != FIN_DONE) return S.e_rc;
-  dg.n_survivors = (int)S.e_n;
-  if (R.greedy) { dg.p_chosen = 1.0f; return FIN_DONE; }
-  dg.s_k = (double)S.e_skfix / WSCALE;
-  if (hot_bits != nullptr) {
-    dg.alpha = (double)S.e_SH / (double)S.e_SK;
-    dg.flags |= SIMPLE_DIAG_SHVS | (S.e_acc ? SIMPLE_DIAG_ACCEPTED : 0u);
+  const u64 fm = (tid < NBF) ? fmass[tid] : 0ull, hm = (use_hot && tid < NBF) ? hmass[tid] : 0ull;
+  u64 ea, eh = 0ull, S_K, S_H = 0ull;
+  blk_excl_scan2<NWV>(S, 0u, fm, z0, ea, z1, S_K);
+  if (use_hot) blk_excl_scan2<NWV>(S, 0u, hm, z0, eh, z1, S_H);
+  bool pick_hot = false;
+  if (use_hot) pick_hot = (S_H > 0ull) && (S.u[1] * (double)S_K <= (double)S_H);
+  const u64 S_cls = use_hot ? (pick_hot ? S_H : S_K - S_H) : S_K;
+  const double u = S.u[use_hot && !pick_hot ? 2 : 0];
+  int rc = cut.known ? FIN_DONE : beyond_list(R);
+  if (rc == FIN_DONE && S_cls == 0ull) rc = FIN_PENDING;  // the chosen class holds no mass here: general kernel
+  u64 tfix = (u64)__double2ull_rd(u * (double)S_cls);
+  if (S_cls > 0ull && tfix >= S_cls) tfix = S_cls - 1ull;
+  {
+    const u64 m2 = pick_hot ? hm : fm - hm, me2 = pick_hot ? eh : ea - eh;
+    if (m2 > 0ull && me2 <= tfix && me2 + m2 > tfix) { S.bd = tid; S.mab_d = me2; }
   }
-  // inverse CDF in ascending token id over the survivors of the chosen class (they lie in [0, e_n))
-  const unsigned n_s = S.e_n;
-  const u64 tfix = S.e_tfix;
-  for (unsigned t = tid; t < n_s; t += NTHR) {
-    const uint32_t my = sid[t];
-    if (my == 0xFFFFFFFFu) continue;
+  __syncthreads();
+  const int bd = S.bd;
+  for (unsigned r = p0; r < min(p1, ns); ++r) {
+    const u64 e = entries[r];
+    if ((int)(entry_id(e) >> ishift) != bd || entry_mass(e) == 0ull) continue;
+    if (use_hot && (hot_bit(hot_bits, entry_id(e)) != 0u) != pick_hot) continue;
+    const unsigned slot = atomicAdd(&S.memb, 1u);
+    if (slot < (unsigned)MEMB2) { mid[slot] = entry_id(e); mw[slot] = entry_mass(e); }
+  }
+  __syncthreads();
+  const unsigned nm = S.memb;
+  if (nm > (unsigned)MEMB2) rc = FIN_PENDING;  // (a range of ids with hundreds of survivors: the general kernel)
+  else if ((unsigned)tid < nm && rc == FIN_DONE) {
     unsigned dummy;
-    const u64 C = sum_where<false>(sid, sw, n_s, my, dummy);
-    if (C > tfix && C - sw[t] <= tfix) { S.out_id = (int)my; S.out_w = sw[t]; }
+    const u64 G = S.mab_d + sum_where<false>(mid, mw, nm, mid[tid], dummy);
+    if (G > tfix && G - mw[tid] <= tfix) { S.out_id = (int)mid[tid]; S.out_w = mw[tid]; }
   }
-  __syncthreads();
-  dg.p_chosen = (float)((double)S.out_w / (double)S.e_SK);
-  return (S.out_id >= 0) ? FIN_DONE : FIN_PENDING;
+  if (tid == 0) { S.e_rc = rc; S.e_n = ns; S.e_SK = S_K; S.e_SH = S_H; S.e_skfix = cut.S_k_fix; S.e_acc = pick_hot ? 1 : 0; }
 }
 
 constexpr float MAX_SPAN = 64.0f;  // a complete list may reach further down: what lies there has no mass and shares the last bucket
 
-// Long lists (more than MEMB certified entries, in LDS as keys lk[] / ids li[]): bucket tables over
-// the key range locate each cut; only the bucket that holds a cut is resolved entry by entry.
-// Same decisions as finalize_small.  SPREAD (rows listed whole): a bucket with more members than are resolved
+// Lists that are not sorted (more than SORT_MAX entries that may survive, or crowded by ties; in LDS as keys lk[] /
+// ids li[]): bucket tables over the key range locate each cut; only the bucket that holds a cut is resolved entry by entry.
+// Same decisions as above.  SPREAD (rows listed whole): a bucket with more members than are resolved
 // at once is spread again; a sampled list leaves its row to the kernels that follow.
 template <int NTHR, bool SPREAD>
 __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n, unsigned n_unc, uint32_t kmax,
@@ -284,12 +416,6 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
   for (unsigned i = tid; i < n; i += NTHR) { const u64 c = composite(lk[i], li[i]); cl = (c > cl) ? c : cl; }
   unsigned da = 0, db = 0; u64 cmax = cl, dd = 0ull;
   blk_reduce<NWV>(S, da, db, cmax, dd);
-  if (R.greedy) {  // the first of the total order
-    if (tid == 0) S.out_id = (int)(0xFFFFFFFFu - (uint32_t)cmax);
-    __syncthreads();
-    dg.n_survivors = 1; dg.p_chosen = 1.0f;
-    return FIN_DONE;
-  }
   constexpr u64 MANY = ~0ull;
   // Among the entries that `in` selects, in descending order of their (distinct) values: the one at which the
   // running mass (or count), `acc` before the first, reaches the target (its value; 0 if none does).  Up to MEMB2 of
@@ -459,13 +585,12 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
   if (use_hot) { unsigned c2, ct2; blk_excl_scan2<NWV>(S, 0u, (tid < NBF) ? hmass[tid] : 0ull, c2, eh, ct2, S_H); }
   bool pick_hot = false;
   if (use_hot) {
-    pick_hot = (S_H > 0ull) && (R.u_acc * (double)S_K <= (double)S_H);
+    pick_hot = (S_H > 0ull) && (S.u[1] * (double)S_K <= (double)S_H);
     dg.alpha = (double)S_H / (double)S_K;
     dg.flags |= SIMPLE_DIAG_SHVS | (pick_hot ? SIMPLE_DIAG_ACCEPTED : 0u);
   }
   const u64 S_cls = use_hot ? (pick_hot ? S_H : S_K - S_H) : S_K;
-  const double u_first = R.u_draw, u_rest = R.u_tail;  // (by value: a choice between R's fields put all of R in memory)
-  const double u = (use_hot && !pick_hot) ? u_rest : u_first;
+  const double u = S.u[use_hot && !pick_hot ? 2 : 0];
   dg.n_survivors = (int)n_surv;
   dg.s_k = (double)S_k_fix / WSCALE;
   if (S_cls == 0ull) { return FIN_PENDING; }  // the chosen class holds no mass here: general kernel
@@ -617,10 +742,10 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     int ids[IDR];
 #pragma unroll
     for (int j = 0; j < IDR; ++j) { const int i = tid + j * NTHR; ids[j] = (!whole && h_active && !stateful && i < nnz) ? hist[i] : -1; }
-    {
+    if (wave == NWV - 1) {  // (one wave of the row, for all)
       double u[3];
       row_uniforms(a.seed, a.row_offset + (uint64_t)row, a.step, u);
-      R.u_draw = u[0]; R.u_acc = u[1]; R.u_tail = u[2];
+      if (lane < 3) S.u[lane] = lane == 0 ? u[0] : lane == 1 ? u[1] : u[2];
     }
     __syncthreads();
     // ---- presence mask of the history (in the shared region); all tables for a row that leaves early ----
@@ -966,12 +1091,14 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     // for rows listed whole 40 to 150 spilled registers (4 rows of 1024 columns 27.7 us, 22.4 so).
 #pragma unroll
     for (int j = 0; j < PER; ++j) asm volatile("" : "+v"(key[j]), "+v"(eid[j]));
-    if (kloc) atomicMax(&S.kmax, kloc);
+    kloc = wave_max_u32(kloc);  // (one atomic per wave)
+    if (kloc && lane == 0) atomicMax(&S.kmax, kloc);
     if (complete) {
       uint32_t kmin = 0xFFFFFFFFu;
 #pragma unroll
       for (int j = 0; j < PER; ++j) if (key[j] > key_g) kmin = min(kmin, key[j]);
-      if (kmin != 0xFFFFFFFFu) atomicMin(&S.kmin, kmin);
+      kmin = wave_min_u32(kmin);
+      if (kmin != 0xFFFFFFFFu && lane == 0) atomicMin(&S.kmin, kmin);
     }
     if (err) atomicOr(&S.flags, SIMPLE_DIAG_ERROR | SIMPLE_DIAG_BAD_LOGIT);
     if (peaked) atomicOr(&S.flags, 1u << 30);
@@ -996,42 +1123,87 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       rc = FIN_WIDE;
       tables_live = true;
     } else {
-      // certified entries (tempered value strictly above fl(g / tau)) as composites
-      u64* mc = reinterpret_cast<u64*>(lds);                       // MEMB * 8
-      u64* sc = mc + MEMB;
-      u64* sw = sc + MEMB;
-      uint32_t* sid = reinterpret_cast<uint32_t*>(sw + MEMB);      // ends at 14 KB
+      // certified entries: tempered value strictly above fl(g / tau).  One reservation per wave and round (a wave's
+      // 64 additions to one word take their turns).  A short list goes to LDS here.
+      u64* mc = reinterpret_cast<u64*>(lds);
+      {
+        uint32_t* base = reinterpret_cast<uint32_t*>(lds + SORT_BASE);
+        for (int i = tid; i < SORT_NB; i += NTHR) base[i] = 0u;
+      }
       unsigned nul = 0;
 #pragma unroll
       for (int j = 0; j < PER; ++j) {
-        if (!key[j]) continue;
-        if (key[j] > key_g) {
-          const unsigned slot = atomicAdd(&S.n2, 1u);
-          if (slot < (unsigned)MEMB) mc[slot] = composite(key[j], eid[j]);
-        } else { ++nul; key[j] = 0u; }
+        if ((unsigned)(j * NTHR) >= n) break;
+        const bool cert = key[j] > key_g;
+        const u64 m = __ballot(cert);
+        nul += (unsigned)__popcll(__ballot(key[j] != 0u)) - (unsigned)__popcll(m);
+        if (m == 0ull) { key[j] = 0u; continue; }
+        unsigned slot = 0u;
+        if (lane == 0) slot = atomicAdd(&S.n2, (unsigned)__popcll(m));
+        slot = (unsigned)__builtin_amdgcn_readfirstlane((int)slot) + lanes_before(m);
+        if (cert && slot < (unsigned)COUNT_MAX) mc[slot] = composite(key[j], eid[j]);
+        if (!cert) key[j] = 0u;
       }
-      if (nul) atomicAdd(&S.nunc, nul);
+      if (nul && lane == 0) atomicAdd(&S.nunc, nul);
       __syncthreads();
       const unsigned n_cert = S.n2, n_unc = S.nunc;
       const int k_asked = R.top_k;  // a complete list shorter than k: the rest of the prefix has no mass
       if (complete && R.k_on) R.top_k = min(R.top_k, (int)n_cert);
       if (R.k_on && !R.greedy && n_cert < (unsigned)R.top_k) rc = FIN_PENDING;  // the sampled threshold admitted too few
-      else if (n_cert <= (unsigned)MEMB) {
-        rc = finalize_small<NTHR>(S, R, n_cert, n_unc, kmax, key_g, C.g, S_below, mc, sc, sw, sid, hot_bits, dg);
-      } else if (n_cert <= (unsigned)a.F.long_cap) {
-        // long list: keys and ids go back to the region, the bucket tables behind them
-        const unsigned lcap = (unsigned)a.F.long_cap;
-        uint32_t* lk = reinterpret_cast<uint32_t*>(lds);
-        uint32_t* lid = lk + lcap;
-        __syncthreads();
-        if (tid == 0) S.n2 = 0u;
-        __syncthreads();
+      else if (R.greedy) {  // the first of the total order
+        u64 cmax = 0ull, zero = 0ull;
+        unsigned z0 = 0u, z1 = 0u;
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-          if (key[j]) { const unsigned slot = atomicAdd(&S.n2, 1u); lk[slot] = key[j]; lid[slot] = eid[j]; }
+        for (int j = 0; j < PER; ++j) { const u64 c = key[j] ? composite(key[j], eid[j]) : 0ull; cmax = c > cmax ? c : cmax; }
+        blk_reduce<NWV>(S, z0, z1, cmax, zero);
+        if (tid == 0) S.out_id = (int)(0xFFFFFFFFu - (uint32_t)cmax);
+        dg.n_survivors = 1; dg.p_chosen = 1.0f;
+        rc = FIN_DONE;
+      } else {
+        const float y_max = keyf(kmax);
+        Listed L = {n_cert, n_unc, y_max, key_g, C.g, S_below, false, 0u};
+        uint32_t key_thr = 0u;
+        if (R.minp_on) {
+          key_thr = fkey(y_max + (float)log((double)R.min_p));
+          L.m_cert = key_thr > key_g;
         }
+        if (n_cert <= (unsigned)COUNT_MAX) sort_by_counting<NTHR>(S, n_cert, y_max, key_thr, lds);
+        else if (!R.k_on && n_cert > (unsigned)SORT_MAX) L.n = 0u;
+        else L.n = sort_by_buckets<NTHR, PER>(S, R, key, eid, n_cert, y_max, complete ? S.kmin : key_g, key_thr, lds);
         __syncthreads();
-        rc = finalize_long<NTHR, WHOLE>(S, R, n_cert, n_unc, kmax, key_g, complete ? S.kmin : key_g, C.need_sum, C.g, S_below, lk, lid, lds + (size_t)lcap * 8u, hot_bits, dg);
+        if (L.n) {
+          if (R.k_on) L.n = min(L.n, (unsigned)R.top_k);
+          L.n_minp = S.memb;
+          if (L.n <= 64u) {
+            if (wave == 0) decide_wave(S, R, L, reinterpret_cast<const u64*>(lds + SORT_OUT), hot_bits);
+          } else decide_block<NTHR>(S, R, L, lds, hot_bits);
+          __syncthreads();
+          rc = S.e_rc;
+          if (rc == FIN_DONE) {
+            dg.n_survivors = (int)S.e_n;
+            dg.s_k = (double)S.e_skfix / WSCALE;
+            if (hot_bits != nullptr) {
+              dg.alpha = (double)S.e_SH / (double)S.e_SK;
+              dg.flags |= SIMPLE_DIAG_SHVS | (S.e_acc ? SIMPLE_DIAG_ACCEPTED : 0u);
+            }
+            dg.p_chosen = (float)((double)S.out_w / (double)S.e_SK);
+            if (S.out_id < 0) rc = FIN_PENDING;
+          }
+        } else if (n_cert <= (unsigned)a.F.long_cap) {
+          // too many, or crowded by ties: keys and ids go back to the region, the bucket tables behind them
+          const unsigned lcap = (unsigned)a.F.long_cap;
+          uint32_t* lk = reinterpret_cast<uint32_t*>(lds);
+          uint32_t* lid = lk + lcap;
+          __syncthreads();
+          if (tid == 0) { S.n2 = 0u; S.memb = 0u; S.bk = -1; S.bp = -1; }
+          __syncthreads();
+#pragma unroll
+          for (int j = 0; j < PER; ++j) {
+            if (key[j]) { const unsigned slot = atomicAdd(&S.n2, 1u); lk[slot] = key[j]; lid[slot] = eid[j]; }
+          }
+          __syncthreads();
+          rc = finalize_long<NTHR, WHOLE>(S, R, n_cert, n_unc, kmax, key_g, complete ? S.kmin : key_g, C.need_sum, C.g, S_below, lk, lid, lds + (size_t)lcap * 8u, hot_bits, dg);
+        }
       }
       // -inf columns without mass among the survivors of a count alone, or where nothing is truncated
       if (complete && !R.greedy && !R.p_on && !R.minp_on) dg.n_survivors = R.k_on ? k_asked : V;

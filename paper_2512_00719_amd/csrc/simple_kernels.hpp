@@ -38,6 +38,7 @@ constexpr int SAMPLE_PER_WAVE = 48;   // keys of the threshold sample a wave han
 // Candidate-list entries per thread that the single-pass kernel's epilogue holds in registers: 3584 to 8192 a row,
 // about twice and more what the threshold aims at.
 constexpr int capf_per_thread(int threads, bool whole) { return threads == 256 ? (whole ? 12 : 14) : threads == 512 ? 12 : 8; }
+constexpr uint32_t FAST_REGION_MIN = 36864;  // bytes of the shared region at least: the sorted epilogue's arrays
 constexpr int MAX_WHOLE = 8192;  // columns of a row that is listed whole
 static_assert(MAX_WHOLE <= 1024 * capf_per_thread(1024, true), "a row that is listed whole fits the registers");
 constexpr int NBF_BITS = 8, NBF = 1 << NBF_BITS;  // buckets of the long-list epilogue's tables

@@ -19,7 +19,6 @@ typedef unsigned long long u64;
 
 constexpr int UNR = 4;       // 16-byte loads per lane and tile
 constexpr int SPW = SAMPLE_PER_WAVE;  // sample entries a wave hands to the merge
-constexpr int MEMB = 512;    // entries the sorted epilogue handles
 constexpr int idr(int threads) { return threads == 1024 ? 8 : 16; }  // history ids a thread keeps in registers (1024 threads have 128 each: no room for more)
 constexpr double WSCALE = 17592186044416.0;  // 2^44: fixed-point scale of probability mass
 constexpr int NBW = 2048;               // bins of the mass histogram (whole-vocabulary nucleus)
@@ -128,6 +127,7 @@ struct FS {
   unsigned distinct;           // distinct history columns of the row
   unsigned tile_ctr;           // next tile of the stream that no wave has taken yet
   u64 e_SK, e_SH, e_tfix, e_skfix;
+  double u[3];                 // the row's uniforms: draw, acceptance, tail draw
   float wmax[16];
   unsigned wcnt[16];
   unsigned r32a[16], r32b[16];
@@ -140,7 +140,6 @@ struct RowCfg {
   int top_k, V;
   bool greedy, k_on, p_on, p_le0, minp_on, need_sum;
   bool all;  // no truncation, and the list holds the whole row
-  double u_draw, u_acc, u_tail;
 };
 
 // ---------------------------------------------------------------- block collectives -----------
@@ -183,31 +182,18 @@ __device__ inline void blk_excl_scan2(FS& S, unsigned c, u64 m, unsigned& ce, u6
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) { return wave_all(v, [](uint32_t x, uint32_t y) { return max(x, y); }); }
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) { return wave_all(v, [](uint32_t x, uint32_t y) { return min(x, y); }); }
 
-// All-pairs helpers over small LDS tables: eight entries are loaded before they are used, so the
+// All-pairs sums over small LDS tables: four entries are loaded before they are used, so the
 // reads overlap instead of each waiting out the LDS latency.
-// #{q < n : a[q] > c}
-__device__ __forceinline__ unsigned count_greater(const u64* a, unsigned n, u64 c) {
-  unsigned r = 0, q = 0;
-  for (; q + 8 <= n; q += 8) {
-    u64 v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = a[q + j];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) r += (v[j] > c) ? 1u : 0u;
-  }
-  for (; q < n; ++q) r += (a[q] > c) ? 1u : 0u;
-  return r;
-}
 // sum of w[q] over q < n with a[q] >= c (ge) or a[q] <= c (!ge); cnt_gt gets #{a[q] > c}
 template <bool GE, typename K>
 __device__ __forceinline__ u64 sum_where(const K* a, const u64* w, unsigned n, K c, unsigned& cnt_gt) {
   u64 s = 0ull; unsigned r = 0, q = 0;
-  for (; q + 8 <= n; q += 8) {
-    K v[8]; u64 x[8];
+  for (; q + 4 <= n; q += 4) {
+    K v[4]; u64 x[4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) { v[j] = a[q + j]; x[j] = w[q + j]; }
+    for (int j = 0; j < 4; ++j) { v[j] = a[q + j]; x[j] = w[q + j]; }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) { s += (GE ? v[j] >= c : v[j] <= c) ? x[j] : 0ull; r += (v[j] > c) ? 1u : 0u; }
+    for (int j = 0; j < 4; ++j) { s += (GE ? v[j] >= c : v[j] <= c) ? x[j] : 0ull; r += (v[j] > c) ? 1u : 0u; }
   }
   for (; q < n; ++q) { const K v = a[q]; s += (GE ? v >= c : v <= c) ? w[q] : 0ull; r += (v > c) ? 1u : 0u; }
   cnt_gt = r;
