@@ -103,7 +103,7 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   const uint32_t tables = NBF * 12u + MEMB2 * 16u;           // bucket tables of the long-list epilogue
   uint32_t body = off < FAST_REGION_MIN ? FAST_REGION_MIN : off;
   if (whole && body < align16((uint32_t)V * 8u + tables)) body = align16((uint32_t)V * 8u + tables);
-  F.threads = ((int64_t)body + 2048 <= (int64_t)lds_limit / 4) ? 256 : 512;  // four workgroups per compute unit, static LDS included
+  F.threads = ((int64_t)body + 3072 <= (int64_t)lds_limit / 4) ? 256 : 512;  // four workgroups per compute unit, static LDS included
   if (V >= ((int64_t)1 << 18)) F.threads = 512;  // a sample of two tiles per wave: four waves' is too small a share of such rows
   if (B <= (int64_t)n_cu) F.threads = 1024;
   else if (B <= 2 * (int64_t)n_cu) F.threads = 512;
@@ -119,8 +119,9 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   const uint32_t roomy = F.threads == 256 ? FAST_REGION_MIN : align16((uint32_t)(capf_per_thread(F.threads, whole) * F.threads) * 8u + tables);
   if (!whole && body < roomy) body = roomy;
   F.long_cap = (body - tables) / 8u;
-  F.samp = body;  // the sample merge area holds SPW keys per wave
-  const uint32_t total = body + align16((uint32_t)(F.threads / 64) * (uint32_t)SAMPLE_PER_WAVE * 4u);
+  F.samp = body;  // the sample merge area holds SPW keys per wave, or the sample's counts
+  const uint32_t merge = align16((uint32_t)(F.threads / 64) * (uint32_t)SAMPLE_PER_WAVE * 4u);
+  const uint32_t total = body + (merge < SAMPLE_COUNTS * 4u ? SAMPLE_COUNTS * 4u : merge);
   const uint32_t reg_cap = (uint32_t)(capf_per_thread(F.threads, whole) * F.threads);  // the epilogue moves the list to registers
   F.list_cap = body / 8u < reg_cap ? body / 8u : reg_cap;
   if ((int64_t)total + 1024 > (int64_t)lds_limit) return F;  // total stays 0

@@ -9,7 +9,8 @@
 //             by the rank of the id among the set bits.  The V-wide histograms of section 2.2 are
 //             never materialised; a column's penalty is looked up only where its bit is set, so
 //             unpenalised columns are never touched (column-wise penalties, section 5.2).
-//   sample    every wave's first two tiles (history columns masked) give, by wave-ballot bisection, a
+//   sample    every wave's first tiles (history columns masked) give, by counts in equal steps or, where the row's
+//             masses are relative to it, by wave-ballot bisection, a
 //             value g that is expected to admit a small multiple of the requested prefix length.
 //   stream    one coalesced pass of 16-byte loads per lane over the raw logits.  Columns with
 //             z >= g go to an LDS candidate list that now occupies the history's region (penalties
@@ -66,12 +67,72 @@ __device__ __forceinline__ u64 wfix(uint32_t key, float y_max) { return exp_fix<
 template <typename DT>
 __device__ __forceinline__ void sample_group(const typename Io<DT>::Raw& A, int idx0, const Hist& H, float (&z)[Io<DT>::EPL]) {
   constexpr int EPL = Io<DT>::EPL;
-  constexpr unsigned EMASK = (1u << EPL) - 1u;
   Io<DT>::unpack(A, z);
   if (H.active) {
-    const uint32_t nib = (H.bm[idx0 >> 5] >> ((unsigned)idx0 & 31u)) & EMASK;
+    const uint32_t nib = H.bm[idx0 >> 5] >> ((unsigned)idx0 & 31u);
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) z[e] = (nib & (1u << e)) ? -INFINITY : z[e];
+    for (int e = 0; e < EPL; ++e) {  // (a column's bit, spread over a word, selects -inf: two instructions)
+      const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)nib, (unsigned)e, 1u);
+      z[e] = __uint_as_float((m & 0xFF800000u) | (~m & __float_as_uint(z[e])));
+    }
+  }
+}
+
+// The threshold of a row whose result does not depend on it (greedy rows, top-k rows): a value that about `need` of the
+// values the lanes kept of the sample (a1 >= a2 >= a3; -inf: none) reach, from counts in equal steps between the largest
+// and the smallest of them; a step that holds too many is divided again.  `counts` (LDS) holds QUICK_NB zeros.  Sets
+// complete where fewer than `need` are finite.  The result is the same in every lane; barriers inside.
+// (A bisection by ballots in every wave and one over all that they kept, 16 waves on one scalar unit: 8 us
+// of a row of 151,936 bfloat16 columns; 2.5 us so, half of it unpacking.)
+constexpr int QUICK_NB = (int)SAMPLE_COUNTS, QUICK_ROUNDS = 4;
+template <int NTHR>
+__device__ __forceinline__ float quick_threshold(FS& S, float a1, float a2, float a3, unsigned need, uint32_t* counts, bool& complete) {
+  constexpr int NWV = NTHR / 64;
+  const int lane = lane_id(), wave = wave_id();
+  {
+    const unsigned have = (unsigned)(__popcll(__ballot(a1 > -INFINITY)) + __popcll(__ballot(a2 > -INFINITY)) + __popcll(__ballot(a3 > -INFINITY)));
+    const float last = a3 > -INFINITY ? a3 : a2 > -INFINITY ? a2 : a1 > -INFINITY ? a1 : INFINITY;
+    const float top = wave_max(a1), low = -wave_max(-last);
+    if (lane == 0) { S.wmax[wave] = top; S.r32a[wave] = __float_as_uint(low); S.wcnt[wave] = have; }
+  }
+  __syncthreads();
+  float hi = -INFINITY, lo = INFINITY;
+  unsigned total = 0u;
+#pragma unroll
+  for (int w = 0; w < NWV; ++w) { hi = fmaxf(hi, S.wmax[w]); lo = fminf(lo, __uint_as_float(S.r32a[w])); total += S.wcnt[w]; }
+  hi = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(hi)));
+  lo = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(lo)));
+  complete = __builtin_amdgcn_readfirstlane(total < need ? 1 : 0) != 0;
+  if (complete) return LOWEST;
+  unsigned acc = 0u;  // values above hi
+#pragma unroll 1
+  for (int round = 0;; ++round) {
+    const float scale = (float)QUICK_NB / fmaxf(hi - lo, 1e-30f);
+    auto count = [&](float v) { if (v >= lo && v <= hi) atomicAdd(&counts[(int)fminf((hi - v) * scale, (float)(QUICK_NB - 1))], 1u); };
+    count(a1); count(a2); count(a3);
+    __syncthreads();
+    if (wave == 0) {
+      constexpr int PL = QUICK_NB / 64;
+      unsigned c[PL], loc = 0u;
+#pragma unroll
+      for (int j = 0; j < PL; ++j) { c[j] = counts[lane * PL + j]; counts[lane * PL + j] = 0u; loc += c[j]; }
+      unsigned run = acc + wave_incl_scan(loc) - loc;
+#pragma unroll
+      for (int j = 0; j < PL; ++j) {
+        if (run < need && need <= run + c[j]) { S.q_step = lane * PL + j; S.q_before = run; S.q_through = run + c[j]; }
+        run += c[j];
+      }
+      // (a divided step may have lost a value to rounding: its lower end then)
+      if (lane == 63 && run < need) { S.q_step = QUICK_NB - 1; S.q_before = run; S.q_through = 0u; }
+    }
+    __syncthreads();
+    const int b = __builtin_amdgcn_readfirstlane(S.q_step);
+    const unsigned through = (unsigned)__builtin_amdgcn_readfirstlane((int)S.q_through), before = (unsigned)__builtin_amdgcn_readfirstlane((int)S.q_before);
+    const float step = (hi - lo) * (1.0f / (float)QUICK_NB);
+    const float low = b == QUICK_NB - 1 ? lo : hi - (float)(b + 1) * step;
+    // a little lower than the step's end, so that values there are certified
+    if (through <= need + need / 4u + 4u || round == QUICK_ROUNDS - 1) return fmaxf(low - 0.05f * step - fabsf(low) * 1e-6f, LOWEST);
+    hi = hi - (float)b * step; lo = low; acc = before;
   }
 }
 
@@ -717,6 +778,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     S.cut_k = 0ull; S.cut_p = 0ull; S.out_id = -1; S.out_w = 0ull; S.kmin = 0xFFFFFFFFu;
     S.n2 = 0u; S.nunc = 0u; S.e_rc = FIN_PENDING; S.e_n = 0u; S.tile_ctr = 0u;
   }
+  if (!whole && NWV > 4) for (int i = tid; i < QUICK_NB; i += NTHR) samp[i] = 0u;  // (the sample's counts: see quick_threshold)
   // ---- loads first: history ids, then this wave's two sample tiles ----
   const int32_t* hist = rh.ids;
   // With a state the tables come ready-made from the row's slot (section 5.2: carried from step to
@@ -801,21 +863,35 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
 
   bool complete = whole;  // the list takes every finite column
   if (!whole) {
-  // ---- threshold from the sample: three largest penalised values per lane, wave select, merge ----
-  float a1 = -INFINITY, a2 = -INFINITY, a3 = -INFINITY;  // branch-free insertion; a NaN is ignored here
-#define SIMPLE_TAKE3(v) do { const float v_ = (v); const float m1_ = fmaxf(a1, v_), l1_ = fminf(a1, v_); \
-    const float m2_ = fmaxf(a2, l1_), l2_ = fminf(a2, l1_); a3 = fmaxf(a3, l2_); a2 = m2_; a1 = m1_; } while (0)
-#pragma unroll
-  for (int u = 0; u < UNR; ++u) {
+  // ---- threshold from the sample: three largest unpenalised values per lane ----
+  float a1 = -INFINITY, a2 = -INFINITY, a3 = -INFINITY;
+  auto take_group = [&](const Raw& X, int idx0) {
     float z[EPL];
-    sample_group<DT>(A[u], t0 * T + u * 64 * EPL + lane * EPL, H, z);
+    sample_group<DT>(X, idx0, H, z);
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) SIMPLE_TAKE3(z[e]);
-    sample_group<DT>(Bf[u], (t0 + 1) * T + u * 64 * EPL + lane * EPL, H, z);
+    for (int e = 0; e < EPL; ++e) {  // sorted insertion: the median of two neighbours and the new value is the lower one's successor
+      a3 = __builtin_amdgcn_fmed3f(a2, a3, z[e]);
+      a2 = __builtin_amdgcn_fmed3f(a1, a2, z[e]);
+      a1 = fmaxf(a1, z[e]);
+    }
+  };
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) SIMPLE_TAKE3(z[e]);
+  for (int u = 0; u < UNR; ++u) take_group(A[u], t0 * T + u * 64 * EPL + lane * EPL);
+  // Rows that the list alone decides: any value that admits enough columns serves, and with eight waves and more
+  // one tile each is sample enough.  (With four waves the search by ballots is the shorter one: 1024 float32 rows of 128,256
+  // columns 201.1 against 202.6 us a call.  The other rows' masses are rounded relative to the threshold, so theirs is
+  // kept as it always was, to the bit: sums of the same columns do not depend on the build.)
+  const float m_quick = (float)k_sel * (float)(NWV * T) / (float)V;
+  const unsigned r_quick = (unsigned)ceilf(1.15f * m_quick + 3.2f * sqrtf(m_quick) + 3.5f);
+  const bool quick = NWV > 4 && (R.greedy || (R.k_on && !big_k) || R.p_le0) && r_quick <= (unsigned)NTHR / 2u;
+  if (!quick) {
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) take_group(Bf[u], (t0 + 1) * T + u * 64 * EPL + lane * EPL);
   }
-#undef SIMPLE_TAKE3
+  if (quick) {
+    C.g = quick_threshold<NTHR>(S, a1, a2, a3, r_quick, samp, complete);
+    C.y_g = R.greedy ? C.g : C.g / R.tau;
+  } else {
   // rank in the sample whose value leaves, with high probability, >= k_sel columns above it in the row
   const float m_exp = (float)k_sel * (float)(NWV * 2 * T) / (float)V;
   const unsigned r_samp = (unsigned)ceilf(1.15f * m_exp + 3.2f * sqrtf(m_exp) + 3.5f);
@@ -839,7 +915,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     if (lane == 0) { S.wmax[wave] = wp; S.wcnt[wave] = have | (have < q ? SHORT_WAVE : 0u); }
   }
   __syncthreads();
-  {
+  if (wave == 0) {  // (one wave for all: a search by ballots keeps the scalar unit busy, which the row's waves share)
     constexpr int NS = (NWV * SPW) / 64;
     uint32_t ks[NS];
     unsigned total = 0;
@@ -854,10 +930,10 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     // instead of a prefix of them.  Before, such rows admitted the masked columns too, overflowed the list
     // and went to the general kernel (32 float32 rows of 128,256 columns, 8 of them with 2000 columns
     // left: the call 451 to 536 us, 106 so).
-    // (the same in every lane: said so, the stream's tests on it stay scalar)
-    complete = __builtin_amdgcn_readfirstlane((complete && total < r_samp) ? 1 : 0) != 0;
+    complete = complete && total < r_samp;
     const unsigned need = max(1u, min(r_samp, total));
-    float g = keyf(wave_threshold<NS>(ks, need, need / 8u + 1u, min(kmn, kmx), kmx));
+    // (all that was handed over: the smallest, where the search would end)
+    float g = keyf(need == total ? min(kmn, kmx) : wave_threshold<NS>(ks, need, need / 8u + 1u, min(kmn, kmx), kmx));
     // A rank beyond what the waves hand over (a long top-k on a short row): the value there, from the slope between
     // the sample's largest value and the last one handed over, with a margin.  (Without, such rows were streamed
     // with a threshold that admits too few, and went to the general kernel after all.)
@@ -874,8 +950,13 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       if (complete && gm > LOWEST) { complete = false; g = gm; }
       else g = fmaxf(g, gm);
     }
-    C.g = g;
-    C.y_g = R.greedy ? g : g / R.tau;
+    if (lane == 0) { S.g = g; S.q_step = complete ? 1 : 0; }
+  }
+  __syncthreads();
+  // (the same in every lane: said so, the stream's tests on them stay scalar)
+  complete = __builtin_amdgcn_readfirstlane(S.q_step) != 0;
+  C.g = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(S.g)));
+  C.y_g = R.greedy ? C.g : C.g / R.tau;
   }
   }
   {

@@ -128,6 +128,8 @@ struct FS {
   unsigned tile_ctr;           // next tile of the stream that no wave has taken yet
   u64 e_SK, e_SH, e_tfix, e_skfix;
   double u[3];                 // the row's uniforms: draw, acceptance, tail draw
+  float g;                     // threshold of the candidate list
+  int q_step; unsigned q_before, q_through;  // what its search hands to all waves
   float wmax[16];
   unsigned wcnt[16];
   unsigned r32a[16], r32b[16];
