@@ -24,7 +24,11 @@ HIPCC_FLAGS = [
 
 # The single-pass kernel reserves list slots with one LDS atomic issued by one lane of a wave; the
 # compiler's wave-level aggregation of atomics would wrap that single lane in a second reduction.
-PER_SOURCE_FLAGS = {"simple_fast.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]}
+# The kernels behind it loop over rows and slices; constants of the double-precision functions, moved in front of those
+# loops, took up to 40 registers from end to end (the finishing kernel then spilled 35, and a kernel that uses scratch memory
+# starts 2 us later).
+PER_SOURCE_FLAGS = {"simple_fast.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
+                    "simple_wide.hip": ["-mllvm", "-disable-machine-licm"]}
 
 
 def build(verbose: bool = False, extra_flags: tuple = (), lib: str = LIB) -> str:

@@ -852,7 +852,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       WideRec rec;
       rec.row = (uint32_t)row; rec.g = g_ref; rec.mode = mode | ((a.f64 || g_ref > C.g) ? WIDE_F64 : 0u); rec.flags = S.flags & 0x3FFFFFFFu;
       rec.tau = R.tau; rec.top_p = R.top_p; rec.rep = par.rep_penalty; rec.freq = par.freq_penalty;
-      rec.pres = par.pres_penalty; rec.nnz = nnz; rec.n_prompt = min(max(rh.n_prompt, 0), nnz); rec.h_active = h_active ? 1 : 0;
+      rec.pres = par.pres_penalty; rec.ln_min_p = R.minp_on ? (float)log((double)R.min_p) : 0.0f; rec.n_prompt = min(max(rh.n_prompt, 0), nnz); rec.h_active = h_active ? 1 : 0;
       rec.min_p = R.min_p; rec.top_k = par.top_k; rec.distinct = H.active ? S.distinct : 0u;
       rec.far_slot = 0u;
       reinterpret_cast<WideRec*>(a.wq + WQ_HEAD)[slot] = rec;

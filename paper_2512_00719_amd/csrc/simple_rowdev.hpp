@@ -347,7 +347,7 @@ struct StreamCtx {
 struct WideRec {  // 64 bytes: everything the later kernels need to know about the row
   uint32_t row; float g; uint32_t mode, flags;
   float tau, top_p, rep, freq;
-  float pres; int nnz, n_prompt, h_active;
+  float pres, ln_min_p; int n_prompt, h_active;
   float min_p; int32_t top_k; uint32_t distinct;
   uint32_t far_slot;  // not this row's: the k-th record holds the slot of the k-th far row
 };

@@ -65,7 +65,7 @@ static_assert(sizeof(WideRec) == 64, "queue record size");
 struct WideRow {
   int row;
   StreamCtx C;
-  float tau, top_p, min_p;
+  float tau, top_p, min_p, ln_min_p;
   uint32_t mode, flags;
   bool h_active;
   float rep, freq, pres;
@@ -90,7 +90,7 @@ __device__ __forceinline__ WideRow load_row(const SampleArgs& a, unsigned slot) 
   slot = uni(slot);
   const WideRec rec = reinterpret_cast<const WideRec*>(a.wq + WQ_HEAD)[slot];
   W.row = uni((int)rec.row); W.mode = uni(rec.mode & WIDE_MODE); W.far = (uni(rec.mode) & WIDE_FAR) != 0u; W.f64 = (uni(rec.mode) & WIDE_F64) != 0u; W.flags = uni(rec.flags);
-  W.tau = uni(rec.tau); W.top_p = uni(rec.top_p); W.min_p = uni(rec.min_p);
+  W.tau = uni(rec.tau); W.top_p = uni(rec.top_p); W.min_p = uni(rec.min_p); W.ln_min_p = uni(rec.ln_min_p);
   W.C.g = uni(rec.g); W.C.y_g = uni(rec.g / rec.tau); W.C.inv_tau = uni(1.0 / (double)rec.tau); W.C.need_sum = true;
   W.C.l2e_tau = 0.0f;
   W.rep = uni(rec.rep); W.freq = uni(rec.freq); W.pres = uni(rec.pres);
@@ -122,7 +122,6 @@ struct SliceTabs {
   float hz[HCAP];       // logit of the history column of rank j in the slice, as read
   uint16_t hcol[HCAP];  // its column, counted from the slice's first
 };
-static_assert(WT == 256, "the finishing kernel maps one tile of each class to a thread");
 static_assert(SLC / 32 + SLC / 64 + 1 <= WT, "one mask word or directory entry per thread");
 // The tables of the slice that starts at column c0 come in two steps, so that their loads overlap
 // with the other loads of an item.  First this thread's mask word or directory entry (the addresses
@@ -151,18 +150,12 @@ __device__ __forceinline__ void slice_store(SliceTabs& T, uint32_t v, const Samp
   }
 }
 // Then, once the directory is in LDS, the counts of the slice's columns; a barrier must follow.
+template <int NTHR>
 __device__ __forceinline__ void slice_counts(SliceTabs& T, const unsigned char* ws, const SampleArgs& a) {
   const uint16_t* gcnt = reinterpret_cast<const uint16_t*>(ws + WS_HT + a.F.cnt);
   const unsigned r0 = T.dir[0];
   const unsigned nc = min(T.dir[SLC / 64] - r0, (unsigned)SLC);
-  for (unsigned t = threadIdx.x; t < nc; t += WT) T.cnt[t] = as_global(gcnt)[r0 + t];
-}
-__device__ inline void load_slice(SliceTabs& T, const WideRow& W, const SampleArgs& a, int c0) {  // ends with a barrier
-  const uint32_t v = slice_fetch(W.ws, a, c0);
-  slice_store(T, v, a, c0, W.distinct);
-  __syncthreads();
-  slice_counts(T, W.ws, a);
-  __syncthreads();
+  for (unsigned t = threadIdx.x; t < nc; t += NTHR) T.cnt[t] = as_global(gcnt)[r0 + t];
 }
 // Z' of column c0 + o, whose mask bit is set.
 __device__ __forceinline__ float slice_value(float z, int o, const SliceTabs& T, const WideRow& W) {
@@ -344,7 +337,7 @@ __device__ inline RowCut row_cut(FS& S, const WideRow& W) {  // every thread cal
   if (W.min_p > 0.0f) {  // min-p, alone or on top of top-p: the shorter prefix wins
     const uint32_t kmax = as_global(reinterpret_cast<const uint32_t*>(W.ws + WS_SCAL))[6];
     c.valid = c.valid && kmax > KEY_NEG_INF;
-    c.thr_y = keyf(kmax) + (float)log((double)W.min_p);  // fl(y_max + fl(ln min_p)), as in the list's epilogue
+    c.thr_y = keyf(kmax) + W.ln_min_p;  // fl(y_max + fl(ln min_p)), as in the list's epilogue
   }
   return c;
 }
@@ -986,29 +979,75 @@ __device__ inline void hand_on(const SampleArgs& a, int row) {
   a.out[row] = PENDING;
 }
 
-// This thread's columns of the slice that starts at c0 (SLC / WT of them, contiguous; -inf behind the row's
-// end), and their hot bits.
+// The slice that starts at c0 in LDS: column o at slice_place(o), so that the columns a thread takes, side by side, lie in
+// other banks than its neighbours'; -inf behind the row's end and, with by_class, for columns that are hot or not other than
+// `cls`.  A row's history tables of the slice are left in Tb, and this thread's own columns are penalised.
+// (Column by column in registers, 256 threads with every weight's code unrolled sixteen times, finding the drawn column
+// took 7 us of a row's 16, much of it the code's own way from memory; 4 us so.)
+constexpr int FT = 512, FNW = FT / 64;  // threads of the finishing kernel's workgroups: two waves per SIMD hide each other's latency
+constexpr int EPT = SLC / FT;
+__device__ __forceinline__ int slice_place(int o) { return o + o / EPT; }
+static_assert(EPT == 8, "a thread's columns are a byte of a mask word, and not less than a 16-byte group's");
+constexpr int SLICE_FLOATS = SLC + FT;
 template <typename DT>
-__device__ __forceinline__ uint32_t slice_columns(float (&z)[SLC / WT], const SampleArgs& a, const DT* rowp, int c0) {
-  constexpr int EPT = SLC / WT, EPL = Io<DT>::EPL;
-  static_assert(EPT == 16, "a thread's hot bits lie in half a word");
-  const int first = c0 + (int)threadIdx.x * EPT;
-  if (first + EPT <= a.V) {
-    typename Io<DT>::Raw r[EPT / EPL];
+__device__ __forceinline__ void stage_slice(float* zt, SliceTabs& Tb, const WideRow& W, const SampleArgs& a, const DT* rowp, int c0, bool by_class, unsigned cls) {
+  constexpr int EPL = Io<DT>::EPL, G = SLC / (FT * EPL);
+  const int tid = fresh_tid(), V = a.V;
+  const uint32_t tab = W.h_active ? slice_fetch(W.ws, a, c0) : 0u;
+  typename Io<DT>::Raw r[G];
+  uint32_t hq[G];
 #pragma unroll
-    for (int k = 0; k < EPT / EPL; ++k) r[k] = Io<DT>::load(rowp + first + k * EPL);
-#pragma unroll
-    for (int k = 0; k < EPT / EPL; ++k) {
-      float v[EPL];
-      Io<DT>::unpack(r[k], v);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) z[k * EPL + e] = v[e];
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) z[e] = first + e < a.V ? Io<DT>::one(rowp + first + e) : -INFINITY;
+  for (int j = 0; j < G; ++j) {
+    const int idx0 = c0 + (j * FT + tid) * EPL;
+    r[j] = typename Io<DT>::Raw();
+    hq[j] = 0u;
+    if (idx0 + EPL <= V) r[j] = Io<DT>::load(rowp + idx0);
+    if (by_class && idx0 < V) hq[j] = as_global(a.hot_bits)[idx0 >> 5] >> ((unsigned)idx0 & 31u);
   }
-  return (a.hot_bits && first < a.V) ? as_global(a.hot_bits)[first >> 5] >> ((unsigned)first & 31u) : 0u;
+  if (W.h_active) slice_store(Tb, tab, a, c0, W.distinct);
+#pragma unroll
+  for (int j = 0; j < G; ++j) {
+    const int o = (j * FT + tid) * EPL;
+    float z[EPL];
+    Io<DT>::unpack(r[j], z);
+    if (c0 + o + EPL > V) {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) z[e] = c0 + o + e < V ? Io<DT>::one(rowp + c0 + o + e) : -INFINITY;
+    }
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) zt[slice_place(o) + e] = (by_class && ((hq[j] >> e) & 1u) != cls) ? -INFINITY : z[e];
+  }
+  __syncthreads();
+  if (!W.h_active) return;
+  slice_counts<FT>(Tb, W.ws, a);
+  __syncthreads();
+  for (uint32_t m = (Tb.bm[tid >> 2] >> ((tid & 3) * EPT)) & 0xFFu; m; m &= m - 1u) {
+    const int o = tid * EPT + __ffs((int)m) - 1;
+    zt[slice_place(o)] = slice_value(zt[slice_place(o)], o, Tb, W);
+  }
+}
+// The sum of f(z, column) over this thread's columns; and, where the running sum over all threads' columns exceeds
+// `at` among them, the column and its term.
+template <int UNROLL_, typename F>
+__device__ __forceinline__ u64 sum_columns(const float* zt, int c0, F&& f) {
+  const int o0 = fresh_tid() * EPT;
+  const float* p = zt + slice_place(o0);
+  u64 s = 0ull;
+#pragma unroll UNROLL_
+  for (int e = 0; e < EPT; ++e) s += f(p[e], c0 + o0 + e);
+  return s;
+}
+template <typename F>
+__device__ __forceinline__ void find_column(FS& S, const float* zt, int c0, u64 run, u64 sum, u64 at, F&& f) {
+  if (!(run <= at && at < run + sum)) return;
+  const int o0 = fresh_tid() * EPT;
+  const float* p = zt + slice_place(o0);
+#pragma unroll 1
+  for (int e = 0; e < EPT; ++e) {
+    const u64 m = f(p[e], c0 + o0 + e);
+    if (m > 0ull && run <= at && at < run + m) { S.out_id = c0 + o0 + e; S.out_w = m; }
+    run += m;
+  }
 }
 
 constexpr int NBK_BITS = 10, NBK = 1 << NBK_BITS;  // buckets of the cut bin's columns
@@ -1016,7 +1055,6 @@ template <typename DT>
 __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, SliceTabs& Tb, u64* rcmp, uint32_t* rl,
                                   u64* dmass, u64* tiles, simple_row_diag& dg) {
   constexpr int T = SLC;            // a tile of the draw's walk is a slice
-  constexpr int EPT = T / WT;       // its columns per thread, contiguous
   const int tid = threadIdx.x;
   const int V = a.V;
   const StreamCtx& C = W.C;
@@ -1029,15 +1067,14 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   const uint32_t* sc = reinterpret_cast<const uint32_t*>(W.ws + WS_SCAL);
   const unsigned n_sure = as_global(sc)[2], n_r = as_global(sc)[3];
   const u64 S_sum = as_global(reinterpret_cast<const u64*>(W.ws + WS_SCAL))[2];  // mass of the row, summed by the classifying pass
-  u64 tv[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) tv[k] = as_global(reinterpret_cast<const u64*>(W.ws + WS_TILES))[k * WT + tid];
+  static_assert(FT == 512, "a tile of one of the two classes per thread");
+  const u64 tv = as_global(reinterpret_cast<const u64*>(W.ws + WS_TILES))[tid];
   const uint32_t kmax = as_global(sc)[6];
   // the cut as the classifying kernel found it
   const int bstar = (int)as_global(sc)[8] - 1;
   const u64 s_bins = as_global(reinterpret_cast<const u64*>(W.ws + WS_SCAL))[5];
   if (bstar < 0) { return false; }
-  const float thr_y = W.min_p > 0.0f ? keyf(kmax) + (float)log((double)W.min_p) : -INFINITY;
+  const float thr_y = W.min_p > 0.0f ? keyf(kmax) + W.ln_min_p : -INFINITY;
   const bool top_p_route = W.mode == WIDE_TOP_P, top_k_route = W.mode == WIDE_TOP_K;
   const bool cut_route = top_p_route || top_k_route;  // a cut inside a bin: by mass, or by count
   const u64 S_tot = top_p_route ? s_bins : S_sum;  // exact mass of the row (from the bins where there are bins)
@@ -1046,16 +1083,17 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   const bool minp_too = top_p_route && W.min_p > 0.0f;
   if (n_r > (unsigned)RCAP || (!cut_route && n_r != 0u) || (cut_route && n_r == 0u && !minp_too)) { return false; }
   if (tid == 0) { S.bd = -1; S.cut_k = 0ull; S.cut_p = ~0ull; S.e_tfix = 0ull; S.out_id = -1; S.out_w = 0ull; }
-  tiles[tid] = tv[0]; tiles[WT + tid] = tv[1];
-  const u64 msure = tv[0] + tv[1];
+  tiles[tid] = tv;
   u64 cut_found = 0ull;  // every collected column at or after it in the order survives; 0: no collected columns
   unsigned r_in = 0;
   if (cut_route && n_r == 0u) cut_found = ~0ull;  // nothing of the bin survives
   if (cut_route && n_r != 0u) {
   // exact masses (top-k: counts) from here: the columns surely inside must stay below the target, the
   // collected bin must reach it
-  const u64 m_sure = blk_sum_u64<WNW>(S, msure);  // barriers inside
-  auto mass_at = [&](unsigned t) -> u64 { return W.f64 ? mass_fix64(keyf((uint32_t)(rcmp[t] >> 32)), C) : (u64)rl[t]; };
+  const u64 m_sure = blk_sum_u64<FNW>(S, tv);  // barriers inside
+  Exp2Poly P{};  // (from memory where they are needed: as literals they took registers from end to end)
+  if (W.f64) P = exp2_poly_from_memory();
+  auto mass_at = [&](unsigned t) -> u64 { return W.f64 ? mass_fix64(keyf((uint32_t)(rcmp[t] >> 32)), C, P) : (u64)rl[t]; };
   const u64 m_above = top_k_route ? (u64)n_sure : m_sure;
   const u64 target = top_k_route ? (u64)W.top_k : (u64)__double2ull_ru((double)W.top_p * (double)S_tot);
   if (m_above >= target) { return false; }
@@ -1063,13 +1101,13 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   {
     u64 cmax_t = 0ull, cmin_t = ~0ull;
     const u64* grl = reinterpret_cast<const u64*>(W.ws + WS_RL);
-    for (unsigned t0 = 0; t0 < n_r; t0 += 4u * WT) {  // four independent loads per thread and round
+    for (unsigned t0 = 0; t0 < n_r; t0 += 4u * FT) {  // four independent loads per thread and round
       u64 e[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { const unsigned t = t0 + (unsigned)(k * WT + tid); e[k] = (t < n_r) ? as_global(grl)[t] : 0ull; }
+      for (int k = 0; k < 4; ++k) { const unsigned t = t0 + (unsigned)(k * FT + tid); e[k] = (t < n_r) ? as_global(grl)[t] : 0ull; }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const unsigned t = t0 + (unsigned)(k * WT + tid);
+        const unsigned t = t0 + (unsigned)(k * FT + tid);
         if (t >= n_r) continue;
         const float z = __uint_as_float((uint32_t)(e[k] >> 32));
         int b; float y;
@@ -1094,21 +1132,22 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
     bool ok = true;
     for (;;) {
       const int sh = max(0, 64 - NBK_BITS - (int)__clzll((long long)(hi - lo)));
-      for (int i = tid; i < NBK; i += WT) dmass[i] = 0ull;
+      for (int i = tid; i < NBK; i += FT) dmass[i] = 0ull;
       if (tid == 0) { S.bp = -1; S.memb = 0u; }
       __syncthreads();
-      for (unsigned t = tid; t < n_r; t += WT) {
+      if (tid == 0) { S.cut_k = 0ull; S.cut_p = ~0ull; }  // (every thread has read them)
+      for (unsigned t = tid; t < n_r; t += FT) {
         const u64 c = rcmp[t];
         if (c >= lo && c <= hi) atomicAdd(&dmass[(unsigned)((hi - c) >> sh)], top_k_route ? 1ull : mass_at(t));
       }
       __syncthreads();
       {
-        constexpr int PT4 = NBK / WT;
+        constexpr int PT4 = NBK / FT;
         u64 mb[PT4], m = 0ull;
 #pragma unroll
         for (int k = 0; k < PT4; ++k) { mb[k] = dmass[tid * PT4 + k]; m += mb[k]; }
         unsigned ce2, ct2; u64 me2, mt2;
-        blk_excl_scan2<WNW>(S, 0u, m, ce2, me2, ct2, mt2);
+        blk_excl_scan2<FNW>(S, 0u, m, ce2, me2, ct2, mt2);
         u64 run = acc + me2;
 #pragma unroll
         for (int k = 0; k < PT4; ++k) {
@@ -1125,17 +1164,19 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
       if (hi - lo >= width) lo = hi - (width - 1ull);
       if (sh == 0) { prefix = hi; break; }
       u64* mc = dmass;        // its members, and their masses
-      u64* mw = dmass + WT;
-      for (unsigned t = tid; t < n_r; t += WT) {
+      u64* mw = dmass + FT;
+      u64 vmax = 0ull, vmin = ~0ull;
+      for (unsigned t = tid; t < n_r; t += FT) {
         const u64 c = rcmp[t];
         if (c >= lo && c <= hi) {
+          vmax = c > vmax ? c : vmax; vmin = c < vmin ? c : vmin;
           const unsigned slot = atomicAdd(&S.memb, 1u);
-          if (slot < (unsigned)WT) { mc[slot] = c; mw[slot] = top_k_route ? 1ull : mass_at(t); }
+          if (slot < (unsigned)FT) { mc[slot] = c; mw[slot] = top_k_route ? 1ull : mass_at(t); }
         }
       }
       __syncthreads();
       const unsigned nm = S.memb;
-      if (nm <= (unsigned)WT) {
+      if (nm <= (unsigned)FT) {
         if ((unsigned)tid < nm) {
           const u64 c = mc[tid], w = mw[tid];
           unsigned above;
@@ -1146,7 +1187,13 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
         prefix = S.e_tfix;
         break;
       }
-      __syncthreads();  // every thread has read the member count
+      // Ties, most often: the next buckets divide the range that the members do take (ids of one value), not all of this
+      // one's.  (Dividing the whole of it took up to four rounds, 26 us of a bfloat16 row whose cut's bin held 3000 ties.)
+      vmax = wave_all(vmax, [](u64 x, u64 y) { return x > y ? x : y; });
+      vmin = wave_all(vmin, [](u64 x, u64 y) { return x < y ? x : y; });
+      if ((tid & 63) == 0) { atomicMax(&S.cut_k, vmax); atomicMin(&S.cut_p, vmin); }
+      __syncthreads();
+      hi = S.cut_k; lo = S.cut_p;
     }
     // the collected columns do not reach the target: with a min-p cut those below it were never
     // collected, and the min-p prefix is the shorter one (all collected columns survive)
@@ -1154,7 +1201,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
     cut_found = ok ? prefix : 1ull;
   }
   if (cut_found == 0ull) { return false; }
-  for (unsigned t = tid; t < n_r; t += WT) {
+  for (unsigned t = tid; t < n_r; t += FT) {
     if (rcmp[t] >= cut_found) {
       const uint32_t id = 0xFFFFFFFFu - (uint32_t)rcmp[t];
       const unsigned hot = use_hot ? hot_bit(hot_bits, id) : 0u;
@@ -1166,7 +1213,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   const u64 cut_c = cut_found;
   __syncthreads();  // the tile masses are complete
   // -- masses of the classes, acceptance (section 5.3), the tile that holds the draw --
-  u64 S0, S1, t0 = tiles[tid], t1 = tiles[256 + tid], e0, e1;  // WT == 256: one tile of each class per thread
+  u64 S0, S1, t0 = tid < 256 ? tiles[tid] : 0ull, t1 = tid < 256 ? tiles[256 + tid] : 0ull, e0, e1;  // a tile of each class per thread
   unsigned ns = r_in + (tid == 0 ? n_sure : 0u);
   {
     const u64 i0 = wave_incl_scan(t0), i1 = use_hot ? wave_incl_scan(t1) : 0ull;
@@ -1175,7 +1222,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
     __syncthreads();
     S0 = 0ull; S1 = 0ull; e0 = i0 - t0; e1 = i1 - t1; ns = 0u;
 #pragma unroll
-    for (int w = 0; w < WNW; ++w) {
+    for (int w = 0; w < FNW; ++w) {
       const u64 x = S.r64a[w], y = S.r64b[w];
       if (w < wave_id()) { e0 += x; e1 += y; }
       S0 += x; S1 += y; ns += S.r32a[w];
@@ -1193,7 +1240,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   const u64 S_cls = use_hot ? (pick_hot ? S1 : S0) : S_K;
   const double u = use_hot ? (pick_hot ? u3[0] : u3[2]) : u3[0];
   dg.n_survivors = (int)ns;
-  dg.s_k = (double)(top_k_route ? S_K : S_tot) / (W.f64 ? (double)(1ull << F64_BITS) : (double)MSCALE) * exp((double)C.y_g - (double)keyf(kmax));
+  if (a.diag) dg.s_k = (double)(top_k_route ? S_K : S_tot) / (W.f64 ? (double)(1ull << F64_BITS) : (double)MSCALE) * exp((double)C.y_g - (double)keyf(kmax));
   if (S_cls == 0ull) { return false; }
   u64 tfix = (u64)__double2ull_rd(u * (double)S_cls);
   if (tfix >= S_cls) tfix = S_cls - 1ull;
@@ -1206,36 +1253,30 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   if (tstar < 0) { return false; }
   // -- the drawn id inside one tile --
   const int c0 = tstar * T;
-  float zv[EPT];  // requested before the tables' barriers
-  const uint32_t hq = slice_columns<DT>(zv, a, rowp, c0);
-  if (W.h_active) load_slice(Tb, W, a, c0);
-  u64 mloc[EPT]; u64 lsum = 0ull;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const int idx = c0 + tid * EPT + e;
-    mloc[e] = 0ull;
-    if (idx < V) {
-      float z = zv[e];
-      if (W.h_active && slice_bit(idx - c0, Tb)) z = slice_value(z, idx - c0, Tb, W);
-      if (!use_hot || ((hq >> e) & 1u) == cls) {
-        int b; float y;
-        const float w = mass_term(z, C, b, y);
-        const bool below = z < C.g;
-        bool in = !below || b < bstar;
-        if (!in && b == bstar) in = composite(fkey(y), (uint32_t)idx) >= cut_c;
-        if (in && y >= thr_y) mloc[e] = W.f64 ? mass_fix64(y, C) : below ? mass_fix_below(w) : mass_fix(w);
-      }
-    }
-    lsum += mloc[e];
-  }
+  float* zt = reinterpret_cast<float*>(rcmp);  // (the collected columns are done with)
+  stage_slice<DT>(zt, Tb, W, a, rowp, c0, use_hot, cls);
+  // (straight-line, a few columns at a time: a branch per column waits for each one's arithmetic)
+  auto mass = [&](float z, int idx) -> u64 {
+    int b; float y;
+    const float w = mass_term(z, C, b, y);
+    const bool below = z < C.g;
+    const bool in = (!below || b < bstar || (b == bstar && composite(fkey(y), (uint32_t)idx) >= cut_c)) && y >= thr_y;
+    const u64 m = mass_fix(fminf(w, W_LIMIT));  // (the same integer as mass_fix_below for what lies below)
+    return in ? m : 0ull;
+  };
+  Exp2Poly P{};
+  if (W.f64) P = exp2_poly_from_memory();
+  auto mass64 = [&](float z, int idx) -> u64 {
+    int b; float y;
+    (void)mass_term(z, C, b, y);
+    const bool in = (!(z < C.g) || b < bstar || (b == bstar && composite(fkey(y), (uint32_t)idx) >= cut_c)) && y >= thr_y;
+    return in ? mass_fix64(y, C, P) : 0ull;
+  };
+  const u64 lsum = W.f64 ? sum_columns<1>(zt, c0, mass64) : sum_columns<2>(zt, c0, mass);
   unsigned ce3, ct3; u64 me3, tot3;
-  blk_excl_scan2<WNW>(S, 0u, lsum, ce3, me3, ct3, tot3);
-  u64 run = S.mab_d + me3;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    if (mloc[e] > 0ull && run <= tfix && run + mloc[e] > tfix) { S.out_id = c0 + tid * EPT + e; S.out_w = mloc[e]; }
-    run += mloc[e];
-  }
+  blk_excl_scan2<FNW>(S, 0u, lsum, ce3, me3, ct3, tot3);
+  if (W.f64) find_column(S, zt, c0, S.mab_d + me3, lsum, tfix, mass64);
+  else find_column(S, zt, c0, S.mab_d + me3, lsum, tfix, mass);
   __syncthreads();
   dg.p_chosen = (float)((double)S.out_w / (double)S_K);
   return S.out_id >= 0;
@@ -1248,11 +1289,10 @@ constexpr float FAR_LIMIT = 88.0f;
 // else (WIDE_FAR) they are scaled to the row maximum, and the draw's place inside its slice is a fraction of
 // the slice's mass.
 template <typename DT>
-__device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS& S, SliceTabs& Tb, simple_row_diag& dg) {
-  constexpr int EPT = SLC / WT;
+__device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS& S, SliceTabs& Tb, float* zt, simple_row_diag& dg) {
   const int tid = threadIdx.x, V = a.V;
   const int n_sl = (V + SLC - 1) / SLC;
-  static_assert(FAST_MAX_V / SLC <= WT, "a slice per thread");
+  static_assert(FAST_MAX_V / SLC <= FT, "a slice per thread");
   const uint32_t* hot_bits = a.hot_bits;
   const bool use_hot = hot_bits != nullptr;
   const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
@@ -1280,7 +1320,7 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
   float y_max = S.wmax[0];
   const bool rel = W.far;
 #pragma unroll
-  for (int w = 1; w < WNW; ++w) y_max = fmaxf(y_max, S.wmax[w]);
+  for (int w = 1; w < FNW; ++w) y_max = fmaxf(y_max, S.wmax[w]);
   if (!(y_max > LOWEST) || y_max == INFINITY) return false;
   u64 m_all = 0ull, m_hot = 0ull;
   bool lost = false;
@@ -1295,8 +1335,8 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
   if (lost) atomicOr(&S.flags, 1u);
   unsigned near = (tid < n_sl && m >= y_max - FAR_LIMIT) ? 1u : 0u, finite = (tid < n_sl && m > LOWEST) ? 1u : 0u;
   u64 S_K = m_all, mx = 0ull;
-  blk_reduce<WNW>(S, near, finite, mx, S_K);  // barriers inside
-  const u64 S_H = use_hot ? blk_sum_u64<WNW>(S, m_hot) : 0ull;
+  blk_reduce<FNW>(S, near, finite, mx, S_K);  // barriers inside
+  const u64 S_H = use_hot ? blk_sum_u64<FNW>(S, m_hot) : 0ull;
   if (S.flags || (rel && near == 1u && finite > 1u)) return false;
   bool pick_hot = false;
   if (use_hot) {
@@ -1312,7 +1352,7 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
   {
     const u64 mc = use_hot ? (pick_hot ? m_hot : m_all - m_hot) : m_all;
     unsigned ce, ct; u64 me, mt;
-    blk_excl_scan2<WNW>(S, 0u, mc, ce, me, ct, mt);
+    blk_excl_scan2<FNW>(S, 0u, mc, ce, me, ct, mt);
     if (mc > 0ull && me <= tfix && tfix < me + mc) { S.bd = tid; S.mab_d = tfix - me; S.mab_k = mc; S.wmax[15] = m; }
   }
   __syncthreads();
@@ -1323,47 +1363,32 @@ __device__ inline bool finish_all_row(const SampleArgs& a, const WideRow& W, FS&
   const float y_ref = rel ? S.wmax[15] : W.C.y_g;
   u64 rq = S.mab_d;
   const double place = (double)S.mab_d / (double)S.mab_k;
-  float zv[EPT];
-  const uint32_t hq = slice_columns<DT>(zv, a, rowp, c0);
-  if (W.h_active) load_slice(Tb, W, a, c0);
-  u64 q[EPT], lsum = 0ull;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const int o = tid * EPT + e;
-    q[e] = 0ull;
-    if (c0 + o < V) {
-      float z = zv[e];
-      if (W.h_active && slice_bit(o, Tb)) z = slice_value(z, o, Tb, W);
-      if (!use_hot || (((hq >> e) & 1u) != 0u) == pick_hot) {
-        const float y = tempered(z, W.C);
-        q[e] = rel ? exp_fix<44>(y, y_ref) : float_to_u64(mass_rel(y, y_ref) * MSCALE);
-      }
-    }
-    lsum += q[e];
-  }
+  stage_slice<DT>(zt, Tb, W, a, rowp, c0, use_hot, pick_hot ? 1u : 0u);
+  auto mass = [&](float z, int) -> u64 { return float_to_u64(mass_rel(tempered(z, W.C), y_ref) * MSCALE); };
+  Exp2Poly P{};
+  if (rel) P = exp2_poly_from_memory();
+  auto mass64 = [&](float z, int) -> u64 { return exp_fix<44>(tempered(z, W.C), y_ref, P); };
+  const u64 lsum = rel ? sum_columns<1>(zt, c0, mass64) : sum_columns<2>(zt, c0, mass);
   unsigned ce, ct; u64 me, Q;
-  blk_excl_scan2<WNW>(S, 0u, lsum, ce, me, ct, Q);
+  blk_excl_scan2<FNW>(S, 0u, lsum, ce, me, ct, Q);
   if (rel) {
     rq = (u64)__double2ull_rd(place * (double)Q);
     if (Q > 0ull && rq >= Q) rq = Q - 1ull;
   }
-  u64 run = me;
-#pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    if (q[e] > 0ull && run <= rq && rq < run + q[e]) { S.out_id = c0 + tid * EPT + e; S.out_w = q[e]; }
-    run += q[e];
-  }
+  if (rel) find_column(S, zt, c0, me, lsum, rq, mass64);
+  else find_column(S, zt, c0, me, lsum, rq, mass);
   __syncthreads();
   dg.n_survivors = V;
-  dg.s_k = rel ? (double)S_K / WSCALE : (double)S_K / (double)MSCALE * exp((double)W.C.y_g - (double)y_max);
+  if (a.diag) dg.s_k = rel ? (double)S_K / WSCALE : (double)S_K / (double)MSCALE * exp((double)W.C.y_g - (double)y_max);
   dg.p_chosen = (float)((double)S.out_w * (rel ? exp((double)y_ref - (double)y_max) : 1.0) / (double)S_K);
   return S.out_id >= 0;
 }
 
 template <typename DT>
-__global__ __launch_bounds__(WT) void wide_finish_kernel(const SampleArgs a) {
+__global__ __launch_bounds__(FT, 4) void wide_finish_kernel(const SampleArgs a) {
   __shared__ SliceTabs Tb;
   __shared__ u64 rcmp[RCAP];
+  static_assert(SLICE_FLOATS * 4 <= RCAP * 8, "a slice takes the collected columns' place");
   __shared__ uint32_t rl[RCAP];
   __shared__ u64 dmass[NBK];
   __shared__ u64 tiles[512];
@@ -1378,7 +1403,7 @@ __global__ __launch_bounds__(WT) void wide_finish_kernel(const SampleArgs a) {
     dg.s_k = 0.0; dg.p_chosen = 0.0f; dg.n_survivors = 0; dg.reserved = 0u;
     dg.flags = SIMPLE_DIAG_WIDE | W.flags;
     if (a.hot_bits && a.hot_flags && *a.hot_flags) dg.flags |= SIMPLE_DIAG_BAD_HOT_SET;
-    const bool ok = W.mode == WIDE_ALL ? finish_all_row<DT>(a, W, S, Tb, dg) : finish_row<DT>(a, W, S, Tb, rcmp, rl, dmass, tiles, dg);
+    const bool ok = W.mode == WIDE_ALL ? finish_all_row<DT>(a, W, S, Tb, reinterpret_cast<float*>(rcmp), dg) : finish_row<DT>(a, W, S, Tb, rcmp, rl, dmass, tiles, dg);
     if (tid == 0) {
       if (!ok) hand_on(a, W.row);
       else {
@@ -1397,19 +1422,19 @@ __global__ __launch_bounds__(WT) void wide_finish_kernel(const SampleArgs a) {
 hipError_t launch_wide(const SampleArgs& a, int dtype, hipStream_t st) {
   // One resident round of workgroups each: six (bins) and five (classify) per compute unit fit by
   // registers and LDS; a workgroup then takes a contiguous run of slices, mostly of one row.
-  const dim3 bins((unsigned)a.n_cu * 5u), cls((unsigned)a.n_cu * 4u), fin(1024), blk(fast::WT);
+  const dim3 bins((unsigned)a.n_cu * 5u), cls((unsigned)a.n_cu * 4u), fin((unsigned)(a.B < 2 * a.n_cu ? a.B : 2 * a.n_cu)), blk(fast::WT), fblk(fast::FT);
   if (dtype == SIMPLE_F32) {
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<float, true>), cls, blk, 0, st, a);
     else hipLaunchKernelGGL((fast::wide_bins_kernel<float, false>), cls, blk, 0, st, a);  // (float32: four workgroups per compute unit, no spilled register)
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_classify_kernel<float, true>), cls, blk, 0, st, a);
     else hipLaunchKernelGGL((fast::wide_classify_kernel<float, false>), cls, blk, 0, st, a);
-    hipLaunchKernelGGL((fast::wide_finish_kernel<float>), fin, blk, 0, st, a);
+    hipLaunchKernelGGL((fast::wide_finish_kernel<float>), fin, fblk, 0, st, a);
   } else {
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, true>), bins, blk, 0, st, a);
     else hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, false>), bins, blk, 0, st, a);
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_classify_kernel<uint16_t, true>), cls, blk, 0, st, a);
     else hipLaunchKernelGGL((fast::wide_classify_kernel<uint16_t, false>), cls, blk, 0, st, a);
-    hipLaunchKernelGGL((fast::wide_finish_kernel<uint16_t>), fin, blk, 0, st, a);
+    hipLaunchKernelGGL((fast::wide_finish_kernel<uint16_t>), fin, fblk, 0, st, a);
   }
   return hipGetLastError();
 }
