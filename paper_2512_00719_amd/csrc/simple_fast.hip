@@ -16,8 +16,9 @@
 //             z >= g go to an LDS candidate list that now occupies the history's region (penalties
 //             that only lower a logit keep z >= z', so nothing with z' >= g is missed); rows whose
 //             nucleus is taken over the whole vocabulary also accumulate exp((z - g) / tau) below g.
-//   epilogue  the list moves to registers, the history tables are rebuilt in the region and the
-//             listed columns are penalised; the mass below g is corrected, exactly, for the
+//   epilogue  the list moves to registers and the listed columns are penalised, by a hash table of the
+//             list that the history looks up, or (rows that need the mass below g) by the history tables,
+//             rebuilt in the region; the mass below g is corrected, exactly, for the
 //             history columns.  The list then certifies itself: every column whose tempered value
 //             exceeds fl(g / tau) is in it, so any prefix of the total order (value descending, id
 //             ascending) that ends above that value is known exactly (truncation first, section
@@ -683,6 +684,88 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
   return (S.out_id >= 0) ? FIN_DONE : FIN_PENDING;
 }
 
+// The penalties of a row's listed columns, without its tables: the listed columns go to a hash table (a row listed
+// whole has a counter per column), the history's ids look themselves up in it and count, then each column takes what was
+// counted for it.  Work goes with the list and the history; the tables go with the vocabulary too (mask cleared, scanned into a
+// directory, looked up through it): 8 bfloat16 rows of 151,936 columns with 2048 ids each 37.9 us a call, 35.9 so.  For rows with a
+// compute unit to themselves: where several share one, the tables' lookups, all in flight at once, are hidden better than
+// the table's chains (4096 rows of 256,000 columns with 8192 ids, 512 threads: 947 us with the tables, 964 with this).
+// Entry j of this thread is list entry tid + j * NTHR; ids[j] is history entry tid + j * NTHR.  Barriers inside; one must follow.
+constexpr unsigned HASH_LIST_MAX = 512;  // listed columns (the table is half full then); longer lists cost more than the tables
+static_assert(MAX_WHOLE * 4 <= FAST_REGION_MIN, "the counters fit the region");
+template <int NTHR, int PER, int NID, bool WHOLE>
+__device__ __forceinline__ void penalise_listed(FS& S, const Hist& H, float (&ez)[PER], const uint32_t (&eid)[PER], unsigned n, const int (&ids)[NID],
+                                                const int32_t* __restrict__ hist, int nnz, int n_prompt, int V, unsigned char* region) {
+  const int tid = threadIdx.x;
+  constexpr unsigned bits = 10u, slots = 1u << bits;
+  uint32_t* count = reinterpret_cast<uint32_t*>(region);  // occurrences in the high half, generated ones in the low half
+  uint32_t* owner = count + slots;                        // column + 1; 0: free
+  auto first = [&](uint32_t id) { return (id * 0x9E3779B1u) >> (32u - bits); };
+  zero16(region, WHOLE ? V * 4 : (int)slots * 8, tid, NTHR);
+  __syncthreads();
+  if constexpr (!WHOLE) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if ((unsigned)(j * NTHR) >= n) break;
+      if ((unsigned)(tid + j * NTHR) < n) {  // (a column is listed once)
+        uint32_t h = first(eid[j]);
+        while (atomicCAS(&owner[h], 0u, eid[j] + 1u) != 0u) h = (h + 1u) & (slots - 1u);
+      }
+    }
+    __syncthreads();
+  }
+  n_prompt = min(max(n_prompt, 0), nnz);
+  bool bad = false;
+  // (four ids' first places are read before any is used)
+  auto occur4 = [&](const int (&id)[4], int i0) {
+    uint32_t o[4];
+    if constexpr (!WHOLE) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = owner[first((uint32_t)id[k])];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int i = i0 + k * NTHR;
+      if (i >= nnz) continue;
+      if ((unsigned)id[k] >= (unsigned)V) { bad = true; continue; }
+      const uint32_t one = 0x10000u + (i >= n_prompt ? 1u : 0u);
+      if constexpr (WHOLE) atomicAdd(&count[id[k]], one);
+      else {
+        uint32_t h = first((uint32_t)id[k]);
+        while (o[k] != 0u && o[k] != (uint32_t)id[k] + 1u) { h = (h + 1u) & (slots - 1u); o[k] = owner[h]; }
+        if (o[k]) atomicAdd(&count[h], one);
+      }
+    }
+  };
+  static_assert(NID % 4 == 0, "whole groups");
+#pragma unroll
+  for (int j = 0; j < NID; j += 4) {
+    if (j * NTHR >= nnz) break;
+    const int id4[4] = {ids[j], ids[j + 1], ids[j + 2], ids[j + 3]};
+    occur4(id4, tid + j * NTHR);
+  }
+  for (int i0 = tid + NID * NTHR; i0 < nnz; i0 += 4 * NTHR) {
+    int id4[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) id4[k] = i0 + k * NTHR < nnz ? hist[i0 + k * NTHR] : 0;
+    occur4(id4, i0);
+  }
+  if (bad) atomicOr(&S.flags, SIMPLE_DIAG_BAD_HISTORY_ID);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    if ((unsigned)(j * NTHR) >= n) break;
+    if ((unsigned)(tid + j * NTHR) >= n) continue;
+    uint32_t h = eid[j];
+    if constexpr (!WHOLE) {
+      h = first(eid[j]);
+      while (owner[h] != eid[j] + 1u) h = (h + 1u) & (slots - 1u);
+    }
+    const uint32_t c = count[h];
+    if (c) ez[j] = H.apply(ez[j], c & 0xFFFFu);
+  }
+}
+
 __device__ inline void queue_pending(const SampleArgs& a, int row) {
   const unsigned slot = atomicAdd(&a.pend[0], 1u);
   a.pend[2 + slot] = (uint32_t)row;
@@ -1082,7 +1165,10 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       eid[j] = (i < n) ? li[i] : 0u;
     }
     __syncthreads();
-    if (H.active) {
+    if ((whole || NTHR == 1024) && H.active && !stateful && !C.need_sum && (whole || n <= HASH_LIST_MAX)) {
+      penalise_listed<NTHR, PER, IDR, WHOLE>(S, H, ez, eid, n, ids, hist, nnz, rh.n_prompt, V, lds);
+      __syncthreads();
+    } else if (H.active) {
       unsigned own = 0u;
       if (stateful) load_tables(true);
       else build_history<NTHR>(S, H, ids, hist, nnz, rh.n_prompt, V, own);
