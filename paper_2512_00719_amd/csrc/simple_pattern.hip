@@ -55,8 +55,20 @@ constexpr int NTILE = FAST_MAX_V / TILE;
 static_assert(NTILE <= PT, "one tile per thread in the scans over tiles");
 constexpr int UN = 4;          // 16-byte loads in flight per lane, twice (two register sets take turns)
 constexpr uint32_t FILL = 0xFF80FF80u;  // two patterns (-inf) of the last bin, whose columns have no mass
-constexpr int CBIT = 58;       // a table entry counts a column of the cut pattern from this bit up
+// The table lies in LDS by sign and magnitude: entry q of 4 bytes (counts) or 8 (masses) from the start, those of the
+// negative patterns from TAB_NEG on, where the pattern's own sign bit puts them.
+constexpr uint32_t TAB_NEG = 0x8000u;
+constexpr int TAB_BYTES = (int)TAB_NEG + NMAG * 8;
+static_assert(NMAG * 8 <= (int)TAB_NEG && TAB_BYTES <= 0x10000, "byte offsets of 16 bits");
+// Masses are integers held as doubles, so that a column is added by one instruction at the full rate (two integer ones
+// otherwise); four columns on top of 2^52 are exact, and the sum's low 52 bits are the integer.
+constexpr int CBIT = 50;       // a table entry counts a column of the cut pattern from this bit up
 constexpr u64 MASS_PART = (1ull << CBIT) - 1ull;
+constexpr double SUM_BASE = 4503599627370496.0;  // 2^52
+constexpr u64 SUM_BASE_BITS = 0x4330000000000000ull;
+constexpr int CHAIN = 4;       // columns added before the sum goes to an integer
+static_assert((u64)CHAIN << CBIT <= 1ull << 52, "a sum of CHAIN entries is exact");
+static_assert((u64)(TILE / 64) << 44 < 1ull << CBIT, "a lane's masses of one tile stay below the count");
 static_assert(TILE / 64 < (1 << (64 - CBIT)), "a lane's columns of one tile fit the count");
 
 typedef short s16x2 __attribute__((ext_vector_type(2)));
@@ -69,23 +81,31 @@ __device__ __forceinline__ int bin_of(uint32_t raw) {
   const int q = min(max(p - (PLO - 1), 0), QMAX);
   return (NMAG - 1) - (q ^ s);
 }
-// The same for the two patterns of a 32-bit word at once (packed 16-bit arithmetic), as byte offsets
-// into a table of (1 << SHIFT)-byte entries, low pattern in the low half.  TRACK: smax gathers the
+// Byte offset of a bin, and of a bit pattern's bin, in the table of (1 << SHIFT)-byte entries.
+template <int SHIFT>
+__device__ __forceinline__ uint32_t bin_offset(int d) {
+  return d < NMAG ? (uint32_t)(NMAG - 1 - d) << SHIFT : TAB_NEG + ((uint32_t)(d - NMAG) << SHIFT);
+}
+template <int SHIFT>
+__device__ __forceinline__ uint32_t raw_offset(uint32_t raw) {
+  const int q = min(max((int)(raw & 0x7FFFu) - (PLO - 1), 0), QMAX);
+  return (raw & TAB_NEG) | ((uint32_t)q << SHIFT);
+}
+// The same for the two patterns of a 32-bit word at once (packed 16-bit arithmetic), low pattern in the low
+// half: five instructions (eight with the bins in descending value).  TRACK: smax gathers the
 // largest patterns read as signed numbers (the largest positive value), umax read as unsigned
 // numbers (the negative value of the largest magnitude, if there is a negative one).
 template <bool TRACK, int SHIFT>
 __device__ __forceinline__ uint32_t bin_offsets2(uint32_t x, s16x2& smax, u16x2& umax) {
-  const s16x2 xs = __builtin_bit_cast(s16x2, x);
   if (TRACK) {
-    smax = __builtin_elementwise_max(smax, xs);
+    smax = __builtin_elementwise_max(smax, __builtin_bit_cast(s16x2, x));
     umax = __builtin_elementwise_max(umax, __builtin_bit_cast(u16x2, x));
   }
-  const s16x2 s = xs >> (short)15;
-  const s16x2 p = xs & (short)0x7FFF;
-  s16x2 q = __builtin_elementwise_max((s16x2)(p - (short)(PLO - 1)), (s16x2)((short)0));
-  q = __builtin_elementwise_min(q, (s16x2)((short)QMAX));
-  const s16x2 d = (short)(NMAG - 1) - (q ^ s);
-  return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, d) << (unsigned short)SHIFT));
+  u16x2 q = __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, x & 0x7FFF7FFFu), (u16x2)((unsigned short)(PLO - 1)));
+  q = __builtin_elementwise_min(q, (u16x2)((unsigned short)QMAX)) << (unsigned short)SHIFT;
+  uint32_t off = (x & (TAB_NEG | TAB_NEG << 16)) | __builtin_bit_cast(uint32_t, q);
+  asm("" : "+v"(off));  // (formed once: the compiler forms it anew for either half)
+  return off;
 }
 // bit pattern of a bin (zero for the merged bins)
 __device__ __forceinline__ uint32_t raw_of(int d) {
@@ -96,6 +116,21 @@ __device__ __forceinline__ uint32_t raw_of(int d) {
 }
 __device__ __forceinline__ bool merged_bin(int d) { return d == NMAG - 1 || d == NMAG; }
 __device__ __forceinline__ float value_of(uint32_t raw) { return __uint_as_float(raw << 16); }
+// Sum over each row of sixteen lanes, the same in all of them (one instruction per step: the move is part of the addition).
+__device__ __forceinline__ uint32_t row16_sum(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_XOR1, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_XOR2, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_HALF_MIRROR, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_MIRROR, 0xF, 0xF, true);
+  return v;
+}
+// The same of masses below 2^CBIT, in two halves.
+__device__ __forceinline__ u64 row16_sum_mass(u64 v) {
+  constexpr int HALF = CBIT / 2;
+  const uint32_t lo = row16_sum((uint32_t)v & ((1u << HALF) - 1u));
+  return (u64)lo + ((u64)row16_sum((uint32_t)(v >> HALF) & ((1u << HALF) - 1u)) << HALF);
+}
+static_assert(CBIT % 2 == 0 && CBIT / 2 + 4 <= 32, "sixteen halves in 32 bits");
 // Sum over the wave, the same in every lane (data-parallel primitives: no LDS, no waiting).
 template <typename T>
 __device__ __forceinline__ T wave_total(T v) { return wave_sum(v); }
@@ -128,7 +163,7 @@ __device__ __forceinline__ uint32_t raw_at(const u32x4& r, int e) {
 
 template <bool USE_HOT>
 __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a) {
-  __shared__ __align__(16) u64 tab[NB];   // 32-bit counts (in its first half) in the first pass, then per bin the mass of a surviving column
+  __shared__ __align__(16) u64 tab[TAB_BYTES / 8];  // 32-bit counts in the first pass, then per bin the mass of a surviving column
   __shared__ u64 tall[NTILE], thot[NTILE];  // per tile: mass of the sure survivors, and of the hot ones among them
   __shared__ uint32_t tcc[NTILE];           // per tile: columns of the cut pattern, the hot ones among them from bit 16
   __shared__ PS P;
@@ -155,6 +190,7 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
   const int n_tiles = (V + TILE - 1) / TILE;
   const float tau = par.temperature;
   unsigned char* tabb = reinterpret_cast<unsigned char*>(tab);
+  auto mass_at = [&](uint32_t off) -> u64 { return (u64)*reinterpret_cast<const double*>(tabb + off); };
   const GlobalU4 rp = (GlobalU4)rowp;
   auto hand_back = [&]() { if (tid == 0) a.out[row] = NOT_TAKEN; };
 
@@ -169,7 +205,8 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
     }
   };
   fetch(A, 0);
-  for (int i = tid; i < NB / 2; i += PT) tab[i] = 0ull;
+  if (tid < NTILE) { tall[tid] = 0ull; thot[tid] = 0ull; tcc[tid] = 0u; }
+  for (int i = tid; i < NMAG / 2; i += PT) reinterpret_cast<u64*>(tabb)[i] = reinterpret_cast<u64*>(tabb + TAB_NEG)[i] = 0ull;
   if (tid == 0) {
     P.dtop = NB; P.dcut = -1; P.bad = 0; P.tdraw = -1; P.id_cut = -1; P.partial = 0;
     P.pos_max = 0; P.neg_max = 0u; P.pos_m = 0u; P.pos_p = 0u; P.jcut = 0u; P.ccut = 0u; P.tcut = 0u; P.rcut = 0u; P.hot_before = 0u; P.hot_in = 0u; P.merged_n = 0u;
@@ -198,7 +235,7 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
   uint32_t neg_max = max((uint32_t)umax.x, (uint32_t)umax.y);
   if (tid < V - n_groups * 8) {  // the ragged end of the row
     const uint32_t raw = (uint32_t)*as_global(rowp + n_groups * 8 + tid);
-    __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(tabb + 4 * bin_of(raw)), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(tabb + raw_offset<2>(raw)), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     pos_max = max(pos_max, (int)(short)raw);
     neg_max = max(neg_max, raw);
   }
@@ -215,7 +252,7 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
     int dfirst = NB;
 #pragma unroll
     for (int j = 0; j < BPT; ++j) {
-      ca[j] = reinterpret_cast<const uint32_t*>(tab)[d_first + j];
+      ca[j] = *reinterpret_cast<const uint32_t*>(tabb + bin_offset<2>(d_first + j));
       csum += ca[j];
       if (ca[j] && dfirst == NB) dfirst = d_first + j;
     }
@@ -311,7 +348,7 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
 #pragma unroll
   for (int j = 0; j < BPT; ++j) {
     const int d = d_first + j;
-    tab[d] = d < dcut ? mb[j] : (d == dcut ? (partial ? 1ull << CBIT : mb[j]) : 0ull);
+    *reinterpret_cast<double*>(tabb + bin_offset<3>(d)) = (double)(d < dcut ? mb[j] : (d == dcut ? (partial ? 1ull << CBIT : mb[j]) : 0ull));
   }
   __syncthreads();
 
@@ -320,41 +357,62 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
     for (int idx = n_groups * 8; idx < V; ++idx) f((uint32_t)*as_global(rowp + idx), idx);
   };
   {
-    TileRegs R{}, N{};
-    if (wave < n_tiles) tile_load<USE_HOT>(R, rowp, hot_bits, wave, lane, n_groups);
-    for (int t = wave; t < n_tiles; t += PNW) {
-      if (t + PNW < n_tiles) tile_load<USE_HOT>(N, rowp, hot_bits, t + PNW, lane, n_groups);
+    // Bound: vector arithmetic, 9 instructions a column with a hot set.  (With integer sums, eight instructions to find two
+    // bins and a whole wave's reduction per tile it was 14.  512 rows of 201,088 columns, top-p, hot set: the call
+    // 152.3 us then, 138.8 so.)
+    auto tile_sums = [&](const TileRegs& R, int t) {
       u64 acc = 0ull, acc_h = 0ull;
 #pragma unroll
       for (int h = 0; h < TG; ++h) {  // (groups behind the row's end hold FILL: -inf, no mass)
         const uint32_t w4[4] = {R.r[h].x, R.r[h].y, R.r[h].z, R.r[h].w};
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          s16x2 unused_s = {0, 0};
-          u16x2 unused_u = {0, 0};
-          const uint32_t off = bin_offsets2<false, 3>(w4[k], unused_s, unused_u);
-          const u64 m0 = *reinterpret_cast<const u64*>(tabb + (off & 0xFFFFu));
-          const u64 m1 = *reinterpret_cast<const u64*>(tabb + (off >> 16));
-          acc += m0 + m1;
-          if (USE_HOT) {
-            const u64 h0 = 0ull - (u64)((R.hq[h] >> (2 * k)) & 1u), h1 = 0ull - (u64)((R.hq[h] >> (2 * k + 1)) & 1u);
-            acc_h += (m0 & h0) + (m1 & h1);
+        for (int c = 0; c < 8; c += CHAIN) {
+          double s = SUM_BASE, s_h = SUM_BASE;
+#pragma unroll
+          for (int k = c / 2; k < (c + CHAIN) / 2; ++k) {
+            s16x2 unused_s = {0, 0};
+            u16x2 unused_u = {0, 0};
+            const uint32_t off = bin_offsets2<false, 3>(w4[k], unused_s, unused_u);
+            const double m0 = *reinterpret_cast<const double*>(tabb + (off & 0xFFFFu));
+            const double m1 = *reinterpret_cast<const double*>(tabb + (off >> 16));
+            s += m0; s += m1;
+            if (USE_HOT) {  // without its upper word an entry is below 2^-1022: it adds nothing
+              int h0 = __builtin_amdgcn_sbfe((int)R.hq[h], 2u * k, 1u), h1 = __builtin_amdgcn_sbfe((int)R.hq[h], 2u * k + 1u, 1u);
+              asm("" : "+v"(h0), "+v"(h1));  // (kept masks: else a test and a select for each)
+              s_h += __hiloint2double(__double2hiint(m0) & h0, __double2loint(m0));
+              s_h += __hiloint2double(__double2hiint(m1) & h1, __double2loint(m1));
+            }
           }
+          acc += (u64)__double_as_longlong(s);
+          if (USE_HOT) acc_h += (u64)__double_as_longlong(s_h);
         }
       }
-      const uint32_t cc = (uint32_t)(acc >> CBIT) | ((uint32_t)(acc_h >> CBIT) << 16);
-      const u64 s_all = wave_total(acc & MASS_PART);
-      const u64 s_hot = USE_HOT ? wave_total(acc_h & MASS_PART) : 0ull;
-      const uint32_t s_cc = partial ? wave_total(cc) : 0u;
-      if (lane == 0) { tall[t] = s_all; thot[t] = s_hot; tcc[t] = s_cc; }
-      R = N;
+      acc -= (u64)(TG * 8 / CHAIN) * SUM_BASE_BITS;
+      if (USE_HOT) acc_h -= (u64)(TG * 8 / CHAIN) * SUM_BASE_BITS;
+      // (four lanes add to the tile's words: less work than the rest of a reduction, and nothing waits for it)
+      const u64 s_all = row16_sum_mass(acc), s_hot = USE_HOT ? row16_sum_mass(acc_h) : 0ull;
+      const uint32_t cc = partial ? row16_sum((uint32_t)(acc >> CBIT) | ((uint32_t)(acc_h >> CBIT) << 16)) : 0u;
+      if ((lane & 15) == 0) {
+        atomicAdd(&tall[t], s_all);
+        if (USE_HOT) atomicAdd(&thot[t], s_hot);
+        if (partial) atomicAdd(&tcc[t], cc);
+      }
+    };
+    TileRegs R{}, N{};  // (two register sets take turns)
+    if (wave < n_tiles) tile_load<USE_HOT>(R, rowp, hot_bits, wave, lane, n_groups);
+    for (int t = wave; t < n_tiles; t += 2 * PNW) {
+      if (t + PNW < n_tiles) tile_load<USE_HOT>(N, rowp, hot_bits, t + PNW, lane, n_groups);
+      tile_sums(R, t);
+      if (t + PNW >= n_tiles) break;
+      if (t + 2 * PNW < n_tiles) tile_load<USE_HOT>(R, rowp, hot_bits, t + 2 * PNW, lane, n_groups);
+      tile_sums(N, t + PNW);
     }
   }
   __syncthreads();
   if (tid == 0 && V > n_groups * 8) {  // the ragged end of the row belongs to the last tile
     u64 s_all = 0ull, s_hot = 0ull; uint32_t cc = 0u;
     ragged_each([&](uint32_t raw, int idx) {
-      const u64 m = tab[bin_of(raw)];
+      const u64 m = mass_at(raw_offset<3>(raw));
       const bool hot = USE_HOT && hot_bit(hot_bits, (uint32_t)idx);
       s_all += m & MASS_PART; cc += (uint32_t)(m >> CBIT);
       if (hot) { s_hot += m & MASS_PART; cc += (uint32_t)(m >> CBIT) << 16; }
@@ -480,7 +538,7 @@ __global__ __launch_bounds__(PT, 4) void pattern_rows_kernel(const SampleArgs a)
     // mass of one column in the drawn class (zero outside it and outside K_b)
     auto col_mass = [&](uint32_t raw, uint32_t hot, int idx) -> u64 {
       if (USE_HOT && hot != cls) return 0ull;
-      const u64 m = tab[bin_of(raw)];
+      const u64 m = mass_at(raw_offset<3>(raw));
       if (m >> CBIT) return idx <= id_cut ? mcut : 0ull;
       return m;
     };
