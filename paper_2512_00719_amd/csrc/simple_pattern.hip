@@ -64,8 +64,6 @@ static_assert(NMAG * 8 <= (int)TAB_NEG && TAB_BYTES <= 0x10000, "byte offsets of
 // otherwise); four columns on top of 2^52 are exact, and the sum's low 52 bits are the integer.
 constexpr int CBIT = 50;       // a table entry counts a column of the cut pattern from this bit up
 constexpr u64 MASS_PART = (1ull << CBIT) - 1ull;
-constexpr double SUM_BASE = 4503599627370496.0;  // 2^52
-constexpr u64 SUM_BASE_BITS = 0x4330000000000000ull;
 constexpr int CHAIN = 4;       // columns added before the sum goes to an integer
 static_assert((u64)CHAIN << CBIT <= 1ull << 52, "a sum of CHAIN entries is exact");
 static_assert((u64)(TILE / 64) << 44 < 1ull << CBIT, "a lane's masses of one tile stay below the count");

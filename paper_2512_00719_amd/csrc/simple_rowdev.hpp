@@ -416,6 +416,13 @@ __device__ __forceinline__ void float_to_parts(float v, uint32_t& hi, uint32_t& 
   hi = (uint32_t)h;
   lo = (uint32_t)(fmaf(-h, 0x1p24f, v) + 0.5f);  // v - h * 2^24 is exact either way
 }
+// The same integer of w * MSCALE as a float: v + 0.5 rounded is below the next integer exactly where the split's low part
+// is, and v itself from 2^24 on (compared for every float from 2^-37 to 2^50).  As a double it joins a sum on top of
+// SUM_BASE, exact up to 2^52, whose low bits are the integer: five instructions a column with the addition, eleven in parts.
+__device__ __forceinline__ float mass_integer(float w) { return floorf(fmaf(w, MSCALE, 0.5f)); }
+constexpr double SUM_BASE = 4503599627370496.0;  // 2^52
+constexpr u64 SUM_BASE_BITS = 0x4330000000000000ull;
+__device__ __forceinline__ u64 sum_to_u64(double s) { return (u64)__double_as_longlong(s) - SUM_BASE_BITS; }
 __device__ __forceinline__ u64 parts_to_u64(uint32_t hi, uint32_t lo) { return ((u64)hi << 24) + (u64)lo; }
 __device__ __forceinline__ u64 float_to_u64(float v) {
   uint32_t hi, lo;

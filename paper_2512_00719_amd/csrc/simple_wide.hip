@@ -465,6 +465,10 @@ __device__ __forceinline__ float mass_rel(float y, float m) {
   const float d = y - m;
   return __builtin_amdgcn_exp2f(fmaf(d, L2E_HI, d * L2E_LO));
 }
+// q where bit e of hq is set, else 0
+__device__ __forceinline__ float hot_only(float q, uint32_t hq, int e) {
+  return __uint_as_float(__float_as_uint(q) & (uint32_t)__builtin_amdgcn_sbfe((int)hq, (unsigned)e, 1u));
+}
 // One slice of a row without truncation: every wave leaves the mass of its columns.  The row is read once;
 // bound: HBM, with about 25 vector instructions a column beside it.  (128,256 float32 columns x 256 rows:
 // classified in the second kernel, a column 2^21 above g sending the row to the general kernel, the call
@@ -477,7 +481,7 @@ __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<
   float y[G][EPL];
   float m = LOWEST;
   bool far = false;  // a mass the fixed point cannot carry, or a NaN
-  uint32_t sh = 0u, sl_ = 0u, hh = 0u, hl = 0u;  // sums of the masses' two parts (16 terms of <= 2^25 and < 2^24)
+  u64 s = 0ull, h = 0ull;
   auto weigh = [&](float yv) {  // exp(y - y_g), as in mass_term
     const float w = mass_rel(yv, W.C.y_g);
     far = far || !(w <= W_LIMIT);
@@ -492,17 +496,18 @@ __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<
       for (int e = 0; e < EPL; ++e) y[j][e] = c0 + o + e < V ? Io<DT>::one(rowp + c0 + o + e) : -INFINITY;
     }
     const uint32_t nib = W.h_active ? Tb.bm[o >> 5] >> ((unsigned)o & 31u) : 0u;  // history columns: below
+    double gs = SUM_BASE, gh = SUM_BASE;  // <= 8 terms of <= 2^49
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
       y[j][e] = ((nib >> e) & 1u) ? -INFINITY : tempered(y[j][e], W.C);
       m = fmaxf(m, y[j][e]);
-      uint32_t hi, lo;
-      float_to_parts(weigh(y[j][e]) * MSCALE, hi, lo);
-      sh += hi; sl_ += lo;
-      if (use_hot) { const uint32_t hm = (uint32_t)(-(int32_t)((L.hq[j] >> e) & 1u)); hh += hi & hm; hl += lo & hm; }
+      const float q = mass_integer(weigh(y[j][e]));
+      gs += (double)q;
+      if (use_hot) gh += (double)hot_only(q, L.hq[j], e);
     }
+    s += sum_to_u64(gs);
+    if (use_hot) h += sum_to_u64(gh);
   }
-  u64 s = parts_to_u64(sh, sl_), h = use_hot ? parts_to_u64(hh, hl) : 0ull;
   if (W.h_active) {
     hist_stage<DT>(Tb, HP, W.ws, a, rowp, c0, V);
     __syncthreads();
@@ -656,10 +661,8 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
             for (int e = 0; e < EPL; ++e) {  // straight-line: the columns at or above g share one more slot
               int b;
               const float w = mass_term<UT>(z[e], W.C, b);
-              uint32_t hi, lo;
-              float_to_parts(fminf(w, W_LIMIT) * MSCALE, hi, lo);
               const bool below = z[e] < W.C.g;
-              u64 v = parts_to_u64(hi, lo);
+              u64 v = sum_to_u64(SUM_BASE + (double)mass_integer(fminf(w, W_LIMIT)));
               if (TOPK) {  // the bin counts the column instead (not the history columns, handled below)
                 v = (below && !((nib >> e) & 1u)) ? 1ull : 0ull;
                 ntop += below ? 0u : 1u;
@@ -905,27 +908,25 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
             // ... but -inf counts as sure when every value does
             if (zc.z_sure == -INFINITY) n_sure -= (unsigned)__popc(~live & EMASK);
           }
-          // group sums of the masses' two parts (units of 2^24, and the rest): <= 8 terms of <= 2^25
-          uint32_t sh = 0u, sl_ = 0u, hh = 0u, hl = 0u, ah = 0u, al = 0u;
+          double gs = SUM_BASE, gh = SUM_BASE, ga = SUM_BASE;  // the group's masses: <= 8 terms of <= 2^49
 #pragma unroll
           for (int e = 0; e < EPL; ++e) {
             int b; float y;
             const float w = mass_term<UT>(z[e], W.C, b, y);
             bad = bad || !(w <= W_LIMIT);  // a mass the fixed point cannot carry, or a NaN
-            uint32_t hi, lo;
-            float_to_parts(w * MSCALE, hi, lo);
+            const float q = mass_integer(w);
             ymax = fmaxf(ymax, y);
             const bool sure = z[e] >= zc.z_sure;
-            const uint32_t his = sure ? hi : 0u, los = sure ? lo : 0u;
-            sh += his; sl_ += los;
-            if (use_hot) { const uint32_t hm = (uint32_t)(-(int32_t)((L.hq[j] >> e) & 1u)); hh += his & hm; hl += los & hm; }
-            if (WANT_ALL) { ah += hi; al += lo; }
+            const float qs = sure ? q : 0.0f;
+            gs += (double)qs;
+            if (use_hot) gh += (double)hot_only(qs, L.hq[j], e);
+            if (WANT_ALL) ga += (double)q;
             n_sure += sure ? 1u : 0u;
             any_edge = any_edge || (z[e] >= zc.z_edge && !sure);
           }
-          acc_s += parts_to_u64(sh, sl_);
-          if (use_hot) acc1 += parts_to_u64(hh, hl);
-          if (WANT_ALL) acc_all += parts_to_u64(ah, al);
+          acc_s += sum_to_u64(gs);
+          if (use_hot) acc1 += sum_to_u64(gh);
+          if (WANT_ALL) acc_all += sum_to_u64(ga);
           if (__ballot(any_edge)) {  // boundary columns: few per wave, element by element
 #pragma unroll
             for (int e = 0; e < EPL; ++e) {
