@@ -390,7 +390,7 @@ __device__ __forceinline__ float mass_term(float z, const StreamCtx& C, int& bin
   y = UNIT_TAU ? z : (float)((double)z * C.inv_tau);
   const float d = y - C.y_g;
   const float t = fmaf(d, L2E_HI, d * L2E_LO);
-  bin = (int)fminf(fmaxf(-t * BINS_PER_LOG2, 0.0f), (float)(NBW - 1));
+  bin = (int)__builtin_amdgcn_fmed3f(-t * BINS_PER_LOG2, 0.0f, (float)(NBW - 1));  // (a NaN: bin 0)
   return __builtin_amdgcn_exp2f(t);
 }
 template <bool UNIT_TAU = false>
