@@ -409,8 +409,7 @@ __device__ __forceinline__ u64 mass_fix64(float y, const StreamCtx& C, const Exp
 }
 __device__ __forceinline__ u64 mass_fix64(float y, const StreamCtx& C) { constexpr Exp2Poly P = EXP2_POLY; return mass_fix64(y, C, P); }
 // Nearest integer of a float in [0, 2^52) as 64 bits, in two 32-bit conversions (the split is exact:
-// a float has 24 significant bits): hi counts units of 2^24.  The two parts of several values can
-// be summed separately in 32 bits and combined once.
+// a float has 24 significant bits): hi counts units of 2^24.
 __device__ __forceinline__ void float_to_parts(float v, uint32_t& hi, uint32_t& lo) {
   const float h = floorf(v * 0x1p-24f);
   hi = (uint32_t)h;
