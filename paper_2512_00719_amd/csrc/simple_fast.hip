@@ -81,11 +81,15 @@ __device__ __forceinline__ void sample_group(const typename Io<DT>::Raw& A, int 
 
 // The threshold of a row whose result does not depend on it (greedy rows, top-k rows): a value that about `need` of the
 // values the lanes kept of the sample (a1 >= a2 >= a3; -inf: none) reach, from counts in equal steps between the largest
-// and the smallest of them; a step that holds too many is divided again.  `counts` (LDS) holds QUICK_NB zeros.  Sets
+// and the smallest of them; a step that holds too many is divided again, in the order of the keys, as is a range too
+// wide for equal steps of the value (columns masked with the lowest finite value: divided by value, its upper step held
+// every real logit, and 191 to 270 of 270 such rows went to the general kernel).  `counts` (LDS) holds QUICK_NB zeros.  Sets
 // complete where fewer than `need` are finite.  The result is the same in every lane; barriers inside.
 // (A bisection by ballots in every wave and one over all that they kept, 16 waves on one scalar unit: 8 us
 // of a row of 151,936 bfloat16 columns; 2.5 us so, half of it unpacking.)
-constexpr int QUICK_NB = (int)SAMPLE_COUNTS, QUICK_ROUNDS = 4;
+constexpr int QUICK_BITS = 9, QUICK_NB = 1 << QUICK_BITS;
+static_assert(QUICK_NB == (int)SAMPLE_COUNTS, "the counters' room");
+constexpr float QUICK_SPAN = (float)QUICK_NB;  // steps of at most one; key steps end a search after four rounds whatever the values
 template <int NTHR>
 __device__ __forceinline__ float quick_threshold(FS& S, float a1, float a2, float a3, unsigned need, uint32_t* counts, bool& complete) {
   constexpr int NWV = NTHR / 64;
@@ -105,12 +109,21 @@ __device__ __forceinline__ float quick_threshold(FS& S, float a1, float a2, floa
   lo = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(lo)));
   complete = __builtin_amdgcn_readfirstlane(total < need ? 1 : 0) != 0;
   if (complete) return LOWEST;
-  unsigned acc = 0u;  // values above hi
+  unsigned acc = 0u;  // values above those that are still in question
+  bool by_key = !(hi - lo <= QUICK_SPAN);
+  uint32_t khi = fkey(hi), klo = fkey(lo);
+  bool in1 = a1 > -INFINITY, in2 = a2 > -INFINITY, in3 = a3 > -INFINITY;
 #pragma unroll 1
-  for (int round = 0;; ++round) {
+  for (;;) {
     const float scale = (float)QUICK_NB / fmaxf(hi - lo, 1e-30f);
-    auto count = [&](float v) { if (v >= lo && v <= hi) atomicAdd(&counts[(int)fminf((hi - v) * scale, (float)(QUICK_NB - 1))], 1u); };
-    count(a1); count(a2); count(a3);
+    const int sh = max(0, 32 - QUICK_BITS - (int)__clz((int)(khi - klo)));
+    auto step_of = [&](float v) -> int {  // (monotone in the value; what rounding puts beyond an end belongs to its step)
+      return by_key ? (int)((khi - min(max(fkey(v), klo), khi)) >> sh) : (int)fminf((hi - v) * scale, (float)(QUICK_NB - 1));
+    };
+    const int s1 = step_of(a1), s2 = step_of(a2), s3 = step_of(a3);
+    if (in1) atomicAdd(&counts[s1], 1u);
+    if (in2) atomicAdd(&counts[s2], 1u);
+    if (in3) atomicAdd(&counts[s3], 1u);
     __syncthreads();
     if (wave == 0) {
       constexpr int PL = QUICK_NB / 64;
@@ -123,17 +136,28 @@ __device__ __forceinline__ float quick_threshold(FS& S, float a1, float a2, floa
         if (run < need && need <= run + c[j]) { S.q_step = lane * PL + j; S.q_before = run; S.q_through = run + c[j]; }
         run += c[j];
       }
-      // (a divided step may have lost a value to rounding: its lower end then)
-      if (lane == 63 && run < need) { S.q_step = QUICK_NB - 1; S.q_before = run; S.q_through = 0u; }
     }
     __syncthreads();
     const int b = __builtin_amdgcn_readfirstlane(S.q_step);
-    const unsigned through = (unsigned)__builtin_amdgcn_readfirstlane((int)S.q_through), before = (unsigned)__builtin_amdgcn_readfirstlane((int)S.q_before);
-    const float step = (hi - lo) * (1.0f / (float)QUICK_NB);
-    const float low = b == QUICK_NB - 1 ? lo : hi - (float)(b + 1) * step;
+    const unsigned through = (unsigned)__builtin_amdgcn_readfirstlane((int)S.q_through);
+    const bool fine = through <= need + need / 4u + 4u;
     // a little lower than the step's end, so that values there are certified
-    if (through <= need + need / 4u + 4u || round == QUICK_ROUNDS - 1) return fmaxf(low - 0.05f * step - fabsf(low) * 1e-6f, LOWEST);
-    hi = hi - (float)b * step; lo = low; acc = before;
+    if (!by_key) {
+      const float step = (hi - lo) * (1.0f / (float)QUICK_NB);
+      float low = b == QUICK_NB - 1 ? lo : hi - (float)(b + 1) * step;
+      low = low - 0.05f * step - fabsf(low) * 1e-6f - 1e-30f;
+      if (fine) return fmaxf(low, LOWEST);
+      klo = fkey(low);
+      khi = max(fkey(hi - (float)b * step), klo);
+      by_key = true;
+    } else {
+      khi -= (uint32_t)b << sh;
+      if (khi - klo >= (1u << sh)) klo = khi - ((1u << sh) - 1u);
+      const float low = keyf(klo);
+      if (fine || sh == 0) return fmaxf(low - fabsf(low) * 1e-6f - 1e-30f, LOWEST);
+    }
+    acc = (unsigned)__builtin_amdgcn_readfirstlane((int)S.q_before);
+    in1 = in1 && s1 == b; in2 = in2 && s2 == b; in3 = in3 && s3 == b;
   }
 }
 

@@ -1,0 +1,58 @@
+"""Greedy and top-k rows whose large or finite logits lie where a sample of the row misjudges them, against the oracle:
+the candidate list still holds them, no row is left to the general kernel.  Few rows (1024 threads each) and more than
+the compute units (512 threads)."""
+import numpy as np
+import pytest
+
+import parity_util as P
+from paper_2512_00719_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+TOP_K = [1, 5, 20, 50, 100, 300]
+SHAPES = [(151_936, "bf16"), (128_256, "f32"), (262_144, "bf16")]
+
+
+def _check(name, make_row, V, dtype, B, history=0):
+    """make_row(rng, b) -> V float32 logits.  Every seventh row is greedy; the oracle decides a sample of the rows."""
+    rng = np.random.default_rng(V + B + len(name))
+    bits = np.empty((B, V), np.uint16 if dtype == "bf16" else np.float32)
+    for b in range(B):
+        z = np.asarray(make_row(rng, b), np.float32)
+        bits[b] = synth.f32_to_bf16_bits(z) if dtype == "bf16" else z
+    temperature = np.where(np.arange(B) % 7 == 6, 0.0, rng.choice([0.6, 1.0, 1.3], B)).astype(np.float32)
+    params = synth.make_params(B, temperature=temperature, top_k=np.resize(np.array(TOP_K, np.int32), B),
+                               top_p=np.resize(np.array([1.0, 0.9, 0.95, 1.0], np.float32), B), rep_penalty=1.1 if history else 1.0,
+                               freq_penalty=0.1 if history else 0.0, n_prompt=history // 2)
+    w = synth.Workload(name, B, V, dtype, bits, params, np.arange(B + 1, dtype=np.int64) * history, rng.integers(0, V, B * history).astype(np.int32))
+    ids, dg = P.run_gpu(w, 0)
+    assert not (dg["flags"] & binding.DIAG_ERROR).any()
+    rows = sorted(set(range(min(B, 14))) | set(range(0, B, 41)))
+    P.compare(ids[rows], dg[rows], P.run_oracle(w, 0, rows=rows), range(len(rows)))
+    handed = np.flatnonzero(dg["flags"] & binding.DIAG_GENERAL)
+    assert handed.size == 0, f"{handed.size} rows left to the general kernel, top-k {sorted(set(params['top_k'][handed]))}"
+
+
+def _profile(V):
+    return (-1.1 * np.log(np.arange(1, V + 1))).astype(np.float32)
+
+
+def _noise(rng, n, sigma):
+    return rng.standard_normal(n, dtype=np.float32) * np.float32(sigma)
+
+
+@pytest.mark.parametrize("V,dtype", SHAPES)
+@pytest.mark.parametrize("B", [14, 270])
+@pytest.mark.parametrize("masked", ["tail 0.07", "tail 0.5", "random 0.5", "random 0.95"])
+def test_columns_masked_with_the_lowest_value(V, dtype, B, masked):
+    """The lowest finite value (a row in three: another large negative one) among the sample's values."""
+    kind, share = masked.split()
+    base = _profile(V)
+    lowest = synth.bf16_bits_to_f32(np.array([0xFF7F], np.uint16))[0] if dtype == "bf16" else np.finfo(np.float32).min
+
+    def row(rng, b):
+        z = base[rng.permutation(V)] + _noise(rng, V, 1.5)
+        where = np.arange(V) >= int(V * (1.0 - float(share))) if kind == "tail" else rng.random(V, dtype=np.float32) < float(share)
+        return np.where(where, np.float32(-1e30) if b % 3 == 2 else lowest, z)
+
+    _check(masked, row, V, dtype, B, history=200 if kind == "random" else 0)
