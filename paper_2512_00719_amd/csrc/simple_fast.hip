@@ -10,8 +10,8 @@
 //             never materialised; a column's penalty is looked up only where its bit is set, so
 //             unpenalised columns are never touched (column-wise penalties, section 5.2).
 //   sample    every wave's first tiles (history columns masked) give, by counts in equal steps or, where the row's
-//             masses are relative to it, by wave-ballot bisection, a
-//             value g that is expected to admit a small multiple of the requested prefix length.
+//             masses are relative to it, by wave-ballot bisection, a value g that is expected to admit a small
+//             multiple of the requested prefix length, wherever in the row its large logits lie.
 //   stream    one coalesced pass of 16-byte loads per lane over the raw logits.  Columns with
 //             z >= g go to an LDS candidate list that now occupies the history's region (penalties
 //             that only lower a logit keep z >= z', so nothing with z' >= g is missed); rows whose
@@ -79,26 +79,70 @@ __device__ __forceinline__ void sample_group(const typename Io<DT>::Raw& A, int 
   }
 }
 
-// The threshold of a row whose result does not depend on it (greedy rows, top-k rows): a value that about `need` of the
-// values the lanes kept of the sample (a1 >= a2 >= a3; -inf: none) reach, from counts in equal steps between the largest
-// and the smallest of them; a step that holds too many is divided again, in the order of the keys, as is a range too
-// wide for equal steps of the value (columns masked with the lowest finite value: divided by value, its upper step held
-// every real logit, and 191 to 270 of 270 such rows went to the general kernel).  `counts` (LDS) holds QUICK_NB zeros.  Sets
-// complete where fewer than `need` are finite.  The result is the same in every lane; barriers inside.
+// ---- the threshold of a row whose result does not depend on it (greedy rows, top-k rows) ----
+// From counts of the largest value of every lane in each of its wave's two tiles, whichever of two ranks is reached first:
+//   the k-th of them all: what lies there is certified, so the list holds k columns wherever in the row they stand;
+//   a rank that a sample of independent columns would give, counted over groups of lanes, of which each counts once: columns of
+//   one place (ids in order of frequency, a run of allowed ids) cannot fill it, however many they are.
+// (With the second rank alone, over the three largest values of every lane in one tile, the first tile of a vocabulary in
+// order of frequency filled it, the list held fewer than k columns and the general kernel took the row: 256 float32 rows
+// of 128,256 columns, top-k 50, 161.7 us a call, 41.9 so; 53.8 with the search by ballots.  Both ranks and both tiles cost
+// 0.8 us where every compute unit has a row, 256 bfloat16 rows of 151,936 columns 40.3 -> 41.1.)
+// Equal steps between the largest and the smallest value; a step that holds too many is divided again, in the order of the
+// keys, as is a range too wide for equal steps of the value (columns masked with the lowest finite value: divided by value, its
+// upper step held every real logit, and 191 to 270 of 270 such rows went to the general kernel).
 // (A bisection by ballots in every wave and one over all that they kept, 16 waves on one scalar unit: 8 us
-// of a row of 151,936 bfloat16 columns; 2.5 us so, half of it unpacking.)
+// of a row of 151,936 bfloat16 columns.)
+struct SampleRanks {
+  unsigned lanes, groups;  // the two ranks
+  int shift;               // lanes of a group, as a power of two; -1: a lane's two tiles are two groups
+  bool ok;                 // groups enough for the second one
+};
+// r: the rank of a sample of independent columns (see below), n_waves waves of it.  A wave's groups are about as many as
+// the keys it would hand over to a search by ballots, r / n_waves and three deviations, but not half of r, and in all
+// not fewer than 3/2 r; r columns then lie in G (1 - exp(-r / G)) of the G groups.
+__device__ __forceinline__ SampleRanks sample_ranks(unsigned k, unsigned r, int n_waves) {
+  const float r_w = (float)r / (float)n_waves, q = r_w + 3.0f * __builtin_amdgcn_sqrtf(r_w) + 2.0f;
+  int c = 4, bits = 2;
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const bool more = ((float)c * 1.1f <= q && 4u * (unsigned)c <= r) || 2u * (unsigned)(c * n_waves) < 3u * r;
+    c += more ? c : 0; bits += more ? 1 : 0;
+  }
+  const float G = (float)(c * n_waves);
+  SampleRanks R;  // (of the row, not of a lane)
+  R.ok = 2u * (unsigned)(c * n_waves) >= 3u * r;
+  R.lanes = (unsigned)__builtin_amdgcn_readfirstlane((int)k);
+  R.groups = (unsigned)__builtin_amdgcn_readfirstlane((int)ceilf(G * (1.0f - __expf(-(float)r * __builtin_amdgcn_rcpf(G)))));
+  R.shift = __builtin_amdgcn_readfirstlane(6 - bits);
+  return R;
+}
 constexpr int QUICK_BITS = 9, QUICK_NB = 1 << QUICK_BITS;
 static_assert(QUICK_NB == (int)SAMPLE_COUNTS, "the counters' room");
-constexpr float QUICK_SPAN = (float)QUICK_NB;  // steps of at most one; key steps end a search after four rounds whatever the values
-template <int NTHR>
-__device__ __forceinline__ float quick_threshold(FS& S, float a1, float a2, float a3, unsigned need, uint32_t* counts, bool& complete) {
-  constexpr int NWV = NTHR / 64;
+constexpr float QUICK_SPAN = 64.0f;  // steps of at most an eighth; key steps end a search after four rounds whatever the values
+constexpr int QUICK_FINE = 14;       // key steps of this many bits are a 512th of their value: wider ones are divided again
+// mA, mB: the lane's largest unpenalised value in each tile (-inf: none); fin: its wave's finite columns among those that
+// begin a 16-byte load.  `counts` (LDS) holds QUICK_NB zeros, the list `cap` columns.  Sets complete where the list may take
+// every finite column.  The result is the same in every lane; barriers inside.
+template <int NTHR, int EPL>
+__device__ __forceinline__ float quick_threshold(FS& S, float mA, float mB, unsigned fin, SampleRanks R, int V, unsigned cap, uint32_t* counts, bool& complete) {
+  constexpr int NWV = NTHR / 64, PER_LANE = EPL * UNR;
+  constexpr float SAMPLE = (float)(NTHR * PER_LANE * 2);
   const int lane = lane_id(), wave = wave_id();
+  const int gs = R.shift;
+  const bool apart = gs < 0;
+  float mG = fmaxf(mA, mB);  // the largest of the lane's group
+  if (gs > 0) mG = fmaxf(mG, dpp_move<DPP_XOR1, 0xF>(mG, mG));
+  if (gs > 1) mG = fmaxf(mG, dpp_move<DPP_XOR2, 0xF>(mG, mG));
+  if (gs > 2) mG = fmaxf(mG, dpp_move<DPP_HALF_MIRROR, 0xF>(mG, mG));
+  if (gs > 3) mG = fmaxf(mG, dpp_move<DPP_MIRROR, 0xF>(mG, mG));
+  bool inA = mA > -INFINITY, inB = mB > -INFINITY;
+  bool inG = !apart && mG > -INFINITY && (lane & ((1 << max(gs, 0)) - 1)) == 0;  // (counted by its first lane)
   {
-    const unsigned have = (unsigned)(__popcll(__ballot(a1 > -INFINITY)) + __popcll(__ballot(a2 > -INFINITY)) + __popcll(__ballot(a3 > -INFINITY)));
-    const float last = a3 > -INFINITY ? a3 : a2 > -INFINITY ? a2 : a1 > -INFINITY ? a1 : INFINITY;
-    const float top = wave_max(a1), low = -wave_max(-last);
-    if (lane == 0) { S.wmax[wave] = top; S.r32a[wave] = __float_as_uint(low); S.wcnt[wave] = have; }
+    const unsigned every = (unsigned)(__popcll(__ballot(inA)) + __popcll(__ballot(inB)));
+    const unsigned groups = apart ? every : (unsigned)__popcll(__ballot(inG));
+    const float top = wave_max(fmaxf(mA, mB)), low = -wave_max(-fminf(inA ? mA : INFINITY, inB ? mB : INFINITY));
+    if (lane == 0) { S.wmax[wave] = top; S.r32a[wave] = __float_as_uint(low); S.r32b[wave] = fin; S.wcnt[wave] = every | groups << 16; }
   }
   __syncthreads();
   float hi = -INFINITY, lo = INFINITY;
@@ -107,12 +151,33 @@ __device__ __forceinline__ float quick_threshold(FS& S, float a1, float a2, floa
   for (int w = 0; w < NWV; ++w) { hi = fmaxf(hi, S.wmax[w]); lo = fminf(lo, __uint_as_float(S.r32a[w])); total += S.wcnt[w]; }
   hi = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(hi)));
   lo = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(lo)));
-  complete = __builtin_amdgcn_readfirstlane(total < need ? 1 : 0) != 0;
-  if (complete) return LOWEST;
-  unsigned acc = 0u;  // values above those that are still in question
+  total = (unsigned)__builtin_amdgcn_readfirstlane((int)total);
+  unsigned need = R.lanes;
+  const unsigned need_g = R.groups;
+  auto reached = [&](unsigned n) { return (n & 0xFFFFu) >= need || (n >> 16) >= need_g; };
+  if (!reached(total)) {
+    // Few finite columns in the sample.  The list takes all there are, if they fit by the sample's share of them or,
+    // should they be neighbours, a run of them that fits touches no more waves' tiles; else a share of them that
+    // leaves between k and `cap` whether they number what was seen or what that stands for.
+    unsigned finite = 0u, waves = 0u;
+    {
+      const unsigned f = lane < NWV ? S.r32b[lane] : 0u;
+      finite = wave_sum(f); waves = (unsigned)__popcll(__ballot(f != 0u));
+    }
+    const float k = (float)need, seen = (float)finite * (float)EPL, ratio = (float)V / SAMPLE;
+    const float share = 1.8f * k / seen;
+    const bool between = 1.8f * k * ratio <= (float)cap && share * (float)PER_LANE <= 4.5f;  // (what a lane's largest value resolves)
+    complete = ((float)finite + 3.0f * sqrtf((float)finite) + 4.0f) * (float)EPL * ratio <= (float)cap ||
+               (!between && ((float)waves - 1.0f) * (float)V <= ((float)cap + 2.0f * (float)(64 * PER_LANE)) * (float)NWV);
+    complete = __builtin_amdgcn_readfirstlane(complete ? 1 : 0) != 0;
+    if (complete) return LOWEST;
+    const float x = (float)PER_LANE * (between ? share : 2.0f * k / (seen * ratio));
+    need = max(1u, (unsigned)ceilf((float)(total & 0xFFFFu) * (1.0f - __expf(-x))));
+    need = (unsigned)__builtin_amdgcn_readfirstlane((int)need);
+  }
+  unsigned acc = 0u;  // values above those that are still in question; groups from bit 16
   bool by_key = !(hi - lo <= QUICK_SPAN);
   uint32_t khi = fkey(hi), klo = fkey(lo);
-  bool in1 = a1 > -INFINITY, in2 = a2 > -INFINITY, in3 = a3 > -INFINITY;
 #pragma unroll 1
   for (;;) {
     const float scale = (float)QUICK_NB / fmaxf(hi - lo, 1e-30f);
@@ -120,10 +185,11 @@ __device__ __forceinline__ float quick_threshold(FS& S, float a1, float a2, floa
     auto step_of = [&](float v) -> int {  // (monotone in the value; what rounding puts beyond an end belongs to its step)
       return by_key ? (int)((khi - min(max(fkey(v), klo), khi)) >> sh) : (int)fminf((hi - v) * scale, (float)(QUICK_NB - 1));
     };
-    const int s1 = step_of(a1), s2 = step_of(a2), s3 = step_of(a3);
-    if (in1) atomicAdd(&counts[s1], 1u);
-    if (in2) atomicAdd(&counts[s2], 1u);
-    if (in3) atomicAdd(&counts[s3], 1u);
+    const int sA = step_of(mA), sB = step_of(mB), sG = step_of(mG);
+    const unsigned one = apart ? 0x10001u : 1u;
+    if (inA) atomicAdd(&counts[sA], one);
+    if (inB) atomicAdd(&counts[sB], one);
+    if (inG) atomicAdd(&counts[sG], 0x10000u);
     __syncthreads();
     if (wave == 0) {
       constexpr int PL = QUICK_NB / 64;
@@ -133,14 +199,15 @@ __device__ __forceinline__ float quick_threshold(FS& S, float a1, float a2, floa
       unsigned run = acc + wave_incl_scan(loc) - loc;
 #pragma unroll
       for (int j = 0; j < PL; ++j) {
-        if (run < need && need <= run + c[j]) { S.q_step = lane * PL + j; S.q_before = run; S.q_through = run + c[j]; }
+        if (!reached(run) && reached(run + c[j])) { S.q_step = lane * PL + j; S.q_before = run; S.q_through = run + c[j]; }
         run += c[j];
       }
     }
     __syncthreads();
     const int b = __builtin_amdgcn_readfirstlane(S.q_step);
     const unsigned through = (unsigned)__builtin_amdgcn_readfirstlane((int)S.q_through);
-    const bool fine = through <= need + need / 4u + 4u;
+    auto close = [](unsigned n, unsigned want) { return n >= want && n <= want + want / 4u + 4u; };
+    const bool fine = close(through & 0xFFFFu, need) || close(through >> 16, need_g);
     // a little lower than the step's end, so that values there are certified
     if (!by_key) {
       const float step = (hi - lo) * (1.0f / (float)QUICK_NB);
@@ -154,10 +221,10 @@ __device__ __forceinline__ float quick_threshold(FS& S, float a1, float a2, floa
       khi -= (uint32_t)b << sh;
       if (khi - klo >= (1u << sh)) klo = khi - ((1u << sh) - 1u);
       const float low = keyf(klo);
-      if (fine || sh == 0) return fmaxf(low - fabsf(low) * 1e-6f - 1e-30f, LOWEST);
+      if ((fine && sh <= QUICK_FINE) || sh == 0) return fmaxf(low - fabsf(low) * 1e-6f - 1e-30f, LOWEST);
     }
     acc = (unsigned)__builtin_amdgcn_readfirstlane((int)S.q_before);
-    in1 = in1 && s1 == b; in2 = in2 && s2 == b; in3 = in3 && s3 == b;
+    inA = inA && sA == b; inB = inB && sB == b; inG = inG && sG == b;
   }
 }
 
@@ -708,6 +775,11 @@ __device__ __forceinline__ int finalize_long(FS& S, const RowCfg& R, unsigned n,
   return (S.out_id >= 0) ? FIN_DONE : FIN_PENDING;
 }
 
+// History entry i (fewer than 2^16 of them: an offset of 32 bits, one register an entry instead of two).
+__device__ __forceinline__ int hist_at(const int32_t* h, int i) {
+  return *as_global(reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(h) + (uint32_t)(i * 4)));
+}
+
 // The penalties of a row's listed columns, without its tables: the listed columns go to a hash table (a row listed
 // whole has a counter per column), the history's ids look themselves up in it and count, then each column takes what was
 // counted for it.  Work goes with the list and the history; the tables go with the vocabulary too (mask cleared, scanned into a
@@ -888,6 +960,8 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   if (!whole && NWV > 4) for (int i = tid; i < QUICK_NB; i += NTHR) samp[i] = 0u;  // (the sample's counts: see quick_threshold)
   // ---- loads first: history ids, then this wave's two sample tiles ----
   const int32_t* hist = rh.ids;
+  // (by a 64-bit place where the row is listed whole: 4 rows of 1024 columns 14.7 us a call, 15.0 to 15.2 with the other)
+  auto hist_entry = [&](int i) -> int { return WHOLE ? hist[i] : hist_at(hist, i); };
   // With a state the tables come ready-made from the row's slot (section 5.2: carried from step to
   // step, not rebuilt): `whole` = mask, rank directory and counts, else the mask alone.  Ends with a barrier.
   auto load_tables = [&](bool whole) {
@@ -910,7 +984,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   {
     int ids[IDR];
 #pragma unroll
-    for (int j = 0; j < IDR; ++j) { const int i = tid + j * NTHR; ids[j] = (!whole && h_active && !stateful && i < nnz) ? hist[i] : -1; }
+    for (int j = 0; j < IDR; ++j) { const int i = tid + j * NTHR; ids[j] = (!whole && h_active && !stateful && i < nnz) ? hist_entry(i) : -1; }
     if (wave == NWV - 1) {  // (one wave of the row, for all)
       double u[3];
       row_uniforms(a.seed, a.row_offset + (uint64_t)row, a.step, u);
@@ -938,7 +1012,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
       else {
         int ids2[IDR];
 #pragma unroll
-        for (int j = 0; j < IDR; ++j) { const int i = tid + j * NTHR; ids2[j] = (i < nnz) ? hist[i] : -1; }
+        for (int j = 0; j < IDR; ++j) { const int i = tid + j * NTHR; ids2[j] = (i < nnz) ? hist_entry(i) : -1; }
         unsigned own;
         build_history<NTHR>(S, H, ids2, hist, nnz, rh.n_prompt, V, own);
       }
@@ -970,11 +1044,42 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
 
   bool complete = whole;  // the list takes every finite column
   if (!whole) {
-  // ---- threshold from the sample: three largest unpenalised values per lane ----
-  float a1 = -INFINITY, a2 = -INFINITY, a3 = -INFINITY;
+  // ---- threshold from the sample (its unpenalised values) ----
+  // rank in the sample whose value leaves, with high probability, >= k_sel columns above it in the row
+  const float m_exp = (float)k_sel * (float)(NWV * 2 * T) / (float)V;
+  const unsigned r_samp = (unsigned)ceilf(1.15f * m_exp + 3.2f * sqrtf(m_exp) + 3.5f);
+  const SampleRanks ranks = sample_ranks((unsigned)k_sel, r_samp, NWV);
+  // Rows that the list alone decides: any value that admits enough columns serves, and with eight waves and more it
+  // comes from counts.  (With four waves the search by ballots is the shorter one: 1024 float32 rows of 128,256
+  // columns 201.1 against 202.6 us a call.  The other rows' masses are rounded relative to the threshold, so theirs is
+  // kept as it always was, to the bit: sums of the same columns do not depend on the build.)
+  const bool quick = NWV > 4 && (R.greedy || (R.k_on && !big_k) || R.p_le0) && ranks.ok;
+  // (either branch takes copies of the tiles: the compiler unpacks them ahead of both otherwise, into registers that then spill)
+  if (quick) {
+    float m[2] = {-INFINITY, -INFINITY};
+    unsigned fin = 0u;
+    auto take_group = [&](const Raw& X, int idx0, float& mx) {
+      float z[EPL];
+      Raw Y = X;
+      asm volatile("" : "+v"(Y));
+      sample_group<DT>(Y, idx0, H, z);
+      fin += (unsigned)__popcll(__ballot(z[0] > -INFINITY));
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) mx = fmaxf(mx, z[e]);  // (a NaN is ignored)
+    };
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) take_group(A[u], t0 * T + u * 64 * EPL + lane * EPL, m[0]);
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) take_group(Bf[u], (t0 + 1) * T + u * 64 * EPL + lane * EPL, m[1]);
+    C.g = quick_threshold<NTHR, EPL>(S, m[0], m[1], fin, ranks, V, (unsigned)a.F.list_cap, samp, complete);
+    C.y_g = R.greedy ? C.g : C.g / R.tau;
+  } else {
+  float a1 = -INFINITY, a2 = -INFINITY, a3 = -INFINITY;  // three largest values per lane
   auto take_group = [&](const Raw& X, int idx0) {
     float z[EPL];
-    sample_group<DT>(X, idx0, H, z);
+    Raw Y = X;
+    asm volatile("" : "+v"(Y));
+    sample_group<DT>(Y, idx0, H, z);
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {  // sorted insertion: the median of two neighbours and the new value is the lower one's successor
       a3 = __builtin_amdgcn_fmed3f(a2, a3, z[e]);
@@ -984,24 +1089,8 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   };
 #pragma unroll
   for (int u = 0; u < UNR; ++u) take_group(A[u], t0 * T + u * 64 * EPL + lane * EPL);
-  // Rows that the list alone decides: any value that admits enough columns serves, and with eight waves and more
-  // one tile each is sample enough.  (With four waves the search by ballots is the shorter one: 1024 float32 rows of 128,256
-  // columns 201.1 against 202.6 us a call.  The other rows' masses are rounded relative to the threshold, so theirs is
-  // kept as it always was, to the bit: sums of the same columns do not depend on the build.)
-  const float m_quick = (float)k_sel * (float)(NWV * T) / (float)V;
-  const unsigned r_quick = (unsigned)ceilf(1.15f * m_quick + 3.2f * sqrtf(m_quick) + 3.5f);
-  const bool quick = NWV > 4 && (R.greedy || (R.k_on && !big_k) || R.p_le0) && r_quick <= (unsigned)NTHR / 2u;
-  if (!quick) {
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) take_group(Bf[u], (t0 + 1) * T + u * 64 * EPL + lane * EPL);
-  }
-  if (quick) {
-    C.g = quick_threshold<NTHR>(S, a1, a2, a3, r_quick, samp, complete);
-    C.y_g = R.greedy ? C.g : C.g / R.tau;
-  } else {
-  // rank in the sample whose value leaves, with high probability, >= k_sel columns above it in the row
-  const float m_exp = (float)k_sel * (float)(NWV * 2 * T) / (float)V;
-  const unsigned r_samp = (unsigned)ceilf(1.15f * m_exp + 3.2f * sqrtf(m_exp) + 3.5f);
+  for (int u = 0; u < UNR; ++u) take_group(Bf[u], (t0 + 1) * T + u * 64 * EPL + lane * EPL);
   {
     const float r_w = (float)r_samp / (float)NWV;
     const unsigned q = min((unsigned)(SPW * 3 / 4), (unsigned)ceilf(r_w + 3.0f * sqrtf(r_w) + 2.0f));
@@ -1148,9 +1237,10 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
   }
   // the epilogue rebuilds the history tables: fetch the ids while the other waves finish
-  int ids[IDR];
+  int ids[IDR], tid_again = tid;  // (formed again: the entries' places, kept from the first fetch, spilled others)
+  if constexpr (!WHOLE) asm volatile("" : "+v"(tid_again));
 #pragma unroll
-  for (int j = 0; j < IDR; ++j) { const int i = tid + j * NTHR; ids[j] = (h_active && (!stateful || R.need_sum) && i < nnz) ? hist[i] : -1; }
+  for (int j = 0; j < IDR; ++j) { const int i = tid_again + j * NTHR; ids[j] = (h_active && (!stateful || R.need_sum) && i < nnz) ? hist_entry(i) : -1; }
   // ragged tail, element by element
   for (int idx = nfull * T + tid; idx < V; idx += NTHR) {
     const float zz = Io<DT>::one(rowp + idx);

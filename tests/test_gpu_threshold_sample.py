@@ -13,7 +13,7 @@ TOP_K = [1, 5, 20, 50, 100, 300]
 SHAPES = [(151_936, "bf16"), (128_256, "f32"), (262_144, "bf16")]
 
 
-def _check(name, make_row, V, dtype, B, history=0):
+def _check(name, make_row, V, dtype, B, history=0, top_k=TOP_K):
     """make_row(rng, b) -> V float32 logits.  Every seventh row is greedy; the oracle decides a sample of the rows."""
     rng = np.random.default_rng(V + B + len(name))
     bits = np.empty((B, V), np.uint16 if dtype == "bf16" else np.float32)
@@ -21,7 +21,7 @@ def _check(name, make_row, V, dtype, B, history=0):
         z = np.asarray(make_row(rng, b), np.float32)
         bits[b] = synth.f32_to_bf16_bits(z) if dtype == "bf16" else z
     temperature = np.where(np.arange(B) % 7 == 6, 0.0, rng.choice([0.6, 1.0, 1.3], B)).astype(np.float32)
-    params = synth.make_params(B, temperature=temperature, top_k=np.resize(np.array(TOP_K, np.int32), B),
+    params = synth.make_params(B, temperature=temperature, top_k=np.resize(np.array(top_k, np.int32), B),
                                top_p=np.resize(np.array([1.0, 0.9, 0.95, 1.0], np.float32), B), rep_penalty=1.1 if history else 1.0,
                                freq_penalty=0.1 if history else 0.0, n_prompt=history // 2)
     w = synth.Workload(name, B, V, dtype, bits, params, np.arange(B + 1, dtype=np.int64) * history, rng.integers(0, V, B * history).astype(np.int32))
@@ -56,3 +56,46 @@ def test_columns_masked_with_the_lowest_value(V, dtype, B, masked):
         return np.where(where, np.float32(-1e30) if b % 3 == 2 else lowest, z)
 
     _check(masked, row, V, dtype, B, history=200 if kind == "random" else 0)
+
+
+@pytest.mark.parametrize("V,dtype", SHAPES + [(50_001, "f32")])
+@pytest.mark.parametrize("B", [14, 270])
+@pytest.mark.parametrize("order", ["frequency", "reversed", "blocks"])
+def test_ids_in_order_of_frequency(V, dtype, B, order):
+    """As a trained vocabulary has them: the first tile of a row holds most of its large logits."""
+    base = _profile(V)
+
+    def row(rng, b):
+        if order == "blocks":  # in order of frequency by thousands, any order inside
+            return base[np.lexsort((rng.random(V, dtype=np.float32), np.arange(V) // 1000))] + _noise(rng, V, 1.5)
+        return (base if order == "frequency" else base[::-1]) + _noise(rng, V, 1.5)
+
+    _check(order, row, V, dtype, B, history=200 if order == "blocks" else 0)
+
+
+@pytest.mark.parametrize("V,dtype", SHAPES)
+@pytest.mark.parametrize("B", [14, 270])
+@pytest.mark.parametrize("allowed,runs", [(300, 1), (1000, 1), (3000, 1), (6000, 1), (3200, 100)])
+def test_runs_of_allowed_ids(V, dtype, B, allowed, runs):
+    """Allow-lists of neighbouring ids, at any place of the row; -inf elsewhere."""
+    def row(rng, b):
+        z = np.full(V, -np.inf, np.float32)
+        n = allowed // runs
+        for start in rng.choice(V // n, runs, replace=False) * n if runs > 1 else [rng.integers(0, V - n)]:
+            z[start:start + n] = _noise(rng, n, 2.0)
+        return z
+
+    _check(f"runs-{allowed}-{runs}", row, V, dtype, B, top_k=TOP_K if allowed > 1000 else TOP_K[:-1])
+
+
+@pytest.mark.parametrize("V,dtype", [(128_256, "f32"), (151_936, "bf16")])
+@pytest.mark.parametrize("B", [14, 270])
+def test_a_raised_band(V, dtype, B):
+    """Three thousand neighbouring ids far above the rest, which is finite."""
+    def row(rng, b):
+        z = _noise(rng, V, 1.0)
+        start = int(rng.integers(0, V - 3000))
+        z[start:start + 3000] += np.float32(8.0)
+        return z
+
+    _check("band", row, V, dtype, B)
