@@ -524,17 +524,42 @@ __device__ __forceinline__ void decide_block(FS& S, const RowCfg& R, const Liste
   }
   __syncthreads();
   const int bd = S.bd;
-  for (unsigned r = p0; r < min(p1, ns); ++r) {
-    const u64 e = entries[r];
-    if ((int)(entry_id(e) >> ishift) != bd || entry_mass(e) == 0ull) continue;
-    if (use_hot && (hot_bit(hot_bits, entry_id(e)) != 0u) != pick_hot) continue;
-    const unsigned slot = atomicAdd(&S.memb, 1u);
-    if (slot < (unsigned)MEMB2) { mid[slot] = entry_id(e); mw[slot] = entry_mass(e); }
+  // this thread's entries of the drawn class with a mass in range `to` of ids, ranges of 1 << width ids
+  auto each = [&](int width, int to, auto&& f) {
+    for (unsigned r = p0; r < min(p1, ns); ++r) {
+      const u64 e = entries[r];
+      if ((int)(entry_id(e) >> width) != to || entry_mass(e) == 0ull) continue;
+      if (use_hot && (hot_bit(hot_bits, entry_id(e)) != 0u) != pick_hot) continue;
+      f(e);
+    }
+  };
+  auto gather = [&](int width, int to) {
+    each(width, to, [&](u64 e) {
+      const unsigned slot = atomicAdd(&S.memb, 1u);
+      if (slot < (unsigned)MEMB2) { mid[slot] = entry_id(e); mw[slot] = entry_mass(e); }
+    });
+    __syncthreads();
+  };
+  gather(ishift, bd);
+  if (S.memb > (unsigned)MEMB2) {  // neighbouring ids (a run of allowed ones, say): the range is divided into as many again
+    // (Left to the general kernel: 14 bfloat16 rows of 151,936 columns, 500 neighbouring ones allowed, top-k 1024, 238 us a
+    // call; 37.5 so.)
+    static_assert(FAST_MAX_V <= NBF * NBF * MEMB2, "a divided range holds no more ids than there is room for");
+    const int fshift = max(0, ishift - NBF_BITS), f0 = bd << (ishift - fshift);
+    for (int i = tid; i < NBF; i += NTHR) fmass[i] = 0ull;
+    __syncthreads();
+    each(ishift, bd, [&](u64 e) { atomicAdd(&fmass[(int)(entry_id(e) >> fshift) - f0], entry_mass(e)); });
+    if (tid == 0) S.memb = 0u;
+    __syncthreads();
+    const u64 m = (tid < NBF) ? fmass[tid] : 0ull, before = S.mab_d;
+    u64 ex, all;
+    blk_excl_scan2<NWV>(S, 0u, m, z0, ex, z1, all);
+    if (m > 0ull && before + ex <= tfix && before + ex + m > tfix) { S.bd = f0 + tid; S.mab_d = before + ex; }
+    __syncthreads();
+    gather(fshift, S.bd);
   }
-  __syncthreads();
   const unsigned nm = S.memb;
-  if (nm > (unsigned)MEMB2) rc = FIN_PENDING;  // (a range of ids with hundreds of survivors: the general kernel)
-  else if ((unsigned)tid < nm && rc == FIN_DONE) {
+  if ((unsigned)tid < nm && rc == FIN_DONE) {
     unsigned dummy;
     const u64 G = S.mab_d + sum_where<false>(mid, mw, nm, mid[tid], dummy);
     if (G > tfix && G - mw[tid] <= tfix) { S.out_id = (int)mid[tid]; S.out_w = mw[tid]; }

@@ -35,3 +35,25 @@ def test_list_lengths(V, dtype, n, values, hot):
         ids, dg = P.run_gpu(w, step)
         assert not (dg["flags"] & binding.DIAG_ERROR).any()
         P.compare(ids, dg, P.run_oracle(w, step), range(B))
+
+
+@pytest.mark.parametrize("V,dtype", [(50_000, "f32"), (151_936, "bf16"), (262_145, "f32"), (500_001, "bf16")])
+@pytest.mark.parametrize("n", [256, 257, 300, 511, 512, 513, 1100, 2048])
+@pytest.mark.parametrize("hot", [False, True])
+def test_neighbouring_ids(V, dtype, n, hot):
+    """Survivors side by side: more of them in the draw's range of ids than are resolved at once."""
+    B = 12
+    rng = np.random.default_rng(V + n)
+    z = np.full((B, V), -np.inf, np.float32)
+    for b in range(B):
+        start = [0, V - n, int(rng.integers(0, V - n)), 1 << 15][b % 4]
+        start = min(start, V - n)
+        z[b, start:start + n] = rng.standard_normal(n) if b % 3 else rng.integers(0, 900, n) / 256.0
+    params = synth.make_params(B, temperature=np.resize(np.array([1.0, 2.0], np.float32), B), top_k=np.resize(np.array([1024, min(n, 1024), 0], np.int32), B),
+                               top_p=np.resize(np.array([1.0, 0.999, 0.9999], np.float32), B), min_p=np.resize(np.array([0.0, 0.0, 1e-4, 0.0], np.float32), B))
+    w = synth.Workload("neighbours", B, V, dtype, synth.f32_to_bf16_bits(z) if dtype == "bf16" else z, params, np.zeros(B + 1, np.int64),
+                       np.zeros(0, np.int32), hot_ids=np.sort(rng.choice(V, V // 3, replace=False)).astype(np.int32) if hot else None)
+    for step in range(2):
+        ids, dg = P.run_gpu(w, step)
+        assert not (dg["flags"] & (binding.DIAG_ERROR | binding.DIAG_GENERAL)).any(), params["top_k"][(dg["flags"] & binding.DIAG_GENERAL) > 0]
+        P.compare(ids, dg, P.run_oracle(w, step), range(B))

@@ -13,7 +13,7 @@ TOP_K = [1, 5, 20, 50, 100, 300]
 SHAPES = [(151_936, "bf16"), (128_256, "f32"), (262_144, "bf16")]
 
 
-def _check(name, make_row, V, dtype, B, history=0, top_k=TOP_K):
+def _check(name, make_row, V, dtype, B, history=0):
     """make_row(rng, b) -> V float32 logits.  Every seventh row is greedy; the oracle decides a sample of the rows."""
     rng = np.random.default_rng(V + B + len(name))
     bits = np.empty((B, V), np.uint16 if dtype == "bf16" else np.float32)
@@ -21,7 +21,7 @@ def _check(name, make_row, V, dtype, B, history=0, top_k=TOP_K):
         z = np.asarray(make_row(rng, b), np.float32)
         bits[b] = synth.f32_to_bf16_bits(z) if dtype == "bf16" else z
     temperature = np.where(np.arange(B) % 7 == 6, 0.0, rng.choice([0.6, 1.0, 1.3], B)).astype(np.float32)
-    params = synth.make_params(B, temperature=temperature, top_k=np.resize(np.array(top_k, np.int32), B),
+    params = synth.make_params(B, temperature=temperature, top_k=np.resize(np.array(TOP_K, np.int32), B),
                                top_p=np.resize(np.array([1.0, 0.9, 0.95, 1.0], np.float32), B), rep_penalty=1.1 if history else 1.0,
                                freq_penalty=0.1 if history else 0.0, n_prompt=history // 2)
     w = synth.Workload(name, B, V, dtype, bits, params, np.arange(B + 1, dtype=np.int64) * history, rng.integers(0, V, B * history).astype(np.int32))
@@ -85,7 +85,7 @@ def test_runs_of_allowed_ids(V, dtype, B, allowed, runs):
             z[start:start + n] = _noise(rng, n, 2.0)
         return z
 
-    _check(f"runs-{allowed}-{runs}", row, V, dtype, B, top_k=TOP_K if allowed > 1000 else TOP_K[:-1])
+    _check(f"runs-{allowed}-{runs}", row, V, dtype, B)
 
 
 @pytest.mark.parametrize("V,dtype", [(128_256, "f32"), (151_936, "bf16")])
