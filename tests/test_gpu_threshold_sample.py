@@ -13,7 +13,7 @@ TOP_K = [1, 5, 20, 50, 100, 300]
 SHAPES = [(151_936, "bf16"), (128_256, "f32"), (262_144, "bf16")]
 
 
-def _check(name, make_row, V, dtype, B, history=0):
+def _check(name, make_row, V, dtype, B, history=0, top_k=TOP_K):
     """make_row(rng, b) -> V float32 logits.  Every seventh row is greedy; the oracle decides a sample of the rows."""
     rng = np.random.default_rng(V + B + len(name))
     bits = np.empty((B, V), np.uint16 if dtype == "bf16" else np.float32)
@@ -21,7 +21,7 @@ def _check(name, make_row, V, dtype, B, history=0):
         z = np.asarray(make_row(rng, b), np.float32)
         bits[b] = synth.f32_to_bf16_bits(z) if dtype == "bf16" else z
     temperature = np.where(np.arange(B) % 7 == 6, 0.0, rng.choice([0.6, 1.0, 1.3], B)).astype(np.float32)
-    params = synth.make_params(B, temperature=temperature, top_k=np.resize(np.array(TOP_K, np.int32), B),
+    params = synth.make_params(B, temperature=temperature, top_k=np.resize(np.array(top_k, np.int32), B),
                                top_p=np.resize(np.array([1.0, 0.9, 0.95, 1.0], np.float32), B), rep_penalty=1.1 if history else 1.0,
                                freq_penalty=0.1 if history else 0.0, n_prompt=history // 2)
     w = synth.Workload(name, B, V, dtype, bits, params, np.arange(B + 1, dtype=np.int64) * history, rng.integers(0, V, B * history).astype(np.int32))
@@ -99,3 +99,21 @@ def test_a_raised_band(V, dtype, B):
         return z
 
     _check("band", row, V, dtype, B)
+
+
+def test_most_of_the_largest_in_the_sample():
+    """25 of a row's 50 largest columns in the sampled tiles (eight waves' first two; 13 are expected), each in another of
+    the 64 groups of eight lanes: the rank asked for lies beyond them."""
+    V, tile, waves = 128_256, 2048, 8
+    starts = [(w * (V // tile) // waves) * tile for w in range(waves)]
+    outside = np.setdiff1d(np.arange(V), np.concatenate([np.arange(s, s + 2 * tile) for s in starts]))
+
+    def row(rng, b):
+        z = _noise(rng, V, 1.0)
+        group = rng.choice(64, 25, replace=False)
+        lane = 8 * (group % 8) + rng.integers(0, 8, 25)
+        z[np.array(starts)[group // 8] + rng.integers(0, 2, 25) * tile + rng.integers(0, 4, 25) * 512 + lane * 8 + rng.integers(0, 8, 25)] = 20.0 + rng.random(25)
+        z[rng.choice(outside, 24, replace=False)] = 18.0 + rng.random(24)
+        return z
+
+    _check("crowded-sample", row, V, "bf16", 270, top_k=[50])
