@@ -816,11 +816,18 @@ __device__ __forceinline__ int hist_at(const int32_t* h, int i) {
 // compute unit to themselves: where several share one, the tables' lookups, all in flight at once, are hidden better than
 // the table's chains (4096 rows of 256,000 columns with 8192 ids, 512 threads: 947 us with the tables, 964 with this).
 // Entry j of this thread is list entry tid + j * NTHR; ids[j] is history entry tid + j * NTHR.  Barriers inside; one must follow.
-constexpr unsigned HASH_LIST_MAX = 512;  // listed columns (the table is half full then); longer lists cost more than the tables
+constexpr unsigned HASH_LIST_MAX = 192;  // listed columns
+// Fewer of them leave shorter chains for the ids that are not listed, most of a history.  Measured on 14 bfloat16 rows of
+// 151,936 columns, 200 float32 rows of 128,256 and 64 of 50,000, with tables less with the hash, us a call: 50 listed columns
+// 2.4 to 9.4 at 512 to 32,000 ids, 150 0.6 to 3.6 up to 12,000, 200 -0.1 to 3.2 up to 8192; 256 -1.2 to 0.1 at 8192, 350 -3.9 to
+// -2.8, 500 -15 to -9.  (A second, higher line for short histories, worth 2 us between 192 and 320 columns, had the compiler
+// write out the loops over the history twice and cost every such call 0.8.)
 static_assert(MAX_WHOLE * 4 <= FAST_REGION_MIN, "the counters fit the region");
 template <int NTHR, int PER, int NID, bool WHOLE>
 __device__ __forceinline__ void penalise_listed(FS& S, const Hist& H, float (&ez)[PER], const uint32_t (&eid)[PER], unsigned n, const int (&ids)[NID],
                                                 const int32_t* __restrict__ hist, int nnz, int n_prompt, int V, unsigned char* region) {
+  constexpr int ROUNDS = WHOLE ? PER : 1;
+  static_assert(HASH_LIST_MAX <= 1024, "a hashed list takes one round of the workgroups that hash it");
   const int tid = threadIdx.x;
   constexpr unsigned bits = 10u, slots = 1u << bits;
   uint32_t* count = reinterpret_cast<uint32_t*>(region);  // occurrences in the high half, generated ones in the low half
@@ -830,7 +837,7 @@ __device__ __forceinline__ void penalise_listed(FS& S, const Hist& H, float (&ez
   __syncthreads();
   if constexpr (!WHOLE) {
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
+    for (int j = 0; j < ROUNDS; ++j) {
       if ((unsigned)(j * NTHR) >= n) break;
       if ((unsigned)(tid + j * NTHR) < n) {  // (a column is listed once)
         uint32_t h = first(eid[j]);
@@ -878,7 +885,7 @@ __device__ __forceinline__ void penalise_listed(FS& S, const Hist& H, float (&ez
   if (bad) atomicOr(&S.flags, SIMPLE_DIAG_BAD_HISTORY_ID);
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
+  for (int j = 0; j < ROUNDS; ++j) {
     if ((unsigned)(j * NTHR) >= n) break;
     if ((unsigned)(tid + j * NTHR) >= n) continue;
     uint32_t h = eid[j];
