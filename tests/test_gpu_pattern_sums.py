@@ -11,6 +11,12 @@ pytestmark = pytest.mark.gpu
 
 # (a dyadic share of equal masses: the cut is exact in float64 sums and in the kernel's integers)
 CONTROLS = [dict(top_p=0.5), dict(top_p=0.875), dict(), dict(min_p=0.5), dict(top_p=0.5, temperature=0.5), dict(top_p=0.03125)]
+SMALLEST = 2.0 ** -14 * 1.015625  # the smallest magnitude with a bin of its own; 255 is the largest
+# No row's cut falls into the bins that zeros share, and with 12 as the maximum what these cost is below a 2^-28th of the
+# mass (e^-12 6.2e-5 = 3.8e-10), so that the kernel completes every one of them.
+ENDS = [[12.0, 12.0, SMALLEST, -SMALLEST, 0.0, -0.0, -255.0, -256.0],
+        [SMALLEST, -SMALLEST, -255.0, -256.0],  # masses of both inner ends within a cut's reach
+        [255.0, 254.0, SMALLEST, -SMALLEST, 0.0, -255.0]]
 
 
 @pytest.mark.parametrize("hot", [False, True])
@@ -22,8 +28,7 @@ def test_sums_at_their_limits(values, V, hot):
     z = np.empty((B, V), np.float32)
     for b in range(B):
         z[b] = {"equal": np.full(V, 3.0 if b % 2 else -3.0), "signs": rng.choice([1.5, -1.5], V),
-                # smallest and largest magnitudes with a bin of their own, zeros, the first one beyond the bins below
-                "ends": rng.choice(np.array([8.0, 8.0, 2.0 ** -14 * 1.015625, -(2.0 ** -14) * 1.015625, 0.0, -0.0, -255.0, -256.0], np.float32), V)}[values]
+                "ends": rng.choice(np.array(ENDS[b % len(ENDS)], np.float32), V)}[values]
     base = dict(temperature=1.0, top_p=1.0, min_p=0.0)
     cols = {k: np.array([c.get(k, v) for c in CONTROLS], np.float32) for k, v in base.items()}
     w = synth.Workload("sums", B, V, "bf16", synth.f32_to_bf16_bits(z), synth.make_params(B, **cols), np.zeros(B + 1, np.int64),
@@ -31,6 +36,5 @@ def test_sums_at_their_limits(values, V, hot):
     for step in range(2):
         ids, dg = P.run_gpu(w, step)
         assert not (dg["flags"] & binding.DIAG_ERROR).any()
-        if values != "ends":
-            assert ((dg["flags"] & binding.DIAG_PATTERN) > 0).all()
+        assert ((dg["flags"] & binding.DIAG_PATTERN) > 0).all()
         P.compare(ids, dg, P.run_oracle(w, step), range(B))
