@@ -89,7 +89,7 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   const uint32_t n_words = (uint32_t)((V + 31) / 32), n_pairs = (n_words + 1u) / 2u;
   // A short vocabulary is listed whole (beyond it a sample needs its two tiles per wave; bfloat16 rows of 8,193
   // to 16,383 columns have neither, and the general kernel serves them: listed whole, 4000 rows of 12,000
-  // columns took 907 us against its 874).  4 float32 rows of 1024 columns: 51 us in the general kernel, 23
+  // columns took 907 us against its 874).  4 float32 rows of 1024 columns: 51 us in the general kernel, 15
   // here; 1000 of 7000: 226 and 169.
   const bool whole = V <= (int64_t)MAX_WHOLE && V / tile < 8;
   uint32_t off = 0;
@@ -103,7 +103,10 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   const uint32_t tables = NBF * 12u + MEMB2 * 16u;           // bucket tables of the long-list epilogue
   uint32_t body = off < FAST_REGION_MIN ? FAST_REGION_MIN : off;
   if (whole && body < align16((uint32_t)V * 8u + tables)) body = align16((uint32_t)V * 8u + tables);
-  F.threads = ((int64_t)body + 3072 <= (int64_t)lds_limit / 4) ? 256 : 512;  // four workgroups per compute unit, static LDS included
+  // Four workgroups per compute unit, merge area and static LDS included.  (Tables of the last kilobyte that would still fit
+  // take 512 threads: with 256, 1024 float32 rows of 128,256 columns and 8600 ids took 230.8 us a call, 224.9 so; bfloat16
+  // rows of 151,936 columns and 6900 ids, whose lists then overflow, 460 and 234.)
+  F.threads = ((int64_t)body + 3072 <= (int64_t)lds_limit / 4) ? 256 : 512;
   if (V >= ((int64_t)1 << 18)) F.threads = 512;  // a sample of two tiles per wave: four waves' is too small a share of such rows
   if (B <= (int64_t)n_cu) F.threads = 1024;
   else if (B <= 2 * (int64_t)n_cu) F.threads = 512;

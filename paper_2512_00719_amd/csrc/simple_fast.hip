@@ -292,8 +292,9 @@ __device__ __forceinline__ u64 whole_row_mass(u64 total_m, unsigned n_unc, uint3
 // ---- the certified entries in the total order ----
 // What follows needs them sorted (value descending, id ascending), and only as many as the survivors can be: with
 // top-k the first k.  Short lists are ranked by counting, longer ones go to buckets linear in the tempered value and are
-// ranked among their bucket's members; no place depends on the order in which the waves appended.  A sorted entry is its
-// weight and its id in one word.  Bound: the latency of LDS and barriers, so their number is what was cut down: with the
+// ranked among their bucket's members.  No place depends on the order in which the waves appended, but for entries so far below
+// the maximum that they have no mass: those share the last bucket as they come, behind all others, where they add to no sum and
+// are never drawn.  A sorted entry is its weight and its id in one word.  Bound: the latency of LDS and barriers, so their number is what was cut down: with the
 // longer lists in bucket tables of masses and counts and the others' decisions on eight entries per lane, 4 float32 rows of
 // 1024 columns (top-k 50, top-p) took 22.8 us a call, 17.3 so; 4096 bfloat16 rows of 256,000 1011 and 973.
 constexpr int COUNT_MAX = 128;   // entries ranked by counting (several threads share an entry's comparisons)
@@ -313,7 +314,7 @@ __device__ __forceinline__ u64 entry_mass(u64 e) { return e >> ID_BITS; }
 __device__ __forceinline__ uint32_t entry_id(u64 e) { return (uint32_t)e & ((1u << ID_BITS) - 1u); }
 
 // n composites at the start of the region to sorted entries at SORT_OUT: an entry's place is the number of entries before
-// it, counted by 16, 4 or 2 neighbouring lanes.  S.memb counts those at or above key_thr.
+// it, counted by 16, 4 or 2 neighbouring lanes.  S.memb, zero on entry, receives the number of those at or above key_thr.
 template <int NTHR>
 __device__ __forceinline__ void sort_by_counting(FS& S, unsigned n, float y_max, uint32_t key_thr, unsigned char* region) {
   static_assert(2 * COUNT_MAX <= NTHR, "two threads per entry at least");
@@ -335,9 +336,9 @@ __device__ __forceinline__ void sort_by_counting(FS& S, unsigned n, float y_max,
   if (first) reinterpret_cast<u64*>(region + SORT_OUT)[r] = pack_entry(c, y_max);
 }
 
-// The same from this thread's entries (key 0: none; S.memb is n_all, the number of all threads'); with top-k only the
-// buckets down to the one that holds the k-th.  Returns the number of sorted entries, or 0 if they are too many or
-// too crowded.  The counters at SORT_BASE are zero.  Barriers inside.
+// The same from this thread's entries (key 0: none), n_all in all threads; with top-k only the buckets down to the one that
+// holds the k-th.  S.memb, zero on entry, receives the number of sorted entries at or above key_thr.  Returns the number of
+// sorted entries, or 0 if they are too many or too crowded.  The counters at SORT_BASE are zero.  Barriers inside.
 template <int NTHR, int PER>
 __device__ __forceinline__ unsigned sort_by_buckets(FS& S, const RowCfg& R, const uint32_t (&key)[PER], const uint32_t (&eid)[PER], unsigned n_all,
                                                     float y_max, uint32_t key_lo, uint32_t key_thr, unsigned char* region) {

@@ -1431,8 +1431,9 @@ __global__ __launch_bounds__(FT, 4) void wide_finish_kernel(const SampleArgs a) 
 
 
 hipError_t launch_wide(const SampleArgs& a, int dtype, hipStream_t st) {
-  // One resident round of workgroups each: six (bins) and five (classify) per compute unit fit by
-  // registers and LDS; a workgroup then takes a contiguous run of slices, mostly of one row.
+  // One resident round of workgroups each: five per compute unit fit by registers and LDS (four: the classifying kernel
+  // and the bins of float32 rows); a workgroup then takes a contiguous run of slices, mostly of one row.  The finishing kernel,
+  // two workgroups per compute unit by its LDS, takes a row at a time.
   const dim3 bins((unsigned)a.n_cu * 5u), cls((unsigned)a.n_cu * 4u), fin((unsigned)(a.B < 2 * a.n_cu ? a.B : 2 * a.n_cu)), blk(fast::WT), fblk(fast::FT);
   if (dtype == SIMPLE_F32) {
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<float, true>), cls, blk, 0, st, a);
