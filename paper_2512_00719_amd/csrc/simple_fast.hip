@@ -1365,22 +1365,22 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
 #pragma unroll
           for (int j = 0; j < IDR; ++j) if (tid + j * NTHR < nnz && claims(ids[j])) own |= 1u << j;
         }
-        float zr[IDR];
+        typename Io<DT>::Elem zr[IDR];  // (as loaded, all of them in flight: converted in its branch, each was waited for)
 #pragma unroll
-        for (int j = 0; j < IDR; ++j) zr[j] = ((own >> j) & 1u) ? Io<DT>::one(rowp + ids[j]) : 0.0f;
+        for (int j = 0; j < IDR; ++j) zr[j] = Io<DT>::raw(rowp + (((own >> j) & 1u) ? ids[j] : 0));
 #pragma unroll
-        for (int j = 0; j < IDR; ++j) if ((own >> j) & 1u) correct(zr[j], ids[j]);
+        for (int j = 0; j < IDR; ++j) if ((own >> j) & 1u) correct(Io<DT>::cvt(zr[j]), ids[j]);
         // entries beyond the registers, four at a time (their trips to memory overlap)
         for (int i0 = tid + IDR * NTHR; i0 < nnz; i0 += 4 * NTHR) {
-          int id4[4]; bool mine[4]; float z4[4];
+          int id4[4]; bool mine[4]; typename Io<DT>::Elem z4[4];
 #pragma unroll
           for (int k = 0; k < 4; ++k) id4[k] = (i0 + k * NTHR < nnz) ? hist[i0 + k * NTHR] : -1;
 #pragma unroll
           for (int k = 0; k < 4; ++k) mine[k] = claims(id4[k]);
 #pragma unroll
-          for (int k = 0; k < 4; ++k) z4[k] = mine[k] ? Io<DT>::one(rowp + id4[k]) : 0.0f;
+          for (int k = 0; k < 4; ++k) z4[k] = Io<DT>::raw(rowp + (mine[k] ? id4[k] : 0));
 #pragma unroll
-          for (int k = 0; k < 4; ++k) if (mine[k]) correct(z4[k], id4[k]);
+          for (int k = 0; k < 4; ++k) if (mine[k]) correct(Io<DT>::cvt(z4[k]), id4[k]);
         }
       }
       __syncthreads();
@@ -1435,9 +1435,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     u64 S_below_int = 0ull, M_list = 0ull, M_cert = 0ull;
     bool wide = false;
     if (C.need_sum) {
-      S_below_int = blk_sum_u64<NWV>(S, below_mass);
-      M_list = blk_sum_u64<NWV>(S, mlist);
-      M_cert = blk_sum_u64<NWV>(S, mcert);
+      blk_sum3<NWV>(S, below_mass, mlist, mcert, S_below_int, M_list, M_cert);
       const u64 target = (u64)__double2ull_ru((double)R.top_p * (double)(M_list + S_below_int));
       // (a column more than 2^21 above g: these sums say nothing, the sorted list does)
       wide = !R.minp_on && M_cert < target && !((S.flags >> 30) & 1u);
