@@ -42,10 +42,6 @@ using namespace fast;
 
 constexpr int PT = 512;        // threads per row
 constexpr int PNW = PT / 64;
-constexpr int PLO = 0x3882;    // smallest magnitude pattern with a bin of its own (just above 2^-14)
-constexpr int PHI = 0x4380;    // 256.0: magnitudes from here on are not handled
-constexpr int QMAX = PHI - PLO + 1;  // magnitude index: 0 merged, 1 .. QMAX - 1 one pattern each, QMAX too large
-constexpr int NMAG = QMAX + 1;
 constexpr int NB = 2 * NMAG;   // bins in descending value: positive patterns from the largest down, then negative ones
 constexpr int BPT = NB / PT;   // bins per thread in the cut phase
 static_assert(NB % PT == 0, "bins divide among the threads");
@@ -68,9 +64,6 @@ constexpr int CHAIN = 4;       // columns added before the sum goes to an intege
 static_assert((u64)CHAIN << CBIT <= 1ull << 52, "a sum of CHAIN entries is exact");
 static_assert((u64)(TILE / 64) << 44 < 1ull << CBIT, "a lane's masses of one tile stay below the count");
 static_assert(TILE / 64 < (1 << (64 - CBIT)), "a lane's columns of one tile fit the count");
-
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 // bin of a bit pattern (its 16 low bits)
 __device__ __forceinline__ int bin_of(uint32_t raw) {

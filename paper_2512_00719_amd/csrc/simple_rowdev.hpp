@@ -115,6 +115,14 @@ __device__ __forceinline__ unsigned lanes_before(u64 m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// bfloat16 patterns with an entry of their own in a table by pattern: magnitudes from 2^-14 to 2^8 (2814 per sign).
+constexpr int PLO = 0x3882;    // smallest such magnitude (just above 2^-14)
+constexpr int PHI = 0x4380;    // 256.0: magnitudes from here on have none
+constexpr int QMAX = PHI - PLO + 1;  // magnitude index: 0 smaller ones, 1 .. QMAX - 1 one pattern each, QMAX larger ones
+constexpr int NMAG = QMAX + 1;
+typedef short s16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
 // Row-wide state in static LDS.
 struct FS {
   unsigned cand_count, flags, kmax, kmin, memb;
@@ -377,6 +385,7 @@ constexpr uint32_t WS_TILES = 16384u;   // u64[2][256]: survivors' mass per tile
 constexpr uint32_t WS_SCAL = 20480u;    // u64 mass at or above g; u32 sure survivors; u32 boundary columns; u64 exact mass
                                         // of the row; u32 largest key of a tempered value; u32 columns at or above g;
                                         // u32 the cut's bin + 1 (0: none); (pad) u64 mass of the row by the bins
+constexpr uint32_t WS_ODD = WS_SCAL + 48u;  // u32[4]: bfloat16 rows' slices with values that have no entry in a table by pattern
 constexpr uint32_t WS_RL = 20544u;      // u64[RCAP]: columns of the boundary bin (value bits << 32 | id)
 constexpr uint32_t WS_HT = 53312u;      // the row's history tables as the single-pass kernel laid them out in LDS
 // [0, WS_RL) must be zero when a row is queued

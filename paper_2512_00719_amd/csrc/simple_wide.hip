@@ -56,8 +56,8 @@ namespace fast {
 constexpr int WT = 256;      // threads per workgroup
 constexpr int WNW = WT / 64;
 constexpr int SLC = 4096;    // columns per slice
-constexpr int ICAP = 1024;   // columns of the boundary bin one slice can always stage
-constexpr int LCAP = 2048;   // size of the stage: written out once fewer than ICAP places are free
+constexpr int ICAP = 512;    // places for boundary columns that a slice finds free in the stage (more go to the row's list one by one)
+constexpr int MAX_SLICES = FAST_MAX_V / SLC;
 static_assert(WS_HT == WIDE_SLOT_FIXED, "workspace slot size");
 static_assert(sizeof(WideRec) == 64, "queue record size");
 
@@ -118,7 +118,7 @@ constexpr int HCAP = 512;  // history columns of a slice that are spread over al
 struct SliceTabs {
   uint32_t bm[SLC / 32];
   uint32_t dir[SLC / 64 + 2];
-  uint16_t cnt[SLC];
+  uint16_t cnt[HCAP];   // counts of the first HCAP of them; the others' are read where they are needed
   float hz[HCAP];       // logit of the history column of rank j in the slice, as read
   uint16_t hcol[HCAP];  // its column, counted from the slice's first
 };
@@ -154,17 +154,22 @@ template <int NTHR>
 __device__ __forceinline__ void slice_counts(SliceTabs& T, const unsigned char* ws, const SampleArgs& a) {
   const uint16_t* gcnt = reinterpret_cast<const uint16_t*>(ws + WS_HT + a.F.cnt);
   const unsigned r0 = T.dir[0];
-  const unsigned nc = min(T.dir[SLC / 64] - r0, (unsigned)SLC);
+  const unsigned nc = min(T.dir[SLC / 64] - r0, (unsigned)HCAP);
   for (unsigned t = threadIdx.x; t < nc; t += NTHR) T.cnt[t] = as_global(gcnt)[r0 + t];
 }
+// The count of the slice's column of rank r in it.
+__device__ __forceinline__ uint32_t slice_count(const SliceTabs& T, const unsigned char* ws, const SampleArgs& a, unsigned r) {
+  if (r < (unsigned)HCAP) return (uint32_t)T.cnt[r];
+  return (uint32_t)as_global(reinterpret_cast<const uint16_t*>(ws + WS_HT + a.F.cnt))[T.dir[0] + min(r, (unsigned)SLC - 1u)];
+}
 // Z' of column c0 + o, whose mask bit is set.
-__device__ __forceinline__ float slice_value(float z, int o, const SliceTabs& T, const WideRow& W) {
+__device__ __forceinline__ float slice_value(float z, int o, const SliceTabs& T, const WideRow& W, const SampleArgs& a) {
   const int wl = o >> 5;
   const uint32_t word = T.bm[wl];
   unsigned r = T.dir[wl >> 1] - T.dir[0];
   if (wl & 1) r += (unsigned)__popc(T.bm[wl - 1]);
   r += (unsigned)__popc(word & ((1u << (o & 31)) - 1u));
-  return apply_penalties(z, (uint32_t)T.cnt[min(r, (unsigned)SLC - 1u)], W.rep, W.inv_rep, W.freq, W.pres);
+  return apply_penalties(z, slice_count(T, W.ws, a, r), W.rep, W.inv_rep, W.freq, W.pres);
 }
 __device__ __forceinline__ bool slice_bit(int o, const SliceTabs& T) { return (T.bm[o >> 5] >> (o & 31)) & 1u; }
 // The history columns of a slice, one mask word per thread.  Their logits and the slice's counts are
@@ -197,7 +202,7 @@ __device__ __forceinline__ void hist_fetch(HistPre<DT>& P, const SliceTabs& T, c
     }
   }
 }
-// The counts go to LDS (first WT of them from the registers, the rest from memory), and so do the
+// The counts of the first HCAP columns go to LDS (WT of them from the registers, the rest from memory), and so do the
 // logits and columns of the first HCAP history columns, by rank; a barrier must follow.
 template <typename DT>
 __device__ __forceinline__ void hist_stage(SliceTabs& T, const HistPre<DT>& P, const unsigned char* ws, const SampleArgs& a,
@@ -207,7 +212,7 @@ __device__ __forceinline__ void hist_stage(SliceTabs& T, const HistPre<DT>& P, c
   const unsigned r0 = T.dir[0];
   const unsigned nc = min(T.dir[SLC / 64] - r0, (unsigned)SLC);
   if ((unsigned)tid < nc) T.cnt[tid] = (uint16_t)P.cnt;
-  for (unsigned t = tid + WT; t < nc; t += WT) T.cnt[t] = as_global(gcnt)[r0 + t];
+  for (unsigned t = tid + WT; t < min(nc, (unsigned)HCAP); t += WT) T.cnt[t] = as_global(gcnt)[r0 + t];
   if (tid < SLC / 32) {
     uint32_t word = T.bm[tid];
     unsigned r = T.dir[tid >> 1] - r0 + ((tid & 1) ? (unsigned)__popc(T.bm[tid - 1]) : 0u);
@@ -228,7 +233,7 @@ __device__ __forceinline__ void hist_stage(SliceTabs& T, const HistPre<DT>& P, c
 // f(z', idx) for each history column of the slice, with its penalised value: the staged ones one per
 // thread, the rest (a slice with more than HCAP of them) by their mask word's thread.
 template <typename DT, typename F>
-__device__ __forceinline__ void hist_columns(const SliceTabs& T, const WideRow& W, const DT* rowp, int c0, int V, F&& f) {
+__device__ __forceinline__ void hist_columns(const SliceTabs& T, const WideRow& W, const SampleArgs& a, const DT* rowp, int c0, int V, F&& f) {
   const int tid = fresh_tid();
   const unsigned nc = min(T.dir[SLC / 64] - T.dir[0], (unsigned)SLC);
   for (unsigned j = tid; j < min(nc, (unsigned)HCAP); j += WT) {
@@ -242,7 +247,7 @@ __device__ __forceinline__ void hist_columns(const SliceTabs& T, const WideRow& 
       const int idx = c0 + 32 * tid + (__ffs((int)word) - 1);
       word &= word - 1u;
       if (r >= (unsigned)HCAP && idx < V)
-        f(apply_penalties(Io<DT>::one(rowp + idx), (uint32_t)T.cnt[min(r, (unsigned)SLC - 1u)], W.rep, W.inv_rep, W.freq, W.pres), idx);
+        f(apply_penalties(Io<DT>::one(rowp + idx), slice_count(T, W.ws, a, r), W.rep, W.inv_rep, W.freq, W.pres), idx);
       ++r;
     }
   }
@@ -269,7 +274,7 @@ __device__ __forceinline__ void weighed_columns(SliceTabs& T, const HistPre<DT>&
   if (W.h_active) {
     hist_stage<DT>(T, HP, W.ws, a, rowp, c0, V);
     __syncthreads();
-    hist_columns<DT>(T, W, rowp, c0, V, [&](float z1, int idx) { f(z1, idx, P); });
+    hist_columns<DT>(T, W, a, rowp, c0, V, [&](float z1, int idx) { f(z1, idx, P); });
   }
 }
 
@@ -413,8 +418,6 @@ __device__ __forceinline__ Items my_items(const SampleArgs& a) {
 }
 
 // What an item needs from memory before its columns can be processed; requested one item ahead.
-// The row and history flag of a queue slot come from the slot's record: a workgroup's items are
-// contiguous, so it keeps them for its current slot and the next.
 template <typename DT>
 struct ItemLoads {
   static constexpr int G = SLC / (WT * Io<DT>::EPL);  // 16-byte groups per thread and slice
@@ -422,41 +425,179 @@ struct ItemLoads {
   uint32_t hq[G];  // hot-set bits of each group's columns
   uint32_t pre;    // this thread's mask word or directory entry
 };
-struct SlotIds {
-  uint32_t row_c, act_c, row_n, act_n;  // current slot, next slot; act: bit 0 history in force, bit 1 no truncation
-  __device__ __forceinline__ void request(const SampleArgs& a, unsigned slot, unsigned n_wide, uint32_t& row, uint32_t& act) {
-    row = 0u; act = 0u;
-    if (slot < n_wide) {
-      const uint32_t* rec = reinterpret_cast<const uint32_t*>(reinterpret_cast<const WideRec*>(a.wq + WQ_HEAD) + slot);
-      row = as_global(rec)[0];
-      act = (as_global(rec)[11] != 0u ? 1u : 0u) | ((as_global(rec)[2] & WIDE_MODE) == (uint32_t)WIDE_ALL ? 2u : 0u);
-    }
-  }
-  // The record is the same in every lane: scalars from here on.  Called where the workgroup waits
-  // for its loads anyway (a row's record), so that no later use has to wait for loads in flight.
-  __device__ __forceinline__ void settle() { row_c = uni(row_c); act_c = uni(act_c); row_n = uni(row_n); act_n = uni(act_n); }
-};
-static_assert(offsetof(WideRec, row) == 0 && offsetof(WideRec, mode) == 8 && offsetof(WideRec, h_active) == 44, "record words read by SlotIds");
-// classify: rows without truncation need nothing from this loop; else (the bins kernel) only they need the hot bits
+// classify: rows without truncation never come here; else (the bins kernel) only they need the hot bits
 template <typename DT, bool use_hot, bool classify>
-__device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a, unsigned item, unsigned n_sl, int cur_slot, const SlotIds& ids) {
+__device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a, const WideRow& W, int c0) {
   constexpr int EPL = Io<DT>::EPL;
   const int tid = threadIdx.x;
-  const int slot = (int)(item / n_sl), c0 = (int)(item % n_sl) * SLC;
-  const uint32_t row = slot == cur_slot ? ids.row_c : ids.row_n;  // scalars (SlotIds::settle)
-  const uint32_t actw = slot == cur_slot ? ids.act_c : ids.act_n;
-  const bool act = (actw & 1u) != 0u;
-  if (classify && (actw & 2u)) return;
-  const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride;
-  L.pre = act ? slice_fetch(a.wws + (size_t)slot * a.ws_stride, a, c0) : 0u;
+  const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
+  L.pre = W.h_active ? slice_fetch(W.ws, a, c0) : 0u;
 #pragma unroll
   for (int j = 0; j < ItemLoads<DT>::G; ++j) {
     const int idx0 = c0 + (j * WT + tid) * EPL;
     L.hq[j] = 0u;
     L.A[j] = typename Io<DT>::Raw();
     if (idx0 + EPL <= a.V) L.A[j] = Io<DT>::load(rowp + idx0);
-    if (use_hot && (classify || (actw & 2u)) && idx0 < a.V) L.hq[j] = (as_global(a.hot_bits)[idx0 >> 5] >> ((unsigned)idx0 & 31u)) & ((1u << EPL) - 1u);
+    if (use_hot && (classify || W.mode == WIDE_ALL) && idx0 < a.V) L.hq[j] = (as_global(a.hot_bits)[idx0 >> 5] >> ((unsigned)idx0 & 31u)) & ((1u << EPL) - 1u);
   }
+}
+
+// ---------------------------------------------------------------- runs of slices -------------
+// bfloat16 rows with a nucleus take a workgroup's slices of one row in a run.  Under one temperature a column's bin, mass and
+// class are functions of its 16 bits, so the bins kernel counts columns per pattern and the classifying kernel looks them up, one
+// LDS access a column, with no barrier and no table of the history from slice to slice; what the run's history columns change is settled
+// once behind it: their weight as read is taken off, the penalised one added (integers: the sums are those of the column by column form).
+// What bounded it: 39 and 54 vector instructions a column, and per slice of 4096 columns four barriers, its tables and its
+// history columns, 2 to 3 us of a slice's 5 to 9.  338 rows of 256,000 columns with 8192 ids each: bins kernel 101 us, 78 so (the slices
+// take 25 to 30, the 173 MB at the HBM rate; the history columns 18); classifying kernel 185, 115 (slices 55).  float32 rows the
+// same way, each column weighed: no gain (90 of 128,256 columns, 21 and 26 us either way).
+// One 4-byte entry a pattern: magnitude index 0 is zero itself, 1 .. QMAX - 1 one pattern each, QMAX, among the negative
+// ones, what lies so far down that it has no mass.  A lane's group with any other value (tiny ones, 256 and more, NaN) goes
+// column by column.
+constexpr uint32_t PT_NEG = 0x4000u;  // byte offset of the negative patterns' entries: the sign bit, moved down one
+constexpr uint32_t PT_BYTES = PT_NEG + (uint32_t)NMAG * 4u;
+// Byte offsets of the two patterns of a word, low pattern in the low half.
+__device__ __forceinline__ uint32_t pattern_offsets2(uint32_t x) {
+  u16x2 q = __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, x & 0x7FFF7FFFu), (u16x2)((unsigned short)(PLO - 1)));
+  q = __builtin_elementwise_min(q, (u16x2)((unsigned short)QMAX)) << (unsigned short)2;
+  uint32_t off = ((x >> 1) & (PT_NEG | PT_NEG << 16)) | __builtin_bit_cast(uint32_t, q);
+  asm("" : "+v"(off));  // (formed once: the compiler forms it anew for either half)
+  return off;
+}
+__device__ __forceinline__ uint32_t pattern_offset(float z) { return pattern_offsets2(__float_as_uint(z) >> 16) & 0xFFFFu; }
+// Value and byte offset of table index i (< 2 NMAG).
+__device__ __forceinline__ float pattern_value(int i, uint32_t& off) {
+  const int neg = i >= NMAG ? 1 : 0, q = i - neg * NMAG;
+  off = (uint32_t)neg * PT_NEG + (uint32_t)q * 4u;
+  return __uint_as_float(((uint32_t)neg << 31) | ((q ? (uint32_t)(q + PLO - 1) : 0u) << 16));
+}
+// Whether all patterns of some groups have an entry.
+struct PatternRange {
+  s16x2 smax = {0, 0};            // the largest positive pattern
+  u16x2 umax = {0, 0};            // the negative one of the largest magnitude
+  u16x2 pmin = {0xFFFF, 0xFFFF};  // the smallest magnitude less one: zero itself is out of the way
+  __device__ __forceinline__ void take(uint32_t x) {
+    smax = __builtin_elementwise_max(smax, __builtin_bit_cast(s16x2, x));
+    umax = __builtin_elementwise_max(umax, __builtin_bit_cast(u16x2, x));
+    pmin = __builtin_elementwise_min(pmin, (u16x2)(__builtin_bit_cast(u16x2, x & 0x7FFF7FFFu) - (u16x2)((unsigned short)1)));
+  }
+  // neg_limit: the largest negative pattern that has one
+  __device__ __forceinline__ bool ok(uint32_t neg_limit) const {
+    return max((int)smax.x, (int)smax.y) < PHI && max((uint32_t)umax.x, (uint32_t)umax.y) <= neg_limit && min((uint32_t)pmin.x, (uint32_t)pmin.y) >= (uint32_t)(PLO - 1);
+  }
+};
+// -256 and all below it (-inf among them) have an entry where they have no mass.
+__device__ __forceinline__ uint32_t pattern_neg_limit(const StreamCtx& C) {
+  int b;
+  const float w = mass_term(-256.0f, C, b);
+  return b == NBW - 1 && mass_integer(w) == 0.0f && C.g > -256.0f ? 0xFF80u : 0x8000u | (uint32_t)(PHI - 1);
+}
+
+// f(idx, z, z', hot) for every history column of the slices [sl0, sl1) of a row: the logit as read and the penalised one.
+// The mask's columns first go to a list in LDS, a column's place its rank less the run's first, so that all threads then have
+// the same number of them, four on their way at a time.  (Taken from a thread's own mask words they came one or two at a
+// time, a trip to memory each: 35 us of a row's 21 slices with 1300 such columns, 18 so.)  Barriers inside.
+constexpr int HLIST = 1024;
+template <typename DT, bool use_hot, typename F>
+__device__ __forceinline__ void hist_run(const WideRow& W, const SampleArgs& a, const DT* rowp, int sl0, int sl1, uint32_t* list, F&& f) {
+  const int n_pairs = (((a.V + 31) >> 5) + 1) >> 1, p0 = sl0 * (SLC / 64), p1 = min(sl1 * (SLC / 64), n_pairs);
+  const unsigned char* ht = W.ws + WS_HT;
+  const u64* mask = reinterpret_cast<const u64*>(ht);
+  const uint16_t* dir = reinterpret_cast<const uint16_t*>(ht + a.F.dir);
+  const uint16_t* cnt = reinterpret_cast<const uint16_t*>(ht + a.F.cnt);
+  const unsigned r0 = uni((uint32_t)as_global(dir)[p0]), n = (p1 < n_pairs ? uni((uint32_t)as_global(dir)[p1]) : W.distinct) - r0;
+  constexpr int AT = 4;
+#pragma unroll 1
+  for (unsigned first = 0; first < n; first += HLIST) {
+    __syncthreads();  // (the list's last use)
+#pragma unroll 1
+    for (int q = p0 + fresh_tid(); q < p1; q += AT * WT) {
+      u64 m[AT]; unsigned r[AT];
+#pragma unroll
+      for (int k = 0; k < AT; ++k) {
+        const int p = min(q + k * WT, p1 - 1);
+        m[k] = as_global(mask)[p]; r[k] = (unsigned)as_global(dir)[p];
+      }
+#pragma unroll
+      for (int k = 0; k < AT; ++k) {
+        if (q + k * WT >= p1) continue;
+        unsigned at = r[k] - r0 - first;
+#pragma unroll 1
+        for (u64 x = m[k]; x; x &= x - 1ull, ++at) if (at < (unsigned)HLIST) list[at] = (uint32_t)(64 * (q + k * WT) + __ffsll((long long)x) - 1);
+      }
+    }
+    __syncthreads();
+    const unsigned nl = min(n - first, (unsigned)HLIST);
+#pragma unroll 1
+    for (unsigned t = (unsigned)fresh_tid(); t < nl; t += AT * WT) {
+      int idx[AT]; typename Io<DT>::Elem z[AT]; uint32_t c[AT], h[AT];
+#pragma unroll
+      for (int k = 0; k < AT; ++k) {
+        const unsigned u = min(t + (unsigned)(k * WT), nl - 1u);
+        idx[k] = (int)list[u];
+        c[k] = (uint32_t)as_global(cnt)[r0 + first + u];
+      }
+#pragma unroll
+      for (int k = 0; k < AT; ++k) {
+        z[k] = Io<DT>::raw(rowp + min(idx[k], a.V - 1));
+        h[k] = use_hot ? as_global(a.hot_bits)[min(idx[k], a.V - 1) >> 5] : 0u;
+      }
+#pragma unroll
+      for (int k = 0; k < AT; ++k) {
+        if (t + (unsigned)(k * WT) >= nl || idx[k] >= a.V) continue;
+        const float zr = Io<DT>::cvt(z[k]);
+        f(idx[k], zr, apply_penalties(zr, c[k], W.rep, W.inv_rep, W.freq, W.pres), ((h[k] >> (idx[k] & 31)) & 1u) != 0u);
+      }
+    }
+  }
+}
+__device__ __forceinline__ bool hist_bit(const WideRow& W, int idx) {  // (from memory)
+  return W.h_active && ((as_global(reinterpret_cast<const uint32_t*>(W.ws + WS_HT))[idx >> 5] >> (idx & 31)) & 1u) != 0u;
+}
+// The 16-byte groups of a slice, and the hot-set words of their columns.  (No load under a branch: at a join the compiler waits
+// for all that is in flight.  A group that the row's end cuts reads other columns, and is not used.)
+template <typename DT> struct RunLoads { typename Io<DT>::Raw A[ItemLoads<DT>::G]; uint32_t hq[ItemLoads<DT>::G]; };
+template <typename DT, bool use_hot>
+__device__ __forceinline__ void run_fetch(RunLoads<DT>& L, const SampleArgs& a, const DT* rowp, int sl, bool none) {
+  constexpr int EPL = Io<DT>::EPL;
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int j = 0; j < ItemLoads<DT>::G; ++j) {
+    const int idx0 = sl * SLC + (j * WT + tid) * EPL;
+    L.A[j] = Io<DT>::load(rowp + (none ? 0 : min(idx0, a.V - EPL)));
+    L.hq[j] = 0u;
+    if (use_hot) L.hq[j] = as_global(a.hot_bits)[none || idx0 >= a.V ? 0 : idx0 >> 5];
+  }
+}
+template <typename DT>
+__device__ __forceinline__ void run_settle(RunLoads<DT>& L) {  // waits for them
+#pragma unroll
+  for (int j = 0; j < ItemLoads<DT>::G; ++j) asm volatile("" : "+v"(L.A[j]), "+v"(L.hq[j]));
+}
+// The i-th of four words (by selects: an indexed array goes to scratch memory).
+__device__ __forceinline__ uint32_t select4(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, int i) {
+  asm("" : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3));
+  const uint32_t lo = (i & 1) ? x1 : x0, hi = (i & 1) ? x3 : x2;
+  return (i & 2) ? hi : lo;
+}
+// Sum over each row of sixteen lanes of values below 2^54, in two halves (one instruction per step: the move is part of the addition).
+__device__ __forceinline__ u64 row16_sum_u64(u64 v) {
+  auto sum = [](uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, DPP_XOR1, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, DPP_XOR2, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, DPP_HALF_MIRROR, 0xF, 0xF, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, DPP_MIRROR, 0xF, 0xF, true);
+    return x;
+  };
+  constexpr uint32_t LOW = (1u << 27) - 1u;
+  return (u64)sum((uint32_t)v & LOW) + ((u64)sum((uint32_t)(v >> 27)) << 27);
+}
+static_assert(SLC / WT * 2 <= 32, "a lane's columns of a slice, below 2^49 each, sum below 2^54");
+// Whether all eight patterns of a group have an entry.
+__device__ __forceinline__ bool group_ok(const u32x4& w, uint32_t neg_limit) {
+  PatternRange R;
+  R.take(w.x); R.take(w.y); R.take(w.z); R.take(w.w);
+  return R.ok(neg_limit);
 }
 
 // ---------------------------------------------------------------- no truncation ---------------
@@ -513,7 +654,7 @@ __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<
   if (W.h_active) {
     hist_stage<DT>(Tb, HP, W.ws, a, rowp, c0, V);
     __syncthreads();
-    hist_columns<DT>(Tb, W, rowp, c0, V, [&](float z, int idx) {
+    hist_columns<DT>(Tb, W, a, rowp, c0, V, [&](float z, int idx) {
       const float yv = tempered(z, W.C);
       m = fmaxf(m, yv);
       const u64 f = mass_fix(weigh(yv));
@@ -535,11 +676,16 @@ __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<
 
 // ---------------------------------------------------------------- bins ------------------------
 template <typename DT, bool use_hot>
-__global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kernel(const SampleArgs a) {
+__global__ __launch_bounds__(WT, 4) void wide_bins_kernel(const SampleArgs a) {
   constexpr int EPL = Io<DT>::EPL;
   constexpr int G = ItemLoads<DT>::G;
+  constexpr bool BF16 = sizeof(DT) == 2;
   __shared__ SliceTabs Tb;
-  __shared__ u64 lh[NBW + 1];  // the bins, and the mass at or above g
+  constexpr uint32_t ACC_BYTES = BF16 ? PT_BYTES : (uint32_t)(NBW + 1) * 8u;
+  static_assert(ACC_BYTES >= (uint32_t)(NBW + 1) * 8u, "the bins fit");
+  __shared__ __align__(16) u64 lh[(ACC_BYTES + 15u) / 16u * 2u];  // the bins, and the mass at or above g; bfloat16 runs: columns per pattern
+  __shared__ uint32_t odd[4];  // bfloat16 runs: slices with groups that went column by column
+  __shared__ uint32_t hlist[HLIST];
   __shared__ FS S;
   const int tid = threadIdx.x;
   const int V = a.V;
@@ -548,53 +694,112 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
   const unsigned wsh = (unsigned)(tid * EPL) & 31u;
   static_assert((WT * EPL) % 32 == 0, "group stride in mask words");
   const Items I = my_items(a);
-  if (I.i0 >= I.i1) return;
-  const unsigned n_wide = min(as_global(a.wq)[0], (unsigned)a.wide_slots);
-  int cur = (int)(I.i0 / I.n_sl);
-  SlotIds ids;
-  ids.request(a, (unsigned)cur, n_wide, ids.row_c, ids.act_c);
-  ids.request(a, (unsigned)cur + 1u, n_wide, ids.row_n, ids.act_n);
-  WideRow W = load_row(a, (unsigned)cur);
-  ids.settle();
-  ItemLoads<DT> N;  // the next item's loads
-  item_fetch<DT, use_hot, false>(N, a, I.i0, I.n_sl, cur, ids);
-  for (int b = tid; b <= NBW; b += WT) lh[b] = 0ull;
+  for (unsigned i0 = I.i0, i1; i0 < I.i1; i0 = i1) {  // the slices [sl0, sl1) of one row
+  const unsigned slot = i0 / I.n_sl;
+  i1 = min(I.i1, (slot + 1u) * I.n_sl);
+  const int sl0 = (int)(i0 - slot * I.n_sl), sl1 = sl0 + (int)(i1 - i0);
+  const WideRow W = load_row(a, slot);
+  const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
+  if (i0 != I.i0) __syncthreads();  // (what the row before left in LDS has been read)
+  zero16(lh, (int)ACC_BYTES, tid, WT);
   u64 mtop = 0ull;
   unsigned ntop = 0u;      // top-k route: columns at or above g seen by this thread
   float ymax = -INFINITY;  // rows with a min-p cut: largest tempered value seen by this thread
+  const bool run = BF16 && W.mode == WIDE_TOP_P && !W.f64;
   auto flush = [&]() {
     __syncthreads();
     if (W.mode == WIDE_TOP_P || W.mode == WIDE_TOP_K) {
       u64* gh = reinterpret_cast<u64*>(W.ws + WS_HIST);
-      for (int b = tid; b < NBW; b += WT) { const u64 v = lh[b]; if (v) atomicAdd(&gh[b], v); }
-      const u64 t = blk_sum_u64<WNW>(S, mtop) + lh[NBW];
+      if (run) {
+#pragma unroll 1
+        for (int i = tid; i < 2 * NMAG - 1; i += WT) {  // (the last entry has no mass)
+          uint32_t off;
+          const float z = pattern_value(i, off);
+          const uint32_t c = reinterpret_cast<const uint32_t*>(lh)[off / 4u];
+          if (c == 0u) continue;
+          int b; float y;
+          const float w = mass_term(z, W.C, b, y);
+          ymax = fmaxf(ymax, y);
+          const u64 m = (u64)c * sum_to_u64(SUM_BASE + (double)mass_integer(fminf(w, W_LIMIT)));
+          if (!(z < W.C.g)) mtop += m;
+          else if (m) atomicAdd(&gh[b], m);
+        }
+        if (tid < 4 && odd[tid]) atomicOr(reinterpret_cast<uint32_t*>(W.ws + WS_ODD) + tid, odd[tid]);
+      } else {
+        for (int b = tid; b < NBW; b += WT) { const u64 v = lh[b]; if (v) atomicAdd(&gh[b], v); }
+      }
+      const u64 t = blk_sum_u64<WNW>(S, mtop) + (run ? 0ull : lh[NBW]);
       if (tid == 0 && t) atomicAdd(reinterpret_cast<u64*>(W.ws + WS_SCAL), t);
       if (W.mode == WIDE_TOP_K) {
         const unsigned nt = wave_sum(ntop);
         if ((tid & 63) == 0 && nt) atomicAdd(reinterpret_cast<uint32_t*>(W.ws + WS_SCAL) + 7, nt);
       }
     }
-    if (W.min_p > 0.0f) {
+    if (W.min_p > 0.0f || run) {  // (counted rows: the classifying kernel does not form it again)
       const float m = wave_max(ymax);
       if ((tid & 63) == 0 && m > -INFINITY) atomicMax(reinterpret_cast<uint32_t*>(W.ws + WS_SCAL) + 6, fkey(m));
     }
-    mtop = 0ull; ntop = 0u; ymax = -INFINITY;
   };
-  for (unsigned it = I.i0; it < I.i1; ++it) {
-    const int slot = (int)(it / I.n_sl), sl = (int)(it % I.n_sl);
+  if constexpr (BF16) if (run) {
+    const uint32_t neg_limit = pattern_neg_limit(W.C);
+    if (tid < 4) odd[tid] = 0u;
+    RunLoads<DT> N;
+    run_fetch<DT, false>(N, a, rowp, sl0, false);
+    __syncthreads();  // the zeroed bins are visible
+    // a column that is not counted by its pattern: straight to the row's bins
+    auto add_column = [&](float z) {
+      int b; float y;
+      const float w = mass_term(z, W.C, b, y);
+      const u64 m = sum_to_u64(SUM_BASE + (double)mass_integer(fminf(w, W_LIMIT)));
+      ymax = fmaxf(ymax, y);
+      if (!(z < W.C.g)) mtop += m;
+      else if (m) atomicAdd(&reinterpret_cast<u64*>(W.ws + WS_HIST)[b], m);
+    };
+    auto count = [&](uint32_t off, uint32_t n) {
+      __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(lh) + off / 4u, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+#pragma unroll 1
+    for (int sl = sl0; sl < sl1; ++sl) {
+      RunLoads<DT> L = N;
+      run_settle(L);
+      run_fetch<DT, false>(N, a, rowp, sl + 1, sl + 1 == sl1);
+#pragma unroll
+      for (int j = 0; j < G; ++j) {
+        const int idx0 = sl * SLC + (j * WT + tid) * EPL;
+        if (idx0 + EPL > V) {  // the ragged end of the row
+          for (int idx = idx0; idx < V; ++idx) if (!hist_bit(W, idx)) add_column(Io<DT>::one(rowp + idx));
+        } else {
+          const u32x4 w = L.A[j];
+          if (group_ok(w, neg_limit)) {
+            const uint32_t w4[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { const uint32_t off = pattern_offsets2(w4[k]); count(off & 0xFFFFu, 1u); count(off >> 16, 1u); }
+          } else {
+            atomicOr(&odd[sl >> 5], 1u << (sl & 31));
+#pragma unroll 1
+            for (int e = 0; e < EPL; ++e) if (!hist_bit(W, idx0 + e)) add_column(Io<DT>::one(rowp + idx0 + e));
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);  // one group at a time: interleaving them costs registers
+      }
+    }
+    if (W.h_active) {
+      const int whole = V & ~(EPL - 1);  // (not those behind the last whole group)
+      hist_run<DT, false>(W, a, rowp, sl0, sl1, hlist, [&](int idx, float z, float zp, bool) {
+        const bool slice_odd = ((odd[idx / SLC >> 5] >> (idx / SLC & 31)) & 1u) != 0u;
+        if (idx < whole && (!slice_odd || group_ok(Io<DT>::load(rowp + (idx & ~(EPL - 1))), neg_limit))) count(pattern_offset(z), 0xFFFFFFFFu);
+        add_column(zp);
+      });
+    }
+    flush();
+    continue;
+  }
+  ItemLoads<DT> N;  // the next item's loads
+  item_fetch<DT, use_hot, false>(N, a, W, sl0 * SLC);
+  for (int sl = sl0; sl < sl1; ++sl) {
     const int c0 = sl * SLC;
     const ItemLoads<DT> L = N;
-    const bool more = it + 1u < I.i1;
-    if (slot != cur) {
-      flush();
-      cur = slot;
-      ids.row_c = ids.row_n; ids.act_c = ids.act_n;
-      ids.request(a, (unsigned)slot + 1u, n_wide, ids.row_n, ids.act_n);
-      W = load_row(a, (unsigned)slot);
-      ids.settle();
-      for (int b = tid; b <= NBW; b += WT) lh[b] = 0ull;
-    }
-    const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
+    const bool more = sl + 1 < sl1;
     HistPre<DT> HP;
     if (W.h_active) {
       slice_store(Tb, L.pre, a, c0, W.distinct);
@@ -610,12 +815,12 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
         if (z < W.C.g) atomicAdd(&lh[b], m); else mtop += m;
       });
       if (W.h_active) __syncthreads();  // the tables are rewritten by the next item
-      if (more) item_fetch<DT, use_hot, false>(N, a, it + 1u, I.n_sl, cur, ids);
+      if (more) item_fetch<DT, use_hot, false>(N, a, W, c0 + SLC);
       continue;
     }
-    if (more) item_fetch<DT, use_hot, false>(N, a, it + 1u, I.n_sl, cur, ids);
+    if (more) item_fetch<DT, use_hot, false>(N, a, W, c0 + SLC);
     if (W.mode == WIDE_ALL) {  // every column survives: this wave's masses
-      all_slice<DT, use_hot>(L, HP, Tb, W, a, rowp, c0, sl, slot);
+      all_slice<DT, use_hot>(L, HP, Tb, W, a, rowp, c0, sl, (int)slot);
       continue;
     }
     auto one = [&](float z, int) {
@@ -692,11 +897,12 @@ __global__ __launch_bounds__(WT, (sizeof(DT) == 4 ? 4 : 5)) void wide_bins_kerne
     if (W.h_active) {  // the history columns, whose logits and counts were requested before the main line
       hist_stage<DT>(Tb, HP, W.ws, a, rowp, c0, V);
       __syncthreads();
-      hist_columns<DT>(Tb, W, rowp, c0, V, one);
+      hist_columns<DT>(Tb, W, a, rowp, c0, V, one);
       __syncthreads();  // the tables are rewritten by the next item
     }
   }
   flush();
+  }
 }
 
 // ---------------------------------------------------------------- classify --------------------
@@ -743,10 +949,18 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
   constexpr int EPL = Io<DT>::EPL;
   constexpr int G = ItemLoads<DT>::G;  // a slice is one tile of the draw's walk
   constexpr unsigned EMASK = (1u << EPL) - 1u;
-  __shared__ SliceTabs Tb;
+  constexpr bool BF16 = sizeof(DT) == 2;
+  constexpr int LCAP = BF16 ? 768 : 2048;  // size of the stage, which is written out once fewer than ICAP places are free
+  // bfloat16 runs: an entry per pattern of the current row; else the tables of a slice
+  __shared__ __align__(16) uint32_t ptab[((BF16 ? PT_BYTES : (uint32_t)sizeof(SliceTabs)) + 15u) / 16u * 4u];
+  static_assert(sizeof(SliceTabs) <= PT_BYTES, "either");
+  SliceTabs& Tb = *reinterpret_cast<SliceTabs*>(ptab);
   __shared__ u64 lrl[LCAP];  // boundary columns of the current row found by this workgroup, not yet written out
   __shared__ u64 ltile[2];
-  __shared__ unsigned l_n, l_base;
+  __shared__ u64 lt[2][MAX_SLICES];  // runs: the slices' masses by class
+  __shared__ uint32_t odd[4];        // bfloat16 runs: slices with groups that go column by column
+  __shared__ uint32_t hlist[HLIST];
+  __shared__ unsigned l_n;
   __shared__ FS S;
   const int tid = threadIdx.x, lane = tid & 63;
   const int V = a.V;
@@ -757,60 +971,63 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
   const uint32_t* hot_bits = a.hot_bits;
   far_rows<DT, use_hot>(Tb, S, a);
   const Items I = my_items(a);
-  if (I.i0 >= I.i1) return;
-  const unsigned n_wide = min(as_global(a.wq)[0], (unsigned)a.wide_slots);
-  int cur = (int)(I.i0 / I.n_sl);
-  SlotIds ids;
-  ids.request(a, (unsigned)cur, n_wide, ids.row_c, ids.act_c);
-  ids.request(a, (unsigned)cur + 1u, n_wide, ids.row_n, ids.act_n);
-  ids.settle();
-  {  // nothing to do for rows without truncation (a workgroup's items lie in at most two slots, or the first is one of them)
-    const int last = (int)((I.i1 - 1u) / I.n_sl);
-    if ((ids.act_c & 2u) && (last == cur || (last == cur + 1 && (ids.act_n & 2u)))) return;
+  if (tid == 0) l_n = 0u;
+  for (unsigned i0 = I.i0, i1; i0 < I.i1; i0 = i1) {  // the slices [sl0, sl1) of one row
+  const unsigned slot = i0 / I.n_sl;
+  i1 = min(I.i1, (slot + 1u) * I.n_sl);
+  const int sl0 = (int)(i0 - slot * I.n_sl), sl1 = sl0 + (int)(i1 - i0);
+  if ((uni(as_global(reinterpret_cast<const uint32_t*>(reinterpret_cast<const WideRec*>(a.wq + WQ_HEAD) + slot))[2]) & WIDE_MODE) == (uint32_t)WIDE_ALL) continue;  // (done by the bins kernel, or above)
+  const WideRow W = load_row(a, slot);
+  const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
+  const RowCut rc = row_cut(S, W);  // barriers inside
+  if (!rc.valid) continue;  // the finishing kernel hands the row on
+  const int bstar = rc.bstar;
+  const float thr_y = rc.thr_y;
+  if (sl0 == 0 && tid == 0) {  // for the finishing kernel
+    reinterpret_cast<uint32_t*>(W.ws + WS_SCAL)[8] = (uint32_t)bstar + 1u;
+    reinterpret_cast<u64*>(W.ws + WS_SCAL)[5] = rc.s_tot;
   }
-  ItemLoads<DT> N;  // the next item's loads
-  item_fetch<DT, use_hot, true>(N, a, I.i0, I.n_sl, cur, ids);
-  WideRow W;
-  int bstar = -1;
-  float thr_y = -INFINITY;
-  bool valid = false;
-  ZCut zc = {INFINITY, INFINITY};
-  auto enter_row = [&](int slot, bool first) {  // barriers inside; first: the item is the row's first slice
-    W = load_row(a, (unsigned)slot);
-    ids.settle();
-    const RowCut rc = row_cut(S, W);
-    bstar = rc.bstar; thr_y = rc.thr_y; valid = rc.valid;
-    valid = valid && W.mode != WIDE_ALL;  // (done by the bins kernel, or above)
-    if (first && tid == 0 && valid) {  // for the finishing kernel
-      reinterpret_cast<uint32_t*>(W.ws + WS_SCAL)[8] = (uint32_t)bstar + 1u;
-      reinterpret_cast<u64*>(W.ws + WS_SCAL)[5] = rc.s_tot;
-    }
-    if (valid) zc = z_cut(W, bstar, thr_y);
-  };
+  const ZCut zc = z_cut(W, bstar, thr_y);
   // What a thread gathers over this workgroup's slices of one row, reduced when the row ends:
   unsigned n_sure = 0u;    // sure columns (those of the main line: counted per wave, in the lane with its first column)
   u64 acc_all = 0ull;      // exact mass of every column (routes without bins)
   float ymax = -INFINITY;  // largest tempered value
   bool bad = false;        // a mass the fixed point cannot carry, or a NaN
+  // Boundary columns go to the stage, in a run by their ids (those that are boundary columns as read), else with their logits
+  // (the others and what finds the stage full: straight to the row's list).
+  bool ids_only = false;
+  uint32_t* lid = reinterpret_cast<uint32_t*>(lrl);
+  auto put = [&](float z, int idx) {
+    const unsigned at = atomicAdd(&reinterpret_cast<uint32_t*>(W.ws + WS_SCAL)[3], 1u);
+    if (at < (unsigned)RCAP) reinterpret_cast<u64*>(W.ws + WS_RL)[at] = ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx;
+  };
+  auto stage = [&](unsigned s, u64 c) { if (s < (unsigned)LCAP) lrl[s] = c; else put(__uint_as_float((uint32_t)(c >> 32)), (int)(uint32_t)c); };
   // Writes the staged boundary columns to the row's list.  All threads call, after a barrier that
   // follows the last append; ends with a barrier.
   auto list_out = [&]() {
-    const unsigned nb = l_n;
+    const unsigned nb = min(l_n, ids_only ? 2u * (unsigned)LCAP : (unsigned)LCAP);
     if (nb == 0u) return;
     uint32_t* sc = reinterpret_cast<uint32_t*>(W.ws + WS_SCAL);
-    // more columns than the stage holds: the count is pushed past the limit, so that the finishing
-    // kernel hands the row on
-    if (tid == 0) l_base = atomicAdd(&sc[3], nb > (unsigned)LCAP ? (unsigned)RCAP + 1u : nb);
+    for (unsigned t0 = 0; t0 < nb; t0 += WT) {
+      const unsigned t = min(t0 + (unsigned)tid, nb - 1u);
+      u64 c = 0ull;
+      bool in = t0 + (unsigned)tid < nb;
+      if (ids_only) {
+        const uint32_t id = lid[t];
+        c = ((u64)__float_as_uint(Io<DT>::one(rowp + id)) << 32) | (u64)id;
+        in = in && !hist_bit(W, (int)id);  // (settled with the history's columns)
+      } else c = lrl[t];
+      const u64 m = __ballot(in);
+      unsigned base = 0u;
+      if (lane == 0 && m) base = atomicAdd(&sc[3], (unsigned)__popcll(m));
+      base = uni(base) + lanes_before(m);
+      if (in && base < (unsigned)RCAP) reinterpret_cast<u64*>(W.ws + WS_RL)[base] = c;
+    }
     __syncthreads();
-    const unsigned base = l_base;
-    if (nb <= (unsigned)LCAP)
-      for (unsigned t = tid; t < nb; t += WT)
-        if (base + t < (unsigned)RCAP) reinterpret_cast<u64*>(W.ws + WS_RL)[base + t] = lrl[t];
     if (tid == 0) l_n = 0u;
     __syncthreads();
   };
   auto leave_row = [&]() {  // barriers inside
-    if (!valid) return;
     __syncthreads();
     list_out();
     uint32_t* sc = reinterpret_cast<uint32_t*>(W.ws + WS_SCAL);
@@ -823,53 +1040,177 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
       if (ns) atomicAdd(&sc[2], ns);
       if (dsum) atomicAdd(reinterpret_cast<u64*>(W.ws + WS_SCAL + 16), dsum);
     }
-    n_sure = 0u; acc_all = 0ull; ymax = -INFINITY; bad = false;
   };
-  if (tid == 0) l_n = 0u;
-  enter_row(cur, I.i0 % I.n_sl == 0u);
-  for (unsigned it = I.i0; it < I.i1; ++it) {
-    const int slot = (int)(it / I.n_sl), sl = (int)(it % I.n_sl);
-    const ItemLoads<DT> L = N;
-    const bool more = it + 1u < I.i1;
-    if (slot != cur) {
-      leave_row();
-      cur = slot;
-      ids.row_c = ids.row_n; ids.act_c = ids.act_n;
-      ids.request(a, (unsigned)slot + 1u, n_wide, ids.row_n, ids.act_n);
-      enter_row(slot, true);
+  u64 acc_s = 0ull, acc1 = 0ull;  // a slice's mass of the sure columns, and of the hot ones among them
+  // one column the slow way: history columns and the ragged end of the row
+  auto one_of = [&](float z, int idx, bool hot) {
+    int b; float y;
+    const float w = mass_term(z, W.C, b, y);
+    const bool below = z < W.C.g;
+    if (!below && !(w <= W_LIMIT)) { bad = true; return; }
+    const u64 m = below ? mass_fix_below(w) : mass_fix(w);
+    acc_all += m;
+    ymax = fmaxf(ymax, y);
+    if (!(y >= thr_y)) return;
+    if (!below || b < bstar) {
+      acc_s += m;
+      if (use_hot && hot) acc1 += m;
+      ++n_sure;
+    } else if (b == bstar) { if (ids_only) put(z, idx); else stage(atomicAdd(&l_n, 1u), ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx); }
+  };
+  auto one = [&](float z, int idx) { one_of(z, idx, use_hot && hot_bit(hot_bits, (uint32_t)idx)); };
+  if constexpr (BF16) if (W.mode == WIDE_TOP_P && !W.f64) {
+    // An entry is the mass of one of the pattern's columns if they surely survive and it is below 2^30 (four times the mass
+    // at g), and MARKED for columns that are looked at one by one: boundary columns, and those with more mass.
+    constexpr uint32_t MARKED = 0x80000000u;
+    // (over: more than the fixed point carries, which the row's later kernels cannot take unless the column is the history's)
+    auto clamped = [&](float z, bool& over) -> u64 {
+      int b;
+      const float w = mass_term(z, W.C, b);
+      over = !(w <= W_LIMIT);
+      return sum_to_u64(SUM_BASE + (double)mass_integer(fminf(w, W_LIMIT)));
+    };
+    ids_only = true;
+    const uint32_t neg_limit = pattern_neg_limit(W.C);
+    uint32_t odd_words = 0u;  // (lanes 0 to 3) slices with groups that go column by column
+    RunLoads<DT> N;
+    run_fetch<DT, use_hot>(N, a, rowp, sl0, false);
+    for (int i = tid; i < 2 * MAX_SLICES; i += WT) lt[i / MAX_SLICES][i % MAX_SLICES] = 0ull;
+    odd_words = as_global(reinterpret_cast<const uint32_t*>(W.ws + WS_ODD))[lane & 3];
+    if (tid < 4) odd[tid] = odd_words;
+#pragma unroll 1
+    for (int i = tid; i < 2 * NMAG; i += WT) {
+      uint32_t off;
+      const float z = pattern_value(i, off);
+      uint32_t e = z >= zc.z_edge ? MARKED : 0u;
+      if (z >= zc.z_sure) { bool over; const u64 m = clamped(z, over); e = m >> 30 ? MARKED : (uint32_t)m; }
+      ptab[off / 4u] = i == 2 * NMAG - 1 ? 0u : e;
     }
-    if (!valid) {  // the finishing kernel hands the row on
-      if (more) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
-      continue;
+    __syncthreads();
+    const bool want_n = a.diag != nullptr;  // (the number of survivors is a diagnostic here)
+    // the columns of a lane's group that are looked at one by one: bit e of em, few
+    auto stage_lane = [&](uint32_t em, int idx0, uint32_t hq, auto&& bits) {
+#pragma unroll 1
+      for (; em; em &= em - 1u) {
+        const int e = __ffs((int)em) - 1;
+        const uint32_t zb = bits(e);
+        const float z = __uint_as_float(zb);
+        if (z >= zc.z_sure) {
+          bool over;
+          const u64 m = clamped(z, over);
+          acc_s += m;
+          if (use_hot && ((hq >> e) & 1u)) acc1 += m;
+          if (over && !hist_bit(W, idx0 + e)) bad = true;
+        } else {
+          const unsigned at = atomicAdd(&l_n, 1u);
+          if (at < 2u * (unsigned)LCAP) lid[at] = (uint32_t)(idx0 + e);
+          else if (!hist_bit(W, idx0 + e)) put(z, idx0 + e);
+        }
+      }
+    };
+#pragma unroll 1
+    for (int sl = sl0; sl < sl1; ++sl) {
+      RunLoads<DT> L = N;
+      run_settle(L);
+      run_fetch<DT, use_hot>(N, a, rowp, sl + 1, sl + 1 == sl1);
+      acc_s = 0ull; acc1 = 0ull;
+#pragma unroll
+      for (int j = 0; j < G; ++j) {
+        const int idx0 = sl * SLC + (j * WT + tid) * EPL;
+        const uint32_t hq = use_hot ? L.hq[j] >> wsh : 0u;
+        if (idx0 + EPL > V) {  // the ragged end of the row
+          for (int idx = idx0; idx < V; ++idx) if (!hist_bit(W, idx)) one(Io<DT>::one(rowp + idx), idx);
+        } else {
+          const u32x4 w = L.A[j];
+          if (!((read_lane(odd_words, sl >> 5) >> (sl & 31)) & 1u) || group_ok(w, neg_limit)) {
+            const uint32_t w4[4] = {w.x, w.y, w.z, w.w};
+            uint32_t ev[EPL], any = 0u, sum[2] = {0u, 0u}, sum_h[2] = {0u, 0u};  // (of four columns: below 2^32, and a mark is 2^31)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const uint32_t off = pattern_offsets2(w4[k]);
+              ev[2 * k] = ptab[(off & 0xFFFFu) / 4u];
+              ev[2 * k + 1] = ptab[(off >> 16) / 4u];
+            }
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) {
+              sum[e / 4] += ev[e];
+              any |= ev[e];
+              if (use_hot) sum_h[e / 4] += ev[e] & (uint32_t)__builtin_amdgcn_sbfe((int)hq, (unsigned)e, 1u);
+            }
+            if (want_n) {
+              float z[EPL];
+              Io<DT>::unpack(w, z);
+#pragma unroll
+              for (int e = 0; e < EPL; ++e) n_sure += z[e] >= zc.z_sure ? 1u : 0u;
+            }
+            if (any & MARKED) {
+              uint32_t em = 0u;
+#pragma unroll
+              for (int e = 0; e < EPL; ++e) em |= (ev[e] >> (31 - e)) & (1u << e);
+#pragma unroll
+              for (int k = 0; k < 2; ++k) {
+                sum[k] -= (uint32_t)__popc(em & (15u << 4 * k)) << 31;
+                if (use_hot) sum_h[k] -= (uint32_t)__popc(em & hq & (15u << 4 * k)) << 31;
+              }
+              stage_lane(em, idx0, hq, [&](int e) {
+                const uint32_t x = select4(w.x, w.y, w.z, w.w, e >> 1);
+                return (e & 1) ? x & 0xFFFF0000u : x << 16;
+              });
+            }
+            acc_s += (u64)sum[0] + (u64)sum[1];
+            if (use_hot) acc1 += (u64)sum_h[0] + (u64)sum_h[1];
+          } else {
+#pragma unroll 1
+            for (int e = 0; e < EPL; ++e) if (!hist_bit(W, idx0 + e)) one(Io<DT>::one(rowp + idx0 + e), idx0 + e);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);  // one group at a time: interleaving them costs registers
+      }
+      // (four lanes add to the slice's words: less work than the rest of a reduction)
+      const u64 s0 = row16_sum_u64(acc_s - acc1), s1 = use_hot ? row16_sum_u64(acc1) : 0ull;
+      if ((lane & 15) == 0) {
+        atomicAdd(&lt[0][sl], s0);
+        if (use_hot) atomicAdd(&lt[1][sl], s1);
+      }
     }
+    if (W.h_active) {
+      const int whole = V & ~(EPL - 1);  // (not those behind the last whole group)
+      hist_run<DT, use_hot>(W, a, rowp, sl0, sl1, hlist, [&](int idx, float z, float zp, bool hot) {
+        const int sl = idx / SLC;
+        u64 was = 0ull;  // what it was taken for
+        if (idx < whole && (!((odd[sl >> 5] >> (sl & 31)) & 1u) || group_ok(Io<DT>::load(rowp + (idx & ~(EPL - 1))), neg_limit))) {
+          was = (u64)ptab[pattern_offset(z) / 4u];
+          if (was & (u64)MARKED) { bool over; was = z >= zc.z_sure ? clamped(z, over) : 0ull; }
+          if (z >= zc.z_sure) --n_sure;
+        }
+        acc_s = 0ull; acc1 = 0ull;
+        one_of(zp, idx, hot);
+        if (acc_s != was) atomicAdd(&lt[use_hot && hot ? 1 : 0][sl], acc_s - was);
+      });
+    }
+    __syncthreads();  // the slices' masses are complete
+    for (int i = tid; i < 2 * (sl1 - sl0); i += WT) {
+      const int cls = i & 1, sl = sl0 + (i >> 1);
+      const u64 m = lt[cls][sl];
+      reinterpret_cast<u64*>(W.ws + WS_TILES)[cls * 256 + sl] = m;
+      if (m >> 55) bad = true;  // 128 tiles of two classes below 2^55 sum below 2^63; more mass in one is not carried
+    }
+    leave_row();
+    continue;
+  }
+  ItemLoads<DT> N;  // the next item's loads
+  item_fetch<DT, use_hot, true>(N, a, W, sl0 * SLC);
+  for (int sl = sl0; sl < sl1; ++sl) {
     const int c0 = sl * SLC;
-    const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)W.row * (size_t)a.stride;
+    const ItemLoads<DT> L = N;
+    const bool more = sl + 1 < sl1;
     if (tid < 2) ltile[tid] = 0ull;
     if (W.h_active) slice_store(Tb, L.pre, a, c0, W.distinct);
     __syncthreads();
     HistPre<DT> HP;
     if (W.h_active) hist_fetch<DT>(HP, Tb, W.ws, a, rowp, c0, V);  // this item's own loads go first: loads return in order
-    if (more && !W.f64) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
-    u64 acc_s = 0ull, acc1 = 0ull;  // this slice: mass of the sure columns, and of the hot ones among them
-    // one column the slow way: history columns and the ragged end of the row
-    auto one = [&](float z, int idx) {
-      int b; float y;
-      const float w = mass_term(z, W.C, b, y);
-      const bool below = z < W.C.g;
-      if (!below && !(w <= W_LIMIT)) { bad = true; return; }
-      const u64 m = below ? mass_fix_below(w) : mass_fix(w);
-      acc_all += m;
-      ymax = fmaxf(ymax, y);
-      if (!(y >= thr_y)) return;
-      if (!below || b < bstar) {
-        acc_s += m;
-        if (use_hot && hot_bit(hot_bits, (uint32_t)idx)) acc1 += m;
-        ++n_sure;
-      } else if (b == bstar) {
-        const unsigned s = atomicAdd(&l_n, 1u);
-        if (s < (unsigned)LCAP) lrl[s] = ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx;
-      }
-    };
+    if (more && !W.f64) item_fetch<DT, use_hot, true>(N, a, W, c0 + SLC);
+    acc_s = 0ull; acc1 = 0ull;
     if (W.f64) {
       weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int idx, const Exp2Poly& P) {
         int b; float y;
@@ -884,11 +1225,10 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
           if (use_hot && hot_bit(hot_bits, (uint32_t)idx)) acc1 += m;
           ++n_sure;
         } else if (b == bstar) {
-          const unsigned s = atomicAdd(&l_n, 1u);
-          if (s < (unsigned)LCAP) lrl[s] = ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx;
+          stage(atomicAdd(&l_n, 1u), ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx);
         }
       });
-      if (more) item_fetch<DT, use_hot, true>(N, a, it + 1u, I.n_sl, cur, ids);
+      if (more) item_fetch<DT, use_hot, true>(N, a, W, c0 + SLC);
     } else {
     // The main line: every column's mass, and its class by the logit alone; boundary columns follow
     // under a wave-wide test.
@@ -943,7 +1283,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
               unsigned base = 0u;
               if (lane == 0) base = atomicAdd(&l_n, (unsigned)__popcll(m));
               const unsigned s = uni(base) + lanes_before(m);
-              if (((m >> lane) & 1ull) && s < (unsigned)LCAP) lrl[s] = ((u64)__float_as_uint(z[e]) << 32) | (u64)(uint32_t)(idx0 + e);
+              if ((m >> lane) & 1ull) stage(s, ((u64)__float_as_uint(z[e]) << 32) | (u64)(uint32_t)(idx0 + e));
             }
           }
         } else {
@@ -964,7 +1304,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     if (W.h_active) {  // the history columns, whose logits and counts were requested before the main line
       hist_stage<DT>(Tb, HP, W.ws, a, rowp, c0, V);
       __syncthreads();
-      hist_columns<DT>(Tb, W, rowp, c0, V, one);
+      hist_columns<DT>(Tb, W, a, rowp, c0, V, one);
     }
     }
     {
@@ -977,10 +1317,10 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
       reinterpret_cast<u64*>(W.ws + WS_TILES)[tid * 256 + sl] = ltile[tid];
       if (ltile[tid] >> 55) bad = true;  // 128 tiles of two classes below 2^55 sum below 2^63; more mass in one is not carried
     }
-    // every slice may add ICAP boundary columns before the stage has to be written out
     if (l_n > (unsigned)(LCAP - ICAP)) list_out();
   }
   leave_row();
+  }
 }
 
 // ---------------------------------------------------------------- finish ----------------------
@@ -1034,7 +1374,7 @@ __device__ __forceinline__ void stage_slice(float* zt, SliceTabs& Tb, const Wide
   __syncthreads();
   for (uint32_t m = (Tb.bm[tid >> 2] >> ((tid & 3) * EPT)) & 0xFFu; m; m &= m - 1u) {
     const int o = tid * EPT + __ffs((int)m) - 1;
-    zt[slice_place(o)] = slice_value(zt[slice_place(o)], o, Tb, W);
+    zt[slice_place(o)] = slice_value(zt[slice_place(o)], o, Tb, W, a);
   }
 }
 // The sum of f(z, column) over this thread's columns; and, where the running sum over all threads' columns exceeds
@@ -1431,19 +1771,18 @@ __global__ __launch_bounds__(FT, 4) void wide_finish_kernel(const SampleArgs a) 
 
 
 hipError_t launch_wide(const SampleArgs& a, int dtype, hipStream_t st) {
-  // One resident round of workgroups each: five per compute unit fit by registers and LDS (four: the classifying kernel
-  // and the bins of float32 rows); a workgroup then takes a contiguous run of slices, mostly of one row.  The finishing kernel,
+  // One resident round of workgroups each: four per compute unit fit by registers and LDS; a workgroup then takes a contiguous run of slices, mostly of one row.  The finishing kernel,
   // two workgroups per compute unit by its LDS, takes a row at a time.
-  const dim3 bins((unsigned)a.n_cu * 5u), cls((unsigned)a.n_cu * 4u), fin((unsigned)(a.B < 2 * a.n_cu ? a.B : 2 * a.n_cu)), blk(fast::WT), fblk(fast::FT);
+  const dim3 cls((unsigned)a.n_cu * 4u), fin((unsigned)(a.B < 2 * a.n_cu ? a.B : 2 * a.n_cu)), blk(fast::WT), fblk(fast::FT);
   if (dtype == SIMPLE_F32) {
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<float, true>), cls, blk, 0, st, a);
-    else hipLaunchKernelGGL((fast::wide_bins_kernel<float, false>), cls, blk, 0, st, a);  // (float32: four workgroups per compute unit, no spilled register)
+    else hipLaunchKernelGGL((fast::wide_bins_kernel<float, false>), cls, blk, 0, st, a);
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_classify_kernel<float, true>), cls, blk, 0, st, a);
     else hipLaunchKernelGGL((fast::wide_classify_kernel<float, false>), cls, blk, 0, st, a);
     hipLaunchKernelGGL((fast::wide_finish_kernel<float>), fin, fblk, 0, st, a);
   } else {
-    if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, true>), bins, blk, 0, st, a);
-    else hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, false>), bins, blk, 0, st, a);
+    if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, true>), cls, blk, 0, st, a);
+    else hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, false>), cls, blk, 0, st, a);
     if (a.hot_bits) hipLaunchKernelGGL((fast::wide_classify_kernel<uint16_t, true>), cls, blk, 0, st, a);
     else hipLaunchKernelGGL((fast::wide_classify_kernel<uint16_t, false>), cls, blk, 0, st, a);
     hipLaunchKernelGGL((fast::wide_finish_kernel<uint16_t>), fin, fblk, 0, st, a);

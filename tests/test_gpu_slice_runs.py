@@ -1,0 +1,66 @@
+"""Rows with a nucleus wider than the candidate list, weighed in runs of slices: history columns settled behind the run,
+bfloat16 columns by their patterns, groups with values that have no entry column by column.  Against the oracle."""
+import numpy as np
+import pytest
+
+import parity_util as P
+from paper_2512_00719_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_of(rng, B, V, hist_ids, nnz, dtype):
+    """Six kinds of rows: ordinary; zeros and tiny values; magnitudes beyond 256; masked columns of three sorts; history
+    columns far above the others as read, far below as penalised; values of one binade, so that many tie."""
+    z = np.empty((B, V), np.float32)
+    tau = np.ones(B, np.float32)
+    pres = np.full(B, 0.2, np.float32)
+    for b in range(B):
+        z[b, rng.permutation(V)] = -1.1 * np.log1p(np.arange(V))
+        z[b] += rng.normal(0.0, 1.5, V)
+        kind = b % 6
+        if kind == 1:
+            z[b] += 6.0
+            z[b, rng.random(V) < 0.2] = 0.0
+            tiny = rng.random(V) < 0.01
+            z[b, tiny] = rng.choice([1e-6, -3e-5, 1e-30, -0.0], int(tiny.sum()))
+        elif kind == 2:
+            z[b] *= 40.0
+            tau[b] = 40.0
+        elif kind == 3:
+            u = rng.random(V)
+            z[b, u < 0.2] = -np.inf
+            z[b, (u >= 0.2) & (u < 0.3)] = -1e4
+            z[b, (u >= 0.3) & (u < 0.31)] = -3.38e38
+        elif kind == 4:
+            z[b, hist_ids[b * nnz:(b + 1) * nnz]] += 30.0
+            pres[b] = 60.0
+        elif kind == 5:
+            z[b] = 96.0 + z[b].clip(-30.0, 30.0)
+    return z, tau, pres
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,B,nnz,hot", [(32_771, 18, 300, False), (40_960, 24, 20_000, True), (150_001, 48, 2500, True),
+                                         (150_007, 48, 2500, False), (9_221, 12, 1, False)])
+def test_runs(dtype, V, B, nnz, hot):
+    if dtype == "bf16" and V < 16_384:
+        V += 16_384  # (shorter bfloat16 rows are the general kernel's)
+    rng = np.random.default_rng(V + nnz)
+    hist_ptr = np.arange(B + 1, dtype=np.int64) * nnz
+    hist_ids = rng.integers(0, V, B * nnz).astype(np.int32)
+    hist_ids[::max(nnz // 2, 1)] = V - 1  # the last column, behind the last whole group
+    z, tau, pres = rows_of(rng, B, V, hist_ids, nnz, dtype)
+    top_p = rng.choice([0.8, 0.95, 0.99], B).astype(np.float32)
+    params = synth.make_params(B, temperature=tau, top_p=top_p, min_p=np.where(np.arange(B) % 4 == 3, 1e-4, 0.0).astype(np.float32),
+                               rep_penalty=1.1, freq_penalty=0.1, pres_penalty=pres, n_prompt=nnz // 3)
+    bits = synth.f32_to_bf16_bits(z) if dtype == "bf16" else z
+    w = synth.Workload("runs", B, V, dtype, bits, params, hist_ptr, hist_ids,
+                       hot_ids=np.sort(rng.choice(V, V // 8, replace=False)).astype(np.int32) if hot else None)
+    wide = 0
+    for step in range(2):
+        ids, dg = P.run_gpu(w, step)
+        assert not (dg["flags"] & binding.DIAG_ERROR).any()
+        wide += int(((dg["flags"] & binding.DIAG_WIDE) != 0).sum())
+        P.compare(ids, dg, P.run_oracle(w, step), range(B))
+    assert wide > B // 2
