@@ -376,7 +376,6 @@ static int sample_impl(simple_ctx* ctx, const simple_state* state, const int32_t
   for (int i = 0; i < 8; ++i) a.eos_ids[i] = ctx->eos_ids[i];
   a.max_nnz = (int)ctx->max_nnz;
   a.pend = ctx->pend;
-  a.order = ctx->order;
   a.n_cu = ctx->n_cu;
   a.wq = ctx->wq; a.wws = ctx->wws; a.wide_slots = ctx->slots; a.ws_stride = ctx->ws_stride;
   a.L = simple::make_layout(V, ctx->max_nnz, with_hist);
@@ -400,7 +399,10 @@ static int sample_impl(simple_ctx* ctx, const simple_state* state, const int32_t
     a.diag = diag_dev ? diag_dev + b0 : nullptr;
     a.logprobs = ctx->logprobs ? ctx->logprobs + b0 : nullptr;
     a.eos_out = ctx->eos_out ? ctx->eos_out + b0 : nullptr;
-    a.order = (a.F.total != 0u && !a.F.whole && !tail && nb > (int64_t)ctx->n_cu) ? ctx->order : nullptr;
+    // (with no more rows than compute units every row has one to itself: nothing to balance)
+    const bool ordered = a.F.total != 0u && !a.F.whole && !tail && nb > (int64_t)ctx->n_cu;
+    a.order = ordered && a.pattern_on ? ctx->order : nullptr;
+    a.pick = ordered && !a.pattern_on ? 1 : 0;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (ctx->prof_ev && ctx->prof_n < PROF_MAX) { ev0 = ctx->prof_ev[2 * ctx->prof_n]; ev1 = ctx->prof_ev[2 * ctx->prof_n + 1]; ++ctx->prof_n; }
     if (tail) {  // the hot-first kernel, then the general kernel on the rows it left

@@ -915,6 +915,46 @@ __device__ inline void queue_pending(const SampleArgs& a, int row) {
   a.out[row] = PENDING;
 }
 
+// ---------------------------------------------------------------- the rows' order -------------
+// Which row a workgroup takes, in a launch with more rows than compute units: rows with long epilogues first.  Workgroups are
+// handed to the compute units in turn, so that a compute unit holds workgroups b, b + (number of compute units), ...: with
+// the long rows at the front every compute unit gets its share of them instead of some holding four (measured on the
+// heterogeneous batch: a compute unit with four such rows finishes 20 us after one with two), and a launch of several rounds starts
+// its longest rows first.  In a bfloat16 call the kernel ahead of this one writes that order for the whole launch; in a float32 call
+// there is none, and a workgroup finds its row among those of 64 neighbouring compute units (16 rounds of them at most), long
+// ones first, each kind in row order.  (A kernel of one workgroup that wrote the order for all: 5 us of the call and its gap.  1024
+// rows of 128,256 columns 197.2 us a call, 195.5 so; 512 with a state 134.8 and 133.9.)  The same in every thread; a barrier inside.
+template <int NTHR>
+__device__ __forceinline__ int pick_row(const SampleArgs& a, FS& S) {
+  constexpr int NWV = NTHR / 64, CUS = 64, ROUNDS = 16;
+  static_assert(CUS * ROUNDS / 64 <= 16, "a word of the workgroup's state per 64 rows");
+  const int lane = lane_id(), n_cu = a.n_cu, b = (int)blockIdx.x;
+  const int q = b / n_cu, j = b - q * n_cu, c0 = j / CUS * CUS, wd = min(CUS, n_cu - c0), q0 = q / ROUNDS * ROUNDS;
+  const int base = q0 * n_cu + c0;
+  const int words = (min(ROUNDS, (a.B - base + n_cu - 1) / n_cu) * wd + 63) / 64;
+  auto member = [&](int m) { const int r = m / wd; return base + r * n_cu + (m - r * wd); };  // the group's m-th row
+#pragma unroll 1
+  for (int k = wave_id(); k < words; k += NWV) {
+    const int m = k * 64 + lane, r = member(m);
+    const bool in = m < wd * ROUNDS && r < a.B;
+    const bool is_long = in && long_epilogue(a.params[in ? r : 0], a.V);
+    const u64 ml = __ballot(is_long), ms = __ballot(in && !is_long);
+    if (lane == 0) { S.r64a[k] = ml; S.r64b[k] = ms; }
+  }
+  __syncthreads();
+  const u64 ml = lane < words ? S.r64a[lane] : 0ull, ms = lane < words ? S.r64b[lane] : 0ull;
+  unsigned at = (unsigned)((q - q0) * wd + (j - c0));  // this workgroup's place
+  const unsigned n_long = wave_sum((unsigned)__popcll(ml));
+  const u64 mask = at < n_long ? ml : ms;
+  at -= at < n_long ? 0u : n_long;
+  const unsigned c = (unsigned)__popcll(mask), incl = wave_incl_scan(c);
+  const int k = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(at >= incl - c && at < incl)) - 1);
+  const u64 word = read_lane(mask, k);
+  at -= read_lane(incl, k) - (unsigned)__popcll(word);
+  const u64 hit = __ballot(((word >> lane) & 1ull) != 0ull && lanes_before(word) == at);
+  return __builtin_amdgcn_readfirstlane(member(k * 64 + __ffsll((long long)hit) - 1));
+}
+
 // ---------------------------------------------------------------- the kernel ------------------
 // (The second launch bound is HIP's: waves per SIMD, not workgroups per compute unit.  Four waves per
 // SIMD, 128 registers each, are sixteen waves per compute unit at every workgroup size: four
@@ -934,7 +974,11 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ FS S;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row = a.order ? a.order[blockIdx.x] : (int)blockIdx.x;  // (rows with long epilogues first: see order_rows_kernel)
+  int row = (int)blockIdx.x;
+  if constexpr (!WHOLE) {
+    if (sizeof(DT) == 2 && a.order) row = a.order[blockIdx.x];
+    else if (sizeof(DT) == 4 && a.pick) row = pick_row<NTHR>(a, S);
+  }
   const int V = a.V;
   const DT* rowp = reinterpret_cast<const DT*>(a.logits) + (size_t)row * (size_t)a.stride;
   // the pattern-count kernel, when it ran before this one, has left NOT_TAKEN on every row that is still to do
@@ -1584,24 +1628,6 @@ static hipError_t launch_fast_dtype(const SampleArgs& a, hipStream_t st) {
   if (a.F.whole) return a.st_rec ? launch_fast_instance<DT, true, true>(a, st) : launch_fast_instance<DT, false, true>(a, st);
   return a.st_rec ? launch_fast_instance<DT, true, false>(a, st) : launch_fast_instance<DT, false, false>(a, st);
 }
-// The order in which the single-pass kernel's workgroups take the rows of a launch: rows with long
-// epilogues first, the others behind them, each group in row order.  Workgroups are handed to the
-// compute units in turn, so that a compute unit holds workgroups b, b + (number of compute units),
-// ...: with the long rows at the front every compute unit gets its share of them instead of some
-// holding four (measured on the heterogeneous batch: a compute unit with four such rows finishes
-// 20 us after one with two), and a launch of several rounds starts its longest rows first.
-constexpr int ORD_T = 1024;
-__global__ __launch_bounds__(ORD_T) void order_rows_kernel(const SampleArgs a) {
-  __shared__ unsigned wsum[ORD_T / 64];
-  order_rows_body<ORD_T>(a, wsum);
-}
-
-hipError_t launch_order(const SampleArgs& a, hipStream_t st) {
-  if (!a.order || a.B <= 0 || a.B > WIDE_SLOTS) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(order_rows_kernel, dim3(1), dim3(ORD_T), 0, st, a);
-  return hipGetLastError();
-}
-
 hipError_t launch_fast(const SampleArgs& a, int dtype, hipStream_t st) {
   return dtype == SIMPLE_F32 ? launch_fast_dtype<float>(a, st) : launch_fast_dtype<uint16_t>(a, st);
 }

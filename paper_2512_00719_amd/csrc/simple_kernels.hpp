@@ -96,8 +96,9 @@ struct SampleArgs {
   // Queues of the rows that a kernel leaves to a later one of the same launch.  The counts are zero between
   // launches: the general kernel, the last one, clears them, so that a captured launch can be replayed.
   uint32_t* pend;  // rows left to the general kernel: [0] count, [1] its workgroups that have read the count, [2 ..] row indices
-  int32_t* order;  // row of each workgroup of the single-pass kernel (written by the ordering kernel of a launch with more rows
-                   // than compute units), or nullptr: workgroup b takes row b
+  int32_t* order;  // bfloat16: row of each workgroup of the single-pass kernel (written by the kernel ahead of it in a launch with more
+                   // rows than compute units), or nullptr: workgroup b takes row b
+  int pick;        // float32: 1 where the launch has more rows than compute units (each workgroup finds its row, long epilogues first)
   uint32_t* wq;    // rows with a whole-vocabulary nucleus wider than the list: [0], [1] counts, records from word 16
   unsigned char* wws;  // one workspace slot per queued row
   int wide_slots;
@@ -181,7 +182,6 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
                             int64_t B, int n_cu);
 hipError_t launch_sample(const SampleArgs& a, int dtype, bool vec, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_fast(const SampleArgs& a, int dtype, hipStream_t st);
-hipError_t launch_order(const SampleArgs& a, hipStream_t st);  // fills a.order; before launch_fast
 hipError_t launch_pattern(const SampleArgs& a, hipStream_t st);  // before launch_fast, when a.pattern_on
 hipError_t launch_wide(const SampleArgs& a, int dtype, hipStream_t st);  // after launch_fast, before the general kernel
 hipError_t set_max_lds(unsigned bytes);
