@@ -1477,16 +1477,20 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     __syncthreads();
     // mass below g (integer, exact) and the decision between the list and the kernels that follow
     u64 S_below_int = 0ull, M_list = 0ull, M_cert = 0ull;
-    bool wide = false;
+    bool wide = false, ties_at_g = false;
     if (C.need_sum) {
       blk_sum3<NWV>(S, below_mass, mlist, mcert, S_below_int, M_list, M_cert);
       const u64 target = (u64)__double2ull_ru((double)R.top_p * (double)(M_list + S_below_int));
       // (a column more than 2^21 above g: these sums say nothing, the sorted list does)
       wide = !R.minp_on && M_cert < target && !((S.flags >> 30) & 1u);
+      ties_at_g = wide && M_list >= target - (target >> 18);  // (the margin: this sum's error against the bins' one)
     }
     const double S_below = (double)S_below_int / (double)MSCALE;
     const uint32_t kmax = S.kmax;
-    if (tid == 0) S.wmax[0] = -INFINITY;  // (lower end of what the sliced kernels may take as above their threshold)
+    // Lower end of what the sliced kernels may take as above their threshold, below which they look for the cut: where the cut lies
+    // among columns equal to g, just above these.  (They gave such a row up and it went to the general kernel: one of 41,000
+    // bfloat16 rows of 256,000 columns with penalties, every tenth call of 4096 rows; such a call 1765 us, 1027 so, 860 without such a row.)
+    if (tid == 0) S.wmax[0] = ties_at_g ? C.y_g + (0.01f + 1e-6f * fabsf(C.y_g)) : -INFINITY;
     if (S.flags & SIMPLE_DIAG_ERROR) rc = FIN_DONE;
     else if (kmax <= key_g || kmax <= KEY_NEG_INF) rc = FIN_PENDING;
     else if (wide) {
