@@ -451,6 +451,14 @@ __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a
 // history columns, 2 to 3 us of a slice's 5 to 9.  338 rows of 256,000 columns with 8192 ids each: bins kernel 101 us, 78 so (the slices
 // take 25 to 30, the 173 MB at the HBM rate; the history columns 18); classifying kernel 185, 115 (slices 55).  float32 rows the
 // same way, each column weighed: no gain (90 of 128,256 columns, 21 and 26 us either way).
+// A run of few slices does not repay its table's making and its reading out, the fewer the more history columns a slice has.  Calls
+// whose workgroups take 1, 4, 8 and 16 slices, 64 ids a row, by slices and by runs: 40,000 columns 88, 139, 206 and 347 us, 96, 143, 185 and
+// 306; 128,256 columns with 2048 ids 93, 127, 175 and 284, 100, 123, 149 and 222; with 8192 ids 10 slices 239 and 250, 16 slices 311 and 293.
+// The two kernels divide the slices alike (one grid), so that the same slices are counted and looked up.
+constexpr int RUN_MIN = 6, RUN_IDS = 24;
+__device__ __forceinline__ bool takes_run(const WideRow& W, unsigned n_sl, int sl0, int sl1) {
+  return W.mode == WIDE_TOP_P && !W.f64 && (unsigned)(sl1 - sl0) >= RUN_MIN + W.distinct / (RUN_IDS * n_sl);
+}
 // One 4-byte entry a pattern: magnitude index 0 is zero itself, 1 .. QMAX - 1 one pattern each, QMAX, among the negative
 // ones, what lies so far down that it has no mass.  A lane's group with any other value (tiny ones, 256 and more, NaN) goes
 // column by column.
@@ -705,7 +713,7 @@ __global__ __launch_bounds__(WT, 4) void wide_bins_kernel(const SampleArgs a) {
   u64 mtop = 0ull;
   unsigned ntop = 0u;      // top-k route: columns at or above g seen by this thread
   float ymax = -INFINITY;  // rows with a min-p cut: largest tempered value seen by this thread
-  const bool run = BF16 && W.mode == WIDE_TOP_P && !W.f64;
+  const bool run = BF16 && takes_run(W, I.n_sl, sl0, sl1);
   auto flush = [&]() {
     __syncthreads();
     if (W.mode == WIDE_TOP_P || W.mode == WIDE_TOP_K) {
@@ -1059,7 +1067,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     } else if (b == bstar) { if (ids_only) put(z, idx); else stage(atomicAdd(&l_n, 1u), ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx); }
   };
   auto one = [&](float z, int idx) { one_of(z, idx, use_hot && hot_bit(hot_bits, (uint32_t)idx)); };
-  if constexpr (BF16) if (W.mode == WIDE_TOP_P && !W.f64) {
+  if constexpr (BF16) if (takes_run(W, I.n_sl, sl0, sl1)) {
     // An entry is the mass of one of the pattern's columns if they surely survive and it is below 2^30 (four times the mass
     // at g), and MARKED for columns that are looked at one by one: boundary columns, and those with more mass.
     constexpr uint32_t MARKED = 0x80000000u;
