@@ -179,14 +179,25 @@ def simple_set_stats(ctx: int, stats_ptr: int) -> int:
 
 
 # (The calls of a decoding step pass plain integers: the argument types convert them.  Wrapped one by one first, a call's arguments took
-# 2.9 us to marshal, 1.7 so.)
+# 2.9 us to marshal, 2.0 so.)
 MASK64 = 2 ** 64 - 1
+
+
+# (As arguments of that type a host `bytes`, `str` or array would be taken for an address too.  Integers pass the disjunction that each
+# call forms of its addresses, 0.3 us of it; anything else comes here.)
+def _addresses(*given):
+    return [ctypes.c_void_p(x).value for x in given]
 
 
 def simple_sample(ctx: int, logits_ptr: int, B: int, V: int, dtype: int, row_stride: int, params_ptr: int,
                   hist_ptr_ptr: int, hist_ids_ptr: int, hot_ids_ptr: int, H: int, seed: int, step: int,
                   row_offset: int, out_ids_ptr: int, diag_ptr: int, stream: int = 0) -> int:
     """Raw call: every *_ptr is a device address (0 for NULL).  Returns the C status code."""
+    try:
+        ctx | logits_ptr | params_ptr | hist_ptr_ptr | hist_ids_ptr | hot_ids_ptr | out_ids_ptr | diag_ptr | stream
+    except TypeError:
+        (ctx, logits_ptr, params_ptr, hist_ptr_ptr, hist_ids_ptr, hot_ids_ptr, out_ids_ptr, diag_ptr, stream) = _addresses(
+            ctx, logits_ptr, params_ptr, hist_ptr_ptr, hist_ids_ptr, hot_ids_ptr, out_ids_ptr, diag_ptr, stream)
     return int(_lib.simple_sample(ctx, logits_ptr, int(B), int(V), int(dtype), int(row_stride),
                                   params_ptr, hist_ptr_ptr, hist_ids_ptr, hot_ids_ptr, int(H),
                                   seed & MASK64, step & MASK64,
@@ -198,6 +209,11 @@ def simple_sample_static(logits_ptr: int, B: int, V: int, dtype: int, row_stride
                          hist_ptr_ptr: int, hist_ids_ptr: int, hot_ids_ptr: int, H: int, seed: int, step: int,
                          row_offset: int, out_ids_ptr: int, diag_ptr: int, stream: int = 0) -> int:
     """Raw call of the entry point that allocates nothing (no context).  Returns the C status code."""
+    try:
+        logits_ptr | params_ptr | hist_ptr_ptr | hist_ids_ptr | hot_ids_ptr | out_ids_ptr | diag_ptr | stream
+    except TypeError:
+        (logits_ptr, params_ptr, hist_ptr_ptr, hist_ids_ptr, hot_ids_ptr, out_ids_ptr, diag_ptr, stream) = _addresses(
+            logits_ptr, params_ptr, hist_ptr_ptr, hist_ids_ptr, hot_ids_ptr, out_ids_ptr, diag_ptr, stream)
     return int(_lib.simple_sample_static(logits_ptr, int(B), int(V), int(dtype), int(row_stride),
                                          params_ptr, hist_ptr_ptr, hist_ids_ptr, hot_ids_ptr, int(H),
                                          seed & MASK64, step & MASK64,
@@ -217,6 +233,11 @@ def simple_sample_hot_first(ctx: int, logits_ptr: int, B: int, V: int, dtype: in
                             tail_stats_ptr: int, seed: int, step: int, row_offset: int, out_ids_ptr: int, diag_ptr: int,
                             stream: int = 0) -> int:
     """Raw call: SHVS on a hot-first vocabulary with per-row tail statistics.  Returns the C status code."""
+    try:
+        ctx | logits_ptr | params_ptr | tail_stats_ptr | out_ids_ptr | diag_ptr | stream
+    except TypeError:
+        (ctx, logits_ptr, params_ptr, tail_stats_ptr, out_ids_ptr, diag_ptr, stream) = _addresses(
+            ctx, logits_ptr, params_ptr, tail_stats_ptr, out_ids_ptr, diag_ptr, stream)
     return int(_lib.simple_sample_hot_first(ctx, logits_ptr, int(B), int(V), int(dtype), int(row_stride), params_ptr, int(H),
                                             tail_stats_ptr, seed & MASK64,
                                             step & MASK64, row_offset & MASK64,
@@ -227,6 +248,11 @@ def simple_apply_logit_constraints(logits_ptr: int, B: int, V: int, dtype: int, 
                                    bias_vals_ptr: int, allow_ptr_ptr: int, allow_ids_ptr: int, out_ptr: int, out_stride: int,
                                    stream: int = 0) -> int:
     """Raw call: logit bias and allow-lists written out as a float32 matrix.  Returns the C status code."""
+    try:
+        logits_ptr | bias_ptr_ptr | bias_ids_ptr | bias_vals_ptr | allow_ptr_ptr | allow_ids_ptr | out_ptr | stream
+    except TypeError:
+        (logits_ptr, bias_ptr_ptr, bias_ids_ptr, bias_vals_ptr, allow_ptr_ptr, allow_ids_ptr, out_ptr, stream) = _addresses(
+            logits_ptr, bias_ptr_ptr, bias_ids_ptr, bias_vals_ptr, allow_ptr_ptr, allow_ids_ptr, out_ptr, stream)
     return int(_lib.simple_apply_logit_constraints(logits_ptr, int(B), int(V), int(dtype), int(row_stride), bias_ptr_ptr,
                                                    bias_ids_ptr, bias_vals_ptr, allow_ptr_ptr, allow_ids_ptr,
                                                    out_ptr, int(out_stride), stream))
@@ -247,11 +273,21 @@ def simple_state_destroy(state: Optional[int]) -> None:
 
 def simple_state_restart(state: int, slots_ptr: int, n: int, prompt_ptr_ptr: int, prompt_ids_ptr: int, n_prompt_ptr: int = 0,
                          stream: int = 0) -> int:
+    try:
+        state | slots_ptr | prompt_ptr_ptr | prompt_ids_ptr | n_prompt_ptr | stream
+    except TypeError:
+        (state, slots_ptr, prompt_ptr_ptr, prompt_ids_ptr, n_prompt_ptr, stream) = _addresses(
+            state, slots_ptr, prompt_ptr_ptr, prompt_ids_ptr, n_prompt_ptr, stream)
     return int(_lib.simple_state_restart(state, slots_ptr, int(n), prompt_ptr_ptr, prompt_ids_ptr, n_prompt_ptr,
                                          stream))
 
 
 def simple_state_append(state: int, slots_ptr: int, new_ids_ptr: int, B: int, stream: int = 0) -> int:
+    try:
+        state | slots_ptr | new_ids_ptr | stream
+    except TypeError:
+        (state, slots_ptr, new_ids_ptr, stream) = _addresses(
+            state, slots_ptr, new_ids_ptr, stream)
     return int(_lib.simple_state_append(state, slots_ptr, new_ids_ptr, int(B), stream))
 
 
@@ -259,6 +295,11 @@ def simple_sample_state(ctx: int, state: int, slots_ptr: int, logits_ptr: int, B
                         params_ptr: int, hot_ids_ptr: int, H: int, seed: int, step: int, row_offset: int,
                         out_ids_ptr: int, diag_ptr: int, stream: int = 0) -> int:
     """Raw call: the sampling call with the rows' histories taken from a state.  Returns the C status code."""
+    try:
+        ctx | state | slots_ptr | logits_ptr | params_ptr | hot_ids_ptr | out_ids_ptr | diag_ptr | stream
+    except TypeError:
+        (ctx, state, slots_ptr, logits_ptr, params_ptr, hot_ids_ptr, out_ids_ptr, diag_ptr, stream) = _addresses(
+            ctx, state, slots_ptr, logits_ptr, params_ptr, hot_ids_ptr, out_ids_ptr, diag_ptr, stream)
     return int(_lib.simple_sample_state(ctx, state, slots_ptr, logits_ptr, int(B), int(V), int(dtype),
                                         int(row_stride), params_ptr, hot_ids_ptr, int(H),
                                         seed & MASK64, step & MASK64,

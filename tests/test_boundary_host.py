@@ -1,5 +1,6 @@
 """Host-side checks of the C boundary that need no GPU: the library loads, exports every symbol
 the header declares, and rejects bad arguments before touching a device."""
+import ctypes
 import os
 import re
 
@@ -99,3 +100,24 @@ def test_synthetic_configs_have_the_stated_shapes():
     # reproducible from the seed
     w2 = synth.make_config(4, B=8, V=4096, H=256)
     assert np.array_equal(w.logits, w2.logits) and np.array_equal(w.hot_ids, w2.hot_ids)
+
+
+@pytest.mark.parametrize("wrong", [b"host bytes", "text", (ctypes.c_int32 * 4)(), 1.5, np.zeros(4)])
+def test_only_integers_are_taken_as_addresses(wrong):
+    refused = pytest.raises((TypeError, ValueError, ctypes.ArgumentError))
+    # the handle stays NULL, so that nothing could run: what is refused is refused ahead of the call
+    with refused:
+        binding.simple_sample(0, wrong, 1, 8, 0, 8, 0, 0, 0, 0, 0, 1, 0, 0, 0, 0)
+    with refused:
+        binding.simple_sample_static(0, 0, 8, 0, 8, wrong, 0, 0, 0, -1, 1, 0, 0, 0, 0)
+    with refused:
+        binding.simple_sample_hot_first(0, 0, 1, 4096, 0, 4096, wrong, 1024, 0, 1, 0, 0, 0, 0)
+    with refused:
+        binding.simple_apply_logit_constraints(0, 0, 8, 0, 8, 0, 0, 0, 0, 0, wrong, 8)
+    with refused:
+        binding.simple_state_restart(0, wrong, 1, 0, 0, 0)
+    with refused:
+        binding.simple_state_append(0, 0, wrong, 1)
+    with refused:
+        binding.simple_sample_state(0, 0, wrong, 0, 1, 8, 0, 8, 0, 0, 0, 1, 0, 0, 0, 0)
+    assert binding.simple_sample(None, None, 1, 8, 0, 8, None, None, None, None, 0, 1, 0, 0, None, None, None) == binding.SIMPLE_EINVAL
