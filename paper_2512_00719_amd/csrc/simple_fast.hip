@@ -1096,7 +1096,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   // Hands the row to the kernels of the whole-vocabulary routes: a queue record, a cleared workspace
   // slot and the row's history tables (rebuilt first if the region no longer holds them).  False if
   // no slot is free.  All threads call.
-  auto queue_wide = [&](uint32_t mode, bool tables_live, float g_ref) -> bool {
+  auto queue_wide = [&](uint32_t mode, bool tables_live, float g_ref, float y_max) -> bool {
     __syncthreads();
     if (H.active && !tables_live) {
       if (stateful) load_tables(true);
@@ -1122,9 +1122,9 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     }
     if (tid == 0) {
       WideRec rec;
-      rec.row = (uint32_t)row; rec.g = g_ref; rec.mode = mode | ((a.f64 || g_ref > C.g) ? WIDE_F64 : 0u); rec.flags = S.flags & 0x3FFFFFFFu;
+      rec.row = (uint32_t)row; rec.g = g_ref; rec.mode = mode | ((a.f64 || g_ref > C.g) ? WIDE_F64 : 0u) | (y_max > -INFINITY ? WIDE_MAX : 0u); rec.flags = S.flags & 0x3FFFFFFFu;
       rec.tau = R.tau; rec.top_p = R.top_p; rec.rep = par.rep_penalty; rec.freq = par.freq_penalty;
-      rec.pres = par.pres_penalty; rec.ln_min_p = R.minp_on ? (float)log((double)R.min_p) : 0.0f; rec.n_prompt = min(max(rh.n_prompt, 0), nnz); rec.h_active = h_active ? 1 : 0;
+      rec.pres = par.pres_penalty; rec.ln_min_p = R.minp_on ? (float)log((double)R.min_p) : 0.0f; rec.y_max = y_max; rec.h_active = h_active ? 1 : 0;
       rec.min_p = R.min_p; rec.top_k = par.top_k; rec.distinct = H.active ? S.distinct : 0u;
       rec.far_slot = 0u;
       reinterpret_cast<WideRec*>(a.wq + WQ_HEAD)[slot] = rec;
@@ -1261,7 +1261,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     return g;
   };
   if (straight) {  // (without truncation the threshold is only the reference of the masses)
-    if (!queue_wide(straight_mode, true, a.f64 ? below_sample_top() : C.g) && tid == 0) queue_pending(a, row);
+    if (!queue_wide(straight_mode, true, a.f64 ? below_sample_top() : C.g, -INFINITY) && tid == 0) queue_pending(a, row);
     return;
   }
   const bool minp_only = !R.greedy && !R.k_on && !R.p_on && R.minp_on;
@@ -1353,6 +1353,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
   // the stream added 2^28 for every column at or above g: all of them were counted for the list
   if (C.need_sum && tid == 0) below_mass -= (u64)n << 28;
   float g_ref = C.g;         // threshold for the sliced kernels
+  float y_rel = -INFINITY;   // what masses are relative to there, if not to the threshold
   bool tables_live = false;  // the region holds the history tables
   // more columns at or above g than the list holds, and a cut that the whole-vocabulary routes find
   // without the list
@@ -1488,7 +1489,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     const double S_below = (double)S_below_int / (double)MSCALE;
     const uint32_t kmax = S.kmax;
     // Lower end of what the sliced kernels may take as above their threshold, below which they look for the cut: where the cut lies
-    // among columns equal to g, just above these.  (They gave such a row up and it went to the general kernel: one of 41,000
+    // among columns equal to g, just above these (WIDE_MAX).  (They gave such a row up and it went to the general kernel: one of 41,000
     // bfloat16 rows of 256,000 columns with penalties, every tenth call of 4096 rows; such a call 1765 us, 1027 so, 860 without such a row.)
     if (tid == 0) S.wmax[0] = ties_at_g ? C.y_g + (0.01f + 1e-6f * fabsf(C.y_g)) : -INFINITY;
     if (S.flags & SIMPLE_DIAG_ERROR) rc = FIN_DONE;
@@ -1586,16 +1587,18 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
 
     // ---- a cut below the list's reach: the row goes to the kernels that follow ----
     // (masses there are relative to the threshold and reach 2^21 above it: where the row maximum stands
-    // higher, the threshold is moved up to e^10 below it, and above a bucket of ties that holds the cut)
+    // higher, the threshold is moved up to e^10 below it, and above a bucket of ties that holds the cut; above ties
+    // at g alone, masses are relative to the maximum)
     if (rc == FIN_WIDE) {
       __syncthreads();
       const float y_m = keyf(kmax);
-      const float y_ref = fmaxf((a.f64 || y_m - C.y_g > 13.5f || S.wmax[0] > -INFINITY) ? y_m - F64_MARGIN : -INFINITY, S.wmax[0]);
-      g_ref = fmaxf(g_ref, y_ref * R.tau);
+      const float y_ref = (a.f64 || y_m - C.y_g > 13.5f || (S.wmax[0] > -INFINITY && !ties_at_g)) ? y_m - F64_MARGIN : -INFINITY;
+      if (ties_at_g && !(y_ref > C.y_g)) y_rel = y_m;
+      g_ref = fmaxf(g_ref, fmaxf(y_ref, S.wmax[0]) * R.tau);
     }
   }
   if (rc == FIN_WIDE) {
-    if (!whole && queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, tables_live, g_ref)) return;  // (no such kernel runs behind rows listed whole)
+    if (!whole && queue_wide(R.need_sum ? WIDE_TOP_P : WIDE_MIN_P, tables_live, g_ref, y_rel)) return;  // (no such kernel runs behind rows listed whole)
     rc = FIN_PENDING;  // no free slot: the general kernel takes the row
   }
   if (tid == 0) {

@@ -89,12 +89,10 @@ __device__ __forceinline__ Exp2Poly exp2_poly_from_memory() {
   for (int i = 0; i < 10; ++i) P.c[i] = as_global(q->c)[i];
   return P;
 }
-// Nearest integer to exp(y - y_ref) * 2^BITS, for y up to (51 - BITS) ln 2 above y_ref: 2^n * 2^f with
+// Nearest integer to exp(y - y_ref) * 2^bits, for y up to (51 - bits) ln 2 above y_ref: 2^n * 2^f with
 // n = rint(x log2 e) and the Taylor polynomial of degree 10 for 2^f on [-1/2, 1/2] (relative error
 // below 1e-12).  Far below y_ref (and for a NaN) it is zero.
-template <int BITS>
-__device__ __forceinline__ u64 exp_fix(float y, float y_ref, const Exp2Poly& P) {
-  static_assert(BITS <= 51, "the integer takes the low 52 bits of a double");
+__device__ __forceinline__ u64 exp_fix(float y, float y_ref, int bits, const Exp2Poly& P) {
   const double x = (double)y - (double)y_ref;
   if (!(x >= -44.0)) return 0ull;
   const double t = x * 1.4426950408889634;
@@ -104,8 +102,13 @@ __device__ __forceinline__ u64 exp_fix(float y, float y_ref, const Exp2Poly& P) 
   for (int i = 1; i < 10; ++i) p = fma(p, f, P.c[i]);
   p = fma(p, f, 1.0);
   // adding 2^52 rounds to the nearest integer and leaves it in the low 52 bits of the sum
-  const double v = ldexp(p, (int)n + BITS) + 0x1p52;
+  const double v = ldexp(p, (int)n + bits) + 0x1p52;
   return (u64)__double_as_longlong(v) & 0x000FFFFFFFFFFFFFull;
+}
+template <int BITS>
+__device__ __forceinline__ u64 exp_fix(float y, float y_ref, const Exp2Poly& P) {
+  static_assert(BITS <= 51, "the integer takes the low 52 bits of a double");
+  return exp_fix(y, y_ref, BITS, P);
 }
 template <int BITS>
 __device__ __forceinline__ u64 exp_fix(float y, float y_ref) { constexpr Exp2Poly P = EXP2_POLY; return exp_fix<BITS>(y, y_ref, P); }
@@ -366,7 +369,7 @@ struct StreamCtx {
 struct WideRec {  // 64 bytes: everything the later kernels need to know about the row
   uint32_t row; float g; uint32_t mode, flags;
   float tau, top_p, rep, freq;
-  float pres, ln_min_p; int n_prompt, h_active;
+  float pres, ln_min_p, y_max; int h_active;  // y_max: the largest tempered value (with WIDE_MAX)
   float min_p; int32_t top_k; uint32_t distinct;
   uint32_t far_slot;  // not this row's: the k-th record holds the slot of the k-th far row
 };
@@ -378,6 +381,7 @@ enum { WIDE_TOP_P = 0,   // the shortest prefix whose mass reaches top_p of the 
 constexpr uint32_t WIDE_MODE = 15u;     // the mode's bits of WideRec::mode; beside them:
 constexpr uint32_t WIDE_F64 = 16u;      // the row's columns are weighed in double precision
 constexpr uint32_t WIDE_FAR = 32u;      // (with WIDE_ALL) ... or a column stands too far above g for the integer masses
+constexpr uint32_t WIDE_MAX = 64u;      // (with WIDE_F64) masses are relative to the row's largest, not to the one at g
 constexpr int WQ_HEAD = 16;             // words before the records: [0] their number, [1] the number of far rows
 constexpr uint32_t WS_HIST = 0u;        // u64[NBW]: mass of the columns below g, by bin (top-k route: their number)
                                         // (rows without truncation: AllPart[128][4], per slice and wave)
@@ -424,10 +428,14 @@ constexpr float W_LIMIT = 2097152.0f;  // 2^21: largest mass relative to the one
 constexpr int F64_BITS = 36;
 constexpr float F64_REACH = 10.39f;    // below 15 ln 2
 constexpr float F64_MARGIN = 10.0f;    // where a threshold is put below the row's maximum
-__device__ __forceinline__ u64 mass_fix64(float y, const StreamCtx& C, const Exp2Poly& P) {
-  return exp_fix<F64_BITS>(fminf(y, C.y_g + F64_REACH), C.y_g, P);
+// Rows whose cut lies among columns equal to g (WIDE_MAX) have their threshold just above these, wherever the maximum stands: their
+// masses are the integers that the general kernel gives the row, 2^43 fixed point relative to the largest (at most 2^43 each, so
+// that a row's sum below 2^63).
+constexpr int F64_MAX_BITS = QBITS;
+struct MassRef { float y, reach; int bits; };  // what masses are relative to, how far above it they are carried, their fixed point
+__device__ __forceinline__ u64 mass_fix64(float y, const MassRef& M, const Exp2Poly& P) {
+  return exp_fix(fminf(y, M.y + M.reach), M.y, M.bits, P);
 }
-__device__ __forceinline__ u64 mass_fix64(float y, const StreamCtx& C) { constexpr Exp2Poly P = EXP2_POLY; return mass_fix64(y, C, P); }
 // Nearest integer of a float in [0, 2^52) as 64 bits, in two 32-bit conversions (the split is exact:
 // a float has 24 significant bits): hi counts units of 2^24.
 __device__ __forceinline__ void float_to_parts(float v, uint32_t& hi, uint32_t& lo) {

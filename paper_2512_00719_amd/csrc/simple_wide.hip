@@ -73,6 +73,7 @@ struct WideRow {
   uint32_t distinct;
   int top_k;
   bool f64, far;
+  MassRef M;  // (f64)
   unsigned char* ws;
 };
 
@@ -93,6 +94,8 @@ __device__ __forceinline__ WideRow load_row(const SampleArgs& a, unsigned slot) 
   W.tau = uni(rec.tau); W.top_p = uni(rec.top_p); W.min_p = uni(rec.min_p); W.ln_min_p = uni(rec.ln_min_p);
   W.C.g = uni(rec.g); W.C.y_g = uni(rec.g / rec.tau); W.C.inv_tau = uni(1.0 / (double)rec.tau); W.C.need_sum = true;
   W.C.l2e_tau = 0.0f;
+  const bool by_max = (uni(rec.mode) & WIDE_MAX) != 0u;
+  W.M = {by_max ? uni(rec.y_max) : W.C.y_g, by_max ? 0.0f : F64_REACH, by_max ? F64_MAX_BITS : F64_BITS};
   W.rep = uni(rec.rep); W.freq = uni(rec.freq); W.pres = uni(rec.pres);
   W.inv_rep = uni(1.0 / (double)rec.rep);
   W.h_active = uni(rec.h_active) != 0;
@@ -819,7 +822,7 @@ __global__ __launch_bounds__(WT, 4) void wide_bins_kernel(const SampleArgs a) {
         int b; float y;
         (void)mass_term(z, W.C, b, y);
         ymax = fmaxf(ymax, y);
-        const u64 m = mass_fix64(y, W.C, P);
+        const u64 m = mass_fix64(y, W.M, P);
         if (z < W.C.g) atomicAdd(&lh[b], m); else mtop += m;
       });
       if (W.h_active) __syncthreads();  // the tables are rewritten by the next item
@@ -1223,8 +1226,8 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
       weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int idx, const Exp2Poly& P) {
         int b; float y;
         (void)mass_term(z, W.C, b, y);
-        bad = bad || !(y - W.C.y_g <= F64_REACH);  // a mass the fixed point cannot carry, or a NaN
-        const u64 m = mass_fix64(y, W.C, P);
+        bad = bad || !(y - W.M.y <= W.M.reach);  // a mass the fixed point cannot carry, or a NaN
+        const u64 m = mass_fix64(y, W.M, P);
         acc_all += m;
         ymax = fmaxf(ymax, y);
         if (!(y >= thr_y)) return;
@@ -1452,7 +1455,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   const u64 m_sure = blk_sum_u64<FNW>(S, tv);  // barriers inside
   Exp2Poly P{};  // (from memory where they are needed: as literals they took registers from end to end)
   if (W.f64) P = exp2_poly_from_memory();
-  auto mass_at = [&](unsigned t) -> u64 { return W.f64 ? mass_fix64(keyf((uint32_t)(rcmp[t] >> 32)), C, P) : (u64)rl[t]; };
+  auto mass_at = [&](unsigned t) -> u64 { return W.f64 ? mass_fix64(keyf((uint32_t)(rcmp[t] >> 32)), W.M, P) : (u64)rl[t]; };
   const u64 m_above = top_k_route ? (u64)n_sure : m_sure;
   const u64 target = top_k_route ? (u64)W.top_k : (u64)__double2ull_ru((double)W.top_p * (double)S_tot);
   if (m_above >= target) { return false; }
@@ -1599,7 +1602,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
   const u64 S_cls = use_hot ? (pick_hot ? S1 : S0) : S_K;
   const double u = use_hot ? (pick_hot ? u3[0] : u3[2]) : u3[0];
   dg.n_survivors = (int)ns;
-  if (a.diag) dg.s_k = (double)(top_k_route ? S_K : S_tot) / (W.f64 ? (double)(1ull << F64_BITS) : (double)MSCALE) * exp((double)C.y_g - (double)keyf(kmax));
+  if (a.diag) dg.s_k = (double)(top_k_route ? S_K : S_tot) / (W.f64 ? (double)(1ull << W.M.bits) : (double)MSCALE) * exp((double)(W.f64 ? W.M.y : C.y_g) - (double)keyf(kmax));
   if (S_cls == 0ull) { return false; }
   u64 tfix = (u64)__double2ull_rd(u * (double)S_cls);
   if (tfix >= S_cls) tfix = S_cls - 1ull;
@@ -1629,7 +1632,7 @@ __device__ inline bool finish_row(const SampleArgs& a, const WideRow& W, FS& S, 
     int b; float y;
     (void)mass_term(z, C, b, y);
     const bool in = (!(z < C.g) || b < bstar || (b == bstar && composite(fkey(y), (uint32_t)idx) >= cut_c)) && y >= thr_y;
-    return in ? mass_fix64(y, C, P) : 0ull;
+    return in ? mass_fix64(y, W.M, P) : 0ull;
   };
   const u64 lsum = W.f64 ? sum_columns<1>(zt, c0, mass64) : sum_columns<2>(zt, c0, mass);
   unsigned ce3, ct3; u64 me3, tot3;
