@@ -1,5 +1,9 @@
-"""Rows with a nucleus wider than the candidate list, weighed in runs of slices: history columns settled behind the run,
-bfloat16 columns by their patterns, groups with values that have no entry column by column.  Against the oracle."""
+"""Rows with a nucleus wider than the candidate list: float32 rows and calls of few rows slice by slice (test_runs), and calls
+whose workgroups take enough of a bfloat16 row's slices in runs of them (test_rows_in_runs): history columns settled behind the run,
+columns by their patterns, groups with values that have no entry column by column.  Against the oracle."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -64,3 +68,51 @@ def test_runs(dtype, V, B, nnz, hot):
         wide += int(((dg["flags"] & binding.DIAG_WIDE) != 0).sum())
         P.compare(ids, dg, P.run_oracle(w, step), range(B))
     assert wide > B // 2
+
+
+def run_rule():
+    """RUN_MIN and RUN_IDS of takes_run: a piece of a row is taken in a run from RUN_MIN + distinct / (RUN_IDS * slices of a row) slices."""
+    src = open(os.path.join(os.path.dirname(binding.__file__), "csrc", "simple_wide.hip")).read()
+    return [int(x) for x in re.search(r"RUN_MIN = (\d+), RUN_IDS = (\d+)", src).groups()]
+
+
+@pytest.mark.parametrize("V,chunk,nnz,hot", [(28_675, 13, 300, True), (40_960, 15, 700, False), (150_001, 21, 2500, True), (150_008, 30, 2500, False)])
+def test_rows_in_runs(V, chunk, nnz, hot):
+    """Nine rows, repeated until a workgroup takes `chunk` slices: pieces of a row long enough for a run, and shorter ones.  The first
+    nine and the last go through the oracle; masses are integers, so every copy of a row has the first one's, however it was cut."""
+    import torch
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    SLC, K = 4096, 9
+    n_sl = -(-V // SLC)
+    B = -(-chunk * 4 * n_cu // (n_sl * K)) * K
+    rng = np.random.default_rng(V + nnz)
+    ids9 = rng.integers(0, V, K * nnz).astype(np.int32)
+    ids9[::max(nnz // 2, 1)] = V - 1  # the last column, behind the last whole group
+    z9, tau9, pres9 = rows_of(rng, K, V, ids9, nnz, "bf16")
+    z9[6] += 300.0   # no value has an entry
+    z9[7] -= 300.0
+    z9[8] = z9[8] / 4.0 + 232.0  # (of kind 2) the largest have none
+    tau9[8] = 10.0
+    params9 = synth.make_params(K, temperature=tau9, top_p=rng.choice([0.8, 0.95, 0.99], K).astype(np.float32),
+                                min_p=np.where(np.arange(K) == 3, 1e-4, 0.0).astype(np.float32), rep_penalty=1.1, freq_penalty=0.1,
+                                pres_penalty=pres9, n_prompt=nnz // 3)
+    times = B // K
+    tile = lambda x: np.tile(x, (times,) + (1,) * (x.ndim - 1))
+    hot_ids = np.sort(rng.choice(V, V // 8, replace=False)).astype(np.int32) if hot else None
+    w = synth.Workload("in runs", B, V, "bf16", tile(synth.f32_to_bf16_bits(z9)), tile(params9), np.arange(B + 1, dtype=np.int64) * nnz, tile(ids9), hot_ids=hot_ids)
+    dev = P.to_device(w)
+    padded = torch.zeros(B, -(-V // 8) * 8, dtype=torch.bfloat16, device="cuda:0")  # (rows at 16-byte boundaries)
+    padded[:, :V] = dev["logits"]
+    dev["logits"] = padded[:, :V]
+    ids, dg = P.run_gpu(w, 1, dev=dev)
+    assert not (dg["flags"] & binding.DIAG_ERROR).any()
+    ends = list(range(K)) + list(range(B - K, B))
+    P.compare(ids, dg, P.run_oracle(w, 1, rows=ends), ends)
+    for f in ("s_k", "n_survivors", "alpha"):
+        assert np.array_equal(dg[f].reshape(times, K), np.broadcast_to(dg[f][:K], (times, K)), equal_nan=f == "alpha"), f
+    # slices a workgroup took, and what a run needs: most rows' pieces are runs
+    wide = int(((dg["flags"] & binding.DIAG_WIDE) != 0).sum())
+    run_min, run_ids = run_rule()
+    distinct = max(len(np.unique(ids9[b * nnz:(b + 1) * nnz])) for b in range(K))
+    assert min(-(-wide * n_sl // (4 * n_cu)), n_sl) >= run_min + distinct // (run_ids * n_sl), (wide, B)
+    assert wide >= B // 2
