@@ -459,12 +459,19 @@ __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a
 // 306; 128,256 columns with 2048 ids 93, 127, 175 and 284, 100, 123, 149 and 222; with 8192 ids 10 slices 239 and 250, 16 slices 311 and 293.
 // The two kernels divide the slices alike (one grid), so that the same slices are counted and looked up.
 constexpr int RUN_MIN = 6, RUN_IDS = 24;
+// A lane's group with a value that has no entry goes column by column, at a cost that only few groups may have: rows whose threshold
+// lies where there is none (a sample's quantile, it stands for the large values), or from which -256 has mass, are taken by
+// slices.  (512 rows of 256,000 columns, every logit raised by 300, by runs and by slices: 14.2 and 3.9 ms a call.)
+__device__ __forceinline__ bool values_in_table(const StreamCtx& C) {
+  int b;
+  const float w = mass_term(-256.0f, C, b), m = fabsf(C.g);
+  return m >= 0x1p-6f && m < 256.0f && b == NBW - 1 && mass_integer(w) == 0.0f;
+}
 __device__ __forceinline__ bool takes_run(const WideRow& W, unsigned n_sl, int sl0, int sl1) {
-  return W.mode == WIDE_TOP_P && !W.f64 && (unsigned)(sl1 - sl0) >= RUN_MIN + W.distinct / (RUN_IDS * n_sl);
+  return W.mode == WIDE_TOP_P && !W.f64 && (unsigned)(sl1 - sl0) >= RUN_MIN + W.distinct / (RUN_IDS * n_sl) && values_in_table(W.C);
 }
 // One 4-byte entry a pattern: magnitude index 0 is zero itself, 1 .. QMAX - 1 one pattern each, QMAX, among the negative
-// ones, what lies so far down that it has no mass.  A lane's group with any other value (tiny ones, 256 and more, NaN) goes
-// column by column.
+// ones, -256 and all below it (-inf among them), which has no mass.  None: other magnitudes below 2^-14, 256 and more, NaN.
 constexpr uint32_t PT_NEG = 0x4000u;  // byte offset of the negative patterns' entries: the sign bit, moved down one
 constexpr uint32_t PT_BYTES = PT_NEG + (uint32_t)NMAG * 4u;
 // Byte offsets of the two patterns of a word, low pattern in the low half.
@@ -492,17 +499,10 @@ struct PatternRange {
     umax = __builtin_elementwise_max(umax, __builtin_bit_cast(u16x2, x));
     pmin = __builtin_elementwise_min(pmin, (u16x2)(__builtin_bit_cast(u16x2, x & 0x7FFF7FFFu) - (u16x2)((unsigned short)1)));
   }
-  // neg_limit: the largest negative pattern that has one
-  __device__ __forceinline__ bool ok(uint32_t neg_limit) const {
-    return max((int)smax.x, (int)smax.y) < PHI && max((uint32_t)umax.x, (uint32_t)umax.y) <= neg_limit && min((uint32_t)pmin.x, (uint32_t)pmin.y) >= (uint32_t)(PLO - 1);
+  __device__ __forceinline__ bool ok() const {
+    return max((int)smax.x, (int)smax.y) < PHI && max((uint32_t)umax.x, (uint32_t)umax.y) <= 0xFF80u && min((uint32_t)pmin.x, (uint32_t)pmin.y) >= (uint32_t)(PLO - 1);
   }
 };
-// -256 and all below it (-inf among them) have an entry where they have no mass.
-__device__ __forceinline__ uint32_t pattern_neg_limit(const StreamCtx& C) {
-  int b;
-  const float w = mass_term(-256.0f, C, b);
-  return b == NBW - 1 && mass_integer(w) == 0.0f && C.g > -256.0f ? 0xFF80u : 0x8000u | (uint32_t)(PHI - 1);
-}
 
 // f(idx, z, z', hot) for every history column of the slices [sl0, sl1) of a row: the logit as read and the penalised one.
 // The mask's columns first go to a list in LDS, a column's place its rank less the run's first, so that all threads then have
@@ -605,10 +605,10 @@ __device__ __forceinline__ u64 row16_sum_u64(u64 v) {
 }
 static_assert(SLC / WT * 2 <= 32, "a lane's columns of a slice, below 2^49 each, sum below 2^54");
 // Whether all eight patterns of a group have an entry.
-__device__ __forceinline__ bool group_ok(const u32x4& w, uint32_t neg_limit) {
+__device__ __forceinline__ bool group_ok(const u32x4& w) {
   PatternRange R;
   R.take(w.x); R.take(w.y); R.take(w.z); R.take(w.w);
-  return R.ok(neg_limit);
+  return R.ok();
 }
 
 // ---------------------------------------------------------------- no truncation ---------------
@@ -752,7 +752,6 @@ __global__ __launch_bounds__(WT, 4) void wide_bins_kernel(const SampleArgs a) {
     }
   };
   if constexpr (BF16) if (run) {
-    const uint32_t neg_limit = pattern_neg_limit(W.C);
     if (tid < 4) odd[tid] = 0u;
     RunLoads<DT> N;
     run_fetch<DT, false>(N, a, rowp, sl0, false);
@@ -781,7 +780,7 @@ __global__ __launch_bounds__(WT, 4) void wide_bins_kernel(const SampleArgs a) {
           for (int idx = idx0; idx < V; ++idx) if (!hist_bit(W, idx)) add_column(Io<DT>::one(rowp + idx));
         } else {
           const u32x4 w = L.A[j];
-          if (group_ok(w, neg_limit)) {
+          if (group_ok(w)) {
             const uint32_t w4[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
             for (int k = 0; k < 4; ++k) { const uint32_t off = pattern_offsets2(w4[k]); count(off & 0xFFFFu, 1u); count(off >> 16, 1u); }
@@ -798,7 +797,7 @@ __global__ __launch_bounds__(WT, 4) void wide_bins_kernel(const SampleArgs a) {
       const int whole = V & ~(EPL - 1);  // (not those behind the last whole group)
       hist_run<DT, false>(W, a, rowp, sl0, sl1, hlist, [&](int idx, float z, float zp, bool) {
         const bool slice_odd = ((odd[idx / SLC >> 5] >> (idx / SLC & 31)) & 1u) != 0u;
-        if (idx < whole && (!slice_odd || group_ok(Io<DT>::load(rowp + (idx & ~(EPL - 1))), neg_limit))) count(pattern_offset(z), 0xFFFFFFFFu);
+        if (idx < whole && (!slice_odd || group_ok(Io<DT>::load(rowp + (idx & ~(EPL - 1)))))) count(pattern_offset(z), 0xFFFFFFFFu);
         add_column(zp);
       });
     }
@@ -1082,7 +1081,6 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
       return sum_to_u64(SUM_BASE + (double)mass_integer(fminf(w, W_LIMIT)));
     };
     ids_only = true;
-    const uint32_t neg_limit = pattern_neg_limit(W.C);
     uint32_t odd_words = 0u;  // (lanes 0 to 3) slices with groups that go column by column
     RunLoads<DT> N;
     run_fetch<DT, use_hot>(N, a, rowp, sl0, false);
@@ -1133,7 +1131,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
           for (int idx = idx0; idx < V; ++idx) if (!hist_bit(W, idx)) one(Io<DT>::one(rowp + idx), idx);
         } else {
           const u32x4 w = L.A[j];
-          if (!((read_lane(odd_words, sl >> 5) >> (sl & 31)) & 1u) || group_ok(w, neg_limit)) {
+          if (!((read_lane(odd_words, sl >> 5) >> (sl & 31)) & 1u) || group_ok(w)) {
             const uint32_t w4[4] = {w.x, w.y, w.z, w.w};
             uint32_t ev[EPL], any = 0u, sum[2] = {0u, 0u}, sum_h[2] = {0u, 0u};  // (of four columns: below 2^32, and a mark is 2^31)
 #pragma unroll
@@ -1189,7 +1187,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
       hist_run<DT, use_hot>(W, a, rowp, sl0, sl1, hlist, [&](int idx, float z, float zp, bool hot) {
         const int sl = idx / SLC;
         u64 was = 0ull;  // what it was taken for
-        if (idx < whole && (!((odd[sl >> 5] >> (sl & 31)) & 1u) || group_ok(Io<DT>::load(rowp + (idx & ~(EPL - 1))), neg_limit))) {
+        if (idx < whole && (!((odd[sl >> 5] >> (sl & 31)) & 1u) || group_ok(Io<DT>::load(rowp + (idx & ~(EPL - 1)))))) {
           was = (u64)ptab[pattern_offset(z) / 4u];
           if (was & (u64)MARKED) { bool over; was = z >= zc.z_sure ? clamped(z, over) : 0ull; }
           if (z >= zc.z_sure) --n_sure;
