@@ -55,6 +55,9 @@ namespace fast {
 
 constexpr int WT = 256;      // threads per workgroup
 constexpr int WNW = WT / 64;
+constexpr uint32_t LDS_PER_CU = 163840u;
+constexpr int WGS = 4;       // workgroups of the bins and the classifying kernel on a compute unit, by registers and LDS ...
+template <typename DT, bool RUNS> constexpr int bins_wgs() { return sizeof(DT) == 2 && !RUNS ? 5 : WGS; }  // ... more where they fit
 constexpr int SLC = 4096;    // columns per slice
 constexpr int ICAP = 512;    // places for boundary columns that a slice finds free in the stage (more go to the row's list one by one)
 constexpr int MAX_SLICES = FAST_MAX_V / SLC;
@@ -686,18 +689,18 @@ __device__ __forceinline__ void all_slice(const ItemLoads<DT>& L, const HistPre<
 }
 
 // ---------------------------------------------------------------- bins ------------------------
-template <typename DT, bool use_hot>
-__global__ __launch_bounds__(WT, 4) void wide_bins_kernel(const SampleArgs a) {
+template <typename DT, bool use_hot, bool RUNS>  // RUNS: the call may bring runs of slices (bfloat16)
+__global__ __launch_bounds__(WT, (bins_wgs<DT, RUNS>())) void wide_bins_kernel(const SampleArgs a) {
   constexpr int EPL = Io<DT>::EPL;
   constexpr int G = ItemLoads<DT>::G;
-  constexpr bool BF16 = sizeof(DT) == 2;
   __shared__ SliceTabs Tb;
-  constexpr uint32_t ACC_BYTES = BF16 ? PT_BYTES : (uint32_t)(NBW + 1) * 8u;
+  constexpr uint32_t ACC_BYTES = RUNS ? PT_BYTES : (uint32_t)(NBW + 1) * 8u;
   static_assert(ACC_BYTES >= (uint32_t)(NBW + 1) * 8u, "the bins fit");
-  __shared__ __align__(16) u64 lh[(ACC_BYTES + 15u) / 16u * 2u];  // the bins, and the mass at or above g; bfloat16 runs: columns per pattern
-  __shared__ uint32_t odd[4];  // bfloat16 runs: slices with groups that went column by column
+  __shared__ __align__(16) u64 lh[(ACC_BYTES + 15u) / 16u * 2u];  // the bins, and the mass at or above g; runs: columns per pattern
+  __shared__ uint32_t odd[4];  // runs: slices with groups that went column by column
   __shared__ uint32_t hlist[HLIST];
   __shared__ FS S;
+  static_assert((sizeof(Tb) + sizeof(lh) + (RUNS ? sizeof(odd) + sizeof(hlist) : 0u) + sizeof(S)) * bins_wgs<DT, RUNS>() <= LDS_PER_CU, "a resident round by LDS");
   const int tid = threadIdx.x;
   const int V = a.V;
   // mask word and bit of this thread's first column in each of its groups (a group step is whole words)
@@ -716,7 +719,7 @@ __global__ __launch_bounds__(WT, 4) void wide_bins_kernel(const SampleArgs a) {
   u64 mtop = 0ull;
   unsigned ntop = 0u;      // top-k route: columns at or above g seen by this thread
   float ymax = -INFINITY;  // rows with a min-p cut: largest tempered value seen by this thread
-  const bool run = BF16 && takes_run(W, I.n_sl, sl0, sl1);
+  const bool run = RUNS && takes_run(W, I.n_sl, sl0, sl1);
   auto flush = [&]() {
     __syncthreads();
     if (W.mode == WIDE_TOP_P || W.mode == WIDE_TOP_K) {
@@ -751,7 +754,7 @@ __global__ __launch_bounds__(WT, 4) void wide_bins_kernel(const SampleArgs a) {
       if ((tid & 63) == 0 && m > -INFINITY) atomicMax(reinterpret_cast<uint32_t*>(W.ws + WS_SCAL) + 6, fkey(m));
     }
   };
-  if constexpr (BF16) if (run) {
+  if constexpr (RUNS) if (run) {
     if (tid < 4) odd[tid] = 0u;
     RunLoads<DT> N;
     run_fetch<DT, false>(N, a, rowp, sl0, false);
@@ -954,24 +957,24 @@ __device__ __forceinline__ void far_rows(SliceTabs& Tb, FS& S, const SampleArgs&
     }
   }
 }
-template <typename DT, bool use_hot>  // use_hot: a hot set is installed (section 5.3): masses are split by class
-__global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a) {
+template <typename DT, bool use_hot, bool RUNS>  // use_hot: a hot set is installed (section 5.3): masses are split by class
+__global__ __launch_bounds__(WT, WGS) void wide_classify_kernel(const SampleArgs a) {
   constexpr int EPL = Io<DT>::EPL;
   constexpr int G = ItemLoads<DT>::G;  // a slice is one tile of the draw's walk
   constexpr unsigned EMASK = (1u << EPL) - 1u;
-  constexpr bool BF16 = sizeof(DT) == 2;
-  constexpr int LCAP = BF16 ? 768 : 2048;  // size of the stage, which is written out once fewer than ICAP places are free
-  // bfloat16 runs: an entry per pattern of the current row; else the tables of a slice
-  __shared__ __align__(16) uint32_t ptab[((BF16 ? PT_BYTES : (uint32_t)sizeof(SliceTabs)) + 15u) / 16u * 4u];
+  constexpr int LCAP = RUNS ? 768 : 2048;  // size of the stage, which is written out once fewer than ICAP places are free
+  // runs: an entry per pattern of the current row; else the tables of a slice
+  __shared__ __align__(16) uint32_t ptab[((RUNS ? PT_BYTES : (uint32_t)sizeof(SliceTabs)) + 15u) / 16u * 4u];
   static_assert(sizeof(SliceTabs) <= PT_BYTES, "either");
   SliceTabs& Tb = *reinterpret_cast<SliceTabs*>(ptab);
   __shared__ u64 lrl[LCAP];  // boundary columns of the current row found by this workgroup, not yet written out
   __shared__ u64 ltile[2];
   __shared__ u64 lt[2][MAX_SLICES];  // runs: the slices' masses by class
-  __shared__ uint32_t odd[4];        // bfloat16 runs: slices with groups that go column by column
+  __shared__ uint32_t odd[4];        // runs: slices with groups that go column by column
   __shared__ uint32_t hlist[HLIST];
   __shared__ unsigned l_n;
   __shared__ FS S;
+  static_assert((sizeof(ptab) + sizeof(lrl) + sizeof(ltile) + (RUNS ? sizeof(lt) + sizeof(odd) + sizeof(hlist) : 0u) + 8u + sizeof(S)) * WGS <= LDS_PER_CU, "a resident round by LDS");
   const int tid = threadIdx.x, lane = tid & 63;
   const int V = a.V;
   // mask word and bit of this thread's first column in each of its groups (a group step is whole words)
@@ -1069,7 +1072,7 @@ __global__ __launch_bounds__(WT, 4) void wide_classify_kernel(const SampleArgs a
     } else if (b == bstar) { if (ids_only) put(z, idx); else stage(atomicAdd(&l_n, 1u), ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx); }
   };
   auto one = [&](float z, int idx) { one_of(z, idx, use_hot && hot_bit(hot_bits, (uint32_t)idx)); };
-  if constexpr (BF16) if (takes_run(W, I.n_sl, sl0, sl1)) {
+  if constexpr (RUNS) if (takes_run(W, I.n_sl, sl0, sl1)) {
     // An entry is the mass of one of the pattern's columns if they surely survive and it is below 2^30 (four times the mass
     // at g), and MARKED for columns that are looked at one by one: boundary columns, and those with more mass.
     constexpr uint32_t MARKED = 0x80000000u;
@@ -1779,21 +1782,26 @@ __global__ __launch_bounds__(FT, 4) void wide_finish_kernel(const SampleArgs a) 
 }  // namespace fast
 
 
+// One resident round of workgroups each, as many per compute unit as fit by registers and LDS; a workgroup then takes a contiguous
+// range of slices, mostly of one row.
+template <typename DT, bool use_hot, bool RUNS>
+static void launch_slices(const SampleArgs& a, hipStream_t st) {
+  const dim3 blk(fast::WT);
+  hipLaunchKernelGGL((fast::wide_bins_kernel<DT, use_hot, RUNS>), dim3((unsigned)(a.n_cu * fast::bins_wgs<DT, RUNS>())), blk, 0, st, a);
+  hipLaunchKernelGGL((fast::wide_classify_kernel<DT, use_hot, RUNS>), dim3((unsigned)(a.n_cu * fast::WGS)), blk, 0, st, a);
+}
 hipError_t launch_wide(const SampleArgs& a, int dtype, hipStream_t st) {
-  // One resident round of workgroups each: four per compute unit fit by registers and LDS; a workgroup then takes a contiguous run of slices, mostly of one row.  The finishing kernel,
-  // two workgroups per compute unit by its LDS, takes a row at a time.
-  const dim3 cls((unsigned)a.n_cu * 4u), fin((unsigned)(a.B < 2 * a.n_cu ? a.B : 2 * a.n_cu)), blk(fast::WT), fblk(fast::FT);
+  // The finishing kernel, two workgroups per compute unit by its LDS, takes a row at a time.
+  const dim3 fin((unsigned)(a.B < 2 * a.n_cu ? a.B : 2 * a.n_cu)), fblk(fast::FT);
   if (dtype == SIMPLE_F32) {
-    if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<float, true>), cls, blk, 0, st, a);
-    else hipLaunchKernelGGL((fast::wide_bins_kernel<float, false>), cls, blk, 0, st, a);
-    if (a.hot_bits) hipLaunchKernelGGL((fast::wide_classify_kernel<float, true>), cls, blk, 0, st, a);
-    else hipLaunchKernelGGL((fast::wide_classify_kernel<float, false>), cls, blk, 0, st, a);
+    if (a.hot_bits) launch_slices<float, true, false>(a, st); else launch_slices<float, false, false>(a, st);
     hipLaunchKernelGGL((fast::wide_finish_kernel<float>), fin, fblk, 0, st, a);
   } else {
-    if (a.hot_bits) hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, true>), cls, blk, 0, st, a);
-    else hipLaunchKernelGGL((fast::wide_bins_kernel<uint16_t, false>), cls, blk, 0, st, a);
-    if (a.hot_bits) hipLaunchKernelGGL((fast::wide_classify_kernel<uint16_t, true>), cls, blk, 0, st, a);
-    else hipLaunchKernelGGL((fast::wide_classify_kernel<uint16_t, false>), cls, blk, 0, st, a);
+    // whether a workgroup can come by enough slices of a row for a run, were every row queued
+    const int64_t n_sl = (a.V + fast::SLC - 1) / fast::SLC, wgs = (int64_t)a.n_cu * fast::WGS, chunk = (a.B * n_sl + wgs - 1) / wgs;
+    const bool runs = !a.f64 && (chunk < n_sl ? chunk : n_sl) >= fast::RUN_MIN;
+    if (a.hot_bits) { if (runs) launch_slices<uint16_t, true, true>(a, st); else launch_slices<uint16_t, true, false>(a, st); }
+    else { if (runs) launch_slices<uint16_t, false, true>(a, st); else launch_slices<uint16_t, false, false>(a, st); }
     hipLaunchKernelGGL((fast::wide_finish_kernel<uint16_t>), fin, fblk, 0, st, a);
   }
   return hipGetLastError();
