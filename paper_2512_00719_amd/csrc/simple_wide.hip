@@ -411,15 +411,15 @@ __device__ __forceinline__ ZCut z_cut(const WideRow& W, int bstar, float thr_y) 
 
 // Work split: items are (queued row, slice) pairs in row-major order; a workgroup takes a
 // contiguous range, so that it meets few distinct rows.
-struct Items { unsigned i0, i1, n_sl; };
+struct Items { unsigned i0, i1, n_sl, chunk; };
 __device__ __forceinline__ Items my_items(const SampleArgs& a) {
   Items I;
   const unsigned n_wide = min(as_global(a.wq)[0], (unsigned)a.wide_slots);
   I.n_sl = (unsigned)((a.V + SLC - 1) / SLC);
   const unsigned items = n_wide * I.n_sl;
-  const unsigned chunk = (items + gridDim.x - 1u) / gridDim.x;
-  I.i0 = min(items, blockIdx.x * chunk);
-  I.i1 = min(items, I.i0 + chunk);
+  I.chunk = (items + gridDim.x - 1u) / gridDim.x;
+  I.i0 = min(items, blockIdx.x * I.chunk);
+  I.i1 = min(items, I.i0 + I.chunk);
   return I;
 }
 
@@ -457,11 +457,16 @@ __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a
 // history columns, 2 to 3 us of a slice's 5 to 9.  338 rows of 256,000 columns with 8192 ids each: bins kernel 101 us, 78 so (the slices
 // take 25 to 30, the 173 MB at the HBM rate; the history columns 18); classifying kernel 185, 115 (slices 55).  float32 rows the
 // same way, each column weighed: no gain (90 of 128,256 columns, 21 and 26 us either way).
-// A run of few slices does not repay its table's making and its reading out, the fewer the more history columns a slice has.  Calls
-// whose workgroups take 1, 4, 8 and 16 slices, 64 ids a row, by slices and by runs: 40,000 columns 88, 139, 206 and 347 us, 96, 143, 185 and
-// 306; 128,256 columns with 2048 ids 93, 127, 175 and 284, 100, 123, 149 and 222; with 8192 ids 10 slices 239 and 250, 16 slices 311 and 293.
+// A run's table and the settling of its history columns cost the workgroups of one resident round the same whether they take few
+// slices or many, and the history columns of a run cost more than a slice's: so from so many slices a workgroup, the more history columns
+// a slice has, up to so many of these.  By slices over by runs, the whole call, V = 20,000 / 40,000 / 128,256 / 256,000 columns:
+//   64 ids a row       2 to 9 history columns a slice:   4 slices a workgroup 1.00 1.01 1.04 0.98, 6: 1.01 1.04 1.04 1.01, 8: 1.06 1.11 1.19 1.10, 16: 1.08 1.15 1.36 1.21
+//   2048 ids           152, 81, 27, 15 of them:          6: 0.93 0.97 1.02 1.01, 9: 0.95 1.05 1.11 1.20, 16: 0.94 1.02 1.28 1.20
+//   8192 ids           431, 238, 85, 45 of them:         7: 0.79 0.84 0.96 1.06, 9: 0.79 0.89 1.02 1.09, 16: 0.79 0.85 1.06 1.11
+// (80,000 columns, 129 history columns a slice: 0.98 with 16 slices, 0.99 with 24.)  Pieces of a row with one or two slices are taken by
+// slices: with 6 slices a workgroup 1.04 against 1.02 (128,256 columns, 64 ids), a longer limit 0.99.
 // The two kernels divide the slices alike (one grid), so that the same slices are counted and looked up.
-constexpr int RUN_MIN = 6, RUN_IDS = 24;
+constexpr int RUN_MIN = 6, RUN_IDS = 24, RUN_MAX_IDS = 96, RUN_PIECE = 3;
 // A lane's group with a value that has no entry goes column by column, at a cost that only few groups may have: rows whose threshold
 // lies where there is none (a sample's quantile, it stands for the large values), or from which -256 has mass, are taken by
 // slices.  (512 rows of 256,000 columns, every logit raised by 300, by runs and by slices: 14.2 and 3.9 ms a call.)
@@ -470,8 +475,9 @@ __device__ __forceinline__ bool values_in_table(const StreamCtx& C) {
   const float w = mass_term(-256.0f, C, b), m = fabsf(C.g);
   return m >= 0x1p-6f && m < 256.0f && b == NBW - 1 && mass_integer(w) == 0.0f;
 }
-__device__ __forceinline__ bool takes_run(const WideRow& W, unsigned n_sl, int sl0, int sl1) {
-  return W.mode == WIDE_TOP_P && !W.f64 && (unsigned)(sl1 - sl0) >= RUN_MIN + W.distinct / (RUN_IDS * n_sl) && values_in_table(W.C);
+__device__ __forceinline__ bool takes_run(const WideRow& W, const Items& I, int sl0, int sl1) {
+  const unsigned per_slice = W.distinct / I.n_sl;
+  return W.mode == WIDE_TOP_P && !W.f64 && sl1 - sl0 >= RUN_PIECE && per_slice <= (unsigned)RUN_MAX_IDS && I.chunk >= RUN_MIN + per_slice / RUN_IDS && values_in_table(W.C);
 }
 // One 4-byte entry a pattern: magnitude index 0 is zero itself, 1 .. QMAX - 1 one pattern each, QMAX, among the negative
 // ones, -256 and all below it (-inf among them), which has no mass.  None: other magnitudes below 2^-14, 256 and more, NaN.
@@ -719,7 +725,7 @@ __global__ __launch_bounds__(WT, (bins_wgs<DT, RUNS>())) void wide_bins_kernel(c
   u64 mtop = 0ull;
   unsigned ntop = 0u;      // top-k route: columns at or above g seen by this thread
   float ymax = -INFINITY;  // rows with a min-p cut: largest tempered value seen by this thread
-  const bool run = RUNS && takes_run(W, I.n_sl, sl0, sl1);
+  const bool run = RUNS && takes_run(W, I, sl0, sl1);
   auto flush = [&]() {
     __syncthreads();
     if (W.mode == WIDE_TOP_P || W.mode == WIDE_TOP_K) {
@@ -1072,7 +1078,7 @@ __global__ __launch_bounds__(WT, WGS) void wide_classify_kernel(const SampleArgs
     } else if (b == bstar) { if (ids_only) put(z, idx); else stage(atomicAdd(&l_n, 1u), ((u64)__float_as_uint(z) << 32) | (u64)(uint32_t)idx); }
   };
   auto one = [&](float z, int idx) { one_of(z, idx, use_hot && hot_bit(hot_bits, (uint32_t)idx)); };
-  if constexpr (RUNS) if (takes_run(W, I.n_sl, sl0, sl1)) {
+  if constexpr (RUNS) if (takes_run(W, I, sl0, sl1)) {
     // An entry is the mass of one of the pattern's columns if they surely survive and it is below 2^30 (four times the mass
     // at g), and MARKED for columns that are looked at one by one: boundary columns, and those with more mass.
     constexpr uint32_t MARKED = 0x80000000u;
@@ -1798,8 +1804,8 @@ hipError_t launch_wide(const SampleArgs& a, int dtype, hipStream_t st) {
     hipLaunchKernelGGL((fast::wide_finish_kernel<float>), fin, fblk, 0, st, a);
   } else {
     // whether a workgroup can come by enough slices of a row for a run, were every row queued
-    const int64_t n_sl = (a.V + fast::SLC - 1) / fast::SLC, wgs = (int64_t)a.n_cu * fast::WGS, chunk = (a.B * n_sl + wgs - 1) / wgs;
-    const bool runs = !a.f64 && (chunk < n_sl ? chunk : n_sl) >= fast::RUN_MIN;
+    const int64_t n_sl = (a.V + fast::SLC - 1) / fast::SLC, wgs = (int64_t)a.n_cu * fast::WGS;
+    const bool runs = !a.f64 && (a.B * n_sl + wgs - 1) / wgs >= fast::RUN_MIN;
     if (a.hot_bits) { if (runs) launch_slices<uint16_t, true, true>(a, st); else launch_slices<uint16_t, true, false>(a, st); }
     else { if (runs) launch_slices<uint16_t, false, true>(a, st); else launch_slices<uint16_t, false, false>(a, st); }
     hipLaunchKernelGGL((fast::wide_finish_kernel<uint16_t>), fin, fblk, 0, st, a);

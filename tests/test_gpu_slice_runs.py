@@ -71,9 +71,10 @@ def test_runs(dtype, V, B, nnz, hot):
 
 
 def run_rule():
-    """RUN_MIN and RUN_IDS of takes_run: a piece of a row is taken in a run from RUN_MIN + distinct / (RUN_IDS * slices of a row) slices."""
+    """The constants of takes_run: with h history columns a slice, at most RUN_MAX_IDS, a row is taken in runs from RUN_MIN + h / RUN_IDS
+    slices a workgroup, but for pieces of fewer than RUN_PIECE slices."""
     src = open(os.path.join(os.path.dirname(binding.__file__), "csrc", "simple_wide.hip")).read()
-    return [int(x) for x in re.search(r"RUN_MIN = (\d+), RUN_IDS = (\d+)", src).groups()]
+    return [int(x) for x in re.search(r"RUN_MIN = (\d+), RUN_IDS = (\d+), RUN_MAX_IDS = (\d+), RUN_PIECE = (\d+)", src).groups()]
 
 
 @pytest.mark.parametrize("V,chunk,nnz,hot", [(28_675, 13, 300, True), (40_960, 15, 700, False), (150_001, 21, 2500, True), (150_008, 30, 2500, False)])
@@ -110,9 +111,9 @@ def test_rows_in_runs(V, chunk, nnz, hot):
     P.compare(ids, dg, P.run_oracle(w, 1, rows=ends), ends)
     for f in ("s_k", "n_survivors", "alpha"):
         assert np.array_equal(dg[f].reshape(times, K), np.broadcast_to(dg[f][:K], (times, K)), equal_nan=f == "alpha"), f
-    # slices a workgroup took, and what a run needs: most rows' pieces are runs
+    # slices a workgroup took, and what runs need
     wide = int(((dg["flags"] & binding.DIAG_WIDE) != 0).sum())
-    run_min, run_ids = run_rule()
-    distinct = max(len(np.unique(ids9[b * nnz:(b + 1) * nnz])) for b in range(K))
-    assert min(-(-wide * n_sl // (4 * n_cu)), n_sl) >= run_min + distinct // (run_ids * n_sl), (wide, B)
+    run_min, run_ids, run_max_ids, run_piece = run_rule()
+    per_slice = max(len(np.unique(ids9[b * nnz:(b + 1) * nnz])) for b in range(K)) // n_sl
+    assert per_slice <= run_max_ids and min(chunk, n_sl) >= run_piece and -(-wide * n_sl // (4 * n_cu)) >= run_min + per_slice // run_ids, (wide, B)
     assert wide >= B // 2
