@@ -38,7 +38,7 @@ struct simple_ctx {
 constexpr int PROF_MAX = 1024;
 
 struct simple_state {
-  int device;
+  int device, n_cu;
   int64_t n_slots, V, lmax;
   uint32_t stride, off_dir, off_cnt;  // bytes of tables per slot; offsets of the rank directory and the counts in them
   simple::StateRec* rec;
@@ -442,9 +442,11 @@ int simple_state_create(simple_state** out, int device, int64_t max_seqs, int64_
   if (!guard.ok) return SIMPLE_EDEVICE;
   int lds = 0;
   if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess) return SIMPLE_EDEVICE;
+  int n_cu = 0;
+  if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n_cu <= 0) return SIMPLE_EDEVICE;
   simple_state* s = new (std::nothrow) simple_state();
   if (!s) return SIMPLE_ENOMEM;
-  s->device = device; s->n_slots = max_seqs; s->V = V; s->lmax = L_max;
+  s->device = device; s->n_cu = n_cu; s->n_slots = max_seqs; s->V = V; s->lmax = L_max;
   // the tables of a slot lie as the single-pass kernel lays them out in LDS (make_fast_layout)
   const uint32_t n_words = (uint32_t)((V + 31) / 32), n_pairs = (n_words + 1u) / 2u;
   s->off_dir = simple::align16(n_pairs * 8u);
@@ -485,7 +487,7 @@ int simple_state_restart(simple_state* state, const int32_t* slots_dev, int64_t 
   simple::DeviceGuard guard(state->device);
   if (!guard.ok) return SIMPLE_EDEVICE;
   if (simple::launch_state_reset(state->rec, state->tokens, state->tables, (int)state->n_slots, (int)state->lmax, (int)state->V, state->stride,
-                                 state->off_dir, state->off_cnt, slots_dev, (int)n, prompt_ptr_dev, prompt_ids_dev, n_prompt_dev,
+                                 state->off_dir, state->off_cnt, slots_dev, (int)n, prompt_ptr_dev, prompt_ids_dev, n_prompt_dev, state->n_cu,
                                  static_cast<hipStream_t>(hip_stream)) != hipSuccess)
     return SIMPLE_EDEVICE;
   return SIMPLE_OK;

@@ -188,7 +188,7 @@ hipError_t set_max_lds(unsigned bytes);
 hipError_t set_max_lds_fast(unsigned bytes);
 hipError_t launch_state_reset(StateRec* rec, int32_t* tokens, unsigned char* tables, int n_slots, int lmax, int V, uint32_t stride,
                               uint32_t off_dir, uint32_t off_cnt, const int32_t* slots, int n, const int64_t* prompt_ptr,
-                              const int32_t* prompt_ids, const int32_t* n_prompt, hipStream_t st);
+                              const int32_t* prompt_ids, const int32_t* n_prompt, int n_cu, hipStream_t st);
 hipError_t launch_state_append(StateRec* rec, int32_t* tokens, unsigned char* tables, int n_slots, int lmax, int V, uint32_t stride,
                                uint32_t off_dir, uint32_t off_cnt, const int32_t* slots, const int32_t* new_ids, int B, hipStream_t st);
 hipError_t set_max_lds_state(unsigned bytes);

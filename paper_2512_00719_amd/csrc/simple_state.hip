@@ -26,8 +26,7 @@ using fast::Hist;
 using fast::u32x4;
 
 constexpr int ST = 256;       // threads per sequence
-constexpr int ST_FEW = 1024;  // of a restart of at most FEW sequences: each has a compute unit to itself
-constexpr int FEW = 256;
+constexpr int ST_FEW = 1024;  // of a restart of no more sequences than compute units: each has one to itself
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
 struct StateArgs {
@@ -183,11 +182,11 @@ __global__ __launch_bounds__(ST) void state_append_kernel(const StateArgs st, co
 // ------------------------------------------------------------------ launchers ------------------
 hipError_t launch_state_reset(StateRec* rec, int32_t* tokens, unsigned char* tables, int n_slots, int lmax, int V, uint32_t stride,
                               uint32_t off_dir, uint32_t off_cnt, const int32_t* slots, int n, const int64_t* prompt_ptr,
-                              const int32_t* prompt_ids, const int32_t* n_prompt, hipStream_t st) {
+                              const int32_t* prompt_ids, const int32_t* n_prompt, int n_cu, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const state::StateArgs a = {rec, tokens, tables, n_slots, lmax, V, stride, off_dir, off_cnt};
   // (both sides of the rule: see the kernel)
-  if (n <= state::FEW)
+  if (n <= n_cu)
     hipLaunchKernelGGL(state::state_reset_kernel<state::ST_FEW>, dim3((unsigned)n), dim3(state::ST_FEW), stride, st, a, slots, n, prompt_ptr, prompt_ids, n_prompt);
   else
     hipLaunchKernelGGL(state::state_reset_kernel<state::ST>, dim3((unsigned)n), dim3(state::ST), stride, st, a, slots, n, prompt_ptr, prompt_ids, n_prompt);
