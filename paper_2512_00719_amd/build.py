@@ -25,11 +25,11 @@ HIPCC_FLAGS = [
 # The single-pass kernel reserves list slots with one LDS atomic issued by one lane of a wave; the
 # compiler's wave-level aggregation of atomics would wrap that single lane in a second reduction.
 # The kernels behind it loop over rows and slices; constants of the double-precision functions, moved in front of those
-# loops, took up to 40 registers from end to end (the finishing kernel spills 14 so, and a kernel that uses scratch memory
-# starts 2 us later).  The bins and classifying kernels spill neither way (72 to 114 registers, 89 to 128 with the constants
-# moved); calls that run all three, with them moved and as built: 256 float32 rows of 128,256 columns, temperature alone, 66.2
-# and 64.5 us; 128 bfloat16 rows of 262,144 141.2 and 139.6; 1024 float32 rows of 128,256 197.7 and 196.7; 128 of 50,001 and 4096
-# bfloat16 rows of 256,000 the same.
+# loops, took up to 40 registers from end to end (the finishing kernel spills 8 so, and a kernel that uses scratch memory
+# starts 2 us later).  Of the bins and classifying kernels none spills a vector register as built (79 to 128 of them), four of
+# those with a hot set 3 to 10 with the constants moved; calls that run all three, with them moved and as built: 256
+# float32 rows of 128,256 columns, temperature alone, 67.8 and 66.2 us; 128 bfloat16 rows of 262,144 136.6 and 136.1; 1024 float32
+# rows of 128,256, 128 of 50,001 and 4096 bfloat16 rows of 256,000 the same.
 PER_SOURCE_FLAGS = {"simple_fast.hip": ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"],
                     "simple_wide.hip": ["-mllvm", "-disable-machine-licm"]}
 
