@@ -106,7 +106,7 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   // Four workgroups per compute unit, merge area and static LDS included.  (Tables of the last kilobyte that would still fit
   // take 512 threads: with 256, 1024 float32 rows of 128,256 columns and 8600 ids took 230.8 us a call, 224.9 so; bfloat16
   // rows of 151,936 columns and 6900 ids, whose lists then overflow, 460 and 234.)
-  F.threads = ((int64_t)body + 3072 <= (int64_t)lds_limit / 4) ? 256 : 512;
+  F.threads = ((int64_t)body + 2048 + STATIC_LDS <= (int64_t)lds_limit / 4) ? 256 : 512;
   if (V >= ((int64_t)1 << 18)) F.threads = 512;  // a sample of two tiles per wave: four waves' is too small a share of such rows
   if (B <= (int64_t)n_cu) F.threads = 1024;
   else if (B <= 2 * (int64_t)n_cu) F.threads = 512;
@@ -127,7 +127,7 @@ FastLayout make_fast_layout(int64_t V, int dtype, int64_t max_nnz, bool with_his
   const uint32_t total = body + (merge < SAMPLE_COUNTS * 4u ? SAMPLE_COUNTS * 4u : merge);
   const uint32_t reg_cap = (uint32_t)(capf_per_thread(F.threads, whole) * F.threads);  // the epilogue moves the list to registers
   F.list_cap = body / 8u < reg_cap ? body / 8u : reg_cap;
-  if ((int64_t)total + 1024 > (int64_t)lds_limit) return F;  // total stays 0
+  if ((int64_t)total + STATIC_LDS > (int64_t)lds_limit) return F;  // total stays 0
   if (!whole && V / tile < 2 * (F.threads / 64)) return F;
   F.total = total;
   return F;
@@ -195,9 +195,9 @@ int simple_create(simple_ctx** out, int device, int64_t max_B, int64_t max_V, in
   int n_cu = 0;
   if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n_cu <= 0) return SIMPLE_EDEVICE;
   const simple::LdsLayout L = simple::make_layout(max_V, max_nnz_per_row, max_nnz_per_row > 0);
-  if ((int64_t)L.total + 1024 > (int64_t)lds) return SIMPLE_ECAPACITY;
-  if (simple::set_max_lds((unsigned)lds - 1024u) != hipSuccess) return SIMPLE_EDEVICE;
-  if (simple::set_max_lds_fast((unsigned)lds - 1024u) != hipSuccess) return SIMPLE_EDEVICE;
+  if ((int64_t)L.total + simple::STATIC_LDS > (int64_t)lds) return SIMPLE_ECAPACITY;
+  if (simple::set_max_lds((unsigned)lds - simple::STATIC_LDS) != hipSuccess) return SIMPLE_EDEVICE;
+  if (simple::set_max_lds_fast((unsigned)lds - simple::STATIC_LDS) != hipSuccess) return SIMPLE_EDEVICE;
   simple_ctx* c = new (std::nothrow) simple_ctx();
   if (!c) return SIMPLE_ENOMEM;
   c->device = device; c->max_V = max_V; c->max_nnz = max_nnz_per_row; c->lds_limit = lds; c->n_cu = n_cu;
@@ -453,7 +453,7 @@ int simple_state_create(simple_state** out, int device, int64_t max_seqs, int64_
   s->off_cnt = simple::align16(s->off_dir + n_pairs * 2u);
   s->stride = (s->off_cnt + (uint32_t)((L_max + 3) / 2) * 4u + 16u + 255u) & ~255u;
   if ((int64_t)s->stride + 2048 > (int64_t)lds) { delete s; return SIMPLE_ECAPACITY; }  // the restart kernel builds a slot's tables in LDS
-  if (simple::set_max_lds_state((unsigned)lds - 1024u) != hipSuccess) { delete s; return SIMPLE_EDEVICE; }
+  if (simple::set_max_lds_state((unsigned)lds - simple::STATIC_LDS) != hipSuccess) { delete s; return SIMPLE_EDEVICE; }
   const size_t rec_b = simple::align256(sizeof(simple::StateRec) * (size_t)max_seqs);
   const size_t tok_b = simple::align256(4u * (size_t)L_max * (size_t)max_seqs);
   const size_t tab_b = (size_t)s->stride * (size_t)max_seqs;
@@ -545,7 +545,7 @@ static simple_ctx* static_ctx(int* err) {
   int lds = 0, n_cu = 0;
   if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n_cu <= 0) { *err = SIMPLE_EDEVICE; return nullptr; }
-  if (set_max_lds((unsigned)lds - 1024u) != hipSuccess || set_max_lds_fast((unsigned)lds - 1024u) != hipSuccess) { *err = SIMPLE_EDEVICE; return nullptr; }
+  if (set_max_lds((unsigned)lds - STATIC_LDS) != hipSuccess || set_max_lds_fast((unsigned)lds - STATIC_LDS) != hipSuccess) { *err = SIMPLE_EDEVICE; return nullptr; }
   const CtxLayout L = ctx_layout(STATIC_MAX_V, STATIC_MAX_NNZ, STATIC_SLOTS, lds, n_cu);
   if (L.total > STATIC_BYTES) { *err = SIMPLE_ECAPACITY; return nullptr; }
   unsigned char* ptr = nullptr;  // this device's copy of the array

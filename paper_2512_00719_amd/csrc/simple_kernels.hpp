@@ -34,6 +34,7 @@ struct FastLayout {
   int threads;        // workgroup size the layout was made for (256, 512 or 1024)
 };
 
+constexpr uint32_t STATIC_LDS = 1024;    // bytes of a compute unit's LDS kept for a workgroup's row-wide state beside its regions
 constexpr uint32_t SAMPLE_COUNTS = 512;  // counters of the threshold sample, where it is counted
 constexpr int SAMPLE_PER_WAVE = 48;   // keys of the threshold sample a wave hands to the merge (sizes the merge area)
 // Candidate-list entries per thread that the single-pass kernel's epilogue holds in registers: 3584 to 8192 a row,

@@ -146,6 +146,7 @@ struct FS {
   unsigned r32a[16], r32b[16];
   u64 r64a[16], r64b[16], r64c[16];
 };
+static_assert(sizeof(FS) <= STATIC_LDS, "what the layouts leave for it");
 
 // Per-row constants, identical in every thread.
 struct RowCfg {
