@@ -144,7 +144,7 @@ struct FS {
   float wmax[16];
   unsigned wcnt[16];
   unsigned r32a[16], r32b[16];
-  u64 r64a[16], r64b[16], r64c[16];
+  u64 r64a[16], r64b[16];
 };
 static_assert(sizeof(FS) <= STATIC_LDS, "what the layouts leave for it");
 
@@ -174,11 +174,11 @@ template <int NWV>
 __device__ inline void blk_sum3(FS& S, u64 x, u64 y, u64 z, u64& X, u64& Y, u64& Z) {
   x = wave_sum(x); y = wave_sum(y); z = wave_sum(z);
   __syncthreads();
-  if (lane_id() == 0) { const int w = wave_id(); S.r64a[w] = x; S.r64b[w] = y; S.r64c[w] = z; }
+  if (lane_id() == 0) { const int w = wave_id(); S.r64a[w] = x; S.r64b[w] = y; S.r32a[w] = (uint32_t)z; S.r32b[w] = (uint32_t)(z >> 32); }
   __syncthreads();
   X = 0ull; Y = 0ull; Z = 0ull;
 #pragma unroll
-  for (int w = 0; w < NWV; ++w) { X += S.r64a[w]; Y += S.r64b[w]; Z += S.r64c[w]; }
+  for (int w = 0; w < NWV; ++w) { X += S.r64a[w]; Y += S.r64b[w]; Z += ((u64)S.r32b[w] << 32) | (u64)S.r32a[w]; }
 }
 template <int NWV>
 __device__ inline u64 blk_sum_u64(FS& S, u64 v) {
