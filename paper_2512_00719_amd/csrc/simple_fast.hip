@@ -1490,7 +1490,7 @@ __global__ __launch_bounds__(NTHR, 4) void fast_rows_kernel(const SampleArgs a) 
     const uint32_t kmax = S.kmax;
     // Lower end of what the sliced kernels may take as above their threshold, below which they look for the cut: where the cut lies
     // among columns equal to g, just above these (WIDE_MAX).  (They gave such a row up and it went to the general kernel: one of 41,000
-    // bfloat16 rows of 256,000 columns with penalties, every tenth call of 4096 rows; such a call 1765 us, 1027 so, 860 without such a row.)
+    // bfloat16 rows of 256,000 columns with penalties, every tenth call of 4096 rows; such a call 1765 us, 1027 so, 865 without such a row.)
     if (tid == 0) S.wmax[0] = ties_at_g ? C.y_g + (0.01f + 1e-6f * fabsf(C.y_g)) : -INFINITY;
     if (S.flags & SIMPLE_DIAG_ERROR) rc = FIN_DONE;
     else if (kmax <= key_g || kmax <= KEY_NEG_INF) rc = FIN_PENDING;

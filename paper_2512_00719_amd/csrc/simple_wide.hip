@@ -454,8 +454,8 @@ __device__ __forceinline__ void item_fetch(ItemLoads<DT>& L, const SampleArgs& a
 // LDS access a column, with no barrier and no table of the history from slice to slice; what the run's history columns change is settled
 // once behind it: their weight as read is taken off, the penalised one added (integers: the sums are those of the column by column form).
 // What bounded it: 39 and 54 vector instructions a column, and per slice of 4096 columns four barriers, its tables and its
-// history columns, 2 to 3 us of a slice's 5 to 9.  338 rows of 256,000 columns with 8192 ids each: bins kernel 101 us, 78 so (the slices
-// take 25 to 30, the 173 MB at the HBM rate; the history columns 18); classifying kernel 185, 115 (slices 55).  float32 rows the
+// history columns, 2 to 3 us of a slice's 5 to 9.  338 rows of 256,000 columns with 8192 ids each: bins kernel 101 us, 83 so (the slices
+// take 25 to 30, the 173 MB at the HBM rate; the history columns 18); classifying kernel 185, 112 (slices 55).  float32 rows the
 // same way, each column weighed: no gain (90 of 128,256 columns, 21 and 26 us either way).
 // A run's table and the settling of its history columns cost the workgroups of one resident round the same whether they take few
 // slices or many, and the history columns of a run cost more than a slice's: so from so many slices a workgroup, the more history columns
