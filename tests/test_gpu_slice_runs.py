@@ -77,7 +77,7 @@ def run_rule():
     return [int(x) for x in re.search(r"RUN_MIN = (\d+), RUN_IDS = (\d+), RUN_MAX_IDS = (\d+), RUN_PIECE = (\d+)", src).groups()]
 
 
-@pytest.mark.parametrize("V,chunk,nnz,hot", [(28_675, 13, 300, True), (40_960, 15, 700, False), (150_001, 21, 2500, True), (150_008, 30, 2500, False)])
+@pytest.mark.parametrize("V,chunk,nnz,hot", [(17_003, 16, 60, True), (28_675, 13, 300, True), (40_960, 15, 700, False), (150_001, 21, 2500, True), (150_008, 30, 2500, False)])
 def test_rows_in_runs(V, chunk, nnz, hot):
     """Nine rows, repeated until a workgroup takes `chunk` slices: pieces of a row long enough for a run, and shorter ones.  The first
     nine and the last go through the oracle; masses are integers, so every copy of a row has the first one's, however it was cut."""
