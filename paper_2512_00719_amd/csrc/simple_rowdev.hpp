@@ -433,9 +433,9 @@ constexpr float F64_MARGIN = 10.0f;    // where a threshold is put below the row
 // masses are the integers that the general kernel gives the row, 2^43 fixed point relative to the largest (at most 2^43 each, so
 // that a row's sum below 2^63).
 constexpr int F64_MAX_BITS = QBITS;
-struct MassRef { float y, reach; int bits; };  // what masses are relative to, how far above it they are carried, their fixed point
+struct MassRef { float y, top; int bits; };  // what masses are relative to, up to where they are carried, their fixed point
 __device__ __forceinline__ u64 mass_fix64(float y, const MassRef& M, const Exp2Poly& P) {
-  return exp_fix(fminf(y, M.y + M.reach), M.y, M.bits, P);
+  return exp_fix(fminf(y, M.top), M.y, M.bits, P);
 }
 // Nearest integer of a float in [0, 2^52) as 64 bits, in two 32-bit conversions (the split is exact:
 // a float has 24 significant bits): hi counts units of 2^24.

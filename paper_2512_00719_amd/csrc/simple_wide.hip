@@ -98,7 +98,8 @@ __device__ __forceinline__ WideRow load_row(const SampleArgs& a, unsigned slot) 
   W.C.g = uni(rec.g); W.C.y_g = uni(rec.g / rec.tau); W.C.inv_tau = uni(1.0 / (double)rec.tau); W.C.need_sum = true;
   W.C.l2e_tau = 0.0f;
   const bool by_max = (uni(rec.mode) & WIDE_MAX) != 0u;
-  W.M = {by_max ? uni(rec.y_max) : W.C.y_g, by_max ? 0.0f : F64_REACH, by_max ? F64_MAX_BITS : F64_BITS};
+  const float y_max = uni(rec.y_max);  // (requested with the rest of the record, not once the mode is known)
+  W.M = {by_max ? y_max : W.C.y_g, uni(by_max ? y_max : W.C.y_g + F64_REACH), by_max ? F64_MAX_BITS : F64_BITS};
   W.rep = uni(rec.rep); W.freq = uni(rec.freq); W.pres = uni(rec.pres);
   W.inv_rep = uni(1.0 / (double)rec.rep);
   W.h_active = uni(rec.h_active) != 0;
@@ -1238,7 +1239,7 @@ __global__ __launch_bounds__(WT, WGS) void wide_classify_kernel(const SampleArgs
       weighed_columns<DT>(Tb, HP, W, a, rowp, c0, V, [&](float z, int idx, const Exp2Poly& P) {
         int b; float y;
         (void)mass_term(z, W.C, b, y);
-        bad = bad || !(y - W.M.y <= W.M.reach);  // a mass the fixed point cannot carry, or a NaN
+        bad = bad || !(y <= W.M.top);  // a mass the fixed point cannot carry, or a NaN
         const u64 m = mass_fix64(y, W.M, P);
         acc_all += m;
         ymax = fmaxf(ymax, y);
